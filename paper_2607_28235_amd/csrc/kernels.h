@@ -51,6 +51,7 @@ struct LevelOp {
   const int* idx = nullptr;
   const T* val = nullptr;
   const T* dinv = nullptr;
+  const T* cval = nullptr;  // fine level: the values in chunks (chunk shape only; see k_level_chunk)
   int lanes = 8;      // lanes per row (power of two, <= 64)
 };
 
@@ -70,7 +71,12 @@ struct FineBlocks {
   const int* ucol = nullptr;
   const void* lidx = nullptr;
   const int* meta = nullptr;  // local-column blocks: per block (first row, first nonzero, first distinct column, 0),
-                              // 16-byte records, nrb + 1 of them
+                              // 16-byte records, nrb + 1 of them (chunk shape: first chunk for first nonzero)
+  // chunk shape: chunk offsets of the rows (n + 1), and per chunk the low bytes of its four column positions and the
+  // bits above them (2 bits per position)
+  const int* cptr = nullptr;
+  const uint32_t* clo = nullptr;
+  const uint8_t* chi = nullptr;
 };
 
 // Fine-level row-block kernel for one right-hand side.  Shapes:
@@ -88,12 +94,22 @@ struct FineBlocks {
 //   11    the blocks of shape 9 taken two per workgroup (k_level_local_vec_nb): both blocks' loads in flight
 //         before the first barrier, each block summed as by shape 9;
 //   12    the blocks of shape 10 taken two per workgroup;
-//   13    the kernel of shape 9 over (3072, 64, 256) blocks (local geometry 4): agglomerated levels only.
+//   13    the kernel of shape 9 over (3072, 64, 256) blocks (local geometry 4): agglomerated levels only;
+//   14    the chunk shape (k_level_chunk; chosen by the set-up timing only): every row padded to whole chunks of four
+//         entries, 9-bit column positions, blocks of at most kChunkCap chunks, kChunkRows rows and kChunkUcap - 1
+//         distinct columns (the slot after the last one holds the zero that padding entries read).
 // With partials != null (F_PLAIN only; shapes 0..8) the launch writes partial sums of u_i (A u)_i to
 // partials[0..np) and returns np (<= fb.nrb).
 constexpr int kCsrGeoms = 3;
 constexpr int kFineShapes = 13;    // shapes 0..12 serve the fine level
-constexpr int kStreamShapes = 14;  // shape 13: the vector kernel over geometry-4 blocks (agglomerated levels)
+constexpr int kChunkShape = 14;    // shape 13: the vector kernel over geometry-4 blocks (agglomerated levels)
+constexpr int kStreamShapes = 15;
+// Blocks of 512 to 1,024 chunks, 64 to 256 rows and 512 to 1,024 columns were measured on twelve meshes (3D Q2 13^3 to
+// 48^3, 3D Q3 16^3, 2D Q1 to Q3 from 1,089 to 591,361 rows, both precisions).  This geometry is within 2% of the best
+// of them everywhere; 512 chunks lose up to 20% where the matrix fits the caches, 256 rows gain 2% in 2D only.
+constexpr int kChunkCap = 768;
+constexpr int kChunkRows = 128;
+constexpr int kChunkUcap = 512;
 constexpr int kVecTwoFirst = 11;  // shapes 11, 12: the blocks of shapes 9, 10 taken two per workgroup
 constexpr int kAggVecShape = 13;
 constexpr int kLocalFirst = 6;
@@ -112,6 +128,11 @@ constexpr int kFinePad = 4;
 template <typename T>
 int launch_level_stream(int shape, const FineBlocks& fb, const LevelOp<T>& op, const T* u, const T* b, T* rho, T* x,
                         T* dout, double c1, double c2, int flags, const int* skip, double* partials, hipStream_t s);
+
+// cval = the values of a CSR matrix with every row padded by zeros to whole chunks of four entries (cptr: chunk
+// offsets of the rows).
+template <typename T>
+void launch_chunk_values(int n, const int* ptr, const int* cptr, const T* val, T* cval, hipStream_t s);
 
 // Block-row variant for the agglomerated levels and one right-hand side (one wave per box; maxnb = largest
 // number of stored blocks in a block row).  Needs blockrow_lds_bytes(B, maxnb * B, sizeof(T)) <= 64 KiB.

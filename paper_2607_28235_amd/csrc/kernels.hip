@@ -278,10 +278,6 @@ template void launch_level<double>(const LevelOp<double>&, int, const double*, c
 
 // ==== fine-level row-block kernels ====
 
-// Sum of the staged products prod[s..e) of one row by TPR consecutive lanes (TPR = 4 or 2) in one canonical
-// order, the same for every row-block shape: a_v = prod[s+v] + prod[s+v+4] + ... (v = 0..3, in increasing
-// position), row sum = (a_0 + a_2) + (a_1 + a_3).  With TPR = 2 each lane carries two of the four partial sums.
-// Lane sub = 0 of the group holds the result.
 // Matrix load of the fused level kernels: ordinary with KEEP (the level's matrix fits the caches and is applied
 // again right away), nontemporal otherwise.  A compile-time choice: a run-time select between the two would be
 // folded into one ordinary load.
@@ -293,23 +289,56 @@ __device__ inline P ld_matrix(const P* ptr) {
     return __builtin_nontemporal_load(ptr);
 }
 
-template <typename T, int TPR>
-__device__ inline T row_sum_canonical(const T* prod, int s, int e, int sub) {
-  static_assert(TPR == 4 || TPR == 2, "lanes per row");
+// Row sums of the row-block kernels, in one canonical order that is the same for every shape.  A row's products are
+// taken in chunks of four from its first entry: c_j = (p_4j + p_4j+2) + (p_4j+1 + p_4j+3), missing entries of the
+// last chunk being +0; a_v = c_v + c_v+4 + ... (v = 0..3, in increasing position); row sum = (a_0 + a_2) + (a_1 + a_3).
+// The products are rounded before they are added (no fused multiply-add), so that it does not matter whether a
+// kernel adds them in registers or from LDS.
+
+// the sum over a row's chunk sums cs(0..nc) by TPR consecutive lanes (4, 2 or 1); lane sub = 0 holds the result
+template <typename T, int TPR, typename F>
+__device__ inline T row_sum_chunks(int nc, int sub, F&& cs) {
+  static_assert(TPR == 4 || TPR == 2 || TPR == 1, "lanes per row");
   if constexpr (TPR == 4) {
     T a = 0;
-    for (int k = s + sub; k < e; k += 4) a += prod[k];
+    for (int j = sub; j < nc; j += 4) a += cs(j);
     a += __shfl_xor(a, 2, 64);
     a += __shfl_xor(a, 1, 64);
     return a;
-  } else {
+  } else if constexpr (TPR == 2) {
     T a = 0, c = 0;
-    for (int k = s + sub; k < e; k += 4) a += prod[k];
-    for (int k = s + sub + 2; k < e; k += 4) c += prod[k];
+    int j = sub;
+    for (; j + 2 < nc; j += 4) {
+      a += cs(j);
+      c += cs(j + 2);
+    }
+    if (j < nc) a += cs(j);
     T t = a + c;
     t += __shfl_xor(t, 1, 64);
     return t;
+  } else {
+    T a[4] = {0, 0, 0, 0};
+    int j = 0;
+    for (; j + 3 < nc; j += 4) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) a[v] += cs(j + v);
+    }
+#pragma unroll
+    for (int v = 0; v < 3; ++v)
+      if (j + v < nc) a[v] += cs(j + v);
+    return (a[0] + a[2]) + (a[1] + a[3]);
   }
+}
+
+// the same over the products prod[s..e) themselves, staged in LDS
+template <typename T, int TPR>
+__device__ inline T row_sum_canonical(const T* prod, int s, int e, int sub) {
+  return row_sum_chunks<T, TPR>((e - s + 3) >> 2, sub, [&](int j) {
+    const int k = s + 4 * j;
+    const T p1 = k + 1 < e ? prod[k + 1] : (T)0, p2 = k + 2 < e ? prod[k + 2] : (T)0;
+    const T p3 = k + 3 < e ? prod[k + 3] : (T)0;
+    return (prod[k] + p2) + (p1 + p3);
+  });
 }
 
 // Row-block ("stream") variant of the fused kernel for the CSR fine level, one right-hand side.  Each
@@ -990,6 +1019,142 @@ __global__ __launch_bounds__(256) void k_level_local_vec_nb(int nrb, const int4*
   }
 }
 
+// Chunk kernel of the fine level (shape kChunkShape).  The matrix is held in chunks of four consecutive entries of one
+// row (rows padded with zero values to whole chunks), so a thread adds the four products of a 16- or 32-byte value
+// load in registers and stages one sum per chunk in LDS.  The kernels above stage every product: four times the LDS
+// traffic, and in 3D half their slots stay empty, because 256 columns (1-byte positions) are reached after about
+// 1,000 of 2,048 entries.  Here the positions have 9 bits (8 in a 4-byte word per chunk, the bits above in a byte per
+// chunk), the blocks are full, and a block of 3,072 entries needs half as many distinct columns per entry.  Padding
+// entries have the position nu, whose slot holds zero, so that they add +0 whatever u holds.
+// Bound by memory: the matrix at 5.25 bytes (float32) per entry, the distinct columns and 7 vector streams.  One
+// application back to back, best of the kernels above -> this one: 3D Q2 48^3 (912,673 rows) float32 81.1 -> 61.1 us
+// (340 MB: 5.6 TB/s, a copy of that size runs at 5.4), float64 y = A p 121.7 -> 109.3; 3D Q2 29^3 float64 27.8 -> 19.3;
+// 3D Q2 24^3 float32 12.0 -> 8.2; 3D Q3 16^3 float32 26.8 -> 13.4; 2D Q3 256^2 float32 17.8 -> 16.4 (6.3 TB/s from the
+// caches), float64 y = A p 22.8 -> 22.4; 2D Q3 101^2 float64 6.4 -> 4.9; 2D Q2 16^2 (1,089 rows) 3.6 -> 3.4.
+template <typename T, int CAPC, int RPB, int UCAP, bool KEEP>
+__global__ __launch_bounds__(256) void k_level_chunk(int nrb, const int4* __restrict__ meta,
+                                                     const int* __restrict__ ucol, const uint32_t* __restrict__ clo,
+                                                     const uint8_t* __restrict__ chi, const int* __restrict__ cptr,
+                                                     const T* __restrict__ cval, const int* __restrict__ ptr,
+                                                     const int* __restrict__ idx, const T* __restrict__ val,
+                                                     const T* __restrict__ u, const T* __restrict__ b, T* rho, T* x,
+                                                     const T* __restrict__ dinv, T* dout, T c1, T c2, int flags,
+                                                     const int* __restrict__ skip) {
+  using V4 = typename Vec4<T>::type;
+  constexpr int TPR = 256 / RPB;
+  constexpr int NCH = CAPC / 256;
+  constexpr int UPT = UCAP / 256;
+  static_assert(CAPC % 256 == 0 && UCAP % 256 == 0 && UCAP <= 1024, "chunk block shape");
+  if (skip && *skip) return;
+  const int lb = xcd_block(nrb);
+  if (lb < 0) return;
+  __shared__ T us[UCAP];
+  __shared__ T cs[CAPC];
+  __shared__ T shr[4];
+  const int4 m0 = meta[lb], m1 = meta[lb + 1];
+  const int r0 = m0.x, r1 = m1.x;
+  const int k0 = m0.y, k1 = m1.y;
+  const int u0 = m0.z, nu = m1.z - u0;
+  const bool staged = nu < UCAP && k1 - k0 <= CAPC;
+  const int rl = threadIdx.x / TPR, sub = threadIdx.x % TPR;
+  const int prow = r0 + rl;
+  // unconditional loads from clamped addresses, as in k_level_local_vec
+  const int prc = min(prow, r1 - 1);  // blocks hold at least one row
+  T p_old = 0, p_x = 0, p_u = 0, p_di = 0;
+  T t = 0;
+  if (staged) {
+    int uc[UPT];
+#pragma unroll
+    for (int m = 0; m < UPT; ++m) uc[m] = ucol[u0 + min((int)threadIdx.x + m * 256, nu - 1)];  // nu >= 1
+    uint32_t lo[NCH], hi[NCH];
+    V4 vv[NCH];
+#pragma unroll
+    for (int m = 0; m < NCH; ++m) {
+      const int k = min(k0 + (int)threadIdx.x + m * 256, k1 - 1);
+      lo[m] = ld_matrix<KEEP>(clo + k);
+      hi[m] = ld_matrix<KEEP>(chi + k);
+      vv[m] = ld_matrix<KEEP>(reinterpret_cast<const V4*>(cval) + k);
+    }
+    const int rs = cptr[min(prow, r1)] - k0, re = cptr[min(prow + 1, r1)] - k0;
+    if (!(flags & F_PLAIN)) {
+      p_old = (flags & F_RHO_FROM_B) ? b[prc] : rho[prc];
+      p_u = u[prc];
+      if (flags & F_X_ADD) p_x = x[prc];
+      if (flags & F_D_OUT) p_di = dinv[prc];
+    }
+#pragma unroll
+    for (int m = 0; m < UPT; ++m) {
+      const T g = u[uc[m]];
+      us[threadIdx.x + m * 256] = (int)threadIdx.x + m * 256 < nu ? g : (T)0;
+    }
+    // keep the streamed entries ahead of the barrier (the compiler would otherwise sink some loads past it)
+#pragma unroll
+    for (int m = 0; m < NCH; ++m) {
+      asm volatile("" ::"v"(lo[m]), "v"(hi[m]));
+#pragma unroll
+      for (int q = 0; q < 4; ++q) asm volatile("" ::"v"(vv[m][q]));
+    }
+    __syncthreads();
+#pragma unroll
+    for (int m = 0; m < NCH; ++m) {
+#pragma clang fp contract(off)
+      V4 p;
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        p[q] = vv[m][q] * us[((lo[m] >> (8 * q)) & 0xff) | (((hi[m] >> (2 * q)) & 3) << 8)];
+      cs[threadIdx.x + m * 256] = (p[0] + p[2]) + (p[1] + p[3]);  // past the block: never read
+    }
+    __syncthreads();
+    t = row_sum_chunks<T, TPR>(re - rs, sub, [&](int j) { return cs[rs + j]; });
+  } else {  // one long row
+    if (!(flags & F_PLAIN)) {
+      p_old = (flags & F_RHO_FROM_B) ? b[prc] : rho[prc];
+      p_u = u[prc];
+      if (flags & F_X_ADD) p_x = x[prc];
+      if (flags & F_D_OUT) p_di = dinv[prc];
+    }
+    const int lane = threadIdx.x & 63;
+    T acc = 0;
+    for (int e = ptr[r0] + threadIdx.x; e < ptr[r0 + 1]; e += 256) acc += val[e] * u[idx[e]];
+    acc = wave_sum(acc, 64);
+    if (lane == 0) shr[threadIdx.x >> 6] = acc;
+    __syncthreads();
+    t = (shr[0] + shr[1]) + (shr[2] + shr[3]);
+  }
+  if (sub == 0 && prow < r1 && (staged || rl == 0)) {
+    const int row = prow;
+    if (flags & F_PLAIN) {
+      rho[row] = t;
+    } else {
+      const T r = p_old - t;
+      if (flags & F_RHO_STORE) rho[row] = r;
+      if (flags & F_X_ASSIGN)
+        x[row] = p_u;
+      else if (flags & F_X_ADD)
+        x[row] = p_x + p_u;
+      if (flags & F_D_OUT) dout[row] = c1 * p_u + c2 * p_di * r;
+    }
+  }
+}
+
+template <typename T>
+__global__ __launch_bounds__(256) void k_chunk_values(int n, const int* __restrict__ ptr, const int* __restrict__ cptr,
+                                                      const T* __restrict__ val, T* cval) {
+  const int row = blockIdx.x * 16 + (threadIdx.x >> 4), lane = threadIdx.x & 15;
+  if (row >= n) return;
+  const int s = ptr[row], len = ptr[row + 1] - s;
+  const int k = cptr[row], w = 4 * (cptr[row + 1] - k);
+  for (int j = lane; j < w; j += 16) cval[4 * (int64_t)k + j] = j < len ? val[s + j] : (T)0;
+}
+
+template <typename T>
+void launch_chunk_values(int n, const int* ptr, const int* cptr, const T* val, T* cval, hipStream_t s) {
+  hipLaunchKernelGGL((k_chunk_values<T>), dim3((n + 15) / 16), dim3(256), 0, s, n, ptr, cptr, val, cval);
+  check_launch("k_chunk_values");
+}
+template void launch_chunk_values<float>(int, const int*, const int*, const float*, float*, hipStream_t);
+template void launch_chunk_values<double>(int, const int*, const int*, const double*, double*, hipStream_t);
+
 template <typename T, int CAP, int RPB>
 static int launch_stream_block(const FineBlocks& fb, const LevelOp<T>& op, const T* u, const T* b, T* rho, T* x,
                                T* dout, double c1, double c2, int flags, const int* skip, double* partials,
@@ -1084,6 +1249,23 @@ static int launch_stream_local_vec(const FineBlocks& fb, const LevelOp<T>& op, c
 }
 
 template <typename T>
+static int launch_chunk(const FineBlocks& fb, const LevelOp<T>& op, const T* u, const T* b, T* rho, T* x, T* dout,
+                        double c1, double c2, int flags, const int* skip, double* partials, hipStream_t s) {
+  if (partials) throw std::runtime_error("chunk kernel: no partial sums");
+  if (!fb.meta || !fb.cptr || !op.cval) throw std::runtime_error("chunk kernel: chunked matrix missing");
+  const int4* meta = reinterpret_cast<const int4*>(fb.meta);
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(xcd_grid(fb.nrb)), dim3(256), 0, s, fb.nrb, meta, fb.ucol, fb.clo, fb.chi, fb.cptr,
+                       op.cval, op.ptr, op.idx, op.val, u, b, rho, x, op.dinv, dout, (T)c1, (T)c2, flags, skip);
+  };
+  if (flags & F_KEEP)
+    go(k_level_chunk<T, kChunkCap, kChunkRows, kChunkUcap, true>);
+  else
+    go(k_level_chunk<T, kChunkCap, kChunkRows, kChunkUcap, false>);
+  return fb.nrb;
+}
+
+template <typename T>
 int launch_level_stream(int shape, const FineBlocks& fb, const LevelOp<T>& op, const T* u, const T* b, T* rho, T* x,
                         T* dout, double c1, double c2, int flags, const int* skip, double* partials, hipStream_t s) {
   if (fb.nrb == 0) return 0;
@@ -1104,6 +1286,7 @@ int launch_level_stream(int shape, const FineBlocks& fb, const LevelOp<T>& op, c
     case 11: np = launch_stream_local_vec<T, 2048, 64, 256, 2>(R3MG_ARGS); break;
     case 12: np = launch_stream_local_vec<T, 3072, 128, 256, 2>(R3MG_ARGS); break;
     case 13: np = launch_stream_local_vec<T, 3072, 64, 256, 1>(R3MG_ARGS); break;
+    case kChunkShape: np = launch_chunk<T>(R3MG_ARGS); break;
     default: throw std::runtime_error("unknown row-block shape");
   }
 #undef R3MG_ARGS

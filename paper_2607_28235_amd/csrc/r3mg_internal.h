@@ -88,6 +88,12 @@ struct LocalBlocks {  // local-column row blocks of a CSR pattern (device form: 
   std::vector<uint8_t> lidx;  // 1 or 2 bytes per nonzero, plus kFinePad padding entries
 };
 
+struct ChunkBlocks {  // row blocks of the chunk kernel (device form: FineBlocks)
+  std::vector<int32_t> rb, ubp, ucol;
+  std::vector<uint32_t> lo;  // per chunk: low bytes of its four column positions
+  std::vector<uint8_t> hi;   // per chunk: the bits above them, 2 per position
+};
+
 struct MrHost {  // blocks of one staging class of the multi-right-hand-side kernel (device form: MrBlocks)
   LocalBlocks lb;
   std::vector<int32_t> ord;  // per block, its rows in order of decreasing row length
@@ -124,6 +130,8 @@ struct Analysis {
   // geometries (block offsets, distinct-column offsets and lists, local column index bytes per nonzero)
   std::vector<int32_t> rb[3];
   LocalBlocks loc[4];
+  std::vector<int32_t> cptr;             // chunk offsets of the rows: every row padded to whole chunks of four
+  ChunkBlocks chunk;
   std::vector<uint8_t> constrained;      // internal order
   std::vector<uint8_t> constrained_user; // caller's order
   std::vector<int32_t> owner;            // internal point -> level-1 box, -1 if constrained
@@ -217,6 +225,13 @@ struct DevLevel {
   DBuf<uint8_t> lidx[kLocalGeomsAll];
   DBuf<int32_t> lmeta[kLocalGeomsAll];  // per-block records of the local-column blocks (FineBlocks::meta)
   FineBlocks fb[kStreamShapes];  // l = 0: row blocks of every kernel shape
+  // l = 0: the chunk kernel's blocks, and the chunked values in the precisions whose chosen shape reads them
+  int64_t nchunk = 0;
+  DBuf<int32_t> cptr, cucol, cmeta;
+  DBuf<uint32_t> clo;
+  DBuf<uint8_t> chi;
+  DBuf<float> cval32;
+  DBuf<double> cval64;
   // l = 0: blocks of the LDS-staged multi-right-hand-side kernel per staging class, built at the first
   // multi-right-hand-side tuning that needs them
   DBuf<int32_t> mrb[kMrClasses], mubp[kMrClasses], mucol[kMrClasses], mord[kMrClasses], mmeta[kMrClasses];

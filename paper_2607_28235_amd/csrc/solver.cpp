@@ -195,9 +195,11 @@ LevelOp<T> level_op(Ctx& c, int l) {
   }
   if constexpr (sizeof(T) == 4) {
     op.val = D.val32.p;
+    op.cval = D.cval32.p;
     op.dinv = D.dinv32.p;
   } else {
     op.val = D.val64.p;
+    op.cval = D.cval64.p;
     op.dinv = D.dinv64.p;
   }
   return op;
@@ -238,6 +240,9 @@ std::string level_kernel_name(const Analysis& an, const DevLevel& D, int l, int 
   const char* t = esz == 4 ? "float" : "double";
   switch (level_kernel(an, D, l, 1, esz)) {
     case LevelKernel::Stream:
+      if (D.shape == kChunkShape)
+        return std::string("k_level_chunk<") + t + "," + std::to_string(4 * kChunkCap) + "," +
+               std::to_string(kChunkRows) + "," + std::to_string(kChunkUcap) + ">";
       if (D.shape >= kLocalFirst) {
         // shapes 9..13 (vector kernel): geometries 0, 3, 0, 3, 4; shapes 11 and 12 ("vec2") take two blocks per
         // workgroup
@@ -853,12 +858,36 @@ static void lanczos_level(Ctx& c, int l, hipStream_t s) {
   D.cheb_c2 = ch.c2;
 }
 
+// the fine level's values in chunks, in the precisions that hold a chunked copy
+static void fill_chunks(DevLevel& D, int esz, hipStream_t s) {
+  if (esz == 8 && D.cval64.p) launch_chunk_values<double>((int)D.n, D.rowptr.p, D.cptr.p, D.val64.p, D.cval64.p, s);
+  if (esz == 4 && D.cval32.p) launch_chunk_values<float>((int)D.n, D.rowptr.p, D.cptr.p, D.val32.p, D.cval32.p, s);
+}
+
+// keeps a chunked copy of the fine values for exactly the precisions in which the chosen shapes read one
+static void keep_chunks(DevLevel& D, bool fp32, hipStream_t s) {
+  const size_t count = 4 * (size_t)D.nchunk;
+  const bool want32 = fp32 && D.shape == kChunkShape, want64 = D.shape64 == kChunkShape;
+  R3MG_HIP_CHECK(hipStreamSynchronize(s));  // the copies may still be read by the timing
+  if (!want32) D.cval32.release();
+  if (!want64) D.cval64.release();
+  if (want32 && !D.cval32.p) {
+    D.cval32.alloc(count);
+    fill_chunks(D, 4, s);
+  }
+  if (want64 && !D.cval64.p) {
+    D.cval64.alloc(count);
+    fill_chunks(D, 8, s);
+  }
+}
+
 void numeric_setup(HandleImpl& h, hipStream_t s) {
   Analysis& an = *h.an;
   Device& dv = *h.dev;
   Ctx c{an, dv, an.opt.vcycle_fp32 != 0};
   const int L = an.nlevels() - 1;
   const int B = an.B;
+  fill_chunks(dv.lv[0], 8, s);
   // Galerkin products level by level (float64)
   for (int l = 1; l <= L; ++l) {
     DevLevel& D = dv.lv[l];
@@ -885,6 +914,7 @@ void numeric_setup(HandleImpl& h, hipStream_t s) {
     if (c.fp32) {
       D.val32.alloc(D.val64.n);
       launch_cast_d2f((int64_t)D.val64.n, D.val64.p, D.val32.p, s);
+      if (l == 0) fill_chunks(D, 4, s);
       D.dinv32.alloc(D.n);
       launch_cast_d2f(D.n, D.dinv64.p, D.dinv32.p, s);
     }
@@ -960,8 +990,12 @@ static std::string tune_signature(const Analysis& an, const Device& dv) {
   return tune_device_key(dv.dev) + "/" + buf;
 }
 
-// Fine-level row-block shape: each candidate shape runs the V-cycle-precision smoother step on level 0 (3
-// warm-up + 5 timed launches, hipEvents); the fastest is kept for every later single-RHS application.
+// Fine-level row-block shape: the candidates run the V-cycle-precision smoother step on level 0 (3 warm-up + 20 timed
+// launches, hipEvents); the fastest is kept for every later single-RHS application.  Candidates are the chunk shape
+// and CSR shape 0, which needs no padding and no column lists (a matrix of very short or very scattered rows).  The
+// other shapes lost to the chunk shape on every mesh measured (see k_level_chunk), so their blocks are built only
+// when fine_kernel names them.
+static bool timed_shape(int sh) { return sh == 0 || sh == kChunkShape; }
 static void tune_stream_shape(HandleImpl& h, hipStream_t s) {
   Analysis& an = *h.an;
   Device& dv = *h.dev;
@@ -977,20 +1011,28 @@ static void tune_stream_shape(HandleImpl& h, hipStream_t s) {
   const bool cache = an.opt.tune_cache != 0 && !dv.tune_sig.empty();
   const std::string key = dv.tune_sig + "/fine1/" + (c.fp32 ? "f32" : "f64");
   int cached = 0;
-  if (cache && tune_cache_get(key, &cached) && cached >= 0 && cached % 100 < kFineShapes &&
-      cached / 100 < kFineShapes && (c.fp32 || cached / 100 == cached % 100)) {
+  if (cache && tune_cache_get(key, &cached) && cached >= 0 && timed_shape(cached % 100) && timed_shape(cached / 100) &&
+      (c.fp32 || cached / 100 == cached % 100)) {
     D.shape = cached % 100;
     D.shape64 = cached / 100;
     D.bytes_apply = D.shape_bytes[D.shape];
+    keep_chunks(D, c.fp32, s);
     return;
   }
+  if (c.fp32) {
+    D.cval32.alloc(4 * (size_t)D.nchunk);
+    fill_chunks(D, 4, s);
+  }
+  D.cval64.alloc(4 * (size_t)D.nchunk);
+  fill_chunks(D, 8, s);
   const int fl = F_RHO_STORE | F_X_ADD | F_D_OUT;
   // two interleaved rounds, best of each shape; another shape replaces the first one only when it is at least
   // 3% faster, so that timing noise does not flip the choice between runs
   float best[kStreamShapes];
   for (int sh = 0; sh < kStreamShapes; ++sh) best[sh] = 1e30f;
   for (int round = 0; round < 2; ++round) {
-    for (int sh = 0; sh < kFineShapes; ++sh) {
+    for (int sh = 0; sh < kStreamShapes; ++sh) {
+      if (!timed_shape(sh)) continue;
       float ms;
       if (c.fp32) {
         LevelOp<float> op = level_op<float>(c, 0);
@@ -1011,7 +1053,7 @@ static void tune_stream_shape(HandleImpl& h, hipStream_t s) {
     }
   }
   int bestS = 0;
-  for (int sh = 1; sh < kFineShapes; ++sh)
+  for (int sh = 1; sh < kStreamShapes; ++sh)
     if (best[sh] < 0.97f * best[bestS]) bestS = sh;
   D.shape = D.shape64 = bestS;
   D.bytes_apply = D.shape_bytes[D.shape];
@@ -1019,6 +1061,7 @@ static void tune_stream_shape(HandleImpl& h, hipStream_t s) {
   R3MG_HIP_CHECK(hipMemsetAsync(D.rho.p, 0, D.rho.n, s));
   if (!c.fp32) {
     if (cache) tune_cache_put(key, D.shape + 100 * D.shape64);
+    keep_chunks(D, false, s);
     return;
   }
   // float32 V-cycle: PCG's float64 operator y = A p is timed on its own (the float64 values double the LDS
@@ -1030,7 +1073,8 @@ static void tune_stream_shape(HandleImpl& h, hipStream_t s) {
   LevelOp<double> op = level_op<double>(c, 0);
   for (int sh = 0; sh < kStreamShapes; ++sh) best[sh] = 1e30f;
   for (int round = 0; round < 2; ++round)
-    for (int sh = 0; sh < kFineShapes; ++sh) {
+    for (int sh = 0; sh < kStreamShapes; ++sh) {
+      if (!timed_shape(sh)) continue;
       const float ms = time_launches(s, 20, [&] {
         launch_level_stream<double>(sh, D.fb[sh], op, u64.p, nullptr, y64.p, nullptr, nullptr, 0.0, 0.0,
                                     F_PLAIN | D.keep64, nullptr, nullptr, s);
@@ -1038,9 +1082,10 @@ static void tune_stream_shape(HandleImpl& h, hipStream_t s) {
       best[sh] = std::min(best[sh], ms);
     }
   bestS = 0;
-  for (int sh = 1; sh < kFineShapes; ++sh)
+  for (int sh = 1; sh < kStreamShapes; ++sh)
     if (best[sh] < 0.97f * best[bestS]) bestS = sh;
   D.shape64 = bestS;
+  keep_chunks(D, true, s);
   if (cache) tune_cache_put(key, D.shape + 100 * D.shape64);
   R3MG_HIP_CHECK(hipStreamSynchronize(s));
 }
@@ -1128,22 +1173,49 @@ void device_setup(HandleImpl& h, hipStream_t s) {
         D.shape_bytes[sh] = by;
       }
     }
-    for (int g = 0; g < kLocalGeoms; ++g) {
-      upload_local(D, g, an.loc[g], an.rowptr, s);
-      D.shape_bytes[kLocalFirst + g] = local_bytes(an.nnz, an.n, g, an.loc[g], sv0);
-    }
     // matrix read with ordinary loads when its stream (values and 1-byte positions) fits the caches
     D.keep32 = keep_rule(an.opt, (double)an.nnz * (4 + 1));
     D.keep64 = keep_rule(an.opt, (double)an.nnz * (8 + 1));
-    // shape 9: the vector-load kernel over the blocks of local geometry 0; shape 10: the same over geometry 3
-    D.fb[kLocalFirst + kLocalGeoms] = D.fb[kLocalFirst];
-    D.shape_bytes[kLocalFirst + kLocalGeoms] = D.shape_bytes[kLocalFirst];
-    upload_local(D, 3, an.loc[3], an.rowptr, s, kLocalFirst + kLocalGeoms + 1);
-    D.shape_bytes[kLocalFirst + kLocalGeoms + 1] = local_bytes(an.nnz, an.n, 3, an.loc[3], sv0);
-    // shapes 11 and 12: the blocks of shapes 9 and 10, two per workgroup
-    for (int sh : {kVecTwoFirst, kVecTwoFirst + 1}) {
-      D.fb[sh] = D.fb[sh - 2];
-      D.shape_bytes[sh] = D.shape_bytes[sh - 2];
+    // local-column shapes 6..8 over geometries 0..2; the vector-load kernel's shapes 9 and 10 over geometries 0 and 3,
+    // and 11 and 12 the same blocks two per workgroup.  Only the geometry of a shape asked for is encoded.
+    for (int g = 0; g <= kLocalGeoms; ++g) {
+      if (an.loc[g].rb.empty()) continue;
+      const int slot = g < kLocalGeoms ? kLocalFirst + g : kLocalFirst + kLocalGeoms + 1;
+      upload_local(D, g, an.loc[g], an.rowptr, s, slot);
+      D.shape_bytes[slot] = local_bytes(an.nnz, an.n, g, an.loc[g], sv0);
+    }
+    auto same_blocks = [&](int sh, int as) {
+      D.fb[sh] = D.fb[as];
+      D.shape_bytes[sh] = D.shape_bytes[as];
+    };
+    same_blocks(kLocalFirst + kLocalGeoms, kLocalFirst);
+    for (int sh : {kVecTwoFirst, kVecTwoFirst + 1}) same_blocks(sh, sh - 2);
+    if (!an.cptr.empty()) {  // chunk shape
+      D.nchunk = an.cptr[an.n];
+      D.cptr.upload(an.cptr, s);
+      const ChunkBlocks& cb = an.chunk;
+      const size_t nb = cb.rb.size();
+      std::vector<int32_t> meta(nb * 4, 0);
+      for (size_t k = 0; k < nb; ++k) {
+        meta[4 * k] = cb.rb[k];
+        meta[4 * k + 1] = an.cptr[cb.rb[k]];
+        meta[4 * k + 2] = cb.ubp[k];
+      }
+      D.cmeta.upload(meta, s);
+      D.cucol.upload(cb.ucol, s);
+      D.clo.upload(cb.lo, s);
+      D.chi.upload(cb.hi, s);
+      R3MG_HIP_CHECK(hipStreamSynchronize(s));  // the records are released on return
+      FineBlocks& f = D.fb[kChunkShape];
+      f.nrb = (int)nb - 1;
+      f.ucol = D.cucol.p;
+      f.meta = D.cmeta.p;
+      f.cptr = D.cptr.p;
+      f.clo = D.clo.p;
+      f.chi = D.chi.p;
+      // values and positions of the chunks, distinct columns, block records, chunk offsets, 7 vector streams
+      D.shape_bytes[kChunkShape] = (double)D.nchunk * (4 * sv0 + 5) + 4.0 * cb.ucol.size() + 16.0 * nb +
+                                   4.0 * (an.n + 1) + 7.0 * an.n * sv0;
     }
     D.dinv64.alloc(D.n);
     if (fp32) {
