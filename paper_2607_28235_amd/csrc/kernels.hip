@@ -3402,35 +3402,38 @@ void launch_diag_inv(int n, int blk, const int* ptr, const int* idx, const doubl
 
 // Galerkin product, fine -> first agglomerated level (Section 4, inherited operators):
 // A1[K,K'] = sum_{i in K free} phi^K(x_i) T_i^T,  T_i[q'] = sum_{j in K' free} A_ij phi^K'_q'(x_j).
-// One 256-thread workgroup per stored output block.  The host lists, per block, the rows i of K whose sorted
-// columns meet box K' with the column run [s, e).  Eight 32-lane groups take eight entries at a time: group g
-// evaluates phi^K(x_i) and T_i into LDS; then every thread adds sum_g phi_g[q] T_g[q'] to the entries (q, q') it
-// owns.  For T_i the group's 32 lanes take 32 entries of the run at a time: each loads its entry's column, value,
-// owner and coordinates (all 32 chains in flight together) and puts the 1D tables of x_j into LDS; then lane q'
-// adds the products of those entries in the run's order.  The summation order is fixed (deterministic).  A1 is
-// symmetric, so only the blocks with K <= K' are formed (workgroup t: block up[t]) and each off-diagonal one is
-// also stored transposed as block mir[t] = (K', K).
+// The host lists, per stored output block, the rows i of K whose sorted columns meet box K' with the column run
+// [s, e).  A 256-thread workgroup takes one work item: a piece of one block's list.  Eight 32-lane groups take eight
+// entries at a time: group g evaluates phi^K(x_i) and T_i into LDS; then every thread adds sum_g phi_g[q] T_g[q'] to
+// the entries (q, q') it owns.  For T_i the group's 32 lanes take 32 entries of the run at a time: each loads its
+// entry's column, value, owner and coordinates (all 32 chains in flight together) and puts A_ij l_0 and the products
+// l_1 l_2 of x_j's 1D tables into LDS; then lane q' adds the products of those entries in the run's order.  A1 is
+// symmetric, so only the blocks with K <= K' are formed and each off-diagonal one is also stored transposed as its
+// mirror (K', K).  The summation order is fixed (deterministic): a block of several items is the sum of their partial
+// blocks in list order (k_galerkin0_sum).
+// Bound by LDS reads and latency.  A diagonal block lists nearly every row of its box (about 1,840), the others a few
+// dozen, so with one workgroup per block a level of 64 boxes kept 64 of 256 compute units busy; and the T loop read
+// five LDS words per product, now two.  3D Q2 24^3 (117,649 rows, 64 boxes, p' = 2): 3,061 -> 183 us.
+constexpr int kGalTabs(int d, int k) { return d == 3 ? k + k * k : 2 * k; }
 template <int D, int KB>
-__global__ __launch_bounds__(256) void k_galerkin0(Basis1D<double> bs, const int* __restrict__ up,
-                                                   const int* __restrict__ mir, const int* __restrict__ brow,
-                                                   const int* __restrict__ bptr, const int* __restrict__ gal_ptr,
+__global__ __launch_bounds__(256) void k_galerkin0(Basis1D<double> bs, const int4* __restrict__ item,
+                                                   const int* __restrict__ up, const int* __restrict__ mir,
+                                                   const int* __restrict__ brow, const int* __restrict__ bptr,
                                                    const int* __restrict__ gal_ent, const int* __restrict__ owner,
                                                    const double* __restrict__ xi, const int* __restrict__ col,
-                                                   const double* __restrict__ val, double* out) {
-  __shared__ double spi[8][64];
-  __shared__ double sT[8][64];
-  __shared__ double sl[8][32][12];  // per group: the 1D tables l[a][j] (at 4 a + j) of 32 entries' x_j
-  __shared__ double sv[8][32];      // their values A_ij
-  __shared__ int sf[8][32];         // their column is free (owner >= 0)
-  const int64_t blkid = up[blockIdx.x];
-  const int K = brow[blkid];
-  const int slot = (int)(blkid - bptr[K]);
-  const int nbK = bptr[K + 1] - bptr[K];
-  // dimension and degree are compile-time (lag1d_k and the digit arithmetic below unroll), with the same
-  // operations in the same order as the run-time forms
+                                                   const double* __restrict__ val, double* part, double* out) {
+  // dimension and degree are compile-time (lag1d_k and the digit arithmetic below unroll)
   constexpr int d = D, k = KB;
   constexpr int B = D == 3 ? KB * KB * KB : KB * KB;
   constexpr int EMAX = (B * B + 255) / 256;
+  constexpr int TAB = kGalTabs(D, KB);
+  constexpr int QMAX = (B + 31) / 32;
+  __shared__ double spi[8][64];
+  __shared__ double sT[8][64];
+  // per group: of 32 entries j the values A_ij l_0[.] (0 for a constrained column) and the products l_1[.] l_2[.]
+  __shared__ double sl[8][32][TAB];
+  const int4 it = item[blockIdx.x];  // block up[it.x], its entries [it.y, it.z), partial slot it.w (-1: the whole block)
+  const int64_t blkid = up[it.x];
   int qi[EMAX], qj[EMAX];
   double acc[EMAX];
 #pragma unroll
@@ -3441,7 +3444,7 @@ __global__ __launch_bounds__(256) void k_galerkin0(Basis1D<double> bs, const int
     acc[m] = 0;
   }
   const int g = threadIdx.x >> 5, lt = threadIdx.x & 31;
-  const int en0 = gal_ptr[blkid], en1 = gal_ptr[blkid + 1];
+  const int en0 = it.y, en1 = it.z;
   for (int base = en0; base < en1; base += 8) {
     const int ent = base + g;
     if (ent < en1) {
@@ -3450,15 +3453,15 @@ __global__ __launch_bounds__(256) void k_galerkin0(Basis1D<double> bs, const int
 #pragma unroll
       for (int a = 0; a < d; ++a) lag1d_k<double, KB>(bs, xi[(int64_t)i * d + a], li[a]);
       for (int q = lt; q < B; q += 32) spi[g][q] = phi_q<double>(li, d, k, q);
-      // lane lt owns q' = lt and lt + 32 (B <= 64); the digits of q' in base k pick the 1D tables
-      int qd[2][3];
-      double t[2] = {0.0, 0.0};
+      // lane lt owns q' = lt and lt + 32 (B <= 64); the digits of q' in base k pick the tables
+      int q0[QMAX], q12[QMAX];
+      double t[QMAX];
 #pragma unroll
-      for (int m = 0; m < 2; ++m) {
-        const int q = lt + 32 * m;
-        qd[m][0] = q % k;
-        qd[m][1] = 4 + (q / k) % k;
-        qd[m][2] = 8 + (q / k / k) % k;
+      for (int m = 0; m < QMAX; ++m) {
+        const int q = min(lt + 32 * m, B - 1);
+        q0[m] = q % k;
+        q12[m] = k + q / k;
+        t[m] = 0.0;
       }
       for (int p0 = s; p0 < e; p0 += 32) {
         const int p = min(p0 + lt, e - 1);  // clamped: every lane loads, the lanes past the run store nothing
@@ -3469,37 +3472,30 @@ __global__ __launch_bounds__(256) void k_galerkin0(Basis1D<double> bs, const int
 #pragma unroll
         for (int a = 0; a < d; ++a) lag1d_k<double, KB>(bs, xi[(int64_t)j * d + a], lj[a]);
         if (p0 + lt < e) {
-          sv[g][lt] = v;
-          sf[g][lt] = own >= 0;
 #pragma unroll
-          for (int a = 0; a < 3; ++a)
+          for (int a = 0; a < k; ++a) sl[g][lt][a] = own >= 0 ? v * lj[0][a] : 0.0;
 #pragma unroll
-            for (int jj = 0; jj < 4; ++jj) sl[g][lt][4 * a + jj] = lj[a][jj];
+          for (int c = 0; c < (D == 3 ? KB : 1); ++c)
+#pragma unroll
+            for (int a = 0; a < k; ++a)
+              sl[g][lt][k + c * k + a] = own < 0 ? 0.0 : D == 3 ? lj[1][a] * lj[2][c] : lj[1][a];
         }
         // the group is half a wave: its LDS writes and reads stay in program order within the wave
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         const int cnt = min(32, e - p0);
-        for (int u = 0; u < cnt; ++u) {
-          if (!sf[g][u]) continue;  // the same for all lanes of the group
-          const double vu = sv[g][u];
-          const double* L = sl[g][u];
+        const double* L = &sl[g][0][0];
+#pragma unroll 4
+        for (int u = 0; u < cnt; ++u, L += TAB)
 #pragma unroll
-          for (int m = 0; m < 2; ++m)
-            if (lt + 32 * m < B) {
-              double ph = L[qd[m][0]];  // phi_q' = l0[q0] l1[q1] (l2[q2]), in phi_q's order
-              ph *= L[qd[m][1]];
-              if (d == 3) ph *= L[qd[m][2]];
-              t[m] += vu * ph;
-            }
-        }
+          for (int m = 0; m < QMAX; ++m) t[m] += L[q0[m]] * L[q12[m]];
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
       }
 #pragma unroll
-      for (int m = 0; m < 2; ++m)
+      for (int m = 0; m < QMAX; ++m)
         if (lt + 32 * m < B) sT[g][lt + 32 * m] = t[m];
     } else {
       for (int q = lt; q < B; q += 32) {
@@ -3519,11 +3515,20 @@ __global__ __launch_bounds__(256) void k_galerkin0(Basis1D<double> bs, const int
     }
     __syncthreads();
   }
+  if (it.w >= 0) {
+#pragma unroll
+    for (int m = 0; m < EMAX; ++m)
+      if (qi[m] >= 0) part[(int64_t)it.w * B * B + threadIdx.x + m * 256] = acc[m];
+    return;
+  }
+  const int K = brow[blkid];
+  const int slot = (int)(blkid - bptr[K]);
+  const int nbK = bptr[K + 1] - bptr[K];
   const int64_t obase = (int64_t)B * B * bptr[K];
 #pragma unroll
   for (int m = 0; m < EMAX; ++m)
     if (qi[m] >= 0) out[obase + (int64_t)qi[m] * nbK * B + (int64_t)slot * B + qj[m]] = acc[m];
-  const int mb = mir[blockIdx.x];
+  const int mb = mir[it.x];
   if (mb >= 0) {  // uniform over the workgroup
     const int Km = brow[mb], slm = mb - bptr[Km], nbm = bptr[Km + 1] - bptr[Km];
     const int64_t mbase = (int64_t)B * B * bptr[Km];
@@ -3533,14 +3538,38 @@ __global__ __launch_bounds__(256) void k_galerkin0(Basis1D<double> bs, const int
   }
 }
 
-void launch_galerkin0(int64_t nup, int d, int pc, const int* up, const int* mir, const int* brow, const int* bptr,
-                      const int* gal_ptr, const int* gal_ent, const int* owner, const double* xi, const int* col,
+// the blocks of several items: multi[t] = (index into up, first partial slot, number of partials)
+__global__ __launch_bounds__(256) void k_galerkin0_sum(int B, const int4* __restrict__ multi, const int* __restrict__ up,
+                                                       const int* __restrict__ mir, const int* __restrict__ brow,
+                                                       const int* __restrict__ bptr, const double* __restrict__ part,
+                                                       double* out) {
+  const int4 w = multi[blockIdx.x];
+  const int blkid = up[w.x], mb = mir[w.x];
+  const int K = brow[blkid], slot = blkid - bptr[K], nbK = bptr[K + 1] - bptr[K];
+  const int64_t obase = (int64_t)B * B * bptr[K];
+  for (int e = threadIdx.x; e < B * B; e += 256) {
+    const double* P = part + (int64_t)w.y * B * B + e;
+    double t = 0;
+#pragma unroll 4
+    for (int c = 0; c < w.z; ++c) t += P[(int64_t)c * B * B];
+    const int q = e / B, q2 = e - q * B;
+    out[obase + (int64_t)q * nbK * B + (int64_t)slot * B + q2] = t;
+    if (mb >= 0) {
+      const int Km = brow[mb], slm = mb - bptr[Km], nbm = bptr[Km + 1] - bptr[Km];
+      out[(int64_t)B * B * bptr[Km] + (int64_t)q2 * nbm * B + (int64_t)slm * B + q] = t;
+    }
+  }
+}
+
+void launch_galerkin0(const GalerkinWork& w, int d, int pc, const int* up, const int* mir, const int* brow,
+                      const int* bptr, const int* gal_ent, const int* owner, const double* xi, const int* col,
                       const double* val, double* out, hipStream_t s) {
   Basis1D<double> bs = make_basis<double>(pc);
-  if (nup == 0) return;
-#define R3MG_G0(DD, KK)                                                                                             \
-  hipLaunchKernelGGL((k_galerkin0<DD, KK>), dim3((unsigned)nup), dim3(256), 0, s, bs, up, mir, brow, bptr, gal_ptr,  \
-                     gal_ent, owner, xi, col, val, out)
+  if (w.nitem == 0) return;
+  const int4* item = reinterpret_cast<const int4*>(w.item);
+#define R3MG_G0(DD, KK)                                                                                              \
+  hipLaunchKernelGGL((k_galerkin0<DD, KK>), dim3((unsigned)w.nitem), dim3(256), 0, s, bs, item, up, mir, brow, bptr, \
+                     gal_ent, owner, xi, col, val, w.part, out)
   switch (d * 8 + pc + 1) {
     case 17: R3MG_G0(2, 1); break;
     case 18: R3MG_G0(2, 2); break;
@@ -3553,6 +3582,11 @@ void launch_galerkin0(int64_t nup, int d, int pc, const int* up, const int* mir,
     default: throw std::runtime_error("Galerkin product: unsupported dimension or degree");
   }
 #undef R3MG_G0
+  if (w.nmulti > 0) {
+    const int k = pc + 1, B = d == 3 ? k * k * k : k * k;
+    hipLaunchKernelGGL(k_galerkin0_sum, dim3((unsigned)w.nmulti), dim3(256), 0, s, B,
+                       reinterpret_cast<const int4*>(w.multi), up, mir, brow, bptr, w.part, out);
+  }
   check_launch("k_galerkin0");
 }
 

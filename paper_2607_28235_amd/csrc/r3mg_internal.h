@@ -249,7 +249,10 @@ struct DevLevel {
   DBuf<int32_t> owner;   // l = 0: n (level-1 box of each point, -1 if constrained)
   DBuf<int32_t> leaf_off;  // l = 0: nbox1 + 1 internal offsets of the level-1 boxes
   DBuf<int32_t> brow;    // l >= 1 during set-up: block -> block row
-  DBuf<int32_t> gal_ptr, gal_ent;  // l = 1: Galerkin work lists
+  DBuf<int32_t> gal_ent;  // l = 1: Galerkin work lists
+  DBuf<int32_t> gal_item, gal_multi;  // l = 1: work items and split blocks (GalerkinWork)
+  DBuf<double> gal_part;
+  GalerkinWork gal;
   DBuf<int32_t> gal_up, gal_mir;   // l = 1: the blocks formed and their mirrors
   DBuf<double> pt64;     // l >= 1 (l < L): nbox x d x (p'+1)^2
   DBuf<float> pt32;

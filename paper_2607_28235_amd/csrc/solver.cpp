@@ -895,8 +895,8 @@ void numeric_setup(HandleImpl& h, hipStream_t s) {
     const int64_t nblk = H.bptr[H.nbox];
     if (l == 1) {
       DevLevel& F0 = dv.lv[0];
-      launch_galerkin0((int64_t)an.gal_up.size(), an.d, an.pc, D.gal_up.p, D.gal_mir.p, D.brow.p, D.bptr.p,
-                       D.gal_ptr.p, D.gal_ent.p, F0.owner.p, F0.xi64.p, F0.col.p, F0.val64.p, D.val64.p, s);
+      launch_galerkin0(D.gal, an.d, an.pc, D.gal_up.p, D.gal_mir.p, D.brow.p, D.bptr.p, D.gal_ent.p, F0.owner.p,
+                       F0.xi64.p, F0.col.p, F0.val64.p, D.val64.p, s);
     } else {
       DevLevel& P = dv.lv[l - 1];
       launch_galerkin_c(nblk, an.d, an.pc, H.child_shift, (int)P.nbox, D.brow.p, D.bptr.p, D.bcol.p, P.bptr.p,
@@ -1128,6 +1128,38 @@ static int keep_rule(const r3mg_options& o, double bytes) {
   return bytes <= kKeepCachedBytes ? F_KEEP : 0;
 }
 
+// Work items of the fine-level Galerkin product.  A block's entry list is cut into pieces of at most `piece` entries,
+// a multiple of the eight entries a workgroup takes at a time: about 2,048 pieces in all (eight workgroups on each of
+// the 256 compute units), but no piece below 64 entries (each one costs a partial block of B^2 values, written and
+// read back) or above 512 (the balance of large levels).  A function of the structure only.
+static void upload_galerkin_items(const Analysis& an, DevLevel& D, hipStream_t s) {
+  int64_t total = 0;
+  for (int32_t b : an.gal_up) total += an.gal_ptr[b + 1] - an.gal_ptr[b];
+  const int64_t piece = std::min<int64_t>(512, std::max<int64_t>(64, (total / 2048 + 7) / 8 * 8));
+  std::vector<int32_t> item, multi;
+  int32_t slots = 0;
+  for (size_t t = 0; t < an.gal_up.size(); ++t) {
+    const int32_t e0 = an.gal_ptr[an.gal_up[t]], e1 = an.gal_ptr[an.gal_up[t] + 1];
+    const int32_t np = (int32_t)std::max<int64_t>(1, (e1 - e0 + piece - 1) / piece);
+    for (int32_t q = 0; q < np; ++q) {
+      const int32_t a = e0 + (int32_t)(q * piece), b = std::min<int32_t>(e1, a + (int32_t)piece);
+      for (int32_t w : {(int32_t)t, a, b, np > 1 ? slots + q : -1}) item.push_back(w);
+    }
+    if (np == 1) continue;
+    for (int32_t w : {(int32_t)t, slots, np, 0}) multi.push_back(w);
+    slots += np;
+  }
+  D.gal_item.upload(item, s);
+  D.gal_multi.upload(multi, s);
+  D.gal_part.alloc((size_t)slots * an.B * an.B);
+  R3MG_HIP_CHECK(hipStreamSynchronize(s));  // the host lists are released on return
+  D.gal.nitem = (int64_t)item.size() / 4;
+  D.gal.nmulti = (int64_t)multi.size() / 4;
+  D.gal.item = D.gal_item.p;
+  D.gal.multi = D.gal_multi.p;
+  D.gal.part = D.gal_part.p;
+}
+
 void device_setup(HandleImpl& h, hipStream_t s) {
   Analysis& an = *h.an;
   h.dev = std::make_unique<Device>();
@@ -1239,10 +1271,10 @@ void device_setup(HandleImpl& h, hipStream_t s) {
       for (int64_t j = H.bptr[k]; j < H.bptr[k + 1]; ++j) br[j] = (int32_t)k;
     D.brow.upload(br, s);
     if (l == 1) {
-      D.gal_ptr.upload(an.gal_ptr, s);
       D.gal_ent.upload(an.gal_ent, s);
       D.gal_up.upload(an.gal_up, s);
       D.gal_mir.upload(an.gal_mir, s);
+      upload_galerkin_items(an, D, s);
     }
     D.val64.alloc((size_t)D.nnz + kFinePad);  // zero padding: the local-column kernel's vector loads
     R3MG_HIP_CHECK(hipMemsetAsync(D.val64.p, 0, D.val64.n * sizeof(double), s));
