@@ -3915,132 +3915,150 @@ __device__ inline void dt_pin(const double (&old)[2][2][4]) {
       for (int r = 0; r < 4; ++r) asm volatile("" ::"v"(old[s][t][r]));
 }
 
-// sum over m in [m0, m1) of x[m sx] y[m sy] from LDS, in eight interleaved partial sums combined in a fixed
-// order, so that the loads of eight terms are in flight together
-__device__ inline double dt_dot8(const double* x, int sx, const double* y, int sy, int m0, int m1) {
-  double a[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  int m = m0;
-  for (; m + 8 <= m1; m += 8)
+// 1. Diagonal tile k0: L with A_kk = L L^T (back to A, zero above the diagonal) and D = L^{-1} (to Dk, 64 x 64), by
+// four waves, in four panels of 16 columns.
+//   Panel: wave 0, lane l holding row l of the panel in registers, right-looking: column j is scaled by
+//   1 / sqrt(pivot) and subtracted from the columns after it, the pivot and the factors L[c][j] coming from other
+//   lanes by v_readlane.  Meanwhile waves 1 to 3 form the off-diagonal 16 x 16 blocks of the D row before.
+//   Then waves 0 to 2 subtract the panel's products from the lower tiles behind it on the FP64 matrix cores, and
+//   wave 3 inverts the panel's diagonal block (lane c: column c, by forward substitution).
+// D_ij = -D_ii sum_{j <= k < i} L_ik D_kj, two chains of matrix instructions per block.
+// Bound by the chain of 64 pivots, one after another (a reciprocal square root, a product, a lane read and a
+// subtraction each), on one compute unit.  The earlier form (left-looking, a dot product from LDS, a square root, a
+// shuffle and a division per column) took 38 us a tile on a 1,728-row level (27 tiles); this one 24 us.
+constexpr int kDiagLD = DT + 1;  // odd row stride in doubles: rows across the lanes spread over the banks
+constexpr int kDiagP = 16;       // panel width
+
+__device__ __forceinline__ double lane_value(double v, int lane) {  // lane: uniform
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                          __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+
+// a / g from y = 1 / g, corrected by the residual
+__device__ __forceinline__ double diag_div(double a, double g, double y) {
+  const double q = a * y;
+  return fma(fma(-q, g, a), y, q);
+}
+
+// 16 x 16 tile product over LDS: C += sum over m < 16 of a[i * kDiagLD + m] B(m, j), B(m, j) = b[m * kDiagLD + j], or
+// b[j * kDiagLD + m] with TB.  Lane l holds C[4 r + l / 16][l % 16], r < 4 (see dt_mfma).
+template <bool TB>
+__device__ __forceinline__ v4d diag_mfma16(const double* a, const double* b, v4d c) {
+  const int li = threadIdx.x & 15, lk = (threadIdx.x & 63) >> 4;
 #pragma unroll
-    for (int u = 0; u < 8; ++u) a[u] += x[(m + u) * sx] * y[(m + u) * sy];
-  for (int u = 0; m < m1; ++m, ++u) a[u] += x[m * sx] * y[m * sy];
-  return ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
+  for (int m = 0; m < kDiagP; m += 4) {
+    const double av = a[li * kDiagLD + m + lk];
+    const double bv = TB ? b[li * kDiagLD + m + lk] : b[(m + lk) * kDiagLD + li];
+    c = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, c, 0, 0, 0);
+  }
+  return c;
 }
 
-// 1. Diagonal tile k0, by two waves.  Wave 0: Cholesky by columns (left-looking): lane l keeps row l of the tile
-// in registers, and the rows of L go to LDS as they become final (zero elsewhere), so that step j reads row j of L
-// as 16-byte broadcasts and each lane forms its dot product with its own registers; segments of eight entries that
-// are still zero are not read.  Wave 1: the inverse D = L^{-1} by rows of D: lane l keeps column l of D in
-// registers (zero above the diagonal), so that row i of D needs row i of L only, which is final once column i is;
-// so wave 1 forms row j - 1 of D while wave 0 forms column j of L.  L goes back to A (zero above the diagonal), D
-// to Dk (64 x 64, zero above the diagonal).  The steps are generated by template recursion, so every register
-// index is a constant; the pivots' square roots are broadcast with a lane shuffle, and one barrier per step orders
-// the LDS rows.  (Forming row J of D in the same step as column J of L in one wave needed 387 registers and ran
-// slower.)
-constexpr int kDiagLD = DT + 2;  // LDS row stride: 16-byte aligned rows, 4-way conflicts at most for row-per-lane reads
-
-// sum over m < 8 ceil(J / 8) of x[m] w[m] (w: an LDS row whose entries from J on are zero), in two interleaved
-// partial sums (four ran slower)
-template <int J, bool XW>
-__device__ __forceinline__ double diag_dot(const double (&x)[DT], const double* w) {
-  double a0 = 0.0, a1 = 0.0;
+// off-diagonal block (i, j) of D, by one wave (its own block of t holds the intermediate sum)
+__device__ __forceinline__ void diag_inv_block(const double* s, double* t, int i, int j) {
+  const int li = threadIdx.x & 15, lk = (threadIdx.x & 63) >> 4;
+  v4d c = {0.0, 0.0, 0.0, 0.0};
+  for (int k = j; k < i; ++k)
+    c = diag_mfma16<false>(s + kDiagP * i * kDiagLD + kDiagP * k, t + kDiagP * k * kDiagLD + kDiagP * j, c);
+  double* q = t + kDiagP * i * kDiagLD + kDiagP * j;
 #pragma unroll
-  for (int c = 0; c < (J + 7) / 8; ++c)
+  for (int r = 0; r < 4; ++r) q[(4 * r + lk) * kDiagLD + li] = c[r];
+  // the wave's LDS writes and reads stay in program order
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  c = diag_mfma16<false>(t + kDiagP * i * (kDiagLD + 1), q, v4d{0.0, 0.0, 0.0, 0.0});
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 #pragma unroll
-    for (int t = 0; t < 8; t += 2) {
-      const double2 v = *reinterpret_cast<const double2*>(w + 8 * c + t);
-      if (XW) {
-        a0 += x[8 * c + t] * v.x;
-        a1 += x[8 * c + t + 1] * v.y;
-      } else {
-        a0 += v.x * x[8 * c + t];
-        a1 += v.y * x[8 * c + t + 1];
-      }
-    }
-  return a0 + a1;
+  for (int r = 0; r < 4; ++r) q[(4 * r + lk) * kDiagLD + li] = -c[r];
 }
 
-// column J of L (left-looking): lane l >= J finishes L[l][J] and puts it in LDS
-template <int J>
-__device__ __forceinline__ void diag_chol_col(double (&r)[DT], double* s, int l, int* bad) {
-  const double acc = diag_dot<J, true>(r, s + J * kDiagLD);  // sum over m < J of L[l][m] L[J][m]
-  double piv = r[J] - acc;  // left-looking: r[J] still holds the tile's entry
-  if (l == J && !(piv > 0.0)) {
-    *bad = 1;
-    piv = 1.0;
-  }
-  const double ljj = __shfl(sqrt(piv), J, 64);
-  if (l >= J) {
-    const double v = (l == J) ? ljj : (r[J] - acc) / ljj;
-    s[l * kDiagLD + J] = v;
-    r[J] = v;
-  }
-}
-
-// row I of D = L^{-1} (column l of D in lane l): d[I][l] = -(sum over l <= m < I of L[I][m] d[m][l]) / L[I][I]
-// (I > l), 1 / L[I][I] (I = l), 0 (I < l); d[m][l] = 0 for m < l, so the sum may run over m < I.  It needs row I
-// of L only.
-template <int I>
-__device__ __forceinline__ void diag_inv_row(double (&d)[DT], const double* s, int l) {
-  const double* ri = s + I * kDiagLD;
-  const double acc = diag_dot<I, false>(d, ri);
-  const double lii = ri[I];
-  d[I] = (I < l) ? 0.0 : (I == l) ? 1.0 / lii : -acc / lii;
-}
-
-// Step J of the two waves: wave 0 forms column J of L, wave 1 row J - 1 of D (row J - 1 of L is final after
-// column J - 1); one barrier per step orders the LDS rows.
-template <int J>
-struct DiagSteps {
-  static __device__ __forceinline__ void run(double (&r)[DT], double (&d)[DT], double* s, int l, bool w0, int* bad) {
-    if constexpr (J <= DT) {
-      if (w0) {
-        if constexpr (J < DT) diag_chol_col<J>(r, s, l, bad);
-      } else {
-        if constexpr (J > 0) diag_inv_row<J - 1>(d, s, l);
-      }
-      if constexpr (J < DT) __syncthreads();
-      DiagSteps<J + 1>::run(r, d, s, l, w0, bad);
-    }
-  }
-};
-
-__global__ __launch_bounds__(128) void k_dchol_diag(int n, int k0, double* A, double* Dk, int* bad) {
-  __shared__ __align__(16) double s[DT * kDiagLD];
-  const int l = threadIdx.x & 63;
-  const bool w0 = threadIdx.x < 64;
+__global__ __launch_bounds__(256) void k_dchol_diag(int n, int k0, double* A, double* Dk, int* bad) {
+  __shared__ double s[DT * kDiagLD];  // the tile, then L
+  __shared__ double t[DT * kDiagLD];  // D
+  __shared__ double ivs[DT];          // 1 / L[j][j]
+  const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
   {
-    // rows 2 q + w, column l of the tile: all 32 loads of a lane from clamped addresses first, entries outside
-    // the matrix masked afterwards (identity there)
-    const int w = threadIdx.x >> 6;
-    double v[DT / 2];
-    const int64_t cl = min(k0 + l, n - 1);
+    double v[kDtK];
+    dt_fetch(v, A, n, k0, k0);
 #pragma unroll
-    for (int q = 0; q < DT / 2; ++q) v[q] = A[(int64_t)min(k0 + 2 * q + w, n - 1) * n + cl];
-#pragma unroll
-    for (int q = 0; q < DT / 2; ++q) {
-      const int i = 2 * q + w;
+    for (int q = 0; q < kDtK; ++q) {
+      const int i = w + 4 * q;
       s[i * kDiagLD + l] = (k0 + i < n && k0 + l < n) ? v[q] : (i == l) ? 1.0 : 0.0;
+      t[i * kDiagLD + l] = 0.0;
     }
   }
   __syncthreads();
-  double r[DT];
+  for (int p = 0; p < DT / kDiagP; ++p) {
+    const int c0 = kDiagP * p;
+    if (w == 0) {
+      double r[kDiagP];
 #pragma unroll
-  for (int m = 0; m < DT; ++m) r[m] = s[l * kDiagLD + m];
-  __syncthreads();
-  for (int e = threadIdx.x; e < DT * kDiagLD; e += 128) s[e] = 0.0;
-  __syncthreads();
-  double d[DT];
+      for (int c = 0; c < kDiagP; ++c) r[c] = s[l * kDiagLD + c0 + c];
 #pragma unroll
-  for (int m = 0; m < DT; ++m) d[m] = 0.0;
-  DiagSteps<0>::run(r, d, s, l, w0, bad);
-  if (!w0) {
+      for (int j = 0; j < kDiagP; ++j) {
+        double piv = lane_value(r[j], c0 + j);
+        if (!(piv > 0.0)) {
+          if (l == 0) *bad = 1;
+          piv = 1.0;
+        }
+        // g = sqrt(piv), y = 1 / g and the quotients r / g, each corrected by its residual (as accurate as a square
+        // root and divisions, without their chains)
+        const double y0 = rsqrt(piv);
+        const double g0 = piv * y0, g = fma(fma(-g0, g0, piv), 0.5 * y0, g0);
+        const double y = fma(fma(-g, y0, 1.0), y0, y0);
+        const double lj = l < c0 + j ? 0.0 : l == c0 + j ? g : diag_div(r[j], g, y);
+        r[j] = lj;
+        if (l == 0) ivs[c0 + j] = y;
 #pragma unroll
-    for (int i = 0; i < DT; ++i) Dk[i * DT + l] = d[i];
+        for (int c = j + 1; c < kDiagP; ++c) r[c] -= lj * lane_value(lj, c0 + c);
+      }
+#pragma unroll
+      for (int c = 0; c < kDiagP; ++c) s[l * kDiagLD + c0 + c] = r[c];
+    } else if (w <= p - 1) {
+      diag_inv_block(s, t, p - 1, w - 1);  // row p - 1 of D
+    }
+    __syncthreads();
+    if (w == 3) {
+      // D_pp: lane c < 16 solves L_pp d = e_c
+      const int c = l & 15;
+      double e[kDiagP];
+#pragma unroll
+      for (int i = 0; i < kDiagP; ++i) e[i] = i == c ? 1.0 : 0.0;
+#pragma unroll
+      for (int j = 0; j < kDiagP; ++j) {
+        e[j] = diag_div(e[j], s[(c0 + j) * kDiagLD + c0 + j], ivs[c0 + j]);
+#pragma unroll
+        for (int i = j + 1; i < kDiagP; ++i) e[i] -= s[(c0 + i) * kDiagLD + c0 + j] * e[j];
+      }
+      if (l < kDiagP) {
+#pragma unroll
+        for (int i = 0; i < kDiagP; ++i) t[(c0 + i) * kDiagLD + c0 + c] = e[i];
+      }
+    } else {
+      // lower tiles (a, b) behind the panel, p < b <= a < 4, dealt to waves 0 to 2
+      int q = 0;
+      for (int a = p + 1; a < DT / kDiagP; ++a)
+        for (int b = p + 1; b <= a; ++b, ++q) {
+          if (q % 3 != w) continue;
+          const v4d c = diag_mfma16<true>(s + kDiagP * a * kDiagLD + c0, s + kDiagP * b * kDiagLD + c0,
+                                          v4d{0.0, 0.0, 0.0, 0.0});
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            s[(kDiagP * a + 4 * r + (l >> 4)) * kDiagLD + kDiagP * b + (l & 15)] -= c[r];
+        }
+    }
+    __syncthreads();
   }
-  for (int e = threadIdx.x; e < DT * DT; e += 128) {
-    const int i = e >> 6, j = e & 63;
-    if (k0 + i < n && k0 + j < n) A[(int64_t)(k0 + i) * n + k0 + j] = s[i * kDiagLD + j];
+  if (w >= 1) diag_inv_block(s, t, DT / kDiagP - 1, w - 1);  // the last row of D
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < kDtK; ++q) {
+    const int i = w + 4 * q;
+    Dk[i * DT + l] = t[i * kDiagLD + l];
+    if (k0 + i < n && k0 + l < n) A[(int64_t)(k0 + i) * n + k0 + l] = s[i * kDiagLD + l];
   }
 }
 
@@ -4217,7 +4235,7 @@ void dense_cholesky_inverse(int n, double* A, double* Inv, double* ws, double* Y
   for (int kb = 0; kb < nt; ++kb) {
     const int k0 = kb * DT;
     double* Dk = ws + (size_t)kb * DT * DT;
-    hipLaunchKernelGGL(k_dchol_diag, dim3(1), dim3(128), 0, s, n, k0, A, Dk, bad);
+    hipLaunchKernelGGL(k_dchol_diag, dim3(1), dim3(256), 0, s, n, k0, A, Dk, bad);
     const int below = nt - kb - 1;
     if (below > 0) {
       hipLaunchKernelGGL(k_dchol_panel, dim3(below), dim3(256), 0, s, n, k0, A, Dk);
