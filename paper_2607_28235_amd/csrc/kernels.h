@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <vector>
 
 namespace r3mg {
 
@@ -298,10 +299,16 @@ template <typename T>
 bool launch_level_lmr(const MrBlocks& mb, const LevelOp<T>& op, int nr, bool pipelined, const T* u, const T* b,
                       T* rho, T* x, T* dout, double c1, double c2, int flags, const int* skip, hipStream_t s);
 // partial sums of w_i x_i y_i (w may be null) -> partials (returns count)
-int launch_dot(int64_t n, const double* w, const double* x, const double* y, double* partials, hipStream_t s);
 void launch_axpby(int64_t n, double a, const double* x, double b, double* y, hipStream_t s);   // y = a x + b y
-void launch_lanczos_u(int64_t n, const double* dinv, const double* Av, double beta_prev, const double* vprev,
-                      double* u, hipStream_t s);  // u = dinv*Av - beta_prev*vprev
+// Lanczos steps in the D inner product (diag = D), at most kLanczosBlocks blocks and twice as many partials.
+// normalise: v /= ||v||_D.  step: w = D^{-1} Av - beta_prev vprev, alpha = <w, v>_D, w -= alpha v, beta = ||w||_D and
+// vprev := w / beta, the next v (last: alpha only; first: no beta_prev term).  alpha, beta, beta_prev: device.
+constexpr int kLanczosBlocks = 1024;
+void launch_lanczos_normalise(int64_t n, const double* diag, double* v, double* partials, hipStream_t s);
+void launch_lanczos_step(int64_t n, const double* dinv, const double* diag, const double* Av, const double* v,
+                         double* vprev, bool first, bool last, double* w, const double* beta_prev, double* alpha,
+                         double* beta, double* partials, hipStream_t s);
+ // u = dinv*Av - beta_prev*vprev
 
 // ---- matrix-free fine operator: the Q_p Laplace stiffness action on multilinear cells ----
 // 1D tables of the cell kernel: B[q][i] = l_i(g_q) and G[q][i] = l_i'(g_q) for the Lagrange basis l_i on the
@@ -345,7 +352,19 @@ void launch_mf_apply_mr(const MfOp& m, int nr, const MfTables<T>& tb, const T* g
 // Dense Cholesky factorisation A = L L^T (lower, in place, row-major n x n) and inverse A^{-1} = L^{-T} L^{-1}
 // into Inv (full), in 64 x 64 tiles on the FP64 matrix cores; *bad set on a non-positive pivot.  ws: ceil(n/64)
 // x 64 x 64 doubles (inverted diagonal tiles); Y: n x n doubles of scratch (L^{-1}).
-void dense_cholesky_inverse(int n, double* A, double* Inv, double* ws, double* Y, int* bad, hipStream_t s);
+struct DenseLookAhead {  // the factorisation's second stream and its events, kept between factorisations of a handle
+  hipStream_t s2 = nullptr;
+  std::vector<hipEvent_t> ev;
+  size_t next = 0;
+  DenseLookAhead() = default;
+  DenseLookAhead(const DenseLookAhead&) = delete;
+  DenseLookAhead& operator=(const DenseLookAhead&) = delete;
+  ~DenseLookAhead();
+  void prepare(size_t count);
+  hipEvent_t event();
+};
+void dense_cholesky_inverse(int n, double* A, double* Inv, double* ws, double* Y, int* bad, DenseLookAhead& la,
+                            hipStream_t s);
 
 // PCG (float64).  Each reduction is a vector kernel storing per-block partial sums (at most kPcgBlocks blocks,
 // a partition that depends only on n and nr, so the iterates do not depend on the kernel that formed A p)

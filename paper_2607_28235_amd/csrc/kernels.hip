@@ -3729,24 +3729,6 @@ void launch_lanczos_start(int n, const int* perm, double* v, hipStream_t s) {
   check_launch("k_lanczos_start");
 }
 
-// per-block partial sums of w_i x_i y_i (fixed grid of at most 1024 blocks, grid-stride)
-__global__ __launch_bounds__(256) void k_dot(int64_t n, const double* __restrict__ w, const double* __restrict__ x,
-                                             const double* __restrict__ y, double* partials) {
-  __shared__ double sh[4];
-  double acc = 0;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
-    acc += (w ? w[i] : 1.0) * x[i] * y[i];
-  double t = block_sum256(acc, sh);
-  if (threadIdx.x == 0) partials[blockIdx.x] = t;
-}
-int launch_dot(int64_t n, const double* w, const double* x, const double* y, double* partials, hipStream_t s) {
-  int64_t g = (n + 255) / 256;
-  if (g > 1024) g = 1024;
-  if (g < 1) g = 1;
-  hipLaunchKernelGGL(k_dot, dim3((unsigned)g), dim3(256), 0, s, n, w, x, y, partials);
-  check_launch("k_dot");
-  return (int)g;
-}
 __global__ void k_axpby(int64_t n, double a, const double* __restrict__ x, double b, double* y) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i < n) y[i] = a * x[i] + b * y[i];
@@ -3754,16 +3736,6 @@ __global__ void k_axpby(int64_t n, double a, const double* __restrict__ x, doubl
 void launch_axpby(int64_t n, double a, const double* x, double b, double* y, hipStream_t s) {
   hipLaunchKernelGGL(k_axpby, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, n, a, x, b, y);
   check_launch("k_axpby");
-}
-__global__ void k_lanczos_u(int64_t n, const double* __restrict__ dinv, const double* __restrict__ Av, double bp,
-                            const double* __restrict__ vp, double* u) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < n) u[i] = dinv[i] * Av[i] - bp * vp[i];
-}
-void launch_lanczos_u(int64_t n, const double* dinv, const double* Av, double beta_prev, const double* vprev,
-                      double* u, hipStream_t s) {
-  hipLaunchKernelGGL(k_lanczos_u, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, n, dinv, Av, beta_prev, vprev, u);
-  check_launch("k_lanczos_u");
 }
 
 // =============================================================================================
@@ -4199,38 +4171,33 @@ __global__ __launch_bounds__(256) void k_dinv_gram(int n, int nt, const double* 
 // diagonal tile and panel kb + 1, which touch column kb + 1 only, overlap it.  Part 1 of step kb + 1 writes column
 // kb + 2, which part 2 of step kb also writes, so it waits for that; parts 2 follow one another on the second
 // stream.
-namespace {
-struct LookAhead {
-  hipStream_t s2 = nullptr;
-  std::vector<hipEvent_t> ev;
-  size_t next = 0;
-  ~LookAhead() {
-    for (auto e : ev) (void)hipEventDestroy(e);
-    if (s2) (void)hipStreamDestroy(s2);
-  }
-  // all events are created before the first launch, so that the host enqueues the steps ahead of the device
-  void create(size_t count) {
-    ev.reserve(count);
-    for (size_t i = 0; i < count; ++i) {
-      hipEvent_t e;
-      if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess)
-        throw std::runtime_error("dense Cholesky: event creation failed");
-      ev.push_back(e);
-    }
-  }
-  hipEvent_t event() {
-    if (next == ev.size()) throw std::runtime_error("dense Cholesky: events exhausted");
-    return ev[next++];
-  }
-};
-}  // namespace
-
-void dense_cholesky_inverse(int n, double* A, double* Inv, double* ws, double* Y, int* bad, hipStream_t s) {
-  const int nt = (n + DT - 1) / DT;
-  LookAhead la;
-  if (hipStreamCreateWithFlags(&la.s2, hipStreamNonBlocking) != hipSuccess)
+DenseLookAhead::~DenseLookAhead() {
+  for (auto e : ev) (void)hipEventDestroy(e);
+  if (s2) (void)hipStreamDestroy(s2);
+}
+// the stream and all events exist before the first launch, so that the host enqueues the steps ahead of the device
+void DenseLookAhead::prepare(size_t count) {
+  if (!s2 && hipStreamCreateWithFlags(&s2, hipStreamNonBlocking) != hipSuccess) {
+    s2 = nullptr;
     throw std::runtime_error("dense Cholesky: stream creation failed");
-  la.create(2 * (size_t)nt);
+  }
+  while (ev.size() < count) {
+    hipEvent_t e;
+    if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess)
+      throw std::runtime_error("dense Cholesky: event creation failed");
+    ev.push_back(e);
+  }
+  next = 0;
+}
+hipEvent_t DenseLookAhead::event() {
+  if (next == ev.size()) throw std::runtime_error("dense Cholesky: events exhausted");
+  return ev[next++];
+}
+
+void dense_cholesky_inverse(int n, double* A, double* Inv, double* ws, double* Y, int* bad, DenseLookAhead& la,
+                            hipStream_t s) {
+  const int nt = (n + DT - 1) / DT;
+  la.prepare(2 * (size_t)nt);
   hipEvent_t prev2 = nullptr;  // part 2 of the previous step done
   for (int kb = 0; kb < nt; ++kb) {
     const int k0 = kb * DT;
@@ -4316,6 +4283,87 @@ __device__ inline void column_totals(const double* __restrict__ part, int nb, in
   }
   column_partials<NR>(acc, sh, tot);
   __syncthreads();
+}
+
+// ---- Lanczos steps of the smoother set-up (D inner product), with alpha and beta on the device.  Each kernel ends in
+// per-block partial sums that the next one totals itself (every block the same sums in the same order), so a step is
+// the operator and three launches, and nothing is read back before the last step of the last level.  Reading each
+// reduction back cost a round trip to the host of about 40 us, 21 of them per level, against 3 to 5 us a launch.
+
+// partials of <x, y>_D
+__global__ __launch_bounds__(256) void k_lanczos_dot(int64_t n, const double* __restrict__ diag,
+                                                     const double* __restrict__ x, const double* __restrict__ y,
+                                                     double* partials) {
+  __shared__ double sh[4];
+  double acc = 0;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
+    acc += diag[i] * x[i] * y[i];
+  const double t = block_sum256(acc, sh);
+  if (threadIdx.x == 0) partials[blockIdx.x] = t;
+}
+// w = D^{-1} Av - beta vprev (vprev null: no such term); partials of <w, v>_D
+__global__ __launch_bounds__(256) void k_lanczos_w(int64_t n, const double* __restrict__ dinv,
+                                                   const double* __restrict__ Av, const double* __restrict__ beta,
+                                                   const double* __restrict__ vprev, const double* __restrict__ diag,
+                                                   const double* __restrict__ v, double* w, double* partials) {
+  __shared__ double sh[4];
+  const double bp = vprev ? *beta : 0.0;
+  double acc = 0;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+    double t = dinv[i] * Av[i];
+    if (vprev) t -= bp * vprev[i];
+    w[i] = t;
+    acc += diag[i] * t * v[i];
+  }
+  const double t = block_sum256(acc, sh);
+  if (threadIdx.x == 0) partials[blockIdx.x] = t;
+}
+// alpha = the partials' total; w -= alpha v; partials of <w, w>_D into the second half
+__global__ __launch_bounds__(256) void k_lanczos_alpha(int64_t n, const double* __restrict__ diag,
+                                                       const double* __restrict__ v, double* w, double* partials,
+                                                       double* alpha) {
+  __shared__ double sh[4];
+  __shared__ double tot[1];
+  column_totals<1>(partials, gridDim.x, 1, sh, tot);
+  const double a = tot[0];
+  if (blockIdx.x == 0 && threadIdx.x == 0) *alpha = a;
+  double acc = 0;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+    const double t = w[i] - a * v[i];
+    w[i] = t;
+    acc += diag[i] * t * t;
+  }
+  const double t = block_sum256(acc, sh);
+  if (threadIdx.x == 0) partials[kLanczosBlocks + blockIdx.x] = t;
+}
+// beta = sqrt(the total of part); v = w / beta
+__global__ __launch_bounds__(256) void k_lanczos_next(int64_t n, const double* w, const double* __restrict__ part,
+                                                      double* v, double* beta) {
+  __shared__ double sh[4];
+  __shared__ double tot[1];
+  column_totals<1>(part, gridDim.x, 1, sh, tot);
+  const double bb = sqrt(tot[0]), s = 1.0 / bb;
+  if (beta && blockIdx.x == 0 && threadIdx.x == 0) *beta = bb;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) v[i] = s * w[i];
+}
+
+static dim3 lanczos_grid(int64_t n) {
+  return dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>(kLanczosBlocks, (n + 255) / 256)));
+}
+void launch_lanczos_normalise(int64_t n, const double* diag, double* v, double* partials, hipStream_t s) {
+  hipLaunchKernelGGL(k_lanczos_dot, lanczos_grid(n), dim3(256), 0, s, n, diag, v, v, partials);
+  hipLaunchKernelGGL(k_lanczos_next, lanczos_grid(n), dim3(256), 0, s, n, v, partials, v, (double*)nullptr);
+  check_launch("k_lanczos_next");
+}
+void launch_lanczos_step(int64_t n, const double* dinv, const double* diag, const double* Av, const double* v,
+                         double* vprev, bool first, bool last, double* w, const double* beta_prev, double* alpha,
+                         double* beta, double* partials, hipStream_t s) {
+  hipLaunchKernelGGL(k_lanczos_w, lanczos_grid(n), dim3(256), 0, s, n, dinv, Av, beta_prev,
+                     first ? (const double*)nullptr : vprev, diag, v, w, partials);
+  hipLaunchKernelGGL(k_lanczos_alpha, lanczos_grid(n), dim3(256), 0, s, n, diag, v, w, partials, alpha);
+  if (!last)
+    hipLaunchKernelGGL(k_lanczos_next, lanczos_grid(n), dim3(256), 0, s, n, w, partials + kLanczosBlocks, vprev, beta);
+  check_launch("k_lanczos_step");
 }
 
 // Two one-column totals at once, each exactly as column_totals<1> forms it (pa[b * sa] and pb[b * sb], b < nb):

@@ -269,6 +269,10 @@ struct PcgScalars;  // device-side PCG state (defined in the solver)
 // a fresh value for Device::graph_epoch (unique over the process)
 uint64_t next_graph_epoch();
 
+// Scratch of the dense factorisation and inverse (two n x n arrays) kept in the handle between numeric set-ups; larger
+// ones (coarsest levels beyond about 5,800 rows) are allocated for each set-up, where the n^3 work dwarfs that.
+constexpr size_t kKeepDenseBytes = size_t(512) << 20;
+
 struct Device {
   int dev = 0;
   // changes whenever this device's captured graphs are dropped (a buffer they use was reallocated, new values,
@@ -294,7 +298,12 @@ struct Device {
   DBuf<char> state;       // PcgState
   DBuf<double> hist;      // CG coefficients and squared residual norms per iteration (PcgState::hist, rhist)
   int hist_rows = 0;
-  DBuf<int> flag;         // set-up error flag
+  // numeric set-up, kept for the next one: Lanczos vectors (diag, v, vprev, w, A v of the largest level), its alpha
+  // and beta per level and step followed by one error flag per level, and the dense factorisation's scratch (kept up
+  // to kKeepDenseBytes)
+  DBuf<double> lzv, lzs;
+  DBuf<double> dense, tiles, ybuf;
+  DenseLookAhead look;
   int64_t pcg_cap = 0;
   // graph cache: (nrhs) -> exec
   std::map<int, hipGraphExec_t> graphs;

@@ -126,15 +126,6 @@ T* vbuf(DBuf<char>& b) {
   return reinterpret_cast<T*>(b.p);
 }
 
-double host_sum(const double* dev, int cnt, hipStream_t s) {
-  std::vector<double> h(cnt);
-  R3MG_HIP_CHECK(hipMemcpyAsync(h.data(), dev, cnt * sizeof(double), hipMemcpyDeviceToHost, s));
-  R3MG_HIP_CHECK(hipStreamSynchronize(s));
-  double acc = 0;
-  for (double v : h) acc += v;
-  return acc;
-}
-
 // every kernel that writes per-block partial sums is checked against the buffer before launch
 void need_partials(Device& dv, int64_t count) {
   if (count > (int64_t)dv.partials.n)
@@ -810,44 +801,42 @@ T* vcycle_rec(Ctx& c, int l, int nr, const T* b_override, const int* skip, hipSt
 // ---------------------------------------------------------------------------------------------
 // Numeric set-up
 // ---------------------------------------------------------------------------------------------
+// error flag of level l's numeric set-up (after the Lanczos scalars)
+static int* level_flag(Device& dv, int L, int steps, int l) {
+  return reinterpret_cast<int*>(dv.lzs.p + (size_t)2 * steps * L) + l;
+}
+
+// inverse diagonal and Lanczos steps of level l, enqueued only: alpha_j and beta_j go to lzs[2 (l steps + j)]
 static void lanczos_level(Ctx& c, int l, hipStream_t s) {
   Analysis& an = c.an;
   Device& dv = c.dv;
   DevLevel& D = dv.lv[l];
   const int64_t n = D.n;
-  DBuf<double> v, vp, u, Av, diag;
-  v.alloc(n);
-  vp.alloc(n);
-  u.alloc(n);
-  Av.alloc(n);
-  diag.alloc(n);
-  // diag = 1 / dinv is recomputed exactly as the diagonal values by the diag kernel
+  const int steps = an.opt.lanczos_steps, L = an.nlevels() - 1;
+  const size_t ld = dv.lzv.n / 5;
+  double *diag = dv.lzv.p, *v = diag + ld, *vp = v + ld, *w = vp + ld, *Av = w + ld;
   LevelOp<double> op = level_op<double>(c, l);
-  R3MG_HIP_CHECK(hipMemsetAsync(dv.flag.p, 0, sizeof(int), s));
-  launch_diag_inv((int)n, op.blk, op.ptr, op.idx, op.val, D.dinv64.p, diag.p, dv.flag.p, s);
-  launch_lanczos_start((int)n, l == 0 ? dv.perm.p : nullptr, v.p, s);
-  R3MG_HIP_CHECK(hipMemsetAsync(vp.p, 0, n * sizeof(double), s));
-  DBuf<double>& part = dv.partials;
-  int np = launch_dot(n, diag.p, v.p, v.p, part.p, s);
-  double nrm = std::sqrt(host_sum(part.p, np, s));
-  launch_axpby(n, 1.0 / nrm, v.p, 0.0, v.p, s);
+  launch_diag_inv((int)n, op.blk, op.ptr, op.idx, op.val, D.dinv64.p, diag, level_flag(dv, L, steps, l), s);
+  launch_lanczos_start((int)n, l == 0 ? dv.perm.p : nullptr, v, s);
+  need_partials(dv, 2 * kLanczosBlocks);
+  launch_lanczos_normalise(n, diag, v, dv.partials.p, s);
+  double* sc = dv.lzs.p + (size_t)2 * steps * l;
+  for (int it = 0; it < steps; ++it) {
+    apply_level<double>(c, l, 1, v, nullptr, Av, nullptr, nullptr, 0, 0, F_PLAIN, nullptr, s);
+    launch_lanczos_step(n, D.dinv64.p, diag, Av, v, vp, it == 0, it + 1 == steps, w, it ? sc + 2 * it - 1 : nullptr,
+                        sc + 2 * it, sc + 2 * it + 1, dv.partials.p, s);
+    std::swap(v, vp);
+  }
+}
+
+// Chebyshev interval and coefficients of level l from its Lanczos scalars sc (host copy)
+static void cheb_level(const Analysis& an, DevLevel& D, const double* sc) {
   std::vector<double> alpha, beta;
-  double bprev = 0.0;
   const int steps = an.opt.lanczos_steps;
   for (int it = 0; it < steps; ++it) {
-    apply_level<double>(c, l, 1, v.p, nullptr, Av.p, nullptr, nullptr, 0, 0, F_PLAIN, nullptr, s);
-    launch_lanczos_u(n, D.dinv64.p, Av.p, bprev, vp.p, u.p, s);
-    np = launch_dot(n, diag.p, u.p, v.p, part.p, s);
-    const double a = host_sum(part.p, np, s);
-    launch_axpby(n, -a, v.p, 1.0, u.p, s);
-    np = launch_dot(n, diag.p, u.p, u.p, part.p, s);
-    const double bb = std::sqrt(host_sum(part.p, np, s));
-    alpha.push_back(a);
-    if (!(bb > 0.0) || it + 1 == steps) break;
-    beta.push_back(bb);
-    std::swap(v.p, vp.p);             // vp <- v
-    launch_axpby(n, 1.0 / bb, u.p, 0.0, v.p, s);  // v <- u / b
-    bprev = bb;
+    alpha.push_back(sc[2 * it]);
+    if (it + 1 == steps || !(sc[2 * it + 1] > 0.0)) break;
+    beta.push_back(sc[2 * it + 1]);
   }
   D.lam_hat = sturm_max(alpha, beta);
   D.lam_hi = an.opt.cheb_boost * D.lam_hat;
@@ -903,13 +892,18 @@ void numeric_setup(HandleImpl& h, hipStream_t s) {
                         P.bcol.p, P.val64.p, P.pt64.p, D.val64.p, s);
     }
   }
+  // everything below is enqueued without reading anything back; the Lanczos scalars and the error flags of all levels
+  // come to the host in one copy at the end
+  const int steps = an.opt.lanczos_steps;
+  size_t nmax = 0;
+  for (int l = 0; l < L; ++l) nmax = std::max(nmax, (size_t)dv.lv[l].n);
+  dv.lzv.alloc(5 * nmax);
+  const size_t nscal = (size_t)2 * steps * L, nflag = ((size_t)L + 2) / 2;
+  dv.lzs.alloc(nscal + nflag);
+  R3MG_HIP_CHECK(hipMemsetAsync(dv.lzs.p, 0, dv.lzs.n * sizeof(double), s));
   // smoother set-up on levels 0..L-1
   for (int l = 0; l < L; ++l) {
     lanczos_level(c, l, s);
-    int bad = 0;
-    R3MG_HIP_CHECK(hipMemcpyAsync(&bad, dv.flag.p, sizeof(int), hipMemcpyDeviceToHost, s));
-    R3MG_HIP_CHECK(hipStreamSynchronize(s));
-    if (bad) throw Error{R3MG_ERR_NOT_SPD, "non-positive diagonal on level " + std::to_string(l)};
     DevLevel& D = dv.lv[l];
     if (c.fp32) {
       D.val32.alloc(D.val64.n);
@@ -923,38 +917,32 @@ void numeric_setup(HandleImpl& h, hipStream_t s) {
   {
     DevLevel& D = dv.lv[L];
     dv.nc = D.n;
-    DBuf<double> dense;
-    dense.alloc((size_t)D.n * D.n);
-    R3MG_HIP_CHECK(hipMemsetAsync(dense.p, 0, (size_t)D.n * D.n * sizeof(double), s));
-    launch_to_dense((int)D.nbox, B, D.bptr.p, D.bcol.p, D.val64.p, dense.p, s);
-    dv.cinv.alloc((size_t)D.n * D.n);
-    R3MG_HIP_CHECK(hipMemsetAsync(dv.flag.p, 0, sizeof(int), s));
-    DBuf<double> tiles, ybuf;
-    tiles.alloc((size_t)((D.n + 63) / 64) * 64 * 64);
-    ybuf.alloc((size_t)D.n * D.n);
-    dense_cholesky_inverse((int)D.n, dense.p, dv.cinv.p, tiles.p, ybuf.p, dv.flag.p, s);
-    int bad = 0;
-    R3MG_HIP_CHECK(hipMemcpyAsync(&bad, dv.flag.p, sizeof(int), hipMemcpyDeviceToHost, s));
-    R3MG_HIP_CHECK(hipStreamSynchronize(s));
-    if (bad) throw Error{R3MG_ERR_NOT_SPD, "coarsest operator is not positive definite"};
+    const size_t nn = (size_t)D.n * D.n;
+    dv.dense.alloc(nn);
+    R3MG_HIP_CHECK(hipMemsetAsync(dv.dense.p, 0, nn * sizeof(double), s));
+    launch_to_dense((int)D.nbox, B, D.bptr.p, D.bcol.p, D.val64.p, dv.dense.p, s);
+    dv.cinv.alloc(nn);
+    dv.tiles.alloc((size_t)((D.n + 63) / 64) * 64 * 64);
+    dv.ybuf.alloc(nn);
+    dense_cholesky_inverse((int)D.n, dv.dense.p, dv.cinv.p, dv.tiles.p, dv.ybuf.p, level_flag(dv, L, steps, L), dv.look,
+                           s);
     // the symmetric inverse's upper tiles, read once per product by up to kDenseSymMaxNR columns (the pass-1
     // slots cost nr/16 of the bytes saved, so wider blocks keep the full inverse)
     const int nt = (int)((D.n + kDenseTile - 1) / kDenseTile);
-    dv.ct = 0;
-    dv.csym.release();
-    dv.csym32.release();
-    dv.cpart.release();
-    dv.ctile.release();
     if (nt <= kDenseSymMaxTiles) {
-      std::vector<int32_t> tl;
-      tl.reserve((size_t)nt * (nt + 1));
-      for (int I = 0; I < nt; ++I)
-        for (int J = I; J < nt; ++J) {
-          tl.push_back(I);
-          tl.push_back(J);
-        }
       const int ntiles = nt * (nt + 1) / 2;
-      dv.ctile.upload(tl, s);
+      if (dv.ct != nt) {  // once per handle: the level sizes do not change
+        std::vector<int32_t> tl;
+        tl.reserve((size_t)nt * (nt + 1));
+        for (int I = 0; I < nt; ++I)
+          for (int J = I; J < nt; ++J) {
+            tl.push_back(I);
+            tl.push_back(J);
+          }
+        dv.ctile.upload(tl, s);
+        dv.cpart.alloc((size_t)nt * nt * kDenseTile * kDenseSymMaxNR);
+        R3MG_HIP_CHECK(hipStreamSynchronize(s));  // the host list is released
+      }
       // the float32 V-cycle reads the tiles rounded to float32 (half the bytes; products still in float64)
       if (c.fp32) {
         dv.csym32.alloc((size_t)ntiles * kDenseTile * kDenseTile);
@@ -963,11 +951,22 @@ void numeric_setup(HandleImpl& h, hipStream_t s) {
         dv.csym.alloc((size_t)ntiles * kDenseTile * kDenseTile);
         launch_dense_pack_sym<double>((int)D.n, ntiles, dv.cinv.p, dv.ctile.p, dv.csym.p, s);
       }
-      dv.cpart.alloc((size_t)nt * nt * kDenseTile * kDenseSymMaxNR);
-      R3MG_HIP_CHECK(hipStreamSynchronize(s));
       dv.ct = nt;
     }
   }
+  std::vector<double> back(nscal + nflag);
+  R3MG_HIP_CHECK(hipMemcpyAsync(back.data(), dv.lzs.p, back.size() * sizeof(double), hipMemcpyDeviceToHost, s));
+  R3MG_HIP_CHECK(hipStreamSynchronize(s));
+  if (2 * dv.dense.n * sizeof(double) > kKeepDenseBytes) {
+    dv.dense.release();
+    dv.ybuf.release();
+    dv.tiles.release();
+  }
+  const int* flags = reinterpret_cast<const int*>(back.data() + nscal);
+  for (int l = 0; l < L; ++l)
+    if (flags[l]) throw Error{R3MG_ERR_NOT_SPD, "non-positive diagonal on level " + std::to_string(l)};
+  if (flags[L]) throw Error{R3MG_ERR_NOT_SPD, "coarsest operator is not positive definite"};
+  for (int l = 0; l < L; ++l) cheb_level(an, dv.lv[l], back.data() + (size_t)2 * steps * l);
   drop_graphs(dv);
 }
 
@@ -1169,7 +1168,6 @@ void device_setup(HandleImpl& h, hipStream_t s) {
   const int B = an.B;
   const bool fp32 = an.opt.vcycle_fp32 != 0;
   dv.lv.resize(L + 1);
-  dv.flag.alloc(1);
   dv.partials.alloc(4096);  // set-up reductions (at most 1024 partials); grown by the solvers
   dv.perm.upload(an.order, s);
   dv.src.upload(an.src, s);
