@@ -167,6 +167,13 @@ template <typename T>
 void launch_level_blockrow_wg(const LevelOp<T>& op, int maxnb, const T* u, const T* b, T* rho, T* x, T* dout,
                               double c1, double c2, int flags, const int* skip, hipStream_t s);
 
+// Agglomerated level for nr in {2, 4, 8, 16} right-hand sides on the matrix cores: boxes of 4, 8, 9, 16, 27 or 64 rows
+// with at most 64 stored blocks in a block row (k_level_box_mr).
+bool box_mr_supported(int blk, int maxnb);
+template <typename T>
+void launch_level_box_mr(const LevelOp<T>& op, int nr, const T* u, const T* b, T* rho, T* x, T* dout, double c1,
+                         double c2, int flags, const int* skip, hipStream_t s);
+
 // q = A p (float64, CSR), per-block partial <p, q> -> partials[blk * nr + k]; returns number of blocks
 int launch_spmv_dot(const LevelOp<double>& op, int nr, const double* p, double* q, double* partials,
                     const int* skip, hipStream_t s);

@@ -30,6 +30,8 @@ using hiputil::check_launch;
 using hiputil::xcd_block;
 using hiputil::xcd_grid;
 
+typedef double v4d __attribute__((ext_vector_type(4)));
+
 template <typename T>
 struct Basis1D {
   T t[4];
@@ -2304,6 +2306,173 @@ template void launch_level_blockrow_wg<float>(const LevelOp<float>&, int, const 
 template void launch_level_blockrow_wg<double>(const LevelOp<double>&, int, const double*, const double*, double*,
                                                double*, double*, double, double, int, const int*, hipStream_t);
 
+// Agglomerated levels for several right-hand sides, on the matrix cores: one workgroup per box, the box's B x w block
+// row times the w x NR gathered rows of u, as 16 x 16 x 4 products (rows of the box x columns x block-row positions).
+// The four waves take every fourth step of 4 KV positions and add their tiles in wave order through LDS; a lane's KV
+// consecutive positions (16 bytes of the matrix row) are the four k groups of KV instructions, the same for both
+// operands.  Epilogue as in k_level, operands fetched first.
+// The lanes kernel gives each lane whole positions and all NR columns, so it is a long chain of loads per lane and a
+// butterfly per column at the end; here a step is one 16-byte load, KV gathered words and KV instructions.  One
+// application, best lanes count -> this kernel: float64 with 8 columns, 9-row boxes, 9,216 rows 14.1 -> 5.7 us and
+// 2,304 rows 10.5 -> 3.9; float32 with 16 columns, 27-row boxes (3D Q3 28^3) 50.5 -> 12.1 us.  Now bound by the three
+// dependent round trips (block row, columns, u) and the launch.
+template <typename T>
+struct Mfma16;
+template <>
+struct Mfma16<float> {
+  typedef float acc __attribute__((ext_vector_type(4)));
+  typedef float load __attribute__((ext_vector_type(4), aligned(4)));
+  static constexpr int KV = 4;
+  static __device__ __forceinline__ acc mma(float a, float b, acc c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+  }
+  static __device__ __forceinline__ int row(int lane, int r) { return 4 * (lane >> 4) + r; }  // of result element r
+};
+template <>
+struct Mfma16<double> {
+  typedef v4d acc;
+  typedef double load __attribute__((ext_vector_type(2), aligned(8)));
+  static constexpr int KV = 2;
+  static __device__ __forceinline__ acc mma(double a, double b, acc c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+  }
+  static __device__ __forceinline__ int row(int lane, int r) { return 4 * r + (lane >> 4); }
+};
+
+template <typename T, int B, int NR>
+__global__ __launch_bounds__(256) void k_level_box_mr(int nbox, const int* __restrict__ bptr,
+                                                      const int* __restrict__ bcol, const T* __restrict__ val,
+                                                      const T* __restrict__ u, const T* __restrict__ b, T* rho, T* x,
+                                                      const T* __restrict__ dinv, T* dout, T c1, T c2, int flags,
+                                                      const int* __restrict__ skip) {
+  using M = Mfma16<T>;
+  constexpr int MT = (B + 15) / 16, KV = M::KV, KS = 4 * KV, UN = 2;
+  constexpr int EP = (B * NR + 255) / 256;
+  if (skip && *skip) return;
+  const int K = xcd_block(nbox);
+  if (K < 0) return;
+  __shared__ T red[4][MT * 16][NR];
+  const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int i = lane & 15, kk = lane >> 4, n = i % NR;
+  const int j0 = bptr[K], nb = bptr[K + 1] - j0, w = nb * B;
+  const int bc = bcol[j0 + min(lane, nb - 1)];  // lane j: block column j (nb <= 64)
+  // epilogue operands: the box's B x NR entries are consecutive
+  const int64_t ebase = (int64_t)K * B * NR;
+  T p_old[EP], p_u[EP], p_x[EP], p_di[EP];
+#pragma unroll
+  for (int m = 0; m < EP; ++m) {
+    const int e = min((int)threadIdx.x + 256 * m, B * NR - 1);
+    p_old[m] = p_u[m] = p_x[m] = p_di[m] = 0;
+    if (!(flags & F_PLAIN)) {
+      p_old[m] = (flags & F_RHO_FROM_B) ? b[ebase + e] : rho[ebase + e];
+      p_u[m] = u[ebase + e];
+      if (flags & F_X_ADD) p_x[m] = x[ebase + e];
+      if (flags & F_D_OUT) p_di[m] = dinv[(int64_t)K * B + e / NR];
+    }
+  }
+  const T* vrow[MT];
+#pragma unroll
+  for (int t = 0; t < MT; ++t) vrow[t] = val + (int64_t)B * B * j0 + (int64_t)min(16 * t + i, B - 1) * w;
+  typename M::acc acc[MT];
+#pragma unroll
+  for (int t = 0; t < MT; ++t) acc[t] = typename M::acc{0, 0, 0, 0};
+  const int S = (w + KS - 1) / KS;
+  for (int s0 = wv; s0 < S; s0 += 4 * UN) {
+    typename M::load av[UN][MT];
+    T uv[UN][KV];
+#pragma unroll
+    for (int h = 0; h < UN; ++h) {
+      const int k0 = (s0 + 4 * h) * KS + kk * KV;
+      // a load that starts inside the row may run past its end by KV - 1 entries (the values carry kFinePad of them)
+#pragma unroll
+      for (int t = 0; t < MT; ++t) av[h][t] = *reinterpret_cast<const typename M::load*>(vrow[t] + min(k0, w - 1));
+#pragma unroll
+      for (int q = 0; q < KV; ++q) {
+        const int k = min(k0 + q, w - 1), jb = k / B;
+        uv[h][q] = u[((int64_t)__shfl(bc, jb, 64) * B + (k - jb * B)) * NR + n];
+      }
+    }
+#pragma unroll
+    for (int h = 0; h < UN; ++h) {
+      const int k0 = (s0 + 4 * h) * KS + kk * KV;
+#pragma unroll
+      for (int q = 0; q < KV; ++q) {
+        const bool in = k0 + q < w;  // beyond the row: zero in both operands
+        const T uq = in ? uv[h][q] : (T)0;
+#pragma unroll
+        for (int t = 0; t < MT; ++t) acc[t] = M::mma(in ? av[h][t][q] : (T)0, uq, acc[t]);
+      }
+    }
+  }
+  if (i < NR) {
+#pragma unroll
+    for (int t = 0; t < MT; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) red[wv][16 * t + M::row(lane, r)][i] = acc[t][r];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int m = 0; m < EP; ++m) {
+    const int e = threadIdx.x + 256 * m;
+    if (e >= B * NR) continue;
+    const int q = e / NR, c = e % NR;
+    const T t = (red[0][q][c] + red[1][q][c]) + (red[2][q][c] + red[3][q][c]);
+    const int64_t o = ebase + e;
+    if (flags & F_PLAIN) {
+      rho[o] = t;
+      continue;
+    }
+    const T r = p_old[m] - t;
+    if (flags & F_RHO_STORE) rho[o] = r;
+    if (flags & F_X_ASSIGN)
+      x[o] = p_u[m];
+    else if (flags & F_X_ADD)
+      x[o] = p_x[m] + p_u[m];
+    if (flags & F_D_OUT) dout[o] = c1 * p_u[m] + c2 * p_di[m] * r;
+  }
+}
+
+bool box_mr_supported(int blk, int maxnb) {
+  return maxnb >= 1 && maxnb <= 64 && (blk == 4 || blk == 8 || blk == 9 || blk == 16 || blk == 27 || blk == 64);
+}
+
+template <typename T, int B>
+static void launch_box_mr_b(const LevelOp<T>& op, int nr, const T* u, const T* b, T* rho, T* x, T* dout, double c1,
+                            double c2, int flags, const int* skip, hipStream_t s) {
+  const int nbox = op.n / B;
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(xcd_grid(nbox)), dim3(256), 0, s, nbox, op.ptr, op.idx, op.val, u, b, rho, x, op.dinv,
+                       dout, (T)c1, (T)c2, flags, skip);
+  };
+  switch (nr) {
+    case 2: go(k_level_box_mr<T, B, 2>); break;
+    case 4: go(k_level_box_mr<T, B, 4>); break;
+    case 8: go(k_level_box_mr<T, B, 8>); break;
+    case 16: go(k_level_box_mr<T, B, 16>); break;
+    default: throw std::runtime_error("multi-RHS box kernel: unsupported number of columns");
+  }
+}
+
+template <typename T>
+void launch_level_box_mr(const LevelOp<T>& op, int nr, const T* u, const T* b, T* rho, T* x, T* dout, double c1,
+                         double c2, int flags, const int* skip, hipStream_t s) {
+  if (op.n == 0) return;
+  switch (op.blk) {
+    case 4: launch_box_mr_b<T, 4>(op, nr, u, b, rho, x, dout, c1, c2, flags, skip, s); break;
+    case 8: launch_box_mr_b<T, 8>(op, nr, u, b, rho, x, dout, c1, c2, flags, skip, s); break;
+    case 9: launch_box_mr_b<T, 9>(op, nr, u, b, rho, x, dout, c1, c2, flags, skip, s); break;
+    case 16: launch_box_mr_b<T, 16>(op, nr, u, b, rho, x, dout, c1, c2, flags, skip, s); break;
+    case 27: launch_box_mr_b<T, 27>(op, nr, u, b, rho, x, dout, c1, c2, flags, skip, s); break;
+    case 64: launch_box_mr_b<T, 64>(op, nr, u, b, rho, x, dout, c1, c2, flags, skip, s); break;
+    default: throw std::runtime_error("multi-RHS box kernel: unsupported box size");
+  }
+  check_launch("k_level_box_mr");
+}
+template void launch_level_box_mr<float>(const LevelOp<float>&, int, const float*, const float*, float*, float*, float*,
+                                         double, double, int, const int*, hipStream_t);
+template void launch_level_box_mr<double>(const LevelOp<double>&, int, const double*, const double*, double*, double*,
+                                          double*, double, double, int, const int*, hipStream_t);
+
 // q = A p with per-block partial sums of p.q (float64 CSR)
 template <int NR>
 __global__ __launch_bounds__(256) void k_spmv_dot(int n, int G, const int* __restrict__ ptr,
@@ -3752,7 +3921,6 @@ void launch_axpby(int64_t n, double a, const double* x, double b, double* y, hip
 // and zeros elsewhere.  A non-positive pivot sets *bad (the factorisation then continues with pivot 1).
 // =============================================================================================
 constexpr int DT = 64;
-typedef double v4d __attribute__((ext_vector_type(4)));
 
 // X[i][j] = M[(R + i) n + C + j] inside the matrix, outside it 1 on the diagonal of a diagonal tile (diag_pad)
 // and 0 elsewhere; stored s[i][j], or s[j][i] with trans.  The tile product reads its operands as s[k][index]

@@ -202,6 +202,7 @@ LevelOp<T> level_op(Ctx& c, int l) {
 // float64 q = A p (with its dot products).
 constexpr int kCodeSplit = 100;
 constexpr int kCodeSplit2 = 200;
+constexpr int kCodeBox = 300;  // agglomerated levels: the box kernel on the matrix cores
 
 // the column-split kernel a code >= kCodeSplit names
 template <typename T>
@@ -356,6 +357,10 @@ void apply_level(Ctx& c, int l, int nr, const T* u, const T* b, T* rho, T* x, T*
               throw std::runtime_error("multi-RHS LDS-staged kernel: no blocks for this shape");
             break;
           }
+          if (it->second == kCodeBox) {
+            launch_level_box_mr<T>(op, nr, u, b, rho, x, dout, c1, c2, flags, skip, s);
+            break;
+          }
           if (it->second >= kCodeSplit) {  // fine level: column-split CSR kernel
             op.ptr = D.rowptr.p;
             op.idx = D.col.p;
@@ -456,7 +461,7 @@ static float time_launches(hipStream_t s, int reps, const std::function<void()>&
 // columns of element size esz (building the LDS-staged kernel's blocks when it names that kernel)
 static bool valid_mr_code(Ctx& c, int l, int nr, int esz, int code, hipStream_t s) {
   auto pow2 = [](int g, int hi) { return g >= 1 && g <= hi && (g & (g - 1)) == 0; };
-  if (l > 0) return pow2(code, 64);
+  if (l > 0) return pow2(code, 64) || (code == kCodeBox && box_mr_supported(c.an.B, c.dv.lv[l].maxnb));
   if (l < 0 && pow2(code, 8)) return true;
   if (l == 0 && pow2(code, 64)) return true;
   if (code == -1 || code == -2) return ensure_mr_blocks(c, mr_class(nr, esz), s);
@@ -504,6 +509,13 @@ static void autotune_spmm(Ctx& c, int nr, hipStream_t s) {
                         nullptr, s);
       });
       consider(G, ms, true, !fine || forced <= 0);
+    }
+    if (!fine && box_mr_supported(c.an.B, D.maxnb)) {
+      const float ms = time_launches(s, 5, [&] {
+        launch_level_box_mr<T>(op, nr, vbuf<T>(D.dA), vbuf<T>(D.b), vbuf<T>(D.rho), vbuf<T>(D.x), vbuf<T>(D.dB), 0.0, 0.0,
+                               fl, nullptr, s);
+      });
+      consider(kCodeBox, ms, true, true);
     }
     if (fine) {
       LevelOp<T> opc = op;

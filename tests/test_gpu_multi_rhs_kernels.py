@@ -1,0 +1,82 @@
+"""Multi-right-hand-side kernels forced through the tuning cache, against the lanes-per-row kernels (which the other tests
+pin to the oracle): the box kernel of the agglomerated levels for every box size and column count.
+
+Tolerances: the same products summed in another order.  The float64 V-cycle is held to 1e-11 and the float32 one to
+1e-5 (the bars of the single-column V-cycles against the oracle and of float32 rounding through a V-cycle); solves to
+1e-9 of each other.
+"""
+import dataclasses
+
+import numpy as np
+import pytest
+
+import fixtures as F
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+LANES, BOX, CHUNK = 8, 300, 400
+
+
+def _need_gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+def _vcycles(make, nrhs, path, monkeypatch, codes, n, seed=3, poison=False):
+    """V-cycle outputs (nrhs, n) with each of the given {level: code} choices, read from the tuning cache."""
+    monkeypatch.setenv("R3MG_TUNE_CACHE", str(path))
+    r = np.random.default_rng(seed).standard_normal((nrhs, n))
+    if poison:
+        r[0, n // 3], r[nrhs - 1, n // 2] = np.inf, np.nan
+    R = torch.from_numpy(r).to("cuda")
+    h = make()
+    h.vcycle(R, torch.empty_like(R))           # times every candidate once and writes the keys
+    h.close()
+    lines = [ln.rsplit(" ", 1)[0] for ln in open(path) if "/mr/" in ln]
+    out = []
+    for choice in codes:
+        with open(path, "a") as f:
+            for key in lines:
+                level = int(key.split("/mr/")[1].split("/")[0])
+                if level in choice:
+                    f.write(f"{key} {choice[level]}\n")
+        before = open(path).read()
+        h = make()
+        Z = torch.empty_like(R)
+        h.vcycle(R, Z)
+        Z2 = torch.empty_like(R)
+        h.vcycle(R, Z2)
+        torch.cuda.synchronize()
+        assert open(path).read() == before      # the forced choices were valid: nothing was timed again
+        assert torch.equal(Z.isnan(), Z2.isnan()) and torch.equal(torch.nan_to_num(Z), torch.nan_to_num(Z2))
+        out.append(Z.cpu().numpy())
+        h.close()
+    return out
+
+
+# (d, p', cells, leaf, largest coarsest level): boxes of 4, 9, 16, 8, 27 and 64 rows on at least one intermediate level
+BOXES = [(2, 1, 30, 64, 300), (2, 2, 30, 64, 300), (2, 3, 30, 100, 300), (3, 1, 10, 150, 100), (3, 2, 10, 300, 300),
+         (3, 3, 10, 700, 200)]
+
+
+@pytest.mark.parametrize("nrhs", [2, 3, 8, 16])
+@pytest.mark.parametrize("d,pc,N,leaf,mc", BOXES)
+def test_box_kernel(d, pc, N, leaf, mc, nrhs, tmp_path, monkeypatch):
+    _need_gpu()
+    import paper_2607_28235_amd as P
+    prob = F.structured_qp(d, N, 2 if d == 3 else 3, jitter=0.2 if d == 2 else 0.0, cfg=2)
+    for fp32 in (0, 1):
+        print(f"[gpu-case] box kernel d={d} p'={pc} nrhs={nrhs} fp32={fp32}", flush=True)
+        o = P.Options(dim=d, coarse_degree=pc, leaf_size=leaf, max_coarse_dofs=mc, vcycle_fp32=fp32)
+        make = lambda: P.Hierarchy(prob.coords, prob.row_ptr, prob.col, prob.val, o)  # noqa: E731
+        h = make()
+        levels = range(1, h.nlevels - 1)
+        h.close()
+        assert len(levels) >= 1
+        same = {0: LANES, -1: LANES}
+        a, b = _vcycles(make, nrhs, tmp_path / f"t{fp32}", monkeypatch,
+                        [{**same, **{l: LANES for l in levels}}, {**same, **{l: BOX for l in levels}}], prob.n)
+        for j in range(nrhs):
+            assert np.linalg.norm(a[j] - b[j]) <= (1e-5 if fp32 else 1e-11) * np.linalg.norm(a[j]), (j, fp32)
+
