@@ -653,10 +653,16 @@ static void encode_local_geom(const int32_t* rowptr, const int32_t* col, int64_t
                       out);
 }
 
-// Row blocks of the chunk kernel, as encode_local_blocks in chunks of four entries: at most kChunkRows rows,
-// kChunkCap chunks and kChunkUcap - 1 distinct columns per block; padding entries get the position of the slot after the last column.
-static void encode_chunk_blocks(const Analysis& an, ChunkBlocks& out) {
-  constexpr int cap = kChunkCap, rows = kChunkRows, ucap = kChunkUcap;
+// chunk offsets of the rows
+static void fill_cptr(Analysis& an) {
+  if (!an.cptr.empty()) return;
+  an.cptr.assign((size_t)an.n + 1, 0);
+  for (int64_t r = 0; r < an.n; ++r) an.cptr[r + 1] = an.cptr[r] + (an.rowptr[r + 1] - an.rowptr[r] + 3) / 4;
+}
+
+// Row blocks of the chunk kernels, as encode_local_blocks in chunks of four entries: at most `rows` rows, `cap` chunks
+// and `ucap` - 1 distinct columns per block; padding entries get the position of the slot after the last column.
+static void encode_chunk_blocks(const Analysis& an, int cap, int rows, int ucap, ChunkBlocks& out) {
   const int32_t *rowptr = an.rowptr.data(), *col = an.col.data(), *cptr = an.cptr.data();
   const int64_t n = an.n;
   const int64_t nseg = std::max<int64_t>(1, std::min<int64_t>(256, n / 4096));
@@ -735,6 +741,19 @@ void encode_mr_blocks(const Analysis& an, int cls, MrHost& out) {
   });
 }
 
+void encode_chunk_mr(Analysis& an, int g, ChunkMrHost& out) {
+  fill_cptr(an);
+  encode_chunk_blocks(an, kChunkMrCap[g], kChunkMrRows[g], kChunkMrUcap[g], out.cb);
+  out.ord.assign((size_t)an.n, 0);
+  parallel_for((int64_t)out.cb.rb.size() - 1, [&](int64_t k) {
+    const int32_t r0 = out.cb.rb[k], r1 = out.cb.rb[k + 1];
+    for (int32_t r = r0; r < r1; ++r) out.ord[r] = (uint8_t)(r - r0);
+    std::stable_sort(out.ord.begin() + r0, out.ord.begin() + r1, [&](uint8_t i, uint8_t j) {
+      return an.cptr[r0 + i + 1] - an.cptr[r0 + i] > an.cptr[r0 + j + 1] - an.cptr[r0 + j];
+    });
+  });
+}
+
 void encode_fine(Analysis& an) {
   encode_csr_blocks(an);
   if (an.opt.fine_kernel >= kLocalFirst) {  // a local-column shape is asked for: its blocks
@@ -743,9 +762,8 @@ void encode_fine(Analysis& an) {
     encode_local_geom(an.rowptr.data(), an.col.data(), an.n, g, an.loc[g]);
   }
   if (an.opt.fine_kernel < 0) {  // the chunk shape takes part in the set-up timing only
-    an.cptr.assign((size_t)an.n + 1, 0);
-    for (int64_t r = 0; r < an.n; ++r) an.cptr[r + 1] = an.cptr[r] + (an.rowptr[r + 1] - an.rowptr[r] + 3) / 4;
-    encode_chunk_blocks(an, an.chunk);
+    fill_cptr(an);
+    encode_chunk_blocks(an, kChunkCap, kChunkRows, kChunkUcap, an.chunk);
   }
   // agglomerated levels with narrow block rows (the 2D hierarchies): CSR row pointers and 1-byte local blocks
   const int L = an.nlevels() - 1;

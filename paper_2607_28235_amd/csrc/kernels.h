@@ -167,6 +167,24 @@ template <typename T>
 void launch_level_blockrow_wg(const LevelOp<T>& op, int maxnb, const T* u, const T* b, T* rho, T* x, T* dout,
                               double c1, double c2, int flags, const int* skip, hipStream_t s);
 
+// Fine level for nr in {2, 4, 8, 16} right-hand sides over chunked rows (k_level_chunk_mr), in two block geometries:
+// chunks, rows and distinct columns (with the zero slot) per block, and threads per workgroup.
+constexpr int kChunkMrGeoms = 2;
+constexpr int kChunkMrCap[kChunkMrGeoms] = {512, 1024};
+constexpr int kChunkMrRows[kChunkMrGeoms] = {64, 128};
+constexpr int kChunkMrUcap[kChunkMrGeoms] = {384, 640};
+constexpr int kChunkMrThreads[kChunkMrGeoms] = {256, 512};
+struct ChunkMrBlocks {
+  int geom = 0, nrb = 0;
+  const int *meta = nullptr, *ucol = nullptr, *cptr = nullptr;  // as FineBlocks of the chunk shape
+  const uint32_t* clo = nullptr;
+  const uint8_t* chi = nullptr;
+  const uint8_t* ord = nullptr;  // per row slot of a block: the block's rows by decreasing length
+};
+template <typename T>
+void launch_level_chunk_mr(const ChunkMrBlocks& cb, const LevelOp<T>& op, int nr, const T* u, const T* b, T* rho, T* x,
+                           T* dout, double c1, double c2, int flags, const int* skip, hipStream_t s);
+
 // Agglomerated level for nr in {2, 4, 8, 16} right-hand sides on the matrix cores: boxes of 4, 8, 9, 16, 27 or 64 rows
 // with at most 64 stored blocks in a block row (k_level_box_mr).
 bool box_mr_supported(int blk, int maxnb);

@@ -2306,6 +2306,223 @@ template void launch_level_blockrow_wg<float>(const LevelOp<float>&, int, const 
 template void launch_level_blockrow_wg<double>(const LevelOp<double>&, int, const double*, const double*, double*,
                                                double*, double*, double, double, int, const int*, hipStream_t);
 
+// Fine level for several right-hand sides over chunked rows (see k_level_chunk; n x NR interleaved vectors).  A workgroup
+// takes a block of at most CAPC chunks, RPB rows and UCAP - 1 distinct columns and stages its values, positions,
+// u rows (all NR columns) and row bounds in LDS, every load of the block issued at once; one barrier later each row is
+// summed by CL x NG lanes (CL chunks at a time, NG pieces of W columns), a lane reading four values, four positions and
+// four W-column pieces of u per step; the CL partial sums are added by a butterfly.  The rows of a block are taken in
+// order of decreasing length, so that the rows a wave sums together are about equally long.  Row sums pass through
+// LDS to the epilogue, whose operands were fetched first and whose accesses are consecutive.
+// One application, best of the other kernels -> this one: float32, 16 columns, 3D Q3 16^3 53.8 -> 41.8 us and 28^3
+// 243 -> 213; 8 columns, 2D Q3 200^2 44.3 -> 24.4; float64, 4 columns, 3D Q2 20^3 21.3 -> 14.1.  With 16 float64
+// columns the column-split kernel stays ahead (62 against 66 us).  At 16 float32 columns LDS is busy 46% of the time
+// (a quarter of that bank conflicts), the vector units 50%, and 16 waves per compute unit wait half of theirs: no one
+// unit bounds it, and reading two chunks a step ahead changed nothing.
+template <typename T, int NR>
+struct MrShape {
+  static constexpr int W = NR * (int)sizeof(T) >= 16 ? 16 / (int)sizeof(T) : NR;  // columns per lane
+  static constexpr int NG = NR / W;                                              // lanes per chunk
+  static constexpr int CL = NG >= 8 ? 2 : 4;                                     // chunks of a row at a time
+  typedef T vec __attribute__((ext_vector_type(W)));
+  // LDS slot of column position p.  A row of u covers 1 / C of the banks.  The entries that CL lanes read together lie
+  // four positions apart where a row's columns are consecutive, in the same part of the banks for C <= 4 (and every
+  // other one for C = 8), so the parts are rotated from one group of positions to the next.
+  static constexpr int C = 256 / (NG * W * (int)sizeof(T));
+  static __device__ __forceinline__ int slot(int p) {
+    if constexpr (C > 8 || C < 2)
+      return p;
+    else
+      return (p & ~(C - 1)) | ((p + (p >> (C == 8 ? 3 : 2))) & (C - 1));
+  }
+};
+template <typename T, int NR, int NT, int CAPC, int RPB, int UCAP, bool KEEP>
+__global__ __launch_bounds__(NT) void k_level_chunk_mr(int nrb, const int4* __restrict__ meta,
+                                                       const int* __restrict__ ucol, const uint32_t* __restrict__ clo,
+                                                       const uint8_t* __restrict__ chi, const int* __restrict__ cptr,
+                                                       const uint8_t* __restrict__ ord, const T* __restrict__ cval,
+                                                       const int* __restrict__ ptr, const int* __restrict__ idx,
+                                                       const T* __restrict__ val, const T* __restrict__ u,
+                                                       const T* __restrict__ b, T* rho, T* x,
+                                                       const T* __restrict__ dinv, T* dout, T c1, T c2, int flags,
+                                                       const int* __restrict__ skip) {
+  using V4 = typename Vec4<T>::type;
+  using MS = MrShape<T, NR>;
+  using VW = typename MS::vec;
+  constexpr int W = MS::W, NG = MS::NG, CL = MS::CL, LPR = CL * NG, RPP = NT / LPR;
+  constexpr int NCH = CAPC / NT, UPT = (UCAP * NG + NT - 1) / NT, EP = (RPB * NG + NT - 1) / NT;
+  static_assert(CAPC % NT == 0 && NT % LPR == 0, "staging shape");
+  if (skip && *skip) return;
+  const int lb = xcd_block(nrb);
+  if (lb < 0) return;
+  __shared__ VW us[UCAP * NG];
+  __shared__ V4 sv[CAPC];
+  __shared__ uint2 sp[CAPC];  // four 16-bit indices into us (of piece 0)
+  __shared__ VW st[RPB * NG];
+  __shared__ int sr[RPB + 1];
+  __shared__ uint8_t so[RPB];
+  const int4 m0 = meta[lb], m1 = meta[lb + 1];
+  const int r0 = m0.x, nr = m1.x - r0;
+  const int k0 = m0.y, nk = m1.y - k0;
+  const int u0 = m0.z, nu = m1.z - u0;
+  const bool staged = nu < UCAP && nk <= CAPC;
+  const VW* uv = reinterpret_cast<const VW*>(u);
+  // epilogue operands: the block's nr x NG pieces are consecutive
+  VW p_old[EP], p_u[EP], p_x[EP];
+  T p_di[EP];
+#pragma unroll
+  for (int m = 0; m < EP; ++m) {
+    const int e = min((int)threadIdx.x + m * NT, nr * NG - 1);
+    const int64_t o = (int64_t)r0 * NG + e;
+    p_old[m] = p_u[m] = p_x[m] = VW(0);
+    p_di[m] = 0;
+    if (!(flags & F_PLAIN)) {
+      p_old[m] = reinterpret_cast<const VW*>((flags & F_RHO_FROM_B) ? b : rho)[o];
+      p_u[m] = uv[o];
+      if (flags & F_X_ADD) p_x[m] = reinterpret_cast<const VW*>(x)[o];
+      if (flags & F_D_OUT) p_di[m] = dinv[r0 + e / NG];
+    }
+  }
+  if (staged) {
+    int uc[UPT];
+#pragma unroll
+    for (int m = 0; m < UPT; ++m) uc[m] = ucol[u0 + min(((int)threadIdx.x + m * NT) / NG, nu - 1)];  // nu >= 1
+    uint32_t lo[NCH], hi[NCH];
+    V4 vv[NCH];
+#pragma unroll
+    for (int m = 0; m < NCH; ++m) {
+      const int k = k0 + min((int)threadIdx.x + m * NT, nk - 1);
+      lo[m] = ld_matrix<KEEP>(clo + k);
+      hi[m] = ld_matrix<KEEP>(chi + k);
+      vv[m] = ld_matrix<KEEP>(reinterpret_cast<const V4*>(cval) + k);
+    }
+    const int rr = min((int)threadIdx.x, RPB);
+    const int cp = cptr[r0 + min(rr, nr)] - k0;
+    const int od = ord[r0 + min(rr, nr - 1)];
+    VW ug[UPT];
+#pragma unroll
+    for (int m = 0; m < UPT; ++m) ug[m] = uv[(int64_t)uc[m] * NG + threadIdx.x % NG];  // NT is a multiple of NG
+    // keep every load ahead of the LDS writes (the compiler would otherwise sink some of them behind others' waits)
+#pragma unroll
+    for (int m = 0; m < NCH; ++m) {
+      asm volatile("" ::"v"(lo[m]), "v"(hi[m]));
+#pragma unroll
+      for (int q = 0; q < 4; ++q) asm volatile("" ::"v"(vv[m][q]));
+    }
+#pragma unroll
+    for (int m = 0; m < NCH; ++m) {
+      const int e = threadIdx.x + m * NT;
+      sv[e] = vv[m];
+      uint32_t q[4];
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        q[v] = NG * MS::slot(((lo[m] >> (8 * v)) & 0xff) | (((hi[m] >> (2 * v)) & 3) << 8));
+      sp[e] = make_uint2(q[0] | (q[1] << 16), q[2] | (q[3] << 16));
+    }
+    if (threadIdx.x <= RPB) sr[threadIdx.x] = cp;
+    if (threadIdx.x < RPB) so[threadIdx.x] = (uint8_t)od;
+#pragma unroll
+    for (int m = 0; m < UPT; ++m) {
+      const int e = threadIdx.x + m * NT;
+      // position nu holds zero: the padding entries' position
+      if (e < UCAP * NG) us[MS::slot(e / NG) * NG + e % NG] = e < nu * NG ? ug[m] : VW(0);
+    }
+    __syncthreads();
+    const int g = threadIdx.x % NG, cl = threadIdx.x / NG % CL;
+    for (int q = threadIdx.x / LPR; q < nr; q += RPP) {
+      const int row = so[q];
+      const int ke = sr[row + 1];
+      VW acc = VW(0);
+#pragma unroll 2
+      for (int k = sr[row] + cl; k < ke; k += CL) {
+        const V4 a = sv[k];
+        const uint2 ps = sp[k];
+        acc += a[0] * us[(ps.x & 0xffff) + g];
+        acc += a[1] * us[(ps.x >> 16) + g];
+        acc += a[2] * us[(ps.y & 0xffff) + g];
+        acc += a[3] * us[(ps.y >> 16) + g];
+      }
+#pragma unroll
+      for (int off = NG; off < LPR; off <<= 1)
+#pragma unroll
+        for (int w = 0; w < W; ++w) acc[w] += __shfl_xor(acc[w], off, 64);
+      if (cl == 0) st[row * NG + g] = acc;
+    }
+  } else {  // one long row, from memory: every NG lanes take an entry, partial sums added in thread order
+    VW acc = VW(0);
+    for (int e = ptr[r0] + threadIdx.x / NG; e < ptr[r0 + 1]; e += NT / NG)
+      acc += val[e] * uv[(int64_t)idx[e] * NG + threadIdx.x % NG];
+    static_assert(UCAP * NG >= NT, "staging of the partial sums");
+    us[threadIdx.x] = acc;
+    __syncthreads();
+    if (threadIdx.x < NG) {
+      VW t = VW(0);
+      for (int q = 0; q < NT / NG; ++q) t += us[q * NG + threadIdx.x];
+      st[threadIdx.x] = t;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int m = 0; m < EP; ++m) {
+    const int e = threadIdx.x + m * NT;
+    if (e >= nr * NG) continue;
+    const int64_t o = (int64_t)r0 * NG + e;
+    const VW t = st[e];
+    if (flags & F_PLAIN) {
+      reinterpret_cast<VW*>(rho)[o] = t;
+      continue;
+    }
+    const VW r = p_old[m] - t;
+    if (flags & F_RHO_STORE) reinterpret_cast<VW*>(rho)[o] = r;
+    if (flags & F_X_ASSIGN)
+      reinterpret_cast<VW*>(x)[o] = p_u[m];
+    else if (flags & F_X_ADD)
+      reinterpret_cast<VW*>(x)[o] = p_x[m] + p_u[m];
+    if (flags & F_D_OUT) reinterpret_cast<VW*>(dout)[o] = c1 * p_u[m] + (c2 * p_di[m]) * r;
+  }
+}
+
+template <typename T, int NR, int G>
+static void launch_chunk_mr_t(const ChunkMrBlocks& cb, const LevelOp<T>& op, const T* u, const T* b, T* rho, T* x,
+                              T* dout, double c1, double c2, int flags, const int* skip, hipStream_t s) {
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(xcd_grid(cb.nrb)), dim3(kChunkMrThreads[G]), 0, s, cb.nrb,
+                       reinterpret_cast<const int4*>(cb.meta), cb.ucol, cb.clo, cb.chi, cb.cptr, cb.ord, op.cval, op.ptr,
+                       op.idx, op.val, u, b, rho, x, op.dinv, dout, (T)c1, (T)c2, flags, skip);
+  };
+  constexpr int NT = kChunkMrThreads[G], C = kChunkMrCap[G], R = kChunkMrRows[G], U = kChunkMrUcap[G];
+  if (flags & F_KEEP)
+    go(k_level_chunk_mr<T, NR, NT, C, R, U, true>);
+  else
+    go(k_level_chunk_mr<T, NR, NT, C, R, U, false>);
+}
+
+template <typename T>
+void launch_level_chunk_mr(const ChunkMrBlocks& cb, const LevelOp<T>& op, int nr, const T* u, const T* b, T* rho, T* x,
+                           T* dout, double c1, double c2, int flags, const int* skip, hipStream_t s) {
+  if (cb.nrb == 0 || !op.cval) throw std::runtime_error("multi-RHS chunk kernel: chunked matrix missing");
+#define R3MG_CMR(NRV)                                                                                    \
+  case NRV:                                                                                              \
+    if (cb.geom == 0)                                                                                    \
+      launch_chunk_mr_t<T, NRV, 0>(cb, op, u, b, rho, x, dout, c1, c2, flags, skip, s);                  \
+    else                                                                                                 \
+      launch_chunk_mr_t<T, NRV, 1>(cb, op, u, b, rho, x, dout, c1, c2, flags, skip, s);                  \
+    break;
+  switch (nr) {
+    R3MG_CMR(2)
+    R3MG_CMR(4)
+    R3MG_CMR(8)
+    R3MG_CMR(16)
+    default: throw std::runtime_error("multi-RHS chunk kernel: unsupported number of columns");
+  }
+#undef R3MG_CMR
+  check_launch("k_level_chunk_mr");
+}
+template void launch_level_chunk_mr<float>(const ChunkMrBlocks&, const LevelOp<float>&, int, const float*, const float*,
+                                           float*, float*, float*, double, double, int, const int*, hipStream_t);
+template void launch_level_chunk_mr<double>(const ChunkMrBlocks&, const LevelOp<double>&, int, const double*,
+                                            const double*, double*, double*, double*, double, double, int, const int*,
+                                            hipStream_t);
+
 // Agglomerated levels for several right-hand sides, on the matrix cores: one workgroup per box, the box's B x w block
 // row times the w x NR gathered rows of u, as 16 x 16 x 4 products (rows of the box x columns x block-row positions).
 // The four waves take every fourth step of 4 KV positions and add their tiles in wave order through LDS; a lane's KV

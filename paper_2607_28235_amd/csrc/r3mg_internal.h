@@ -94,6 +94,11 @@ struct ChunkBlocks {  // row blocks of the chunk kernel (device form: FineBlocks
   std::vector<uint8_t> hi;   // per chunk: the bits above them, 2 per position
 };
 
+struct ChunkMrHost {  // blocks of one geometry of the multi-right-hand-side chunk kernel (device form: ChunkMrBlocks)
+  ChunkBlocks cb;
+  std::vector<uint8_t> ord;  // per block, its rows in order of decreasing row length
+};
+
 struct MrHost {  // blocks of one staging class of the multi-right-hand-side kernel (device form: MrBlocks)
   LocalBlocks lb;
   std::vector<int32_t> ord;  // per block, its rows in order of decreasing row length
@@ -161,6 +166,8 @@ std::unique_ptr<Analysis> analyze(const double* coords, int64_t n, const int64_t
 void encode_fine(Analysis& an);
 // blocks of staging class cls (kMrCap / kMrRows / kMrUcap) of the multi-right-hand-side kernel over the fine level
 void encode_mr_blocks(const Analysis& an, int cls, MrHost& out);
+// blocks of geometry g of the multi-right-hand-side chunk kernel over the fine level (fills an.cptr if it is empty)
+void encode_chunk_mr(Analysis& an, int g, ChunkMrHost& out);
 
 // bisection R-tree (Section 3, Section 4 point-based agglomeration); offsets[k] per depth k
 void bisection_rtree(const double* coords, int64_t n, int d, int leaf, int& depth, std::vector<int32_t>& order,
@@ -237,6 +244,13 @@ struct DevLevel {
   DBuf<int32_t> mrb[kMrClasses], mubp[kMrClasses], mucol[kMrClasses], mord[kMrClasses], mmeta[kMrClasses];
   DBuf<uint16_t> mlidx[kMrClasses];
   MrBlocks mr[kMrClasses];
+  // l = 0: blocks of the multi-right-hand-side chunk kernel per geometry, built likewise; chunk_mr32 / chunk_mr64: a
+  // timed choice reads the chunked values in that precision
+  DBuf<int32_t> cmrmeta[kChunkMrGeoms], cmrucol[kChunkMrGeoms];
+  DBuf<uint32_t> cmrlo[kChunkMrGeoms];
+  DBuf<uint8_t> cmrhi[kChunkMrGeoms], cmrord[kChunkMrGeoms];
+  ChunkMrBlocks cmr[kChunkMrGeoms];
+  bool chunk_mr32 = false, chunk_mr64 = false;
   double shape_bytes[kStreamShapes] = {};  // algorithmic bytes of one application with each shape
   int shape = 0;        // l = 0: kernel shape chosen by timing at set-up
   int shape64 = 0;      // l = 0: shape of the float64 operator PCG applies (with a float64 V-cycle: shape)

@@ -202,12 +202,27 @@ LevelOp<T> level_op(Ctx& c, int l) {
 // float64 q = A p (with its dot products).
 constexpr int kCodeSplit = 100;
 constexpr int kCodeSplit2 = 200;
-constexpr int kCodeBox = 300;  // agglomerated levels: the box kernel on the matrix cores
+constexpr int kCodeBox = 300;    // agglomerated levels: the box kernel on the matrix cores
+constexpr int kCodeChunk = 400;  // fine level: kCodeChunk + g = the chunk kernel over blocks of geometry g
+// The chunk kernel's blocks are encoded on the host at a handle's first block solve (about 10 ms for 1.4 M nonzeros), so
+// it has to be 5% faster than a kernel over the CSR arrays.
+constexpr float kChunkMrMargin = 1.05f;
 
-// the column-split kernel a code >= kCodeSplit names
+// F_KEEP when the level's matrix stream in precision T is small enough to stay in the caches
 template <typename T>
-static bool launch_split_code(int code, const LevelOp<T>& op, int nr, const T* u, const T* b, T* rho, T* x, T* dout,
+static int keep_flag(const DevLevel& D) {
+  return sizeof(T) == 4 ? D.keep32 : D.keep64;
+}
+
+// the fine-level kernel a code >= kCodeSplit names: column-split or chunk
+template <typename T>
+static bool launch_fine_code(int code, const DevLevel& D, const LevelOp<T>& op, int nr, const T* u, const T* b, T* rho, T* x, T* dout,
                               double c1, double c2, int flags, const int* skip, hipStream_t s) {
+  if (code >= kCodeChunk) {
+    launch_level_chunk_mr<T>(D.cmr[code - kCodeChunk], op, nr, u, b, rho, x, dout, c1, c2, flags | keep_flag<T>(D), skip,
+                             s);
+    return true;
+  }
   if (code >= kCodeSplit2)
     return launch_level_split2<T>(op, nr, code - kCodeSplit2, u, b, rho, x, dout, c1, c2, flags, skip, s);
   return launch_level_split<T>(op, nr, code - kCodeSplit, u, b, rho, x, dout, c1, c2, flags, skip, s);
@@ -295,12 +310,6 @@ static bool ensure_mr_blocks(Ctx& c, int cls, hipStream_t s) {
   return true;
 }
 
-// F_KEEP when the level's matrix stream in precision T is small enough to stay in the caches
-template <typename T>
-static int keep_flag(const DevLevel& D) {
-  return sizeof(T) == 4 ? D.keep32 : D.keep64;
-}
-
 template <typename T>
 void apply_level(Ctx& c, int l, int nr, const T* u, const T* b, T* rho, T* x, T* dout, double c1, double c2, int flags,
                  const int* skip, hipStream_t s, const BoxRestrict<T>* rs = nullptr) {
@@ -361,11 +370,11 @@ void apply_level(Ctx& c, int l, int nr, const T* u, const T* b, T* rho, T* x, T*
             launch_level_box_mr<T>(op, nr, u, b, rho, x, dout, c1, c2, flags, skip, s);
             break;
           }
-          if (it->second >= kCodeSplit) {  // fine level: column-split CSR kernel
+          if (it->second >= kCodeSplit) {  // fine level: column-split or chunk kernel
             op.ptr = D.rowptr.p;
             op.idx = D.col.p;
-            if (!launch_split_code<T>(it->second, op, nr, u, b, rho, x, dout, c1, c2, flags, skip, s))
-              throw std::runtime_error("multi-RHS column-split kernel: unsupported shape");
+            if (!launch_fine_code<T>(it->second, D, op, nr, u, b, rho, x, dout, c1, c2, flags, skip, s))
+              throw std::runtime_error("multi-RHS fine-level kernel: unsupported shape");
             break;
           }
           op.lanes = it->second;
@@ -374,6 +383,76 @@ void apply_level(Ctx& c, int l, int nr, const T* u, const T* b, T* rho, T* x, T*
       launch_level<T>(op, nr, u, b, rho, x, dout, c1, c2, flags, skip, s);
     }
   }
+}
+
+// the fine level's values in chunks, in the precisions that hold a chunked copy
+static void fill_chunks(DevLevel& D, int esz, hipStream_t s) {
+  if (esz == 8 && D.cval64.p) launch_chunk_values<double>((int)D.n, D.rowptr.p, D.cptr.p, D.val64.p, D.cval64.p, s);
+  if (esz == 4 && D.cval32.p) launch_chunk_values<float>((int)D.n, D.rowptr.p, D.cptr.p, D.val32.p, D.cval32.p, s);
+}
+
+// keeps a chunked copy of the fine values for exactly the precisions in which the chosen kernels read one
+static void keep_chunks(DevLevel& D, bool fp32, hipStream_t s) {
+  const size_t count = 4 * (size_t)D.nchunk;
+  const bool want32 = fp32 && (D.shape == kChunkShape || D.chunk_mr32);
+  const bool want64 = D.shape64 == kChunkShape || D.chunk_mr64;
+  R3MG_HIP_CHECK(hipStreamSynchronize(s));  // the copies may still be read by the timing
+  if (!want32) D.cval32.release();
+  if (!want64) D.cval64.release();
+  if (want32 && !D.cval32.p) {
+    D.cval32.alloc(count);
+    fill_chunks(D, 4, s);
+  }
+  if (want64 && !D.cval64.p) {
+    D.cval64.alloc(count);
+    fill_chunks(D, 8, s);
+  }
+}
+
+// Blocks of geometry g of the multi-right-hand-side chunk kernel and the chunked values in element size esz, built the
+// first time a tuning needs them (false: the fine level is matrix-free)
+static bool ensure_chunk_mr(Ctx& c, int g, int esz, hipStream_t s) {
+  DevLevel& D = c.dv.lv[0];
+  if (g < 0 || g >= kChunkMrGeoms || D.mf) return false;
+  if (D.cmr[g].nrb == 0) {
+    ChunkMrHost h;
+    encode_chunk_mr(c.an, g, h);
+    const size_t nb = h.cb.rb.size();
+    std::vector<int32_t> meta(nb * 4, 0);
+    for (size_t k = 0; k < nb; ++k) {
+      meta[4 * k] = h.cb.rb[k];
+      meta[4 * k + 1] = c.an.cptr[h.cb.rb[k]];
+      meta[4 * k + 2] = h.cb.ubp[k];
+    }
+    if (!D.cptr.p) {
+      D.cptr.upload(c.an.cptr, s);
+      D.nchunk = c.an.cptr[c.an.n];
+    }
+    D.cmrmeta[g].upload(meta, s);
+    D.cmrucol[g].upload(h.cb.ucol, s);
+    D.cmrlo[g].upload(h.cb.lo, s);
+    D.cmrhi[g].upload(h.cb.hi, s);
+    D.cmrord[g].upload(h.ord, s);
+    R3MG_HIP_CHECK(hipStreamSynchronize(s));  // the host vectors are released on return
+    ChunkMrBlocks& m = D.cmr[g];
+    m.geom = g;
+    m.meta = D.cmrmeta[g].p;
+    m.ucol = D.cmrucol[g].p;
+    m.cptr = D.cptr.p;
+    m.clo = D.cmrlo[g].p;
+    m.chi = D.cmrhi[g].p;
+    m.ord = D.cmrord[g].p;
+    m.nrb = (int)nb - 1;
+  }
+  if (esz == 4 && !D.cval32.p) {
+    D.cval32.alloc(4 * (size_t)D.nchunk);
+    fill_chunks(D, 4, s);
+  }
+  if (esz == 8 && !D.cval64.p) {
+    D.cval64.alloc(4 * (size_t)D.nchunk);
+    fill_chunks(D, 8, s);
+  }
+  return true;
 }
 
 static void ensure_level_vectors(Ctx& c, int nr) {
@@ -465,6 +544,7 @@ static bool valid_mr_code(Ctx& c, int l, int nr, int esz, int code, hipStream_t 
   if (l < 0 && pow2(code, 8)) return true;
   if (l == 0 && pow2(code, 64)) return true;
   if (code == -1 || code == -2) return ensure_mr_blocks(c, mr_class(nr, esz), s);
+  if (code >= kCodeChunk) return ensure_chunk_mr(c, code - kCodeChunk, esz, s);
   return pow2(code - kCodeSplit, 64) || pow2(code - kCodeSplit2, 64);
 }
 
@@ -479,6 +559,11 @@ static void autotune_spmm(Ctx& c, int nr, hipStream_t s) {
   Device& dv = c.dv;
   const int L = c.an.nlevels() - 1;
   const int tag = nr * 2 + (sizeof(T) == 4 ? 1 : 0);
+  {
+    bool all = dv.lv[0].mf || dv.tuned.count({-1, nr * 2});
+    for (int l = 0; l < L; ++l) all = all && ((l == 0 && dv.lv[0].mf) || dv.tuned.count({l, tag}));
+    if (all) return;  // nothing to time, nothing to wait for
+  }
   const int forced = c.an.opt.multi_rhs_kernel;  // -1 timed, 0 lanes, 1 / 2 LDS-staged, 3 / 4 column-split
   const bool cache = forced == -1 && c.an.opt.tune_cache != 0 && !dv.tune_sig.empty();
   const int fl = F_RHO_STORE | F_X_ADD | F_D_OUT;
@@ -530,6 +615,15 @@ static void autotune_spmm(Ctx& c, int nr, hipStream_t s) {
                                    vbuf<T>(D.x), vbuf<T>(D.dB), 0.0, 0.0, fl | keep_flag<T>(D), nullptr, s);
         });
         consider(-1 - g, ms, ok, true);
+      }
+      for (int g = 0; g < kChunkMrGeoms && forced == -1; ++g) {
+        if (!ensure_chunk_mr(c, g, (int)sizeof(T), s)) continue;
+        opc.cval = level_op<T>(c, 0).cval;
+        const float ms = time_launches(s, 5, [&] {
+          launch_level_chunk_mr<T>(D.cmr[g], opc, nr, vbuf<T>(D.dA), vbuf<T>(D.b), vbuf<T>(D.rho), vbuf<T>(D.x),
+                                   vbuf<T>(D.dB), 0.0, 0.0, fl | keep_flag<T>(D), nullptr, s);
+        });
+        consider(kCodeChunk + g, kChunkMrMargin * ms, true, true);
       }
       if (forced == -1 || forced == 3)
         for (int G = 1; G <= 64; G <<= 1) {
@@ -601,6 +695,19 @@ static void autotune_spmm(Ctx& c, int nr, hipStream_t s) {
         bestCode = -1 - g;
       }
     }
+    for (int g = 0; g < kChunkMrGeoms && forced == -1; ++g) {
+      if (!ensure_chunk_mr(c, g, 8, s)) continue;
+      op.cval = level_op<double>(c, 0).cval;
+      const float ms = time_launches(s, 5, [&] {
+        launch_level_chunk_mr<double>(D0.cmr[g], op, nr, dv.pp.p, nullptr, dv.pq.p, nullptr, nullptr, 0.0, 0.0,
+                                      F_PLAIN | D0.keep64, nullptr, s);
+        launch_pcg_dot_alpha((int)c.an.n, nr, dv.pp.p, dv.pq.p, dv.partials.p, st0, s);
+      });
+      if (kChunkMrMargin * ms < best) {
+        best = kChunkMrMargin * ms;
+        bestCode = kCodeChunk + g;
+      }
+    }
     if (forced == -1 || forced == 3)
       for (int G = 1; G <= 64; G <<= 1) {
         bool ok = true;
@@ -630,7 +737,15 @@ static void autotune_spmm(Ctx& c, int nr, hipStream_t s) {
     dv.tuned[{-1, nr * 2}] = bestCode;
     if (cache) tune_cache_put(mr_tune_key(dv, -1, nr, 8), bestCode);
   }
-  R3MG_HIP_CHECK(hipStreamSynchronize(s));
+  // chunked values stay in the precisions that some choice reads (levels 0 and -1, any column count)
+  DevLevel& Df = dv.lv[0];
+  Df.chunk_mr32 = Df.chunk_mr64 = false;
+  for (const auto& t : dv.tuned)
+    if (t.first.first <= 0 && t.second >= kCodeChunk) {
+      const bool f32 = t.first.first == 0 && (t.first.second & 1);
+      (f32 ? Df.chunk_mr32 : Df.chunk_mr64) = true;
+    }
+  keep_chunks(Df, c.fp32, s);
 }
 
 // Chebyshev coefficients of a level: first direction scale 1/theta, then (c1, c2) of steps k = 1..K-1
@@ -857,29 +972,6 @@ static void cheb_level(const Analysis& an, DevLevel& D, const double* sc) {
   D.cheb_inv_theta = ch.inv_theta;
   D.cheb_c1 = ch.c1;
   D.cheb_c2 = ch.c2;
-}
-
-// the fine level's values in chunks, in the precisions that hold a chunked copy
-static void fill_chunks(DevLevel& D, int esz, hipStream_t s) {
-  if (esz == 8 && D.cval64.p) launch_chunk_values<double>((int)D.n, D.rowptr.p, D.cptr.p, D.val64.p, D.cval64.p, s);
-  if (esz == 4 && D.cval32.p) launch_chunk_values<float>((int)D.n, D.rowptr.p, D.cptr.p, D.val32.p, D.cval32.p, s);
-}
-
-// keeps a chunked copy of the fine values for exactly the precisions in which the chosen shapes read one
-static void keep_chunks(DevLevel& D, bool fp32, hipStream_t s) {
-  const size_t count = 4 * (size_t)D.nchunk;
-  const bool want32 = fp32 && D.shape == kChunkShape, want64 = D.shape64 == kChunkShape;
-  R3MG_HIP_CHECK(hipStreamSynchronize(s));  // the copies may still be read by the timing
-  if (!want32) D.cval32.release();
-  if (!want64) D.cval64.release();
-  if (want32 && !D.cval32.p) {
-    D.cval32.alloc(count);
-    fill_chunks(D, 4, s);
-  }
-  if (want64 && !D.cval64.p) {
-    D.cval64.alloc(count);
-    fill_chunks(D, 8, s);
-  }
 }
 
 void numeric_setup(HandleImpl& h, hipStream_t s) {
@@ -1478,7 +1570,7 @@ static void pcg_operator(Ctx& c, int NR, const double* p, double* q, const int* 
     const bool ok = it->second < 0
                         ? cls >= 0 && launch_level_lmr<double>(D0.mr[cls], op64, NR, it->second == -1, p, nullptr, q,
                                                                nullptr, nullptr, 0.0, 0.0, F_PLAIN | D0.keep64, skip, s)
-                        : launch_split_code<double>(it->second, op64, NR, p, nullptr, q, nullptr, nullptr, 0.0, 0.0,
+                        : launch_fine_code<double>(it->second, D0, op64, NR, p, nullptr, q, nullptr, nullptr, 0.0, 0.0,
                                                     F_PLAIN, skip, s);
     if (!ok) throw std::runtime_error("multi-RHS fine-level kernel: unsupported shape");
     return;
@@ -1550,7 +1642,7 @@ static void pcg_iteration(Ctx& c, int NR, bool flexible, hipStream_t s, int part
                                                     nullptr, nullptr, 0.0, 0.0, F_PLAIN | D0.keep64, skip, s);
         }
         else
-          ok = launch_split_code<double>(it->second, op64, NR, dv.pp.p, nullptr, dv.pq.p, nullptr, nullptr, 0.0, 0.0,
+          ok = launch_fine_code<double>(it->second, D0, op64, NR, dv.pp.p, nullptr, dv.pq.p, nullptr, nullptr, 0.0, 0.0,
                                          F_PLAIN, skip, s);
         if (!ok) throw std::runtime_error("multi-RHS fine-level kernel: unsupported shape");
         launch_pcg_dot_alpha(n, NR, dv.pp.p, dv.pq.p, dv.partials.p, st, s);
@@ -2167,6 +2259,12 @@ static double level_bytes(Ctx& c, int l, int nr, int esz) {
       // values, 2-byte positions, distinct-column lists, block records, row order and row pointers
       const double nuc = (double)D.mucol[cls].n - 1, nrb = (double)D.mr[cls].nrb;
       return nnz * (esz + 2) + 4.0 * nuc + 16.0 * (nrb + 1) + 4.0 * n + 4.0 * (n + 1) + vec * nr;
+    }
+    if (it != c.dv.tuned.end() && it->second >= kCodeChunk) {
+      // values and positions of the chunks, distinct columns, block records, row order, chunk offsets
+      const int g = it->second - kCodeChunk;
+      return (double)D.nchunk * (4.0 * esz + 5) + 4.0 * (double)D.cmrucol[g].n + 16.0 * (D.cmr[g].nrb + 1.0) + n +
+             4.0 * (n + 1) + vec * nr;
     }
     return nnz * (esz + 4) + 4.0 * (n + 1) + vec * nr;  // CSR kernels
   }

@@ -1,5 +1,6 @@
 """Multi-right-hand-side kernels forced through the tuning cache, against the lanes-per-row kernels (which the other tests
-pin to the oracle): the box kernel of the agglomerated levels for every box size and column count.
+pin to the oracle): the box kernel of the agglomerated levels for every box size and column count, and the fine
+level's chunk kernel in both block geometries, at the edges of its blocks.
 
 Tolerances: the same products summed in another order.  The float64 V-cycle is held to 1e-11 and the float32 one to
 1e-5 (the bars of the single-column V-cycles against the oracle and of float32 rounding through a V-cycle); solves to
@@ -80,3 +81,82 @@ def test_box_kernel(d, pc, N, leaf, mc, nrhs, tmp_path, monkeypatch):
         for j in range(nrhs):
             assert np.linalg.norm(a[j] - b[j]) <= (1e-5 if fp32 else 1e-11) * np.linalg.norm(a[j]), (j, fp32)
 
+
+def _matrix(name):
+    import scipy.sparse as sp
+    if name == "q1":                            # 9 entries a row: the block's row limit
+        prob = F.structured_qp(2, 40, 1, jitter=0.2, cfg=2)
+        return prob.coords, prob.scipy().tocsr(), 2
+    if name == "q3":                            # the chunk limit
+        prob = F.structured_qp(2, 20, 3, jitter=0.2, cfg=2)
+        return prob.coords, prob.scipy().tocsr(), 2
+    if name == "3d":                            # the column limit
+        prob = F.structured_qp(3, 8, 2)
+        return prob.coords, prob.scipy().tocsr(), 3
+    # one row of `count` entries: within, at and beyond the column lists of 383 and 639
+    count = int(name[3:])
+    prob = F.structured_qp(2, 30, 1)
+    A = prob.scipy().tocsr()
+    free = np.flatnonzero(~prob.boundary)
+    k = int(free[len(free) // 2])
+    js = np.setdiff1d(free, A.indices[A.indptr[k]:A.indptr[k + 1]])[:count - 9]
+    v = np.full(len(js), 1e-2)
+    C = sp.csr_matrix((np.concatenate([v, v, v, [v.sum()]]),
+                       (np.concatenate([np.full(len(js), k), js, js, [k]]),
+                        np.concatenate([js, np.full(len(js), k), js, [k]]))), shape=A.shape)
+    A = (A + C).tocsr()
+    A.sort_indices()
+    return prob.coords, A, 2
+
+
+@pytest.mark.parametrize("nrhs", [2, 4, 5, 16])
+@pytest.mark.parametrize("name", ["q1", "q3", "3d", "row383", "row384", "row639", "row640"])
+def test_chunk_kernel(name, nrhs, tmp_path, monkeypatch):
+    _need_gpu()
+    import paper_2607_28235_amd as P
+    coords, A, d = _matrix(name)
+    n = A.shape[0]
+    for fp32 in (0, 1):
+        print(f"[gpu-case] chunk kernel {name} nrhs={nrhs} fp32={fp32}", flush=True)
+        o = P.Options(dim=d, coarse_degree=1, leaf_size=64, max_coarse_dofs=300, skip_leaf_level=int(d == 3),
+                      vcycle_fp32=fp32)
+        make = lambda: P.Hierarchy(coords, A.indptr.astype(np.int64), A.indices.astype(np.int32), A.data, o)  # noqa: E731
+        h = make()
+        rest = {l: LANES for l in range(1, h.nlevels - 1)}
+        h.close()
+        for poison in (False, True):
+            out = _vcycles(make, nrhs, tmp_path / f"t{fp32}{int(poison)}", monkeypatch,
+                           [{**rest, 0: c, -1: c} for c in (LANES, CHUNK, CHUNK + 1)], n, poison=poison)
+            for z in out[1:]:
+                for j in range(nrhs):
+                    if poison and j in (0, nrhs - 1):   # an infinity or NaN reaches the same entries of its column only
+                        assert np.array_equal(np.isfinite(z[j]), np.isfinite(out[0][j]))
+                        continue
+                    assert np.linalg.norm(z[j] - out[0][j]) <= (1e-5 if fp32 else 1e-11) * np.linalg.norm(out[0][j])
+
+    # the float64 operator of a block solve through the same kernel, new values included
+    path = tmp_path / "solve"
+    monkeypatch.setenv("R3MG_TUNE_CACHE", str(path))
+    B = torch.from_numpy((A @ np.random.default_rng(1).standard_normal((n, nrhs))).T.copy()).to("cuda")
+    h = make()
+    h.vcycle(B, torch.empty_like(B))
+    h.close()
+    keys = [ln.rsplit(" ", 1)[0] for ln in open(path) if "/mr/0/" in ln or "/mr/-1/" in ln]
+    sols = []
+    for c in (LANES, CHUNK, CHUNK + 1):
+        with open(path, "a") as f:
+            for k in keys:
+                f.write(f"{k} {c}\n")
+        h = make()
+        for vals in (A.data, 1.5 * A.data):
+            if vals is not A.data:
+                h.update_values(torch.from_numpy(vals).to("cuda"))
+            X = torch.zeros_like(B)
+            _, _, ok = h.pcg(B, X, rtol=1e-11, maxit=300)
+            assert ok
+            sols.append(X.cpu().numpy())
+        h.close()
+    for k in (2, 4):
+        assert np.linalg.norm(sols[k] - sols[0]) <= 1e-9 * np.linalg.norm(sols[0])
+        assert np.linalg.norm(sols[k + 1] - sols[1]) <= 1e-9 * np.linalg.norm(sols[1])
+    assert np.linalg.norm(1.5 * sols[1] - sols[0]) <= 1e-8 * np.linalg.norm(sols[0])
