@@ -149,7 +149,7 @@ bool boxrow_supported(int blk, int maxnb);
 // Restriction fused into a box-row launch (2D, four children per parent box, boxes 4 G .. 4 G + 3 the children
 // of parent G): the launch's residuals rho = b - A x of each parent's children are restricted with the
 // children's 1D factors pt (2 k^2 per child, k = p' + 1) into bnext[G B + a], and dnext = dinv_next bnext
-// inv_theta_next when dnext is set; the same sums in the same order as launch_restrict_c.  rho is still stored.
+// inv_theta_next when dnext is set; launch_restrict_c's sums in another order.  rho is still stored.
 template <typename T>
 struct BoxRestrict {
   const T* pt = nullptr;
