@@ -1095,7 +1095,9 @@ static std::string tune_signature(const Analysis& an, const Device& dv) {
 
 // Fine-level row-block shape: the candidates run the V-cycle-precision smoother step on level 0 (3 warm-up + 20 timed
 // launches, hipEvents); the fastest is kept for every later single-RHS application.  Candidates are the chunk shape
-// and CSR shape 0, which needs no padding and no column lists (a matrix of very short or very scattered rows).  The
+// and CSR shape 0, which needs no padding and no column lists (a matrix of very short or very scattered rows) but has to
+// be 3% faster.  Under 8 us the launches time the host's rate: there the chunk shape, which is the faster one in a
+// captured sweep (3D Q2 13^3 3.9 against 5.3 us, 16^3 4.3 against 6.6), is taken unless padding doubles the matrix.  The
 // other shapes lost to the chunk shape on every mesh measured (see k_level_chunk), so their blocks are built only
 // when fine_kernel names them.
 static bool timed_shape(int sh) { return sh == 0 || sh == kChunkShape; }
@@ -1129,8 +1131,7 @@ static void tune_stream_shape(HandleImpl& h, hipStream_t s) {
   D.cval64.alloc(4 * (size_t)D.nchunk);
   fill_chunks(D, 8, s);
   const int fl = F_RHO_STORE | F_X_ADD | F_D_OUT;
-  // two interleaved rounds, best of each shape; another shape replaces the first one only when it is at least
-  // 3% faster, so that timing noise does not flip the choice between runs
+  // two interleaved rounds, best of each shape
   float best[kStreamShapes];
   for (int sh = 0; sh < kStreamShapes; ++sh) best[sh] = 1e30f;
   for (int round = 0; round < 2; ++round) {
@@ -1155,9 +1156,12 @@ static void tune_stream_shape(HandleImpl& h, hipStream_t s) {
       best[sh] = std::min(best[sh], ms);
     }
   }
-  int bestS = 0;
-  for (int sh = 1; sh < kStreamShapes; ++sh)
-    if (best[sh] < 0.97f * best[bestS]) bestS = sh;
+  auto pick = [&]() {
+    const float chunk = best[kChunkShape];
+    const bool csr = std::min(best[0], chunk) < 0.008f ? 4 * D.nchunk > 2 * D.nnz : best[0] < 0.97f * chunk;
+    return csr ? 0 : kChunkShape;
+  };
+  int bestS = pick();
   D.shape = D.shape64 = bestS;
   D.bytes_apply = D.shape_bytes[D.shape];
   R3MG_HIP_CHECK(hipMemsetAsync(D.x.p, 0, D.x.n, s));
@@ -1184,9 +1188,7 @@ static void tune_stream_shape(HandleImpl& h, hipStream_t s) {
       });
       best[sh] = std::min(best[sh], ms);
     }
-  bestS = 0;
-  for (int sh = 1; sh < kStreamShapes; ++sh)
-    if (best[sh] < 0.97f * best[bestS]) bestS = sh;
+  bestS = pick();
   D.shape64 = bestS;
   keep_chunks(D, true, s);
   if (cache) tune_cache_put(key, D.shape + 100 * D.shape64);
