@@ -270,12 +270,15 @@ __global__ __launch_bounds__(256) void k_mf_cell(int ncells, const int* __restri
       cidx[4 * a4 + 3] = c4.w;
     }
   }
-  // gather u_e (constrained DoFs, padding and cells past the end read as zero)
+  // gather u_e (constrained DoFs, padding and cells past the end read as zero; the loads are unconditional from clamped
+  // indices, as loads under a lane's own condition are waited for one by one)
   T ue[NL];
 #pragma unroll
-  for (int a = 0; a < NL; ++a) ue[a] = cidx[a] >= 0 ? u[cidx[a]] : (T)0;
+  for (int a = 0; a < NL; ++a) ue[a] = u[max(cidx[a], 0)];
   T gm[NG];
   load_geometry<T, D, AFF>(geo, ncells, e, valid, gm);
+#pragma unroll
+  for (int a = 0; a < NL; ++a) ue[a] = cidx[a] >= 0 ? ue[a] : (T)0;
   T v[NL];
   cell_action<T, D, K, AFF>(ue, gm, tb, v);
 
@@ -310,7 +313,28 @@ __global__ __launch_bounds__(256) void k_mf_cell(int ncells, const int* __restri
   }
 }
 
-template <typename T>
+// Sum of a DoF's cell outputs Y[inc[s0 .. s1)] in ascending order, NB at a time: their list entries and outputs are
+// loaded from clamped positions and masked afterwards, so that each batch is two round trips for the whole wave (a loop
+// over a lane's own count is two round trips per output).  NB = 2^d, the most cells an interior vertex belongs to.
+template <typename T, int NB>
+__device__ __forceinline__ T incidence_sum(const int* __restrict__ inc, const T* __restrict__ Y, int s0, int s1) {
+  T t = 0;
+  for (int k = s0; __any(k < s1); k += NB) {
+    int c[NB];
+    T y[NB];
+#pragma unroll
+    for (int m = 0; m < NB; ++m) c[m] = inc[min(k + m, max(s1 - 1, 0))];
+#pragma unroll
+    for (int m = 0; m < NB; ++m) y[m] = Y[c[m]];
+#pragma unroll
+    for (int m = 0; m < NB; ++m) t += k + m < s1 ? y[m] : (T)0;
+  }
+  return t;
+}
+
+// Bound by the two round trips of the incidence lists and the launch.  The epilogue operands are fetched first.  3D Q2
+// 40^3 float32 (531,441 DoFs): 10.9 -> 9.5 us.
+template <typename T, int NB>
 __global__ __launch_bounds__(256) void k_mf_gather(int n, const int* __restrict__ inc_ptr, const int* __restrict__ inc,
                                                    const T* __restrict__ Y, const T* __restrict__ cd,
                                                    const T* __restrict__ u, const T* __restrict__ b, T* rho, T* x,
@@ -320,35 +344,29 @@ __global__ __launch_bounds__(256) void k_mf_gather(int n, const int* __restrict_
   const int lb = xcd_block(nlog);
   if (lb < 0) return;
   const int i = lb * 256 + (int)threadIdx.x;
-  if (i >= n) return;
-  const int s0 = inc_ptr[i], s1 = inc_ptr[i + 1];
-  T t = 0;
-  if (s0 == s1) {
-    t = cd[i] * u[i];
-  } else {
-    // up to 8 outputs in flight, summed in ascending order
-    int k = s0;
-    for (; k + 8 <= s1; k += 8) {
-      T yv[8];
-#pragma unroll
-      for (int m = 0; m < 8; ++m) yv[m] = Y[inc[k + m]];
-#pragma unroll
-      for (int m = 0; m < 8; ++m) t += yv[m];
-    }
-    for (; k < s1; ++k) t += Y[inc[k]];
+  const int ic = min(i, n - 1);
+  const int s0 = inc_ptr[ic], s1 = inc_ptr[ic + 1];
+  const T ui = u[ic], cdi = cd[ic];
+  T p_old = 0, p_x = 0, p_di = 0;
+  if (!(flags & F_PLAIN)) {
+    p_old = (flags & F_RHO_FROM_B) ? b[ic] : rho[ic];
+    if (flags & F_X_ADD) p_x = x[ic];
+    if (flags & F_D_OUT) p_di = dinv[ic];
   }
+  const T sum = incidence_sum<T, NB>(inc, Y, s0, s1);
+  if (i >= n) return;
+  const T t = s0 == s1 ? cdi * ui : sum;
   if (flags & F_PLAIN) {
     rho[i] = t;
     return;
   }
-  const T r = ((flags & F_RHO_FROM_B) ? b[i] : rho[i]) - t;
+  const T r = p_old - t;
   if (flags & F_RHO_STORE) rho[i] = r;
-  const T ui = u[i];
   if (flags & F_X_ASSIGN)
     x[i] = ui;
   else if (flags & F_X_ADD)
-    x[i] += ui;
-  if (flags & F_D_OUT) dout[i] = c1 * ui + c2 * dinv[i] * r;
+    x[i] = p_x + ui;
+  if (flags & F_D_OUT) dout[i] = c1 * ui + c2 * p_di * r;
 }
 
 // Several right-hand sides (nr columns, n x nr interleaved vectors): each thread applies its cell to the columns
@@ -422,7 +440,9 @@ __global__ __launch_bounds__(256) void k_mf_cell_mr(int ncells, int nr, const in
     for (int c = 0; c < NG; ++c) asm volatile("" : "+v"(gm[c]));
     T ue[NL];
 #pragma unroll
-    for (int a = 0; a < NL; ++a) ue[a] = cidx[a] >= 0 ? u[cidx[a] + k] : (T)0;
+    for (int a = 0; a < NL; ++a) ue[a] = u[max(cidx[a], 0) + k];
+#pragma unroll
+    for (int a = 0; a < NL; ++a) ue[a] = cidx[a] >= 0 ? ue[a] : (T)0;
     T v[NL];
     cell_action<T, D, K, AFF>(ue, gm, tb, v);
     T* plane = Y + (int64_t)k * total;
@@ -457,7 +477,7 @@ __global__ __launch_bounds__(256) void k_mf_cell_mr(int ncells, int nr, const in
 
 // One thread per (DoF, column), columns fastest: the column's sum over the DoF's cell outputs in ascending (cell,
 // node) order, then the epilogue of the multi-RHS level kernels for that entry.
-template <typename T>
+template <typename T, int NB>
 __global__ __launch_bounds__(256) void k_mf_gather_mr(int n, int nr, int64_t plane, const int* __restrict__ inc_ptr,
                                                       const int* __restrict__ inc, const T* __restrict__ Y,
                                                       const T* __restrict__ cd, const T* __restrict__ u,
@@ -468,37 +488,31 @@ __global__ __launch_bounds__(256) void k_mf_gather_mr(int n, int nr, int64_t pla
   const int lb = xcd_block(nlog);
   if (lb < 0) return;
   const int64_t t = (int64_t)lb * 256 + threadIdx.x;
-  const int64_t i = t / nr;
-  const int k = (int)(t - i * nr);
-  if (i >= n) return;
+  const int64_t tc = min(t, (int64_t)n * nr - 1);
+  const int64_t i = tc / nr;
+  const int k = (int)(tc - i * nr);
   const int s0 = inc_ptr[i], s1 = inc_ptr[i + 1];
-  const T* yk = Y + (int64_t)k * plane;
-  T acc = 0;
-  if (s0 == s1) {
-    acc = cd[i] * u[t];
-  } else {
-    int j = s0;
-    for (; j + 8 <= s1; j += 8) {
-      T yv[8];
-#pragma unroll
-      for (int m = 0; m < 8; ++m) yv[m] = yk[inc[j + m]];
-#pragma unroll
-      for (int m = 0; m < 8; ++m) acc += yv[m];
-    }
-    for (; j < s1; ++j) acc += yk[inc[j]];
+  const T ui = u[tc], cdi = cd[i];
+  T p_old = 0, p_x = 0, p_di = 0;
+  if (!(flags & F_PLAIN)) {
+    p_old = (flags & F_RHO_FROM_B) ? b[tc] : rho[tc];
+    if (flags & F_X_ADD) p_x = x[tc];
+    if (flags & F_D_OUT) p_di = dinv[i];
   }
+  const T sum = incidence_sum<T, NB>(inc, Y + (int64_t)k * plane, s0, s1);
+  if (t != tc) return;
+  const T acc = s0 == s1 ? cdi * ui : sum;
   if (flags & F_PLAIN) {
     rho[t] = acc;
     return;
   }
-  const T r = ((flags & F_RHO_FROM_B) ? b[t] : rho[t]) - acc;
+  const T r = p_old - acc;
   if (flags & F_RHO_STORE) rho[t] = r;
-  const T ui = u[t];
   if (flags & F_X_ASSIGN)
     x[t] = ui;
   else if (flags & F_X_ADD)
-    x[t] += ui;
-  if (flags & F_D_OUT) dout[t] = c1 * ui + c2 * dinv[i] * r;
+    x[t] = p_x + ui;
+  if (flags & F_D_OUT) dout[t] = c1 * ui + c2 * p_di * r;
 }
 
 template <typename T, int D, int K>
@@ -521,8 +535,14 @@ void launch_gather_mr(const MfOp& m, int nr, const T* Y, const T* cd, const T* d
   const int64_t threads = (int64_t)m.n * nr;
   const int nlog = (int)((threads + 255) / 256);
   const int64_t plane = (int64_t)m.ncells * m.nlocp;
-  hipLaunchKernelGGL((k_mf_gather_mr<T>), dim3(xcd_grid(nlog)), dim3(256), 0, s, m.n, nr, plane, m.inc_ptr, m.inc,
-                     Y, cd, u, b, rho, x, dinv, dout, (T)c1, (T)c2, flags, skip, nlog);
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(xcd_grid(nlog)), dim3(256), 0, s, m.n, nr, plane, m.inc_ptr, m.inc, Y, cd, u, b, rho,
+                       x, dinv, dout, (T)c1, (T)c2, flags, skip, nlog);
+  };
+  if (m.d == 2)
+    go(k_mf_gather_mr<T, 4>);
+  else
+    go(k_mf_gather_mr<T, 8>);
 }
 
 template <typename T, int D, int K>
@@ -560,8 +580,14 @@ void launch_mf_apply(const MfOp& m, const MfTables<T>& tb, const T* geo, const T
     check_launch("k_mf_cell");
   }
   const int nlog = (m.n + 255) / 256;
-  hipLaunchKernelGGL((k_mf_gather<T>), dim3(xcd_grid(nlog)), dim3(256), 0, s, m.n, m.inc_ptr, m.inc, Y, cd, u, b,
-                     rho, x, dinv, dout, (T)c1, (T)c2, flags, skip, nlog);
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(xcd_grid(nlog)), dim3(256), 0, s, m.n, m.inc_ptr, m.inc, Y, cd, u, b, rho, x, dinv,
+                       dout, (T)c1, (T)c2, flags, skip, nlog);
+  };
+  if (m.d == 2)
+    go(k_mf_gather<T, 4>);
+  else
+    go(k_mf_gather<T, 8>);
   check_launch("k_mf_gather");
 }
 template <typename T>
