@@ -217,9 +217,9 @@ r3mg_status r3mg_pcg_solve(r3mg_handle h, const double* b_dev, double* x_dev, in
 r3mg_status r3mg_pcg_solve_ex(r3mg_handle h, const double* b_dev, double* x_dev, int nrhs, double rtol, double atol,
                               int maxit, void* stream, int* iters, double* relres, double* cond);
 
-/* Several independent problems (each with its own handle, one right-hand side each) solved by PCG in one
- * launch sequence: the iterations of all problems are captured into one hipGraph and replayed together.
- * b[k], x[k] are device vectors of handle k.  iters/relres: host arrays of `count` (may be NULL). */
+/* Several independent problems (each with its own handle, one right-hand side each) solved by PCG at once: the
+ * iterations of each problem run on a stream of the library's own, beside those of the others.
+ * b[k], x[k] are device vectors of handle k.  iters/relres: host arrays of `count` (may be NULL).  Synchronises. */
 r3mg_status r3mg_pcg_solve_group(int count, r3mg_handle* hs, const double* const* b, double* const* x,
                                  double rtol, int maxit, void* stream, int* iters, double* relres);
 

@@ -10,12 +10,10 @@
 // residual at the start of an application and the residual that is restricted are obtained from the last
 // direction instead of a separate b - A x pass.  In exact arithmetic the iterates equal the textbook ones.
 #include <algorithm>
-#include <atomic>
 #include <cmath>
 #include <cstring>
 #include <functional>
 #include <map>
-#include <mutex>
 #include <numeric>
 #include <vector>
 
@@ -25,11 +23,6 @@
 #include "r3mg_internal.h"
 
 namespace r3mg {
-
-uint64_t next_graph_epoch() {
-  static std::atomic<uint64_t> epoch{0};
-  return ++epoch;
-}
 
 namespace {
 
@@ -138,7 +131,6 @@ void drop_graphs(Device& dv) {
   for (auto& kv : dv.graph_defs) (void)hipGraphDestroy(kv.second);
   dv.graphs.clear();
   dv.graph_defs.clear();
-  dv.graph_epoch = next_graph_epoch();
 }
 
 }  // namespace
@@ -1584,7 +1576,7 @@ static void pcg_operator(Ctx& c, int NR, const double* p, double* q, const int* 
 // One PCG iteration (all launches skip once every column has converged).  part 0: the whole iteration; part 1:
 // q = A p, alpha, the x and r updates and the stop test; part 2: the V-cycle, z, beta and the new p.
 template <typename T>
-static void pcg_iteration(Ctx& c, int NR, bool flexible, hipStream_t s, int part = 0, bool vcycle_skips = false) {
+static void pcg_iteration(Ctx& c, int NR, bool flexible, hipStream_t s, int part = 0) {
   Analysis& an = c.an;
   Device& dv = c.dv;
   const int L = an.nlevels() - 1;
@@ -1614,9 +1606,8 @@ static void pcg_iteration(Ctx& c, int NR, bool flexible, hipStream_t s, int part
     }
     const T* bl0 = (sizeof(T) == 4) ? vbuf<T>(D0.b) : reinterpret_cast<const T*>(dv.pr.p);
     T* pend = nullptr;
-    // with vcycle_skips (group solves, where problems converge at different iterations) the V-cycle's kernels
-    // return at once after convergence; otherwise they do not read the flag (one memory latency less each)
-    if (L > 0) pend = vcycle_rec<T>(c, 0, 1, bl0, vcycle_skips ? skip : nullptr, s);
+    // the V-cycle's kernels do not read the skip flag (one memory latency less each)
+    if (L > 0) pend = vcycle_rec<T>(c, 0, 1, bl0, nullptr, s);
     const T* x0 = (L > 0) ? vbuf<T>(D0.x) : bl0;
     launch_pcg_z1<T>(n, st, part == 0, x0, pend, dv.pz.p, dv.pr.p, flexible ? dv.pq.p : nullptr, P, s);
     launch_pcg_p1(n, st, dv.pz.p, dv.pp.p, P, s);
@@ -1922,214 +1913,172 @@ int residual_history(HandleImpl& h, int col, double* rr, int cap) {
   return m;
 }
 
-// Several problems in one launch sequence: one iteration of every problem (its two halves, so that the stop test
-// comes before the V-cycle, whose kernels return at once for a converged problem) is captured into one hipGraph
-// with one branch per problem, and the graph is replayed
-// in chunks as in pcg_block (whole iterations only: a problem
-// restarted by residual replacement must not receive the second half of an iteration); at the end of a chunk
-// every problem's state lands in one pinned array, read after one synchronisation.  Problems with a float32
-// V-cycle get the same true-residual check and restart.
+// Several problems at once: every problem is solved as by pcg_block, its launches enqueued on a stream of its own, so that
+// the problems' chains of small kernels run beside one another.  The host enqueues the whole predicted solve of each
+// problem (the largest first, whose chain is the longest), then waits for one after another and enqueues more where a
+// prediction fell short.  (One graph with a branch per problem ran the branches nearly one after another: four 3D Q2
+// cubes of 13 to 25 cells an axis took 4.28 ms that way, 2.14 ms on their own streams.)
 namespace {
-struct BranchStreams {
+// streams and events of the branches, created once per thread and device and reused by every group solve
+struct Branches {
   std::vector<hipStream_t> s;
-  ~BranchStreams() {
+  std::vector<hipEvent_t> ev;
+  hipEvent_t fork = nullptr;
+  ~Branches() {
     for (auto q : s) (void)hipStreamDestroy(q);
+    for (auto e : ev) (void)hipEventDestroy(e);
+    if (fork) (void)hipEventDestroy(fork);
   }
 };
-// capture-only streams, created once per thread and device and reused by every group solve
-std::vector<hipStream_t>& branch_streams(int dev, int count) {
-  static thread_local std::map<int, BranchStreams> pool;
-  BranchStreams& b = pool[dev];
-  while ((int)b.s.size() < count + 1) {
+Branches& branches(int dev, int count) {
+  static thread_local std::map<int, Branches> pool;
+  Branches& b = pool[dev];
+  if (!b.fork) R3MG_HIP_CHECK(hipEventCreateWithFlags(&b.fork, hipEventDisableTiming));
+  while ((int)b.s.size() < count) {
     hipStream_t q;
     R3MG_HIP_CHECK(hipStreamCreateWithFlags(&q, hipStreamNonBlocking));
     b.s.push_back(q);
   }
-  return b.s;
+  while ((int)b.ev.size() < count) {
+    hipEvent_t e;
+    R3MG_HIP_CHECK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+    b.ev.push_back(e);
+  }
+  return b;
 }
 
-// The instantiated group graphs, by device and (handle, graph epoch, V-cycle precision) of every problem in order:
-// a later group solve of the same handles, none of whose graphs was dropped since, replays it without capturing
-// again.  A key never matches a freed or changed handle (epochs are unique), and at most kGroupGraphs are kept.
-struct GroupGraph {
-  hipGraph_t g = nullptr;
-  hipGraphExec_t ex = nullptr;
-  std::vector<hipEvent_t> evs;  // the capture's fork and join events, kept with the graph
-  uint64_t used = 0;
+struct GroupTask {
+  HandleImpl* h = nullptr;
+  hipStream_t s = nullptr;
+  hipEvent_t ev = nullptr;
+  bool f32 = false;
+  hipGraphExec_t ex[3] = {nullptr, nullptr, nullptr};
+  int k = 0;           // iterations enqueued
+  bool split = false;  // the last one enqueued stopped after its stop test
+  int restarts = 0;
+  bool done = false;
+  PcgState st;
 };
-constexpr size_t kGroupGraphs = 16;
-std::mutex g_group_mu;
-std::map<std::vector<uint64_t>, GroupGraph> g_group_graphs;
-uint64_t g_group_clock = 0;
-
-void destroy_group_graph(GroupGraph& gg) {
-  if (gg.ex) (void)hipGraphExecDestroy(gg.ex);
-  if (gg.g) (void)hipGraphDestroy(gg.g);
-  for (auto e : gg.evs) (void)hipEventDestroy(e);
-  gg = GroupGraph{};
-}
 }  // namespace
 
 r3mg_status pcg_group(int count, HandleImpl** hs, const double* const* b, double* const* x, double rtol, int maxit,
                       hipStream_t s, int* iters, double* relres) {
   int dev = 0;
   R3MG_HIP_CHECK(hipGetDevice(&dev));
-  std::vector<hipStream_t>& br = branch_streams(dev, count);
-  hipStream_t cap = br[count];
-  GroupGraph fresh;       // a graph captured by this call, until it is cached
-  hipGraphExec_t ex = nullptr;
-  std::vector<hipEvent_t> evs;
-  void* pin = nullptr;
-  std::unique_lock<std::mutex> lk(g_group_mu, std::defer_lock);
-  auto cleanup = [&]() {
-    destroy_group_graph(fresh);
-    for (auto e : evs) (void)hipEventDestroy(e);
-    if (pin) (void)hipHostFree(pin);
+  Branches& br = branches(dev, count);
+  std::vector<GroupTask> tasks(count);
+  std::vector<int> order(count);
+  std::iota(order.begin(), order.end(), 0);
+  std::stable_sort(order.begin(), order.end(), [&](int i, int j) { return hs[i]->an->n > hs[j]->an->n; });
+  auto ctx = [](GroupTask& t) { return Ctx{*t.h->an, *t.h->dev, t.f32}; };
+  auto start = [&](GroupTask& t, bool restart) {
+    Ctx c = ctx(t);
+    if (t.f32)
+      pcg_start<float>(c, 1, 1, rtol, 0.0, true, restart, t.s);
+    else
+      pcg_start<double>(c, 1, 1, rtol, 0.0, false, restart, t.s);
   };
-  auto is32 = [&](int k) { return hs[k]->an->opt.vcycle_fp32 != 0; };
+  auto launch_part = [&](GroupTask& t, int part) {
+    Ctx c = ctx(t);
+    if (t.ex[part])
+      R3MG_HIP_CHECK(hipGraphLaunch(t.ex[part], t.s));
+    else if (t.f32)
+      pcg_iteration<float>(c, 1, true, t.s, part);
+    else
+      pcg_iteration<double>(c, 1, false, t.s, part);
+  };
+  auto enqueue_to = [&](GroupTask& t, int target) {
+    if (t.split && t.k < target) {
+      launch_part(t, 2);
+      t.split = false;
+    }
+    while (t.k < target) {
+      const bool last = t.k + 1 == target;
+      launch_part(t, last ? 1 : 0);
+      ++t.k;
+      t.split = last;
+    }
+  };
+  // the end of a chunk: the float32 V-cycle's true residual, the solution and the state
+  auto finish_chunk = [&](GroupTask& t, double* xk) {
+    Ctx c = ctx(t);
+    Device& dv = c.dv;
+    const int n = (int)c.an.n;
+    PcgState* dst = reinterpret_cast<PcgState*>(dv.state.p);
+    if (t.f32) {
+      pcg_operator(c, 1, dv.px.p, dv.pz.p, nullptr, t.s);
+      launch_pcg_true_residual(n, 1, dv.pb.p, dv.pz.p, dv.partials.p, dst, t.s);
+    }
+    launch_scatter_cols(n, 1, 1, dv.perm.p, dv.px.p, xk, n, t.s);
+    launch_pcg_state_out(dst, static_cast<PcgState*>(dv.pinned_dev), t.s);
+    R3MG_HIP_CHECK(hipEventRecord(t.ev, t.s));
+  };
   try {
-    R3MG_HIP_CHECK(hipHostMalloc(&pin, (size_t)count * sizeof(PcgState) + 64, hipHostMallocDefault));
-    void* pin_dev = nullptr;
-    R3MG_HIP_CHECK(hipHostGetDevicePointer(&pin_dev, pin, 0));
-    // set-up of every problem (plain launches on s)
-    for (int k = 0; k < count; ++k) {
-      HandleImpl& h = *hs[k];
-      Ctx c{*h.an, *h.dev, is32(k)};
+    // buffers and iteration graphs of every problem first: these may allocate
+    for (int q = 0; q < count; ++q) {
+      GroupTask& t = tasks[q];
+      t.h = hs[q];
+      t.s = br.s[q];
+      t.ev = br.ev[q];
+      t.f32 = hs[q]->an->opt.vcycle_fp32 != 0;
+      Ctx c = ctx(t);
       ensure_level_vectors(c, 1);
       ensure_pcg_vectors(c, 1);
-      ensure_hist(*h.dev, std::max(maxit, 1));
-      const int n = (int)h.an->n;
-      launch_gather_cols(n, 1, 1, h.dev->perm.p, b[k], n, h.dev->pb.p, s);
-      launch_gather_cols(n, 1, 1, h.dev->perm.p, x[k], n, h.dev->px.p, s);
-      if (c.fp32)
-        pcg_start<float>(c, 1, 1, rtol, 0.0, true, false, s);
-      else
-        pcg_start<double>(c, 1, 1, rtol, 0.0, false, false, s);
+      ensure_hist(c.dv, std::max(maxit, 1));
+      if (c.an.opt.use_graph)
+        for (int part = 0; part < 3; ++part)
+          t.ex[part] = t.f32 ? iteration_graph<float>(c, 1, true, part) : iteration_graph<double>(c, 1, false, part);
     }
-    // one iteration of every problem, each on its own branch: the cached graph of these handles, else captured now
-    std::vector<uint64_t> key{(uint64_t)dev};
-    for (int k = 0; k < count; ++k) {
-      key.push_back((uint64_t)(uintptr_t)hs[k]);
-      key.push_back(hs[k]->dev->graph_epoch);
-      key.push_back(is32(k) ? 1 : 0);
+    R3MG_HIP_CHECK(hipEventRecord(br.fork, s));
+    for (int q : order) {
+      GroupTask& t = tasks[q];
+      Device& dv = *t.h->dev;
+      const int n = (int)t.h->an->n;
+      R3MG_HIP_CHECK(hipStreamWaitEvent(t.s, br.fork, 0));
+      launch_gather_cols(n, 1, 1, dv.perm.p, b[q], n, dv.pb.p, t.s);
+      launch_gather_cols(n, 1, 1, dv.perm.p, x[q], n, dv.px.p, t.s);
+      start(t, false);
+      enqueue_to(t, predict_first(dv, record_key(1, t.f32), rtol, 0.0, maxit));
+      finish_chunk(t, x[q]);
     }
-    lk.lock();  // held until the solve ends: the cached graph is not evicted or replayed by another call meanwhile
-    auto hit = g_group_graphs.find(key);
-    if (hit != g_group_graphs.end()) {
-      hit->second.used = ++g_group_clock;
-      ex = hit->second.ex;
-    } else {
-      hipEvent_t fork;
-      R3MG_HIP_CHECK(hipEventCreateWithFlags(&fork, hipEventDisableTiming));
-      fresh.evs.push_back(fork);
-      R3MG_HIP_CHECK(hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal));
-      try {
-        R3MG_HIP_CHECK(hipEventRecord(fork, cap));
-        for (int k = 0; k < count; ++k) {
-          HandleImpl& h = *hs[k];
-          Ctx c{*h.an, *h.dev, is32(k)};
-          R3MG_HIP_CHECK(hipStreamWaitEvent(br[k], fork, 0));
-          // the iteration in its two halves: the stop test precedes the V-cycle, whose kernels then return at
-          // once in the iteration where the problem converges (problems converge at different iterations)
-          for (int part = 1; part <= 2; ++part) {
-            if (c.fp32)
-              pcg_iteration<float>(c, 1, true, br[k], part, true);
-            else
-              pcg_iteration<double>(c, 1, false, br[k], part, true);
-          }
-          hipEvent_t j;
-          R3MG_HIP_CHECK(hipEventCreateWithFlags(&j, hipEventDisableTiming));
-          fresh.evs.push_back(j);
-          R3MG_HIP_CHECK(hipEventRecord(j, br[k]));
-          R3MG_HIP_CHECK(hipStreamWaitEvent(cap, j, 0));
+    for (int open = count; open > 0;)
+      for (int q : order) {
+        GroupTask& t = tasks[q];
+        if (t.done) continue;
+        R3MG_HIP_CHECK(hipEventSynchronize(t.ev));
+        std::memcpy(&t.st, t.h->dev->pinned, sizeof(PcgState));
+        if (t.st.all_done && t.f32 && t.st.restart && t.restarts < 2 && t.k < maxit) {
+          ++t.restarts;
+          start(t, true);
+          t.split = false;
+          enqueue_to(t, std::min(maxit, t.k + 2));
+        } else if (t.st.all_done || t.k >= maxit) {
+          t.done = true;
+          --open;
+          continue;
+        } else {
+          enqueue_to(t, std::min(maxit, t.k + predict_more(t.st, 1)));
         }
-      } catch (...) {
-        hipGraph_t dead;
-        (void)hipStreamEndCapture(cap, &dead);
-        if (dead) (void)hipGraphDestroy(dead);
-        throw;
+        finish_chunk(t, x[q]);
       }
-      R3MG_HIP_CHECK(hipStreamEndCapture(cap, &fresh.g));
-      R3MG_HIP_CHECK(hipGraphInstantiate(&fresh.ex, fresh.g, nullptr, nullptr, 0));
-      ex = fresh.ex;
-      if (g_group_graphs.size() >= kGroupGraphs) {  // evict the least recently used
-        auto old = g_group_graphs.begin();
-        for (auto it = g_group_graphs.begin(); it != g_group_graphs.end(); ++it)
-          if (it->second.used < old->second.used) old = it;
-        destroy_group_graph(old->second);
-        g_group_graphs.erase(old);
-      }
-      fresh.used = ++g_group_clock;
-      g_group_graphs[key] = fresh;
-      fresh = GroupGraph{};  // owned by the cache now
-    }
-    hipEvent_t done_ev;
-    R3MG_HIP_CHECK(hipEventCreateWithFlags(&done_ev, hipEventDisableTiming));
-    evs.push_back(done_ev);
-    std::vector<PcgState> st(count);
-    const PcgState* hst = static_cast<const PcgState*>(pin);
-    int k = 0;
-    auto enqueue_to = [&](int target) {
-      for (; k < target; ++k) R3MG_HIP_CHECK(hipGraphLaunch(ex, s));
-    };
-    auto finish_chunk = [&]() {
-      for (int q = 0; q < count; ++q) {
-        HandleImpl& h = *hs[q];
-        Device& dv = *h.dev;
-        PcgState* dst = reinterpret_cast<PcgState*>(dv.state.p);
-        if (is32(q)) {
-          Ctx c{*h.an, dv, true};
-          apply_level<double>(c, 0, 1, dv.px.p, nullptr, dv.pz.p, nullptr, nullptr, 0, 0, F_PLAIN, nullptr, s);
-          launch_pcg_true_residual((int)h.an->n, 1, dv.pb.p, dv.pz.p, dv.partials.p, dst, s);
-        }
-        launch_scatter_cols((int)h.an->n, 1, 1, dv.perm.p, dv.px.p, x[q], h.an->n, s);
-        launch_pcg_state_out(dst, static_cast<PcgState*>(pin_dev) + q, s);
-      }
-      R3MG_HIP_CHECK(hipEventRecord(done_ev, s));
-      R3MG_HIP_CHECK(hipEventSynchronize(done_ev));
-      std::memcpy(st.data(), hst, (size_t)count * sizeof(PcgState));
-    };
-    int first = 0;
-    for (int q = 0; q < count; ++q)
-      first = std::max(first, predict_first(*hs[q]->dev, record_key(1, is32(q)), rtol, 0.0, maxit));
-    enqueue_to(first);
-    std::vector<int> restarts(count, 0);
-    for (;;) {
-      finish_chunk();
-      bool all = true, restarted = false;
-      int more = 1;
-      for (int q = 0; q < count; ++q) {
-        if (!st[q].all_done) {
-          all = false;
-          more = std::max(more, predict_more(st[q], 1));
-        } else if (is32(q) && st[q].restart && restarts[q] < 2 && k < maxit) {
-          ++restarts[q];
-          Ctx c{*hs[q]->an, *hs[q]->dev, true};
-          pcg_start<float>(c, 1, 1, rtol, 0.0, true, true, s);
-          restarted = true;
-          all = false;
-        }
-      }
-      if (all || k >= maxit) break;
-      if (restarted) more = std::max(more, 2);
-      enqueue_to(std::min(maxit, k + more));
-    }
-    r3mg_status res = R3MG_OK;
-    for (int q = 0; q < count; ++q) {
-      const bool f32 = is32(q);
-      const double rr = f32 ? st[q].rr_true[0] : st[q].rr[0];
-      if (iters) iters[q] = st[q].iters[0];
-      if (relres) relres[q] = st[q].rr0[0] > 0 ? std::sqrt(rr / st[q].rr0[0]) : 0.0;
-      const bool conv = st[q].done[0] && (!f32 || rr <= st[q].tau2[0]);
-      if (!conv) res = R3MG_NOT_CONVERGED;
-      if (conv && restarts[q] == 0) record_solve(*hs[q]->dev, record_key(1, f32), rtol, 0.0, st[q], 1);
-    }
-    cleanup();
-    return res;
   } catch (...) {
-    cleanup();
+    // nothing of the group may still read the caller's vectors after the call
+    for (GroupTask& t : tasks)
+      if (t.s) (void)hipStreamSynchronize(t.s);
     throw;
   }
+  r3mg_status res = R3MG_OK;
+  for (int q = 0; q < count; ++q) {
+    GroupTask& t = tasks[q];
+    const double rr = t.f32 ? t.st.rr_true[0] : t.st.rr[0];
+    if (iters) iters[q] = t.st.iters[0];
+    if (relres) relres[q] = t.st.rr0[0] > 0 ? std::sqrt(rr / t.st.rr0[0]) : 0.0;
+    const bool conv = t.st.done[0] && (!t.f32 || rr <= t.st.tau2[0]);
+    if (!conv) res = R3MG_NOT_CONVERGED;
+    t.h->dev->last_restarts = t.restarts;
+    if (conv && t.restarts == 0) record_solve(*t.h->dev, record_key(1, t.f32), rtol, 0.0, t.st, 1);
+  }
+  return res;
 }
 
 // ---------------------------------------------------------------------------------------------
