@@ -2560,16 +2560,8 @@ template void launch_level_chunk_mr<double>(const ChunkMrBlocks&, const LevelOp<
                                             const double*, double*, double*, double*, double, double, int, const int*,
                                             hipStream_t);
 
-// Agglomerated levels for several right-hand sides, on the matrix cores: one workgroup per box, the box's B x w block
-// row times the w x NR gathered rows of u, as 16 x 16 x 4 products (rows of the box x columns x block-row positions).
-// The four waves take every fourth step of 4 KV positions and add their tiles in wave order through LDS; a lane's KV
-// consecutive positions (16 bytes of the matrix row) are the four k groups of KV instructions, the same for both
-// operands.  Epilogue as in k_level, operands fetched first.
-// The lanes kernel gives each lane whole positions and all NR columns, so it is a long chain of loads per lane and a
-// butterfly per column at the end; here a step is one 16-byte load, KV gathered words and KV instructions.  One
-// application, best lanes count -> this kernel: float64 with 8 columns, 9-row boxes, 9,216 rows 14.1 -> 5.7 us and
-// 2,304 rows 10.5 -> 3.9; float32 with 16 columns, 27-row boxes (3D Q3 28^3) 50.5 -> 12.1 us.  Now bound by the three
-// dependent round trips (block row, columns, u) and the launch.
+// 16 x 16 x 4 matrix instructions.  Lane l supplies A[l % 16][l / 16] and B[l / 16][l % 16]; result element r of lane l is
+// C[row(l, r)][l % 16].
 template <typename T>
 struct Mfma16;
 template <>
@@ -2593,6 +2585,16 @@ struct Mfma16<double> {
   static __device__ __forceinline__ int row(int lane, int r) { return 4 * r + (lane >> 4); }
 };
 
+// Agglomerated levels for several right-hand sides, on the matrix cores: one workgroup per box, the box's B x w block
+// row times the w x NR gathered rows of u, as 16 x 16 x 4 products (rows of the box x columns x block-row positions).
+// The four waves take every fourth step of 4 KV positions and add their tiles in wave order through LDS; a lane's KV
+// consecutive positions (16 bytes of the matrix row) are the four k groups of KV instructions, the same for both
+// operands.  Epilogue as in k_level, operands fetched first.
+// The lanes kernel gives each lane whole positions and all NR columns, so it is a long chain of loads per lane and a
+// butterfly per column at the end; here a step is one 16-byte load, KV gathered words and KV instructions.  One
+// application, best lanes count -> this kernel: float64 with 8 columns, 9-row boxes, 9,216 rows 14.1 -> 5.7 us and
+// 2,304 rows 10.5 -> 3.9; float32 with 16 columns, 27-row boxes (3D Q3 28^3) 50.5 -> 12.1 us.  Now bound by the three
+// dependent round trips (block row, columns, u) and the launch.
 template <typename T, int B, int NR>
 __global__ __launch_bounds__(256) void k_level_box_mr(int nbox, const int* __restrict__ bptr,
                                                       const int* __restrict__ bcol, const T* __restrict__ val,
@@ -2809,6 +2811,26 @@ constexpr int col_vw() {
 // the vector path needs 16-byte aligned vectors (always so for the library's buffers)
 static inline bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
+// f(dk) with the dimension and the nodes per axis as the compile-time constants dk.D, dk.K
+template <int DD, int KK>
+struct BoxShape {
+  static constexpr int D = DD, K = KK;
+};
+template <typename F>
+static void box_dispatch(int d, int k, F&& f) {
+  switch (d * 8 + k) {
+    case 17: f(BoxShape<2, 1>{}); break;
+    case 18: f(BoxShape<2, 2>{}); break;
+    case 19: f(BoxShape<2, 3>{}); break;
+    case 20: f(BoxShape<2, 4>{}); break;
+    case 25: f(BoxShape<3, 1>{}); break;
+    case 26: f(BoxShape<3, 2>{}); break;
+    case 27: f(BoxShape<3, 3>{}); break;
+    case 28: f(BoxShape<3, 4>{}); break;
+    default: throw std::runtime_error("transfer: unsupported dimension or degree");
+  }
+}
+
 // Restriction fine -> first agglomerated level, one workgroup of up to eight waves per box K:
 // b[K B + q] = sum over the box's free points of phi_q(x_i) src_i.  A thread adds the B products of its points (two at
 // a time, loads from clamped addresses, masked afterwards) in registers; the waves' lanes are then added by one
@@ -2870,99 +2892,91 @@ __global__ __launch_bounds__(512) void k_restrict0(Basis1D<T> bs, int nr, const 
   }
 }
 
-// Restriction to the first agglomerated level for nr > 1 columns: one workgroup per box K, in teams of tsize
-// threads.  Thread (g, j) of a team takes the KB consecutive coarse functions q = KB g .. KB g + KB - 1 (same q1,
-// q2) and column chunk j.  Team t takes the box's points in chunks of 32 (chunks t, t + nteam, ...) through its own
-// LDS: the chunk's 1D basis values (one thread per point) and nr entries of src (zero at constrained points); each
-// thread adds phi_q(xi_i) src_i over the chunk's points in index order, phi_q formed as l0[q0] (l1[q1] l2[q2]).
-// The team sums are then added in team order.  A team is one wave when its threads fit one (four teams, synchronised
-// per wave), else the whole workgroup (one team).
-template <typename T, int D, int KB, int VW>
-__global__ __launch_bounds__(512) void k_restrict0_mr(Basis1D<T> bs, int nr, int tsize, const int* __restrict__ leaf_off,
+// Restriction fine -> first agglomerated level for NR > 1 columns, one workgroup of up to eight waves per box, on the
+// matrix cores: the B x points matrix phi_q(x_i) times the points x NR entries of src, four points an instruction.
+// Lane (i, k) evaluates phi_q at point k for q = 16 t + i in every tile t (its weights and nodes per axis are held in
+// registers) and supplies column i % NR of src at that point (zero at constrained points and past the box).  The waves
+// take the points in turn and their tiles are added in wave order through LDS.
+// The earlier kernel staged 32 points' values and entries in LDS per team of lanes and summed point by point: 3D Q3
+// 16^3, 16 float32 columns (64 boxes of 1,838 points) 63 us with four teams, 36.5 with eight, now 28.3.
+template <typename T, int D, int KB, int NR>
+__global__ __launch_bounds__(512) void k_restrict0_mr(Basis1D<T> bs, const int* __restrict__ leaf_off,
                                                       const int* __restrict__ owner, const T* __restrict__ xi,
                                                       const T* __restrict__ src, T* bnext,
                                                       const T* __restrict__ dinv_next, T* dnext, T inv_theta_next,
                                                       const int* __restrict__ skip) {
-  using VT = typename ColVec<T, VW>::type;
+  using M = Mfma16<T>;
   constexpr int B = D == 3 ? KB * KB * KB : KB * KB;
-  constexpr int P = 32;
-  constexpr int LW = D * KB;  // 1D values per point
+  constexpr int MT = (B + 15) / 16, UN = 2;
   if (skip && *skip) return;
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  const int nch = nr / VW;
-  const int nteam = blockDim.x / tsize, team = threadIdx.x / tsize, tt = threadIdx.x - team * tsize;
-  const bool wave_teams = nteam > 1;  // then tsize == 64
-  const size_t region = ((size_t)P * nch * sizeof(VT) + (size_t)P * LW * sizeof(T) + 15) / 16 * 16;
-  VT* ss = reinterpret_cast<VT*>(smem_raw + team * region);  // [P][nch] entries of src
-  T* lt = reinterpret_cast<T*>(ss + P * nch);                  // [P][LW] 1D values
-  auto team_sync = [&]() {
-    if (wave_teams) {
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    } else {
-      __syncthreads();
-    }
-  };
+  __shared__ T red[8][MT * 16][NR];
+  const int W = blockDim.x >> 6, wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int i = lane & 15, kk = lane >> 4, n = i % NR;
   const int K = blockIdx.x;
   const int i0 = leaf_off[K], i1 = leaf_off[K + 1];
-  const int g = tt / nch, j = tt - g * nch;
-  const bool active = g < B / KB;
-  const int q1 = g % KB, q2 = g / KB;
-  VT acc[KB];
+  // phi_q = prod over axes of w (s - t_1) .. (s - t_{KB-1}): the weight and the other nodes of this lane's functions
+  T wq[MT], tn[MT][D][KB > 1 ? KB - 1 : 1];
 #pragma unroll
-  for (int a = 0; a < KB; ++a) acc[a] = (VT)0;
-  for (int base = i0 + team * P; base < i1; base += nteam * P) {
-    const int np = min(P, i1 - base);
-    for (int t = tt; t < np * nch; t += tsize) {
-      const int pp = t / nch, jj = t - pp * nch;
-      const int i = base + pp;
-      const VT sv = *reinterpret_cast<const VT*>(src + (int64_t)i * nr + jj * VW);
-      ss[t] = owner[i] >= 0 ? sv : (VT)0;
-    }
-    if (tt < np) {
-      const int i = base + tt;
-      T l[3][4];
+  for (int t = 0; t < MT; ++t) {
+    int q = min(16 * t + i, B - 1);
+    wq[t] = 1;
 #pragma unroll
-      for (int a = 0; a < D; ++a) lag1d_k<T, KB>(bs, xi[(int64_t)i * D + a], l[a]);
+    for (int a = 0; a < D; ++a) {
+      const int j = q % KB;
+      q /= KB;
+      T w = bs.w[0];
 #pragma unroll
-      for (int a = 0; a < D; ++a)
+      for (int m = 1; m < KB; ++m) w = j == m ? bs.w[m] : w;
+      wq[t] *= w;
 #pragma unroll
-        for (int m = 0; m < KB; ++m) lt[tt * LW + a * KB + m] = l[a][m];
-    }
-    team_sync();
-    if (active) {
-      for (int pp = 0; pp < np; ++pp) {
-        const T* lp = lt + pp * LW;
-        T l12 = lp[KB + q1];
-        if (D == 3) l12 *= lp[2 * KB + q2];
-        const VT sv = ss[pp * nch + j];
-#pragma unroll
-        for (int a = 0; a < KB; ++a) acc[a] += (lp[a] * l12) * sv;
+      for (int m = 0; m + 1 < KB; ++m) {
+        // the m-th node other than node j
+        tn[t][a][m] = j <= m ? bs.t[m + 1] : bs.t[m];
       }
     }
-    team_sync();
   }
-  if (wave_teams) {  // team sums through LDS, added in team order by team 0
-    VT* comb = reinterpret_cast<VT*>(smem_raw + nteam * region);  // [nteam][KB][64]
+  typename M::acc acc[MT];
 #pragma unroll
-    for (int a = 0; a < KB; ++a) comb[(team * KB + a) * 64 + tt] = acc[a];
-    __syncthreads();
-    if (team != 0) return;
+  for (int t = 0; t < MT; ++t) acc[t] = typename M::acc{0, 0, 0, 0};
+  for (int p0 = i0 + 4 * wv; p0 < i1; p0 += 4 * W * UN) {
+    T x[UN][D], r[UN];
+    int ow[UN];
 #pragma unroll
-    for (int a = 0; a < KB; ++a) {
-      VT t = comb[a * 64 + tt];
-      for (int u = 1; u < nteam; ++u) t += comb[(u * KB + a) * 64 + tt];
-      acc[a] = t;
+    for (int h = 0; h < UN; ++h) {
+      const int p = min(p0 + 4 * W * h + kk, i1 - 1);
+      ow[h] = owner[p];
+      r[h] = src[(int64_t)p * NR + n];
+#pragma unroll
+      for (int a = 0; a < D; ++a) x[h][a] = xi[(int64_t)p * D + a];
+    }
+#pragma unroll
+    for (int h = 0; h < UN; ++h) {
+      const T rv = (ow[h] >= 0 && p0 + 4 * W * h + kk < i1) ? r[h] : (T)0;
+#pragma unroll
+      for (int t = 0; t < MT; ++t) {
+        T ph = wq[t];
+#pragma unroll
+        for (int a = 0; a < D; ++a)
+#pragma unroll
+          for (int m = 0; m + 1 < KB; ++m) ph *= x[h][a] - tn[t][a][m];
+        acc[t] = M::mma(ph, rv, acc[t]);
+      }
     }
   }
-  if (active) {
+  if (i < NR) {
 #pragma unroll
-    for (int a = 0; a < KB; ++a) {
-      const int64_t row = (int64_t)K * B + g * KB + a;
-      *reinterpret_cast<VT*>(bnext + row * nr + j * VW) = acc[a];
-      if (dnext) *reinterpret_cast<VT*>(dnext + row * nr + j * VW) = (dinv_next[row] * acc[a]) * inv_theta_next;
-    }
+    for (int t = 0; t < MT; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) red[wv][16 * t + M::row(lane, r)][i] = acc[t][r];
+  }
+  __syncthreads();
+  for (int e = threadIdx.x; e < B * NR; e += blockDim.x) {
+    const int q = e / NR, c = e % NR;
+    T v = 0;
+    for (int u = 0; u < W; ++u) v += red[u][q][c];
+    const int64_t row = (int64_t)K * B + q;
+    bnext[row * NR + c] = v;
+    if (dnext) dnext[row * NR + c] = dinv_next[row] * v * inv_theta_next;
   }
 }
 
@@ -2977,41 +2991,22 @@ void launch_restrict0(int nbox, int64_t n_points, int d, int pc, int nr, const i
   int W = 1;
   while (W < 8 && (int64_t)W * 128 * nbox < n_points) W <<= 1;
   const Basis1D<T> bs = make_basis<T>(pc);
-  constexpr int VW = col_vw<T>();
-  if (nr > 1 && nr % std::min(nr, VW) == 0 && aligned16(src) && aligned16(bnext) && (!dnext || aligned16(dnext))) {
-    const int vw = std::min(nr, VW), nch = nr / vw;
-    const int tsize = ((B / k) * nch + 63) / 64 * 64;  // threads of a team
-    if (tsize > 512) throw std::runtime_error("restriction: too many columns");
-    const size_t esz = vw * sizeof(T);  // bytes of one column chunk
-    const size_t region = ((size_t)32 * nch * esz + (size_t)32 * d * k * sizeof(T) + 15) / 16 * 16;
-    auto lds = [&](int teams) { return teams * region + (teams > 1 ? (size_t)teams * k * 64 * esz : 0); };
-    // eight one-wave teams for boxes of many points (a level of 64 boxes leaves most compute units idle: 3D Q3 16^3,
-    // 16 float32 columns, 1,838 points a box: 63 us with four teams, 36.5 with eight), else four
-    int nteam = tsize == 64 ? ((int64_t)512 * nbox <= n_points ? 8 : 4) : 1;
-    while (nteam > 1 && lds(nteam) > 65536) nteam >>= 1;
-    const int thr = tsize * nteam;
-    const size_t shm = lds(nteam);
-#define R3MG_R0M(DD, KK)                                                                                           \
-  do {                                                                                                             \
-    if (vw == 2)                                                                                                   \
-      hipLaunchKernelGGL((k_restrict0_mr<T, DD, KK, 2>), dim3(nbox), dim3(thr), shm, s, bs, nr, tsize, leaf_off,    \
-                         owner, xi, src, bnext, dinv_next, dnext, (T)inv_theta_next, skip);                          \
-    else                                                                                                           \
-      hipLaunchKernelGGL((k_restrict0_mr<T, DD, KK, VW>), dim3(nbox), dim3(thr), shm, s, bs, nr, tsize, leaf_off,   \
-                         owner, xi, src, bnext, dinv_next, dnext, (T)inv_theta_next, skip);                          \
-  } while (0)
-    switch (d * 8 + k) {
-      case 17: R3MG_R0M(2, 1); break;
-      case 18: R3MG_R0M(2, 2); break;
-      case 19: R3MG_R0M(2, 3); break;
-      case 20: R3MG_R0M(2, 4); break;
-      case 25: R3MG_R0M(3, 1); break;
-      case 26: R3MG_R0M(3, 2); break;
-      case 27: R3MG_R0M(3, 3); break;
-      case 28: R3MG_R0M(3, 4); break;
-      default: throw std::runtime_error("restriction: unsupported dimension or degree");
-    }
-#undef R3MG_R0M
+  if (nr == 2 || nr == 4 || nr == 8 || nr == 16) {
+    // waves per box: 32 points (eight instructions a tile) each in an average box, at most eight
+    int Wm = 1;
+    while (Wm < 8 && (int64_t)Wm * 32 * nbox < n_points) Wm <<= 1;
+    box_dispatch(d, k, [&](auto dk) {
+      auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(nbox), dim3(64 * Wm), 0, s, bs, leaf_off, owner, xi, src, bnext, dinv_next, dnext,
+                           (T)inv_theta_next, skip);
+      };
+      switch (nr) {
+        case 2: go(k_restrict0_mr<T, dk.D, dk.K, 2>); break;
+        case 4: go(k_restrict0_mr<T, dk.D, dk.K, 4>); break;
+        case 8: go(k_restrict0_mr<T, dk.D, dk.K, 8>); break;
+        default: go(k_restrict0_mr<T, dk.D, dk.K, 16>); break;
+      }
+    });
     check_launch("k_restrict0_mr");
     return;
   }
@@ -3124,7 +3119,7 @@ __global__ __launch_bounds__(256) void k_prolong0_box(Basis1D<T> bs, int nr, int
 // (i, j) of the box then takes fine point i and column chunk j (chunks of one point adjacent), in k_prolong0's
 // order.  Reading the entries from LDS instead of L2 for every point and chunk was what bounded the kernel.
 template <typename T, int D, int KB, int VW>
-__global__ __launch_bounds__(256) void k_prolong0_mr(Basis1D<T> bs, int nr, const int* __restrict__ leaf_off,
+__global__ __launch_bounds__(256) void k_prolong0_mr(Basis1D<T> bs, int nr, int per, const int* __restrict__ leaf_off,
                                                      const int* __restrict__ owner, const T* __restrict__ xi,
                                                      const T* __restrict__ e, const T* __restrict__ epend, T* v,
                                                      const int* __restrict__ skip) {
@@ -3134,7 +3129,7 @@ __global__ __launch_bounds__(256) void k_prolong0_mr(Basis1D<T> bs, int nr, cons
   extern __shared__ __align__(16) unsigned char smem_raw[];
   VT* es = reinterpret_cast<VT*>(smem_raw);  // [B][nch]
   const int nch = nr / VW;
-  const int K = blockIdx.x;
+  const int K = blockIdx.x / per, part = blockIdx.x - K * per;
   const int i0 = leaf_off[K], i1 = leaf_off[K + 1];
   for (int t = threadIdx.x; t < B * nch; t += blockDim.x) {
     const int64_t o = (int64_t)K * B * nr + (int64_t)t * VW;  // entry (K B + t / nch), chunk t % nch
@@ -3144,7 +3139,7 @@ __global__ __launch_bounds__(256) void k_prolong0_mr(Basis1D<T> bs, int nr, cons
   }
   __syncthreads();
   const int total = (i1 - i0) * nch;
-  for (int idx = threadIdx.x; idx < total; idx += blockDim.x) {
+  for (int idx = part * 256 + threadIdx.x; idx < total; idx += per * 256) {
     const int i = i0 + idx / nch, j = idx - (idx / nch) * nch;
     const int ow = owner[i];  // unconditional loads; a constrained point's value is replaced by zero
     T l[3][4];
@@ -3166,13 +3161,16 @@ void launch_prolong0(int n, int nbox, int d, int pc, int nr, const int* leaf_off
     const int k = pc + 1, B = (d == 3) ? k * k * k : k * k;
     if (nbox == 0) return;
     const size_t shm = (size_t)16 * B * nch;
+    // workgroups per box: two entries a thread in an average box, as long as the chip is not full (a level of 64 boxes
+    // on 64 compute units: 3D Q3 16^3, 16 float32 columns 29.8 -> 7.0 us)
+    const int per = (int)std::max<int64_t>(1, std::min<int64_t>({((int64_t)n / nbox * nch + 511) / 512, 4096 / nbox, 64}));
 #define R3MG_P0M(DD, KK)                                                                                           \
   do {                                                                                                             \
     if (vw == 2)                                                                                                   \
-      hipLaunchKernelGGL((k_prolong0_mr<T, DD, KK, 2>), dim3(nbox), dim3(256), shm, s, bs, nr, leaf_off, owner, xi, \
+      hipLaunchKernelGGL((k_prolong0_mr<T, DD, KK, 2>), dim3(nbox * per), dim3(256), shm, s, bs, nr, per, leaf_off, owner, xi, \
                          e, epend, v, skip);                                                                         \
     else                                                                                                           \
-      hipLaunchKernelGGL((k_prolong0_mr<T, DD, KK, VW>), dim3(nbox), dim3(256), shm, s, bs, nr, leaf_off, owner,    \
+      hipLaunchKernelGGL((k_prolong0_mr<T, DD, KK, VW>), dim3(nbox * per), dim3(256), shm, s, bs, nr, per, leaf_off, owner, \
                          xi, e, epend, v, skip);                                                                     \
   } while (0)
     switch (d * 8 + pc + 1) {
@@ -3237,26 +3235,6 @@ __device__ inline T pt_entry(const T* __restrict__ pt, int64_t c, int d, int k, 
     v *= m[(2 * k + qc % k) * k + qp % k];
   }
   return v;
-}
-
-// f(dk) with the dimension and the nodes per axis as the compile-time constants dk.D, dk.K
-template <int DD, int KK>
-struct BoxShape {
-  static constexpr int D = DD, K = KK;
-};
-template <typename F>
-static void box_dispatch(int d, int k, F&& f) {
-  switch (d * 8 + k) {
-    case 17: f(BoxShape<2, 1>{}); break;
-    case 18: f(BoxShape<2, 2>{}); break;
-    case 19: f(BoxShape<2, 3>{}); break;
-    case 20: f(BoxShape<2, 4>{}); break;
-    case 25: f(BoxShape<3, 1>{}); break;
-    case 26: f(BoxShape<3, 2>{}); break;
-    case 27: f(BoxShape<3, 3>{}); break;
-    case 28: f(BoxShape<3, 4>{}); break;
-    default: throw std::runtime_error("transfer: unsupported dimension or degree");
-  }
 }
 
 // Tensor application of a child box's 1D factors m (D x KB x KB, m[x][child node][parent node]) to the KB^D values in
@@ -4798,13 +4776,16 @@ __device__ inline void column_totals(const double* __restrict__ part, int nb, in
   const int k = threadIdx.x % NR;
   constexpr int S = 256 / NR;
   double acc = 0;
-  // four of the thread's partials at a time: loads issued together (clamped), added in index order
-  for (int b0 = threadIdx.x / NR; b0 < nb; b0 += 4 * S) {
-    double v[4];
+  // U of the thread's partials at a time: loads issued together (clamped), added in index order.  With 1,024 partials
+  // of 16 columns a thread has 64 of them: in batches of four, 16 round trips, k_pcg_beta of 16 columns took 9.6 us,
+  // k_pcg_alpha 5.6 and the stop test 12.9-14.5; now 6.4, 4.7 and 12.4
+  constexpr int U = NR >= 4 ? 16 : 4;
+  for (int b0 = threadIdx.x / NR; b0 < nb; b0 += U * S) {
+    double v[U];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) v[u] = part[(int64_t)min(b0 + u * S, nb - 1) * stride + k];
+    for (int u = 0; u < U; ++u) v[u] = part[(int64_t)min(b0 + u * S, nb - 1) * stride + k];
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
+    for (int u = 0; u < U; ++u)
       if (b0 + u * S < nb) acc += v[u];
   }
   column_partials<NR>(acc, sh, tot);

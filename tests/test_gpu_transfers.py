@@ -38,3 +38,29 @@ def test_transfers(d, pc, N, leaf, mc):
         got = z.cpu().numpy()
         h.close()
         assert np.linalg.norm(got - want) <= tol * np.linalg.norm(want)
+
+
+@pytest.mark.parametrize("nrhs", [2, 5, 16])
+@pytest.mark.parametrize("d,pc,N,leaf,mc", CASES[1::2])
+def test_transfers_of_several_columns(d, pc, N, leaf, mc, nrhs):
+    """The several-column transfers (matrix-core restriction, boxes split over workgroups), every column against the
+    oracle's V-cycle of it."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2607_28235_amd as P
+    prob = F.structured_qp(d, N, 2 if d == 3 else 3, jitter=0.2 if d == 2 else 0.0, cfg=2)
+    ho = O.build_hierarchy(prob.coords, prob.scipy(), coarse_degree=pc, leaf_size=leaf, max_coarse_dofs=mc)
+    r = np.random.default_rng(8).standard_normal((nrhs, prob.n))
+    r[:, ho.constrained] = 0.0
+    want = [O.vcycle(ho, r[j]) for j in range(nrhs)]
+    for fp32, tol in ((0, 1e-11), (1, 1e-5)):
+        print(f"[gpu-case] transfers d={d} p'={pc} leaf={leaf} nrhs={nrhs} fp32={fp32}", flush=True)
+        h = P.Hierarchy(prob.coords, prob.row_ptr, prob.col, prob.val,
+                        P.Options(dim=d, coarse_degree=pc, leaf_size=leaf, max_coarse_dofs=mc, vcycle_fp32=fp32))
+        R = torch.from_numpy(r).to("cuda")
+        Z = torch.zeros_like(R)
+        h.vcycle(R, Z)
+        got = Z.cpu().numpy()
+        h.close()
+        for j in range(nrhs):
+            assert np.linalg.norm(got[j] - want[j]) <= tol * np.linalg.norm(want[j]), j
