@@ -200,6 +200,20 @@ constexpr int kCodeChunk = 400;  // fine level: kCodeChunk + g = the chunk kerne
 // it has to be 5% faster than a kernel over the CSR arrays.
 constexpr float kChunkMrMargin = 1.05f;
 
+// Block geometry of the chunk kernel for several right-hand sides, -1 = not a candidate.  Long rows need the larger
+// block to share columns, the sooner the less its staging takes; shorter ones gain more from more workgroups on a
+// compute unit.  Whole solves in ms, geometry 0 / 1:
+//   float32: 3D Q3 16^3 x 16 8.69 / 6.78, 28^3 x 16 42.0 / 29.7, 12^3 x 4 3.15 / 3.05; 3D Q2 24^3 x 16 3.79 / 3.44,
+//            16^3 x 8 1.47 / 1.43, 20^3 x 3 1.36 / 1.37; 2D Q3 200^2 x 8 6.03 / 6.36
+//   float64: 3D Q3 14^3 x 16 9.05 / 8.11, 12^3 x 4 3.99 / 3.70; 3D Q2 20^3 x 16 3.94 / 4.15, x 4 1.79 / 1.85;
+//            2D Q2 150^2 x 5 3.14 / 3.47
+// Rows of nine entries (2D Q1) leave a quarter of their chunks empty: 40^2 x 16 0.88 / 0.92 against 0.76 for the
+// column-split kernel.  PCG's operator takes the V-cycle's geometry (within 2% either way), so that one set of blocks
+// is encoded.
+static int chunk_mr_geom(const DevLevel& D, bool fp32) {
+  return D.nnz < 12 * D.n ? -1 : D.nnz > (fp32 ? 40 : 80) * D.n ? 1 : 0;
+}
+
 // F_KEEP when the level's matrix stream in precision T is small enough to stay in the caches
 template <typename T>
 static int keep_flag(const DevLevel& D) {
@@ -508,24 +522,26 @@ static void ensure_pcg_vectors(Ctx& c, int nr) {
   }
 }
 
-// Multi-RHS SpMM tile autotuner: the lanes-per-row tile of every level kernel (and of PCG's float64 SpMV) is
-// chosen per (level, nrhs, precision) by timing each candidate with hipEvents on the level's own work vectors
-// (3 warm-up + 5 timed launches), once per handle; the choice is cached and used by every later solve.  Must run
-// outside graph capture (it synchronises).
-static float time_launches(hipStream_t s, int reps, const std::function<void()>& f) {
+// fastest of four groups of `reps` launches: a candidate of a few microseconds is timed on an empty stream, where one
+// late launch doubles a group's mean.  A candidate whose first group is over 1.4 times `bound` is given up there.
+static float time_launches(hipStream_t s, int reps, float bound, const std::function<void()>& f) {
   hipEvent_t e0, e1;
   R3MG_HIP_CHECK(hipEventCreate(&e0));
   R3MG_HIP_CHECK(hipEventCreate(&e1));
-  for (int r = 0; r < 3; ++r) f();
-  R3MG_HIP_CHECK(hipEventRecord(e0, s));
-  for (int r = 0; r < reps; ++r) f();
-  R3MG_HIP_CHECK(hipEventRecord(e1, s));
-  R3MG_HIP_CHECK(hipEventSynchronize(e1));
-  float ms = 0;
-  R3MG_HIP_CHECK(hipEventElapsedTime(&ms, e0, e1));
+  for (int r = 0; r < 2; ++r) f();
+  float best = 1e30f;
+  for (int g = 0; g < 4 && !(g == 1 && best > 1.4f * bound); ++g) {
+    R3MG_HIP_CHECK(hipEventRecord(e0, s));
+    for (int r = 0; r < reps; ++r) f();
+    R3MG_HIP_CHECK(hipEventRecord(e1, s));
+    R3MG_HIP_CHECK(hipEventSynchronize(e1));
+    float ms = 0;
+    R3MG_HIP_CHECK(hipEventElapsedTime(&ms, e0, e1));
+    best = std::min(best, ms / reps);
+  }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
-  return ms / reps;
+  return best;
 }
 
 // whether a multi-RHS kernel code read from the tuning cache can apply level l (-1: PCG's float64 operator) for nr
@@ -545,6 +561,10 @@ static std::string mr_tune_key(const Device& dv, int l, int nr, int esz) {
   return dv.tune_sig + "/mr/" + std::to_string(l) + "/" + std::to_string(nr) + "/" + std::to_string(esz);
 }
 
+// Multi-RHS SpMM autotuner: the kernel of the fine level, of agglomerated levels that the box kernel does not take,
+// and of PCG's float64 operator is chosen per (level, nrhs, precision) by timing each candidate with hipEvents on the
+// level's own work vectors, once per handle; the choice is cached and used by every later solve.  Must run outside
+// graph capture (it synchronises).
 template <typename T>
 static void autotune_spmm(Ctx& c, int nr, hipStream_t s) {
   if (nr <= 1) return;
@@ -559,6 +579,8 @@ static void autotune_spmm(Ctx& c, int nr, hipStream_t s) {
   const int forced = c.an.opt.multi_rhs_kernel;  // -1 timed, 0 lanes, 1 / 2 LDS-staged, 3 / 4 column-split
   const bool cache = forced == -1 && c.an.opt.tune_cache != 0 && !dv.tune_sig.empty();
   const int fl = F_RHO_STORE | F_X_ADD | F_D_OUT;
+  // column-split kernels: the lanes per row that have won somewhere (4 for 2D Q2, 16 for Q1, 32 for 3D Q3)
+  const int splitFirst = forced == -1 ? 4 : 1, splitLast = forced == -1 ? 32 : 64;
   for (int l = 0; l < L; ++l) {
     if (dv.tuned.count({l, tag})) continue;
     DevLevel& D = dv.lv[l];
@@ -572,69 +594,60 @@ static void autotune_spmm(Ctx& c, int nr, hipStream_t s) {
     LevelOp<T> op = level_op<T>(c, l);
     float best = 1e30f;
     int bestCode = D.lanes;
-    auto consider = [&](int code, float ms, bool ok, bool allowed) {
-      if (ok && allowed && ms < best) {
+    auto consider = [&](int code, float margin, auto&& launch) {
+      bool ok = true;
+      const float ms = margin * time_launches(s, 3, best / margin, [&] { ok = launch() && ok; });
+      if (ok && ms < best) {
         best = ms;
         bestCode = code;
       }
     };
     const bool fine = l == 0;
-    for (int G = 1; G <= 64; G <<= 1) {
-      op.lanes = G;
-      const float ms = time_launches(s, 5, [&] {
-        launch_level<T>(op, nr, vbuf<T>(D.dA), vbuf<T>(D.b), vbuf<T>(D.rho), vbuf<T>(D.x), vbuf<T>(D.dB), 0.0, 0.0, fl,
-                        nullptr, s);
-      });
-      consider(G, ms, true, !fine || forced <= 0);
-    }
     if (!fine && box_mr_supported(c.an.B, D.maxnb)) {
-      const float ms = time_launches(s, 5, [&] {
-        launch_level_box_mr<T>(op, nr, vbuf<T>(D.dA), vbuf<T>(D.b), vbuf<T>(D.rho), vbuf<T>(D.x), vbuf<T>(D.dB), 0.0, 0.0,
-                               fl, nullptr, s);
-      });
-      consider(kCodeBox, ms, true, true);
-    }
-    if (fine) {
+      // the box kernel wherever its tiles fit, untimed: 12.1 / 5.7 / 3.9 / 4.5 / 3.5 us against 50 / 14.1 / 10.5 / 5.6 /
+      // 4.9 for the best lane count (16 columns of 3D Q3 16^3, 8 of 2D Q2 150^2, level by level in the iteration graph),
+      // and below about 8 us launches timed one by one rank the host's launch gaps
+      bestCode = kCodeBox;
+    } else if (!fine || forced == 0) {
+      for (int G = 1; G <= 64; G <<= 1)
+        consider(G, 1.0f, [&] {
+          op.lanes = G;
+          launch_level<T>(op, nr, vbuf<T>(D.dA), vbuf<T>(D.b), vbuf<T>(D.rho), vbuf<T>(D.x), vbuf<T>(D.dB), 0.0, 0.0, fl,
+                          nullptr, s);
+          return true;
+        });
+    } else {
       LevelOp<T> opc = op;
       opc.ptr = D.rowptr.p;
       opc.idx = D.col.p;
-      const int cls = mr_class(nr, (int)sizeof(T));
-      for (int g = 0; g < 2; ++g) {
-        if ((forced != -1 && forced != 1 + g) || !ensure_mr_blocks(c, cls, s)) continue;
-        bool ok = true;
-        const float ms = time_launches(s, 5, [&] {
-          ok = launch_level_lmr<T>(D.mr[cls], opc, nr, g == 0, vbuf<T>(D.dA), vbuf<T>(D.b), vbuf<T>(D.rho),
-                                   vbuf<T>(D.x), vbuf<T>(D.dB), 0.0, 0.0, fl | keep_flag<T>(D), nullptr, s);
-        });
-        consider(-1 - g, ms, ok, true);
-      }
-      for (int g = 0; g < kChunkMrGeoms && forced == -1; ++g) {
-        if (!ensure_chunk_mr(c, g, (int)sizeof(T), s)) continue;
+      if (forced == -1 && ensure_chunk_mr(c, chunk_mr_geom(D, c.fp32), (int)sizeof(T), s)) {
+        const int g = chunk_mr_geom(D, c.fp32);
         opc.cval = level_op<T>(c, 0).cval;
-        const float ms = time_launches(s, 5, [&] {
+        consider(kCodeChunk + g, kChunkMrMargin, [&] {
           launch_level_chunk_mr<T>(D.cmr[g], opc, nr, vbuf<T>(D.dA), vbuf<T>(D.b), vbuf<T>(D.rho), vbuf<T>(D.x),
                                    vbuf<T>(D.dB), 0.0, 0.0, fl | keep_flag<T>(D), nullptr, s);
+          return true;
         });
-        consider(kCodeChunk + g, kChunkMrMargin * ms, true, true);
       }
-      if (forced == -1 || forced == 3)
-        for (int G = 1; G <= 64; G <<= 1) {
-          bool ok = true;
-          const float ms = time_launches(s, 5, [&] {
-            ok = launch_level_split<T>(opc, nr, G, vbuf<T>(D.dA), vbuf<T>(D.b), vbuf<T>(D.rho), vbuf<T>(D.x),
-                                       vbuf<T>(D.dB), 0.0, 0.0, fl, nullptr, s);
+      const int cls = mr_class(nr, (int)sizeof(T));
+      for (int g = 0; g < 2; ++g)
+        if (forced == 1 + g && ensure_mr_blocks(c, cls, s))
+          consider(-1 - g, 1.0f, [&] {
+            return launch_level_lmr<T>(D.mr[cls], opc, nr, g == 0, vbuf<T>(D.dA), vbuf<T>(D.b), vbuf<T>(D.rho),
+                                       vbuf<T>(D.x), vbuf<T>(D.dB), 0.0, 0.0, fl | keep_flag<T>(D), nullptr, s);
           });
-          consider(kCodeSplit + G, ms, ok, true);
-        }
-      if (forced == -1 || forced == 4)
-        for (int G = 1; G <= 64; G <<= 1) {
-          bool ok = true;
-          const float ms = time_launches(s, 5, [&] {
-            ok = launch_level_split2<T>(opc, nr, G, vbuf<T>(D.dA), vbuf<T>(D.b), vbuf<T>(D.rho), vbuf<T>(D.x),
-                                        vbuf<T>(D.dB), 0.0, 0.0, fl, nullptr, s);
+      for (int G = splitLast; G >= splitFirst; G >>= 1) {
+        if (forced == -1 || forced == 4)
+          consider(kCodeSplit2 + G, 1.0f, [&] {
+            return launch_level_split2<T>(opc, nr, G, vbuf<T>(D.dA), vbuf<T>(D.b), vbuf<T>(D.rho), vbuf<T>(D.x),
+                                          vbuf<T>(D.dB), 0.0, 0.0, fl, nullptr, s);
           });
-          consider(kCodeSplit2 + G, ms, ok, true);
-        }
+        if (forced == -1 || forced == 3)
+          consider(kCodeSplit + G, 1.0f, [&] {
+            return launch_level_split<T>(opc, nr, G, vbuf<T>(D.dA), vbuf<T>(D.b), vbuf<T>(D.rho), vbuf<T>(D.x),
+                                         vbuf<T>(D.dB), 0.0, 0.0, fl, nullptr, s);
+          });
+      }
     }
     dv.tuned[{l, tag}] = bestCode;
     if (cache) tune_cache_put(mr_tune_key(dv, l, nr, (int)sizeof(T)), bestCode);
@@ -657,75 +670,68 @@ static void autotune_spmm(Ctx& c, int nr, hipStream_t s) {
     // every candidate ends with alpha in the state: time them on a cleared state (not converged, gamma = 0)
     R3MG_HIP_CHECK(hipMemsetAsync(dv.state.p, 0, sizeof(PcgState), s));
     PcgState* st0 = reinterpret_cast<PcgState*>(dv.state.p);
-    if (forced <= 0)
+    auto consider = [&](int code, float margin, auto&& launch) {
+      bool ok = true;
+      const float ms = margin * time_launches(s, 3, best / margin, [&] { ok = launch() && ok; });
+      if (ok && ms < best) {
+        best = ms;
+        bestCode = code;
+      }
+    };
+    auto dot = [&] { launch_pcg_dot_alpha((int)c.an.n, nr, dv.pp.p, dv.pq.p, dv.partials.p, st0, s); };
+    if (forced == 0)
       for (int G = 1; G <= 8; G <<= 1) {
         op.lanes = G;
         need_partials(dv, (int64_t)((c.an.n + 256 / G - 1) / (256 / G)) * nr);
-        const float ms = time_launches(s, 5, [&] {
+        consider(G, 1.0f, [&] {
           const int np = launch_spmv_dot(op, nr, dv.pp.p, dv.pq.p, dv.partials.p, nullptr, s);
           launch_pcg_alpha(nr, st0, dv.partials.p, np, s);
+          return true;
         });
-        if (ms < best) {
-          best = ms;
-          bestCode = G;
-        }
       }
     op.ptr = D0.rowptr.p;
     op.idx = D0.col.p;
     need_partials(dv, (int64_t)kPcgBlocks * 2 * nr);
-    const int cls = mr_class(nr, 8);
-    for (int g = 0; g < 2; ++g) {
-      if ((forced != -1 && forced != 1 + g) || !ensure_mr_blocks(c, cls, s)) continue;
-      bool ok = true;
-      const float ms = time_launches(s, 5, [&] {
-        ok = launch_level_lmr<double>(D0.mr[cls], op, nr, g == 0, dv.pp.p, nullptr, dv.pq.p, nullptr, nullptr, 0.0,
-                                      0.0, F_PLAIN | D0.keep64, nullptr, s);
-        if (ok) launch_pcg_dot_alpha((int)c.an.n, nr, dv.pp.p, dv.pq.p, dv.partials.p, st0, s);
-      });
-      if (ok && ms < best) {
-        best = ms;
-        bestCode = -1 - g;
-      }
-    }
-    for (int g = 0; g < kChunkMrGeoms && forced == -1; ++g) {
-      if (!ensure_chunk_mr(c, g, 8, s)) continue;
+    if (forced == -1 && ensure_chunk_mr(c, chunk_mr_geom(D0, c.fp32), 8, s)) {
+      const int g = chunk_mr_geom(D0, c.fp32);
       op.cval = level_op<double>(c, 0).cval;
-      const float ms = time_launches(s, 5, [&] {
+      consider(kCodeChunk + g, kChunkMrMargin, [&] {
         launch_level_chunk_mr<double>(D0.cmr[g], op, nr, dv.pp.p, nullptr, dv.pq.p, nullptr, nullptr, 0.0, 0.0,
                                       F_PLAIN | D0.keep64, nullptr, s);
-        launch_pcg_dot_alpha((int)c.an.n, nr, dv.pp.p, dv.pq.p, dv.partials.p, st0, s);
+        dot();
+        return true;
       });
-      if (kChunkMrMargin * ms < best) {
-        best = kChunkMrMargin * ms;
-        bestCode = kCodeChunk + g;
-      }
     }
-    if (forced == -1 || forced == 3)
-      for (int G = 1; G <= 64; G <<= 1) {
-        bool ok = true;
-        const float ms = time_launches(s, 5, [&] {
-          ok = launch_level_split<double>(op, nr, G, dv.pp.p, nullptr, dv.pq.p, nullptr, nullptr, 0.0, 0.0, F_PLAIN,
-                                          nullptr, s);
-          if (ok) launch_pcg_dot_alpha((int)c.an.n, nr, dv.pp.p, dv.pq.p, dv.partials.p, st0, s);
+    const int cls = mr_class(nr, 8);
+    for (int g = 0; g < 2; ++g)
+      if (forced == 1 + g && ensure_mr_blocks(c, cls, s))
+        consider(-1 - g, 1.0f, [&] {
+          if (!launch_level_lmr<double>(D0.mr[cls], op, nr, g == 0, dv.pp.p, nullptr, dv.pq.p, nullptr, nullptr, 0.0,
+                                        0.0, F_PLAIN | D0.keep64, nullptr, s))
+            return false;
+          dot();
+          return true;
         });
-        if (ok && ms < best) {
-          best = ms;
-          bestCode = kCodeSplit + G;
-        }
-      }
-    if (forced == -1 || forced == 4)
-      for (int G = 1; G <= 64; G <<= 1) {
-        bool ok = true;
-        const float ms = time_launches(s, 5, [&] {
-          ok = launch_level_split2<double>(op, nr, G, dv.pp.p, nullptr, dv.pq.p, nullptr, nullptr, 0.0, 0.0, F_PLAIN,
-                                           nullptr, s);
-          if (ok) launch_pcg_dot_alpha((int)c.an.n, nr, dv.pp.p, dv.pq.p, dv.partials.p, st0, s);
+    for (int G = splitLast; G >= splitFirst; G >>= 1) {
+      if (forced == -1 || forced == 4)
+        consider(kCodeSplit2 + G, 1.0f, [&] {
+          if (!launch_level_split2<double>(op, nr, G, dv.pp.p, nullptr, dv.pq.p, nullptr, nullptr, 0.0, 0.0, F_PLAIN,
+                                           nullptr, s))
+            return false;
+          dot();
+          return true;
         });
-        if (ok && ms < best) {
-          best = ms;
-          bestCode = kCodeSplit2 + G;
-        }
-      }
+      if (forced == -1 || forced == 3)
+        consider(kCodeSplit + G, 1.0f, [&] {
+          if (!launch_level_split<double>(op, nr, G, dv.pp.p, nullptr, dv.pq.p, nullptr, nullptr, 0.0, 0.0, F_PLAIN,
+                                          nullptr, s))
+            return false;
+          dot();
+          return true;
+        });
+    }
+    if (bestCode <= 8 && bestCode > 0)
+      need_partials(dv, (int64_t)((c.an.n + 256 / bestCode - 1) / (256 / bestCode)) * nr);
     dv.tuned[{-1, nr * 2}] = bestCode;
     if (cache) tune_cache_put(mr_tune_key(dv, -1, nr, 8), bestCode);
   }
@@ -1132,14 +1138,14 @@ static void tune_stream_shape(HandleImpl& h, hipStream_t s) {
       float ms;
       if (c.fp32) {
         LevelOp<float> op = level_op<float>(c, 0);
-        ms = time_launches(s, 20, [&] {
+        ms = time_launches(s, 10, best[sh], [&] {
           launch_level_stream<float>(sh, D.fb[sh], op, vbuf<float>(D.dA), vbuf<float>(D.b),
                                      vbuf<float>(D.rho), vbuf<float>(D.x), vbuf<float>(D.dB), 0.0, 0.0,
                                      fl | D.keep32, nullptr, nullptr, s);
         });
       } else {
         LevelOp<double> op = level_op<double>(c, 0);
-        ms = time_launches(s, 20, [&] {
+        ms = time_launches(s, 10, best[sh], [&] {
           launch_level_stream<double>(sh, D.fb[sh], op, vbuf<double>(D.dA), vbuf<double>(D.b),
                                       vbuf<double>(D.rho), vbuf<double>(D.x), vbuf<double>(D.dB), 0.0, 0.0,
                                       fl | D.keep64, nullptr, nullptr, s);
@@ -1174,7 +1180,7 @@ static void tune_stream_shape(HandleImpl& h, hipStream_t s) {
   for (int round = 0; round < 2; ++round)
     for (int sh = 0; sh < kStreamShapes; ++sh) {
       if (!timed_shape(sh)) continue;
-      const float ms = time_launches(s, 20, [&] {
+      const float ms = time_launches(s, 10, best[sh], [&] {
         launch_level_stream<double>(sh, D.fb[sh], op, u64.p, nullptr, y64.p, nullptr, nullptr, 0.0, 0.0,
                                     F_PLAIN | D.keep64, nullptr, nullptr, s);
       });
