@@ -4,10 +4,10 @@
 // columns and rows) and cd holds the diagonal of the constrained rows.
 //
 // Two launches, both deterministic (no floating-point atomics):
-//   k_mf_cell    one thread per cell: gather u_e, y_e = K_e u_e by sum factorisation (one Gauss-point slice at
-//                a time along the last axis, which bounds the registers; the geometric factors of multilinear
-//                cells evaluated at each Gauss point from the map's coefficients), store y_e to the cell-local
-//                buffer Y;
+//   k_mf_cell    one thread per cell (k_mf_cell3: one wave per Gauss slice of 64 cells): gather u_e, y_e = K_e u_e
+//                by sum factorisation (one Gauss-point slice at a time along the last axis, which bounds the
+//                registers; the geometric factors of multilinear cells evaluated at each Gauss point from the
+//                map's coefficients), store y_e to the cell-local buffer Y;
 //   k_mf_gather  one thread per DoF: t_i = sum of its cell-local outputs in ascending (cell, node) order, then
 //                the smoother epilogue of the CSR level kernels.
 #include <hip/hip_runtime.h>
@@ -67,6 +67,63 @@ __device__ inline void geo_point(const T* gm, T w, T x1, T x2, T x3, T* c) {
     for (int r = 0; r < 3; ++r)
 #pragma unroll
       for (int t = r; t < 3; ++t) c[k++] = s * (m[r][0] * m[t][0] + m[r][1] * m[t][1] + m[r][2] * m[t][2]);
+  }
+}
+
+// Gauss slice qz of a 3D cell: the z-contracted values z0 = B_z u, z1 = G_z u (per (x, y) node) through the x and y
+// contractions, the flux and the transposed x and y contractions; h0 and h1 await the transposed z contraction.
+template <typename T, int K, bool AFF>
+__device__ __forceinline__ void slice_action(int qz, const T* z0, const T* z1, const T* gm, const MfTables<T>& tb,
+                                             T* h0, T* h1) {
+#pragma unroll
+  for (int j = 0; j < K * K; ++j) h0[j] = h1[j] = 0;
+#pragma unroll
+  for (int qy = 0; qy < K; ++qy) {
+    T y00[K], y01[K], y10[K];
+#pragma unroll
+    for (int ix = 0; ix < K; ++ix) {
+      T a0 = 0, a1 = 0, a2 = 0;
+#pragma unroll
+      for (int iy = 0; iy < K; ++iy) {
+        a0 += tb.B[qy][iy] * z0[ix + K * iy];
+        a1 += tb.G[qy][iy] * z0[ix + K * iy];
+        a2 += tb.B[qy][iy] * z1[ix + K * iy];
+      }
+      y00[ix] = a0;
+      y01[ix] = a1;
+      y10[ix] = a2;
+    }
+    T fx[K], fy[K], fz[K];
+#pragma unroll
+    for (int qx = 0; qx < K; ++qx) {
+      T gx = 0, gy = 0, gz = 0;
+#pragma unroll
+      for (int ix = 0; ix < K; ++ix) {
+        gx += tb.G[qx][ix] * y00[ix];
+        gy += tb.B[qx][ix] * y01[ix];
+        gz += tb.B[qx][ix] * y10[ix];
+      }
+      T c[6];
+      geo_point<T, 3, AFF>(gm, tb.W[qx] * tb.W[qy] * tb.W[qz], tb.X[qx], tb.X[qy], tb.X[qz], c);
+      fx[qx] = c[0] * gx + c[1] * gy + c[2] * gz;
+      fy[qx] = c[1] * gx + c[3] * gy + c[4] * gz;
+      fz[qx] = c[2] * gx + c[4] * gy + c[5] * gz;
+    }
+#pragma unroll
+    for (int ix = 0; ix < K; ++ix) {
+      T px = 0, py = 0, pz = 0;
+#pragma unroll
+      for (int qx = 0; qx < K; ++qx) {
+        px += tb.G[qx][ix] * fx[qx];
+        py += tb.B[qx][ix] * fy[qx];
+        pz += tb.B[qx][ix] * fz[qx];
+      }
+#pragma unroll
+      for (int iy = 0; iy < K; ++iy) {
+        h0[ix + K * iy] += tb.B[qy][iy] * px + tb.G[qy][iy] * py;
+        h1[ix + K * iy] += tb.B[qy][iy] * pz;
+      }
+    }
   }
 }
 
@@ -137,57 +194,8 @@ __device__ __forceinline__ void cell_action(const T* ue, const T* gm, const MfTa
         z0[j] = s0;
         z1[j] = s1;
       }
-      T h0[K * K], h1[K * K];  // slice accumulators of the transposed y contraction
-#pragma unroll
-      for (int j = 0; j < K * K; ++j) h0[j] = h1[j] = 0;
-#pragma unroll
-      for (int qy = 0; qy < K; ++qy) {
-        T y00[K], y01[K], y10[K];
-#pragma unroll
-        for (int ix = 0; ix < K; ++ix) {
-          T a0 = 0, a1 = 0, a2 = 0;
-#pragma unroll
-          for (int iy = 0; iy < K; ++iy) {
-            a0 += tb.B[qy][iy] * z0[ix + K * iy];
-            a1 += tb.G[qy][iy] * z0[ix + K * iy];
-            a2 += tb.B[qy][iy] * z1[ix + K * iy];
-          }
-          y00[ix] = a0;
-          y01[ix] = a1;
-          y10[ix] = a2;
-        }
-        T fx[K], fy[K], fz[K];
-#pragma unroll
-        for (int qx = 0; qx < K; ++qx) {
-          T gx = 0, gy = 0, gz = 0;
-#pragma unroll
-          for (int ix = 0; ix < K; ++ix) {
-            gx += tb.G[qx][ix] * y00[ix];
-            gy += tb.B[qx][ix] * y01[ix];
-            gz += tb.B[qx][ix] * y10[ix];
-          }
-          T c[6];
-          geo_point<T, 3, AFF>(gm, tb.W[qx] * tb.W[qy] * tb.W[qz], tb.X[qx], tb.X[qy], tb.X[qz], c);
-          fx[qx] = c[0] * gx + c[1] * gy + c[2] * gz;
-          fy[qx] = c[1] * gx + c[3] * gy + c[4] * gz;
-          fz[qx] = c[2] * gx + c[4] * gy + c[5] * gz;
-        }
-#pragma unroll
-        for (int ix = 0; ix < K; ++ix) {
-          T px = 0, py = 0, pz = 0;
-#pragma unroll
-          for (int qx = 0; qx < K; ++qx) {
-            px += tb.G[qx][ix] * fx[qx];
-            py += tb.B[qx][ix] * fy[qx];
-            pz += tb.B[qx][ix] * fz[qx];
-          }
-#pragma unroll
-          for (int iy = 0; iy < K; ++iy) {
-            h0[ix + K * iy] += tb.B[qy][iy] * px + tb.G[qy][iy] * py;
-            h1[ix + K * iy] += tb.B[qy][iy] * pz;
-          }
-        }
-      }
+      T h0[K * K], h1[K * K];
+      slice_action<T, K, AFF>(qz, z0, z1, gm, tb, h0, h1);
 #pragma unroll
       for (int iz = 0; iz < K; ++iz)
 #pragma unroll
@@ -310,6 +318,108 @@ __global__ __launch_bounds__(256) void k_mf_cell(int ncells, const int* __restri
       for (int m = 0; m < VW; ++m) t[m] = (a0 + m < NL) ? v[a0 + m] : (T)0;
       *reinterpret_cast<V16*>(yp + a0) = t;
     }
+  }
+}
+
+// 3D, Q2 and Q3: one wave per Gauss slice of 64 cells (K waves a workgroup), so that a cell's chain is 1 / K as long and
+// K times as many waves are in flight: with one thread per cell, 3D Q2 40^3 (64,000 cells) is one wave on each SIMD,
+// and a Q3 cell's 128 values spill.  The cells' entries are gathered once, four a thread, into LDS; each wave contracts
+// them to its slice and leaves its h0 and h1 in LDS; then wave iz forms the outputs of node plane iz, adding the slices
+// in order.  Bound by the gather and, on small meshes, by the chain of loads.
+// One application with its gather kernel, one thread per cell -> this: Q2 8^3 float32 10.2 -> 7.1 us, 24^3 multilinear
+// 14.9 -> 9.6 (float64 17.9 -> 11.5), 40^3 19.8 -> 18.9 (23.7 -> 23.9); Q3 24^3 29.7 -> 15.8 (70.9 -> 23.1), 16^3
+// multilinear 33.1 -> 14.2 (97.6 -> 18.9).  Q1 cells (two slices of few operations) keep one thread per cell: 64^3
+// float64 21.2 against 21.8.
+template <typename T, int K, bool AFF>
+__global__ __launch_bounds__(64 * K) void k_mf_cell3(int ncells, const int* __restrict__ conn,
+                                                     const T* __restrict__ geo, MfTables<T> tb,
+                                                     const T* __restrict__ u, T* __restrict__ Y,
+                                                     const int* __restrict__ skip, int nlog) {
+  constexpr int NL = K * K * K, NP = (NL + 3) / 4 * 4, NT = 64 * K;
+  constexpr int NG = AFF ? 6 : 22;
+  constexpr int NV = 64 * NP / 4, EPT = (NV + NT - 1) / NT;  // four-entry pieces of the tile, and per thread
+  typedef T V4 __attribute__((ext_vector_type(4)));
+  // 64 cells x NP entries of u, then h as [slice][component][cell], then the outputs: one region, so that four double
+  // workgroups of Q2 cells fit a compute unit
+  constexpr int NH = 2 * K * K * NT;
+  __shared__ V4 tile[NV > NH / 4 ? NV : NH / 4];
+  T* hs = reinterpret_cast<T*>(tile);
+  if (skip && *skip) return;
+  const int lb = xcd_block(nlog);
+  if (lb < 0) return;
+  const int lane = (int)threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int64_t base = (int64_t)lb * NV, last = (int64_t)ncells * (NP / 4) - 1;
+  int4 c4[EPT];
+#pragma unroll
+  for (int m = 0; m < EPT; ++m)
+    c4[m] = reinterpret_cast<const int4*>(conn)[min(base + (int)threadIdx.x + m * NT, last)];
+  T gm[NG];
+  load_geometry<T, 3, AFF>(geo, ncells, min(lb * 64 + lane, ncells - 1), true, gm);
+  V4 g4[EPT];
+#pragma unroll
+  for (int m = 0; m < EPT; ++m) {  // constrained DoFs and padding read as zero
+    g4[m][0] = u[max(c4[m].x, 0)];
+    g4[m][1] = u[max(c4[m].y, 0)];
+    g4[m][2] = u[max(c4[m].z, 0)];
+    g4[m][3] = u[max(c4[m].w, 0)];
+  }
+#pragma unroll
+  for (int m = 0; m < EPT; ++m) {
+    const int q = threadIdx.x + m * NT;
+    V4 t;
+    t[0] = c4[m].x >= 0 ? g4[m][0] : (T)0;
+    t[1] = c4[m].y >= 0 ? g4[m][1] : (T)0;
+    t[2] = c4[m].z >= 0 ? g4[m][2] : (T)0;
+    t[3] = c4[m].w >= 0 ? g4[m][3] : (T)0;
+    if (q < NV) tile[q] = t;
+  }
+  __syncthreads();
+  T ue[NP];
+#pragma unroll
+  for (int a = 0; a < NP / 4; ++a) {
+    const V4 t = tile[lane * (NP / 4) + a];
+#pragma unroll
+    for (int m = 0; m < 4; ++m) ue[4 * a + m] = t[m];
+  }
+  T z0[K * K], z1[K * K], h0[K * K], h1[K * K];
+#pragma unroll
+  for (int j = 0; j < K * K; ++j) z0[j] = z1[j] = 0;
+#pragma unroll
+  for (int iz = 0; iz < K; ++iz)
+#pragma unroll
+    for (int j = 0; j < K * K; ++j) {
+      z0[j] += tb.B[wv][iz] * ue[j + K * K * iz];
+      z1[j] += tb.G[wv][iz] * ue[j + K * K * iz];
+    }
+  slice_action<T, K, AFF>(wv, z0, z1, gm, tb, h0, h1);
+  __syncthreads();  // every wave has read its entries
+#pragma unroll
+  for (int j = 0; j < K * K; ++j) {
+    hs[((2 * wv) * K * K + j) * 64 + lane] = h0[j];
+    hs[((2 * wv + 1) * K * K + j) * 64 + lane] = h1[j];
+  }
+  __syncthreads();
+  T v[K * K];
+#pragma unroll
+  for (int j = 0; j < K * K; ++j) v[j] = 0;
+#pragma unroll
+  for (int qz = 0; qz < K; ++qz)
+#pragma unroll
+    for (int j = 0; j < K * K; ++j)
+      v[j] += tb.B[qz][wv] * hs[((2 * qz) * K * K + j) * 64 + lane] +
+              tb.G[qz][wv] * hs[((2 * qz + 1) * K * K + j) * 64 + lane];
+  __syncthreads();
+  T* out = reinterpret_cast<T*>(tile) + lane * NP;
+#pragma unroll
+  for (int j = 0; j < K * K; ++j) out[j + K * K * wv] = v[j];
+  if (wv == 0)
+#pragma unroll
+    for (int a = NL; a < NP; ++a) out[a] = 0;
+  __syncthreads();
+#pragma unroll
+  for (int m = 0; m < EPT; ++m) {
+    const int q = threadIdx.x + m * NT;
+    if (q < NV && base + q <= last) reinterpret_cast<V4*>(Y)[base + q] = tile[q];
   }
 }
 
@@ -551,12 +661,21 @@ void launch_cell(const MfOp& m, const MfTables<T>& tb, const T* geo, const T* u,
   const int nlog = (m.ncells + 255) / 256;
   constexpr int NL = D == 2 ? K * K : K * K * K;
   if (m.nlocp != (NL + 3) / 4 * 4) throw std::runtime_error("matrix-free operator: connectivity stride mismatch");
-  if (m.affine)
+  if constexpr (D == 3 && K > 2) {
+    const int nl3 = (m.ncells + 63) / 64;
+    if (m.affine)
+      hipLaunchKernelGGL((k_mf_cell3<T, K, true>), dim3(xcd_grid(nl3)), dim3(64 * K), 0, s, m.ncells, m.conn, geo, tb,
+                         u, Y, skip, nl3);
+    else
+      hipLaunchKernelGGL((k_mf_cell3<T, K, false>), dim3(xcd_grid(nl3)), dim3(64 * K), 0, s, m.ncells, m.conn, geo, tb,
+                         u, Y, skip, nl3);
+  } else if (m.affine) {
     hipLaunchKernelGGL((k_mf_cell<T, D, K, true>), dim3(xcd_grid(nlog)), dim3(256), 0, s, m.ncells, m.conn, geo, tb,
                        u, Y, skip, nlog);
-  else
+  } else {
     hipLaunchKernelGGL((k_mf_cell<T, D, K, false>), dim3(xcd_grid(nlog)), dim3(256), 0, s, m.ncells, m.conn, geo,
                        tb, u, Y, skip, nlog);
+  }
 }
 
 }  // namespace
