@@ -1091,13 +1091,13 @@ static std::string tune_signature(const Analysis& an, const Device& dv) {
   return tune_device_key(dv.dev) + "/" + buf;
 }
 
-// Fine-level row-block shape: the candidates run the V-cycle-precision smoother step on level 0 (3 warm-up + 20 timed
-// launches, hipEvents); the fastest is kept for every later single-RHS application.  Candidates are the chunk shape
+// Fine-level row-block shape: the candidates run the V-cycle-precision smoother step on level 0 (best of four groups of
+// ten launches, twice); the fastest is kept for every later single-RHS application.  Candidates are the chunk shape
 // and CSR shape 0, which needs no padding and no column lists (a matrix of very short or very scattered rows) but has to
-// be 3% faster.  Under 8 us the launches time the host's rate: there the chunk shape, which is the faster one in a
-// captured sweep (3D Q2 13^3 3.9 against 5.3 us, 16^3 4.3 against 6.6), is taken unless padding doubles the matrix.  The
-// other shapes lost to the chunk shape on every mesh measured (see k_level_chunk), so their blocks are built only
-// when fine_kernel names them.
+// be 3% faster.  Under 30 us the launches can time the host's rate: there the chunk shape, which is the faster one in a
+// captured sweep (3D Q2 13^3 3.9 against 5.3 us, 16^3 4.3 against 6.6, 22^3 5.3 against 6.9), is taken unless padding
+// doubles the matrix.  The other shapes lost to the chunk shape on every mesh measured (see k_level_chunk), so their
+// blocks are built only when fine_kernel names them.
 static bool timed_shape(int sh) { return sh == 0 || sh == kChunkShape; }
 static void tune_stream_shape(HandleImpl& h, hipStream_t s) {
   Analysis& an = *h.an;
@@ -1156,7 +1156,7 @@ static void tune_stream_shape(HandleImpl& h, hipStream_t s) {
   }
   auto pick = [&]() {
     const float chunk = best[kChunkShape];
-    const bool csr = std::min(best[0], chunk) < 0.008f ? 4 * D.nchunk > 2 * D.nnz : best[0] < 0.97f * chunk;
+    const bool csr = std::min(best[0], chunk) < 0.03f ? 4 * D.nchunk > 2 * D.nnz : best[0] < 0.97f * chunk;
     return csr ? 0 : kChunkShape;
   };
   int bestS = pick();
