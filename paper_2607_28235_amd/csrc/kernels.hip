@@ -3583,17 +3583,74 @@ __global__ __launch_bounds__(256) void k_dense_apply(int nc, const double* __res
     if (lane == k) x[(int64_t)row * NR + k] = (T)acc[k];
   }
 }
+// The same for nr > 1 columns on the matrix cores: 16 rows and all columns per workgroup, the columns of the inverse dealt
+// to 16 waves 16 at a time (lane (i, k) reads four consecutive entries of row i, the k groups of four instructions), and
+// the waves' tiles added in wave order through LDS.  A lane of the kernel above holds whole columns of the inverse and
+// reads all nr entries of b for each, then does a butterfly per column.  Four steps of a wave are loaded at once.
+// Bound by the inverse (24 MB at 1,728 unknowns) and its round trips.  16 float32 columns 21.5 -> 13.7 us (18.9 with two
+// steps at once).  Fewer than four unknowns (the last four of a row are read as one vector) keep the kernel above.
+template <typename T, int NR>
+__global__ __launch_bounds__(1024) void k_dense_apply_mr(int nc, const double* __restrict__ cinv,
+                                                         const T* __restrict__ b, T* x, const int* __restrict__ skip) {
+  using M = Mfma16<double>;
+  constexpr int NW = 16, UN = 4;
+  typedef double V4 __attribute__((ext_vector_type(4), aligned(8)));
+  if (skip && *skip) return;
+  __shared__ double red[NW][256];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int i = lane & 15, kk = lane >> 4;
+  const int row0 = blockIdx.x * 16;
+  const double* a = cinv + (int64_t)min(row0 + i, nc - 1) * nc;
+  M::acc acc = {0.0, 0.0, 0.0, 0.0};
+  for (int k0 = 16 * w; k0 < nc; k0 += 16 * NW * UN) {
+    V4 av[UN];
+    T bv[UN][4];
+#pragma unroll
+    for (int m = 0; m < UN; ++m) {  // the last four entries where a lane's own pass the end (nc >= 4)
+      const int k = min(k0 + 16 * NW * m + 4 * kk, nc - 4);
+      av[m] = *reinterpret_cast<const V4*>(a + k);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) bv[m][q] = b[(int64_t)(k + q) * NR + i % NR];
+    }
+#pragma unroll
+    for (int m = 0; m < UN; ++m) {
+      const int k1 = k0 + 16 * NW * m + 4 * kk, k = min(k1, nc - 4);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const bool own = k + q >= k1;  // each entry once, and neither operand otherwise: 0 * inf would be NaN
+        acc = M::mma(own ? av[m][q] : 0.0, own ? (double)bv[m][q] : 0.0, acc);
+      }
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) red[w][M::row(lane, r) * 16 + i] = acc[r];
+  __syncthreads();
+  if (threadIdx.x < 256) {
+    const int r = row0 + (int)threadIdx.x / 16, c = threadIdx.x % 16;
+    double t = 0;
+#pragma unroll
+    for (int v = 0; v < NW; ++v) t += red[v][threadIdx.x];
+    if (r < nc && c < NR) x[(int64_t)r * NR + c] = (T)t;
+  }
+}
 template <typename T>
 void launch_dense_apply(int nc, int nr, const double* cinv, const T* b, T* x, const int* skip, hipStream_t s) {
-  dim3 g((nc + 3) / 4);
+#define R3_DAP(NRV)                                                                                              \
+  case NRV:                                                                                                      \
+    if (NRV == 1 || nc < 4)                                                                                      \
+      hipLaunchKernelGGL((k_dense_apply<T, NRV>), dim3((nc + 3) / 4), dim3(256), 0, s, nc, cinv, b, x, skip);    \
+    else                                                                                                         \
+      hipLaunchKernelGGL((k_dense_apply_mr<T, NRV>), dim3((nc + 15) / 16), dim3(1024), 0, s, nc, cinv, b, x, skip); \
+    break;
   switch (nr) {
-    case 1: hipLaunchKernelGGL((k_dense_apply<T, 1>), g, dim3(256), 0, s, nc, cinv, b, x, skip); break;
-    case 2: hipLaunchKernelGGL((k_dense_apply<T, 2>), g, dim3(256), 0, s, nc, cinv, b, x, skip); break;
-    case 4: hipLaunchKernelGGL((k_dense_apply<T, 4>), g, dim3(256), 0, s, nc, cinv, b, x, skip); break;
-    case 8: hipLaunchKernelGGL((k_dense_apply<T, 8>), g, dim3(256), 0, s, nc, cinv, b, x, skip); break;
-    case 16: hipLaunchKernelGGL((k_dense_apply<T, 16>), g, dim3(256), 0, s, nc, cinv, b, x, skip); break;
+    R3_DAP(1)
+    R3_DAP(2)
+    R3_DAP(4)
+    R3_DAP(8)
+    R3_DAP(16)
     default: throw std::runtime_error("unsupported nrhs block");
   }
+#undef R3_DAP
   check_launch("k_dense_apply");
 }
 template void launch_dense_apply<float>(int, int, const double*, const float*, float*, const int*, hipStream_t);
@@ -4778,7 +4835,7 @@ __device__ inline void column_totals(const double* __restrict__ part, int nb, in
   double acc = 0;
   // U of the thread's partials at a time: loads issued together (clamped), added in index order.  With 1,024 partials
   // of 16 columns a thread has 64 of them: in batches of four, 16 round trips, k_pcg_beta of 16 columns took 9.6 us,
-  // k_pcg_alpha 5.6 and the stop test 12.9-14.5; now 6.4, 4.7 and 12.4
+  // k_pcg_alpha 5.6 and the stop test 12.9-14.5; now 6.4, 4.7 and 4.7 (12.4 while one thread went through the columns)
   constexpr int U = NR >= 4 ? 16 : 4;
   for (int b0 = threadIdx.x / NR; b0 < nb; b0 += U * S) {
     double v[U];
@@ -5041,21 +5098,21 @@ __global__ __launch_bounds__(256) void k_pcg_check(PcgState* st, const double* _
   __shared__ double tot[NR];
   if (st->all_done) return;
   column_totals<NR>(partials, nb, NR, sh, tot);
-  if (threadIdx.x == 0) {
-    int all = 1;
-    for (int c = 0; c < NR; ++c) {
-      if (!st->done[c]) {
-        const double rr = tot[c];
-        st->rr_prev[c] = st->rr[c];
-        st->rr[c] = rr;
-        const int j = st->iters[c] + 1;
-        st->iters[c] = j;
-        if (st->rhist && j <= st->hist_rows) st->rhist[(int64_t)j * kMaxNR + c] = rr;
-        if (rr <= st->tau2[c]) st->done[c] = 1;
-      }
-      all &= st->done[c];
+  if (threadIdx.x < 64) {  // a lane per column
+    const int c = threadIdx.x;
+    int d = c < NR ? st->done[c] : 1;
+    if (!d) {
+      const double rr = tot[c];
+      st->rr_prev[c] = st->rr[c];
+      st->rr[c] = rr;
+      const int j = st->iters[c] + 1;
+      st->iters[c] = j;
+      if (st->rhist && j <= st->hist_rows) st->rhist[(int64_t)j * kMaxNR + c] = rr;
+      d = rr <= st->tau2[c];
+      if (d) st->done[c] = 1;
     }
-    st->all_done = all;
+    const int all = __all(d);
+    if (threadIdx.x == 0) st->all_done = all;
   }
 }
 template <typename T>

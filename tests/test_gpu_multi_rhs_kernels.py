@@ -160,3 +160,31 @@ def test_chunk_kernel(name, nrhs, tmp_path, monkeypatch):
         assert np.linalg.norm(sols[k] - sols[0]) <= 1e-9 * np.linalg.norm(sols[0])
         assert np.linalg.norm(sols[k + 1] - sols[1]) <= 1e-9 * np.linalg.norm(sols[1])
     assert np.linalg.norm(1.5 * sols[1] - sols[0]) <= 1e-8 * np.linalg.norm(sols[0])
+
+
+# (d, p', cells, leaf): coarsest systems of 1, 4, 36, 216 and 1,728 unknowns, right above the leaves
+@pytest.mark.parametrize("nrhs", [8, 11, 16])
+@pytest.mark.parametrize("d,pc,N,leaf,nc", [(2, 0, 5, 300, 1), (2, 1, 5, 300, 4), (2, 2, 12, 200, 36),
+                                            (3, 2, 8, 700, 216), (3, 2, 16, 700, 1728)])
+def test_coarsest_solve_of_columns(d, pc, N, leaf, nc, nrhs):
+    """Dense coarsest solve of several columns on the matrix cores, against one column at a time (another kernel)."""
+    _need_gpu()
+    import paper_2607_28235_amd as P
+    prob = F.structured_qp(d, N, 2, jitter=0.0, cfg=2)
+    R = np.random.default_rng(5).standard_normal((nrhs, prob.n))
+    for fp32 in (0, 1):
+        print(f"[gpu-case] coarsest nc={nc} nrhs={nrhs} fp32={fp32}", flush=True)
+        o = P.Options(dim=d, coarse_degree=pc, leaf_size=leaf, max_coarse_dofs=2000, vcycle_fp32=fp32)
+        h = P.Hierarchy(prob.coords, prob.row_ptr, prob.col, prob.val, o)
+        assert h.nlevels == 2 and h.info()[1]["n"] == nc
+        Z = torch.empty((nrhs, prob.n), dtype=torch.float64, device="cuda")
+        h.vcycle(torch.from_numpy(R).to("cuda"), Z)
+        torch.cuda.synchronize()
+        Z = Z.cpu().numpy()
+        for c in range(nrhs):
+            z = torch.empty(prob.n, dtype=torch.float64, device="cuda")
+            h.vcycle(torch.from_numpy(R[c]).to("cuda"), z)
+            torch.cuda.synchronize()
+            z = z.cpu().numpy()
+            assert np.linalg.norm(Z[c] - z) <= (1e-5 if fp32 else 1e-11) * np.linalg.norm(z)
+        h.close()
