@@ -4452,13 +4452,14 @@ __device__ inline void dt_pin(const double (&old)[2][2][4]) {
 // four waves, in four panels of 16 columns.
 //   Panel: wave 0, lane l holding row l of the panel in registers, right-looking: column j is scaled by
 //   1 / sqrt(pivot) and subtracted from the columns after it, the pivot and the factors L[c][j] coming from other
-//   lanes by v_readlane.  Meanwhile waves 1 to 3 form the off-diagonal 16 x 16 blocks of the D row before.
-//   Then waves 0 to 2 subtract the panel's products from the lower tiles behind it on the FP64 matrix cores, and
-//   wave 3 inverts the panel's diagonal block (lane c: column c, by forward substitution).
+//   lanes by v_readlane.  Meanwhile wave 3 inverts the diagonal block of the panel before (lane c: column c, by
+//   forward substitution) and waves 1 and 2 form the off-diagonal 16 x 16 blocks of the D row before that.
+//   Then the four waves subtract the panel's products from the lower tiles behind it on the FP64 matrix cores.
 // D_ij = -D_ii sum_{j <= k < i} L_ik D_kj, two chains of matrix instructions per block.
 // Bound by the chain of 64 pivots, one after another (a reciprocal square root, a product, a lane read and a
 // subtraction each), on one compute unit.  The earlier form (left-looking, a dot product from LDS, a square root, a
-// shuffle and a division per column) took 38 us a tile on a 1,728-row level (27 tiles); this one 24 us.
+// shuffle and a division per column) took 38 us a tile on a 1,728-row level (27 tiles); this one 22.3 us (24.7 with the
+// diagonal block inverted between the panels).
 constexpr int kDiagLD = DT + 1;  // odd row stride in doubles: rows across the lanes spread over the banks
 constexpr int kDiagP = 16;       // panel width
 
@@ -4508,6 +4509,24 @@ __device__ __forceinline__ void diag_inv_block(const double* s, double* t, int i
   for (int r = 0; r < 4; ++r) q[(4 * r + lk) * kDiagLD + li] = -c[r];
 }
 
+// diagonal block p of D, by one wave: lane c < 16 solves L_pp d = e_c
+__device__ __forceinline__ void diag_inv_diag(const double* s, double* t, const double* ivs, int p) {
+  const int c0 = kDiagP * p, c = threadIdx.x & 15;
+  double e[kDiagP];
+#pragma unroll
+  for (int i = 0; i < kDiagP; ++i) e[i] = i == c ? 1.0 : 0.0;
+#pragma unroll
+  for (int j = 0; j < kDiagP; ++j) {
+    e[j] = diag_div(e[j], s[(c0 + j) * kDiagLD + c0 + j], ivs[c0 + j]);
+#pragma unroll
+    for (int i = j + 1; i < kDiagP; ++i) e[i] -= s[(c0 + i) * kDiagLD + c0 + j] * e[j];
+  }
+  if ((threadIdx.x & 63) < kDiagP) {
+#pragma unroll
+    for (int i = 0; i < kDiagP; ++i) t[(c0 + i) * kDiagLD + c0 + c] = e[i];
+  }
+}
+
 __global__ __launch_bounds__(256) void k_dchol_diag(int n, int k0, double* A, double* Dk, int* bad) {
   __shared__ double s[DT * kDiagLD];  // the tile, then L
   __shared__ double t[DT * kDiagLD];  // D
@@ -4550,42 +4569,32 @@ __global__ __launch_bounds__(256) void k_dchol_diag(int n, int k0, double* A, do
       }
 #pragma unroll
       for (int c = 0; c < kDiagP; ++c) s[l * kDiagLD + c0 + c] = r[c];
-    } else if (w <= p - 1) {
-      diag_inv_block(s, t, p - 1, w - 1);  // row p - 1 of D
+    } else if (w == 3) {
+      if (p >= 1) diag_inv_diag(s, t, ivs, p - 1);
+    } else if (w <= p - 2) {
+      diag_inv_block(s, t, p - 2, w - 1);  // row p - 2 of D
     }
     __syncthreads();
-    if (w == 3) {
-      // D_pp: lane c < 16 solves L_pp d = e_c
-      const int c = l & 15;
-      double e[kDiagP];
+    // lower tiles (a, b) behind the panel, p < b <= a < 4
+    int q = 0;
+    for (int a = p + 1; a < DT / kDiagP; ++a)
+      for (int b = p + 1; b <= a; ++b, ++q) {
+        if (q % 4 != w) continue;
+        const v4d c = diag_mfma16<true>(s + kDiagP * a * kDiagLD + c0, s + kDiagP * b * kDiagLD + c0,
+                                        v4d{0.0, 0.0, 0.0, 0.0});
 #pragma unroll
-      for (int i = 0; i < kDiagP; ++i) e[i] = i == c ? 1.0 : 0.0;
-#pragma unroll
-      for (int j = 0; j < kDiagP; ++j) {
-        e[j] = diag_div(e[j], s[(c0 + j) * kDiagLD + c0 + j], ivs[c0 + j]);
-#pragma unroll
-        for (int i = j + 1; i < kDiagP; ++i) e[i] -= s[(c0 + i) * kDiagLD + c0 + j] * e[j];
+        for (int r = 0; r < 4; ++r)
+          s[(kDiagP * a + 4 * r + (l >> 4)) * kDiagLD + kDiagP * b + (l & 15)] -= c[r];
       }
-      if (l < kDiagP) {
-#pragma unroll
-        for (int i = 0; i < kDiagP; ++i) t[(c0 + i) * kDiagLD + c0 + c] = e[i];
-      }
-    } else {
-      // lower tiles (a, b) behind the panel, p < b <= a < 4, dealt to waves 0 to 2
-      int q = 0;
-      for (int a = p + 1; a < DT / kDiagP; ++a)
-        for (int b = p + 1; b <= a; ++b, ++q) {
-          if (q % 3 != w) continue;
-          const v4d c = diag_mfma16<true>(s + kDiagP * a * kDiagLD + c0, s + kDiagP * b * kDiagLD + c0,
-                                          v4d{0.0, 0.0, 0.0, 0.0});
-#pragma unroll
-          for (int r = 0; r < 4; ++r)
-            s[(kDiagP * a + 4 * r + (l >> 4)) * kDiagLD + kDiagP * b + (l & 15)] -= c[r];
-        }
-    }
     __syncthreads();
   }
-  if (w >= 1) diag_inv_block(s, t, DT / kDiagP - 1, w - 1);  // the last row of D
+  constexpr int last = DT / kDiagP - 1;
+  if (w == 3)
+    diag_inv_diag(s, t, ivs, last);
+  else if (w >= 1)
+    diag_inv_block(s, t, last - 1, w - 1);  // row last - 1 of D
+  __syncthreads();
+  if (w >= 1) diag_inv_block(s, t, last, w - 1);  // the last row of D
   __syncthreads();
 #pragma unroll
   for (int q = 0; q < kDtK; ++q) {
