@@ -766,6 +766,12 @@ static Cheb cheb_coeffs(double lo, double hi, int K) {
   return ch;
 }
 
+// Float64 coarsest systems of up to this many unknowns are multiplied row by row from the full inverse, in one launch
+// instead of two, where no prolongation is fused into the second; larger ones read the packed half.  Two-level solves,
+// packed -> rows, one column / four: 32 unknowns 525 -> 492 us / 609 -> 576, 512 628 -> 593 / 738 -> 725, 1,024 628 -> 610 /
+// 788 -> 780; 1,152 562 -> 550 / 657 -> 664, 2,048 646 -> 700 / 938 -> 949.
+constexpr int64_t kDenseRowsMax = 1024;
+
 // Coarsest solve x = A_L^{-1} b: the symmetric inverse's packed tiles (float32 tiles for the float32 V-cycle) for
 // up to kDenseSymMaxNR columns, else the full float64 inverse.  With pr, the prolongation to the level above
 // follows (fused into the tiled product's last pass, else k_prolong_c).
@@ -773,7 +779,8 @@ template <typename T>
 static void coarsest_apply(Ctx& c, int nr, const T* b, T* x, const DenseProlong<T>* pr, const int* skip,
                            hipStream_t s) {
   Device& dv = c.dv;
-  if (dv.ct > 0 && nr <= kDenseSymMaxNR) {
+  const bool rows = sizeof(T) == 8 && !pr && dv.nc <= kDenseRowsMax;
+  if (dv.ct > 0 && nr <= kDenseSymMaxNR && !rows) {
     if constexpr (sizeof(T) == 4) {
       if (dv.csym32.p) {
         launch_dense_apply_sym<T, float>((int)dv.nc, dv.ct, nr, dv.csym32.p, dv.ctile.p, dv.cpart.p, b, x, pr, skip,

@@ -188,3 +188,28 @@ def test_coarsest_solve_of_columns(d, pc, N, leaf, nc, nrhs):
             z = z.cpu().numpy()
             assert np.linalg.norm(Z[c] - z) <= (1e-5 if fp32 else 1e-11) * np.linalg.norm(z)
         h.close()
+
+
+# (d, p', cells, leaf): two-level float64 hierarchies on both sides of the size at which the packed inverse takes over
+@pytest.mark.parametrize("d,pc,N,leaf,nc", [(2, 1, 8, 64, 32), (2, 1, 48, 40, 1024), (2, 2, 32, 64, 1152)])
+def test_coarsest_solve_by_rows(d, pc, N, leaf, nc):
+    """Two-level float64 V-cycle of one and of four columns against the oracle (the float64 V-cycle bar, 1e-11)."""
+    _need_gpu()
+    import oracle as O
+    import paper_2607_28235_amd as P
+    print(f"[gpu-case] coarsest by rows nc={nc}", flush=True)
+    prob = F.structured_qp(d, N, 2, jitter=0.0, cfg=2)
+    ho = O.build_hierarchy(prob.coords, prob.scipy(), coarse_degree=pc, leaf_size=leaf, max_coarse_dofs=3000, max_levels=2)
+    o = P.Options(dim=d, coarse_degree=pc, leaf_size=leaf, max_coarse_dofs=3000, max_levels=2, vcycle_fp32=0)
+    h = P.Hierarchy(prob.coords, prob.row_ptr, prob.col, prob.val, o)
+    assert h.nlevels == 2 and h.info()[1]["n"] == nc
+    R = np.random.default_rng(6).standard_normal((4, prob.n))
+    R[:, prob.boundary] = 0.0
+    zo = np.stack([O.vcycle(ho, r) for r in R])
+    for nr in (1, 4):
+        Z = torch.empty((nr, prob.n), dtype=torch.float64, device="cuda")
+        h.vcycle(torch.from_numpy(R[:nr]).to("cuda"), Z)
+        torch.cuda.synchronize()
+        for c in range(nr):
+            assert np.linalg.norm(Z[c].cpu().numpy() - zo[c]) <= 1e-11 * np.linalg.norm(zo[c])
+    h.close()
