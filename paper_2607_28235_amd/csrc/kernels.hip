@@ -5080,21 +5080,39 @@ __global__ __launch_bounds__(256) void k_pcg_xr(int n, const PcgState* __restric
   const double al = st->alpha[k];
   const int64_t tn = (int64_t)n * NR;
   double acc = 0;
+  // U elements at a time, loads issued together (clamped addresses: loads under a lane's own condition are waited for
+  // one by one), in the order of the elements.  3D Q3 16^3, 16 columns, float32 V-cycle 26 -> 19.4 us (80 MB), k_pcg_z
+  // 15.1 -> 12.1
+  constexpr int U = NR < 4 ? NR : 4;
   for (int64_t base = (int64_t)blockIdx.x * 256 * NR; base < tn; base += (int64_t)gridDim.x * 256 * NR)
 #pragma unroll
-    for (int m = 0; m < NR; ++m) {
-      const int64_t o = base + threadIdx.x + 256 * m;
-      if (o < tn) {
-        x[o] += al * p[o];
-        const double rv = r[o] - al * q[o];
-        r[o] = rv;
-        acc += rv * rv;
-        if (b0) {
-          const T bv = (T)rv;
-          b0[o] = bv;
-          if (d0) d0[o] = dinv0[o / NR] * bv * inv_theta0;
-        } else if (d0) {
-          d0[o] = dinv0[o / NR] * (T)rv * inv_theta0;
+    for (int m0 = 0; m0 < NR; m0 += U) {
+      double xv[U], pv[U], rv[U], qv[U];
+      T dv[U];
+#pragma unroll
+      for (int m = 0; m < U; ++m) {
+        const int64_t o = min(base + threadIdx.x + 256 * (m0 + m), tn - 1);
+        xv[m] = x[o];
+        pv[m] = p[o];
+        rv[m] = r[o];
+        qv[m] = q[o];
+        dv[m] = d0 ? dinv0[o / NR] : (T)0;
+      }
+#pragma unroll
+      for (int m = 0; m < U; ++m) {
+        const int64_t o = base + threadIdx.x + 256 * (m0 + m);
+        if (o < tn) {
+          x[o] = xv[m] + al * pv[m];
+          const double r1 = rv[m] - al * qv[m];
+          r[o] = r1;
+          acc += r1 * r1;
+          if (b0) {
+            const T bv = (T)r1;
+            b0[o] = bv;
+            if (d0) d0[o] = dv[m] * bv * inv_theta0;
+          } else if (d0) {
+            d0[o] = dv[m] * (T)r1 * inv_theta0;
+          }
         }
       }
     }
@@ -5151,19 +5169,33 @@ __global__ __launch_bounds__(256) void k_pcg_z(int n, const PcgState* __restrict
   if (mode != 0 && st->all_done) return;
   const int64_t tn = (int64_t)n * NR;
   double a1 = 0, a2 = 0;
+  constexpr int U = NR < 4 ? NR : 4;  // elements at a time, as in k_pcg_xr
   for (int64_t base = (int64_t)blockIdx.x * 256 * NR; base < tn; base += (int64_t)gridDim.x * 256 * NR)
 #pragma unroll
-    for (int m = 0; m < NR; ++m) {
-      const int64_t o = base + threadIdx.x + 256 * m;
-      if (o < tn) {
-        T v = x0[o];
-        if (dp) v += dp[o];
-        const double zv = (double)v;
-        z[o] = zv;
-        if (mode == 1) pvec[o] = zv;
-        if (mode != 0) {
-          a1 += r[o] * zv;
-          if (q) a2 += q[o] * zv;
+    for (int m0 = 0; m0 < NR; m0 += U) {
+      T vv[U], dv[U];
+      double rv[U], qv[U];
+#pragma unroll
+      for (int m = 0; m < U; ++m) {
+        const int64_t o = min(base + threadIdx.x + 256 * (m0 + m), tn - 1);
+        vv[m] = x0[o];
+        dv[m] = dp ? dp[o] : (T)0;
+        rv[m] = mode != 0 ? r[o] : 0.0;
+        qv[m] = mode != 0 && q ? q[o] : 0.0;
+      }
+#pragma unroll
+      for (int m = 0; m < U; ++m) {
+        const int64_t o = base + threadIdx.x + 256 * (m0 + m);
+        if (o < tn) {
+          T v = vv[m];
+          if (dp) v += dv[m];
+          const double zv = (double)v;
+          z[o] = zv;
+          if (mode == 1) pvec[o] = zv;
+          if (mode != 0) {
+            a1 += rv[m] * zv;
+            if (q) a2 += qv[m] * zv;
+          }
         }
       }
     }
