@@ -16,7 +16,10 @@
 #include <climits>
 #include <cmath>
 #include <cstring>
+#include <exception>
+#include <mutex>
 #include <numeric>
+#include <system_error>
 #include <thread>
 
 #include "kernels.h"
@@ -26,24 +29,37 @@ namespace r3mg {
 
 namespace {
 
+// f(0), ..., f(count - 1) on up to 16 threads; fewer than `least` items run on the calling thread (a thread costs about
+// 20 us, so 64 small items; large ones, such as segments of thousands of rows, pass 2).  The first exception of an
+// item is thrown again on the calling thread, after the others have ended.
 template <typename F>
-void parallel_for(int64_t count, F&& f) {
-  unsigned hw = std::max(1u, std::min(16u, std::thread::hardware_concurrency()));
-  if (count < 64 || hw == 1) {
+void parallel_for(int64_t count, F&& f, int64_t least = 64) {
+  const int64_t hw = std::max(1u, std::min(16u, std::thread::hardware_concurrency()));
+  if (count < least || hw == 1) {
     for (int64_t i = 0; i < count; ++i) f(i);
     return;
   }
   std::atomic<int64_t> next{0};
+  std::exception_ptr failed;
+  std::mutex mu;
+  auto work = [&] {
+    try {
+      for (int64_t i; (i = next.fetch_add(1)) < count;) f(i);
+    } catch (...) {
+      std::lock_guard<std::mutex> lk(mu);
+      if (!failed) failed = std::current_exception();
+      next = count;
+    }
+  };
   std::vector<std::thread> th;
-  for (unsigned t = 0; t < hw; ++t)
-    th.emplace_back([&] {
-      for (;;) {
-        int64_t i = next.fetch_add(1);
-        if (i >= count) break;
-        f(i);
-      }
-    });
+  th.reserve((size_t)hw);
+  try {
+    for (int64_t t = 0; t < std::min(hw, count); ++t) th.emplace_back(work);
+  } catch (const std::system_error&) {
+    if (th.empty()) work();  // no thread to be had: here
+  }
   for (auto& t : th) t.join();
+  if (failed) std::rethrow_exception(failed);
 }
 
 int tree_depth(int64_t n, int64_t leaf) {
@@ -634,7 +650,7 @@ static void encode_local_blocks(const int32_t* rowptr, const int32_t* col, int64
       S.ucol.insert(S.ucol.end(), uq.begin(), uq.end());
       r = r1;
     }
-  });
+  }, 2);
   out.rb.assign(1, 0);
   out.ubp.assign(1, 0);
   out.ucol.clear();
@@ -714,7 +730,7 @@ static void encode_chunk_blocks(const Analysis& an, int cap, int rows, int ucap,
       S.ucol.insert(S.ucol.end(), uq.begin(), uq.end());
       r = r1;
     }
-  });
+  }, 2);
   out.rb.assign(1, 0);
   out.ubp.assign(1, 0);
   out.ucol.clear();
