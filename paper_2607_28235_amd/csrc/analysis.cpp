@@ -669,80 +669,6 @@ static void encode_local_geom(const int32_t* rowptr, const int32_t* col, int64_t
                       out);
 }
 
-// chunk offsets of the rows
-static void fill_cptr(Analysis& an) {
-  if (!an.cptr.empty()) return;
-  an.cptr.assign((size_t)an.n + 1, 0);
-  for (int64_t r = 0; r < an.n; ++r) an.cptr[r + 1] = an.cptr[r] + (an.rowptr[r + 1] - an.rowptr[r] + 3) / 4;
-}
-
-// Row blocks of the chunk kernels, as encode_local_blocks in chunks of four entries: at most `rows` rows, `cap` chunks
-// and `ucap` - 1 distinct columns per block; padding entries get the position of the slot after the last column.
-static void encode_chunk_blocks(const Analysis& an, int cap, int rows, int ucap, ChunkBlocks& out) {
-  const int32_t *rowptr = an.rowptr.data(), *col = an.col.data(), *cptr = an.cptr.data();
-  const int64_t n = an.n;
-  const int64_t nseg = std::max<int64_t>(1, std::min<int64_t>(256, n / 4096));
-  struct Seg {
-    std::vector<int32_t> ends, ucnt, ucol;
-  };
-  std::vector<Seg> segs((size_t)nseg);
-  out.lo.assign((size_t)cptr[n], 0);
-  out.hi.assign((size_t)cptr[n], 0);
-  parallel_for(nseg, [&](int64_t sg) {
-    static thread_local std::vector<int32_t> pos;  // 0, or 1 + position (while a block is collected: 1)
-    if ((int64_t)pos.size() < n) pos.assign((size_t)n, 0);
-    Seg& S = segs[(size_t)sg];
-    const int64_t ra = sg * n / nseg, rz = (sg + 1) * n / nseg;
-    std::vector<int32_t> uq;
-    for (int64_t r = ra; r < rz;) {
-      uq.clear();
-      int64_t r1 = r;
-      while (r1 < rz && r1 - r < rows) {
-        const int32_t a = rowptr[r1], b = rowptr[r1 + 1];
-        int64_t add = 0;
-        for (int32_t e = a; e < b; ++e) add += pos[col[e]] ? 0 : 1;
-        if (r1 > r && (cptr[r1 + 1] - cptr[r] > cap || (int64_t)uq.size() + add > ucap - 1)) break;
-        for (int32_t e = a; e < b; ++e)
-          if (!pos[col[e]]) {
-            pos[col[e]] = 1;
-            uq.push_back(col[e]);
-          }
-        ++r1;
-      }
-      std::sort(uq.begin(), uq.end());
-      for (size_t i = 0; i < uq.size(); ++i) pos[uq[i]] = (int32_t)i + 1;
-      if ((int64_t)uq.size() < ucap)
-        for (int64_t q = r; q < r1; ++q)
-          for (int32_t k = cptr[q]; k < cptr[q + 1]; ++k) {
-            uint32_t lo = 0, hi = 0;
-            for (int m = 0; m < 4; ++m) {
-              const int32_t e = rowptr[q] + 4 * (k - cptr[q]) + m;
-              const uint32_t ps = e < rowptr[q + 1] ? (uint32_t)(pos[col[e]] - 1) : (uint32_t)uq.size();
-              lo |= (ps & 0xff) << (8 * m);
-              hi |= (ps >> 8) << (2 * m);
-            }
-            out.lo[(size_t)k] = lo;
-            out.hi[(size_t)k] = (uint8_t)hi;
-          }
-      for (int32_t c : uq) pos[c] = 0;
-      S.ends.push_back((int32_t)r1);
-      S.ucnt.push_back((int32_t)uq.size());
-      S.ucol.insert(S.ucol.end(), uq.begin(), uq.end());
-      r = r1;
-    }
-  }, 2);
-  out.rb.assign(1, 0);
-  out.ubp.assign(1, 0);
-  out.ucol.clear();
-  for (const Seg& S : segs) {
-    for (size_t k = 0; k < S.ends.size(); ++k) {
-      out.rb.push_back(S.ends[k]);
-      out.ubp.push_back(out.ubp.back() + S.ucnt[k]);
-    }
-    out.ucol.insert(out.ucol.end(), S.ucol.begin(), S.ucol.end());
-  }
-}
-
 void encode_mr_blocks(const Analysis& an, int cls, MrHost& out) {
   encode_local_blocks(an.rowptr.data(), an.col.data(), an.n, an.n, kMrCap[cls], kMrRows[cls], kMrUcap[cls], 2, kMrPad,
                       out.lb);
@@ -757,29 +683,12 @@ void encode_mr_blocks(const Analysis& an, int cls, MrHost& out) {
   });
 }
 
-void encode_chunk_mr(Analysis& an, int g, ChunkMrHost& out) {
-  fill_cptr(an);
-  encode_chunk_blocks(an, kChunkMrCap[g], kChunkMrRows[g], kChunkMrUcap[g], out.cb);
-  out.ord.assign((size_t)an.n, 0);
-  parallel_for((int64_t)out.cb.rb.size() - 1, [&](int64_t k) {
-    const int32_t r0 = out.cb.rb[k], r1 = out.cb.rb[k + 1];
-    for (int32_t r = r0; r < r1; ++r) out.ord[r] = (uint8_t)(r - r0);
-    std::stable_sort(out.ord.begin() + r0, out.ord.begin() + r1, [&](uint8_t i, uint8_t j) {
-      return an.cptr[r0 + i + 1] - an.cptr[r0 + i] > an.cptr[r0 + j + 1] - an.cptr[r0 + j];
-    });
-  });
-}
-
 void encode_fine(Analysis& an) {
   encode_csr_blocks(an);
   if (an.opt.fine_kernel >= kLocalFirst) {  // a local-column shape is asked for: its blocks
     static const int geom[kFineShapes - kLocalFirst] = {0, 1, 2, 0, 3, 0, 3};
     const int g = geom[an.opt.fine_kernel - kLocalFirst];
     encode_local_geom(an.rowptr.data(), an.col.data(), an.n, g, an.loc[g]);
-  }
-  if (an.opt.fine_kernel < 0) {  // the chunk shape takes part in the set-up timing only
-    fill_cptr(an);
-    encode_chunk_blocks(an, kChunkCap, kChunkRows, kChunkUcap, an.chunk);
   }
   // agglomerated levels with narrow block rows (the 2D hierarchies): CSR row pointers and 1-byte local blocks
   const int L = an.nlevels() - 1;

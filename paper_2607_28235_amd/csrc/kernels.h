@@ -111,6 +111,14 @@ constexpr int kStreamShapes = 15;
 constexpr int kChunkCap = 768;
 constexpr int kChunkRows = 128;
 constexpr int kChunkUcap = 512;
+// Block geometries over chunked rows (most chunks, rows and, with the zero slot, distinct columns of a block): 0 and 1 of
+// the several-column kernel, 2 of the one-column kernel.  The several-column kernel over geometry 2 was up to 30% slower
+// (3D Q3 16^3, 16 float32 columns: whole solve 8.5 ms against 6.5), so the geometries stay apart.
+constexpr int kChunkGeoms = 3;
+constexpr int kChunkOneGeom = 2;
+constexpr int kChunkCapOf[kChunkGeoms] = {512, 1024, kChunkCap};
+constexpr int kChunkRowsOf[kChunkGeoms] = {64, 128, kChunkRows};
+constexpr int kChunkUcapOf[kChunkGeoms] = {384, 640, kChunkUcap};
 constexpr int kVecTwoFirst = 11;  // shapes 11, 12: the blocks of shapes 9, 10 taken two per workgroup
 constexpr int kAggVecShape = 13;
 constexpr int kLocalFirst = 6;
@@ -167,12 +175,25 @@ template <typename T>
 void launch_level_blockrow_wg(const LevelOp<T>& op, int maxnb, const T* u, const T* b, T* rho, T* x, T* dout,
                               double c1, double c2, int flags, const int* skip, hipStream_t s);
 
-// Fine level for nr in {2, 4, 8, 16} right-hand sides over chunked rows (k_level_chunk_mr), in two block geometries:
-// chunks, rows and distinct columns (with the zero slot) per block, and threads per workgroup.
+// Blocks of one geometry over the chunked rows, encoded on the device from the CSR arrays in two steps.  Step 1 cuts the
+// rows into blocks, greedily within nseg independent row segments: blk[first row of the segment + k] = (first row,
+// distinct columns) of its k-th block, segn[segment] = (blocks, their distinct columns in all).  Step 2, once the arrays
+// are sized by the sums of segn, fills the block records, the column lists, the positions and, where ord is set, the rows
+// of every block by decreasing number of chunks.
+constexpr int kChunkSegRows = 4096;  // rows of a segment, at least (a matrix of fewer is one segment)
+struct ChunkLists {
+  int geom = 0, n = 0, nseg = 0, nrb = 0;
+  const int *rowptr = nullptr, *cptr = nullptr, *col = nullptr;
+  int2 *blk = nullptr, *segn = nullptr;
+  int *meta = nullptr, *ucol = nullptr;
+  uint32_t* clo = nullptr;
+  uint8_t *chi = nullptr, *ord = nullptr;
+};
+void launch_chunk_cut(const ChunkLists& c, hipStream_t s);
+void launch_chunk_lists(const ChunkLists& c, hipStream_t s);
+
+// Fine level for nr in {2, 4, 8, 16} right-hand sides over chunked rows (k_level_chunk_mr), in block geometries 0 and 1
 constexpr int kChunkMrGeoms = 2;
-constexpr int kChunkMrCap[kChunkMrGeoms] = {512, 1024};
-constexpr int kChunkMrRows[kChunkMrGeoms] = {64, 128};
-constexpr int kChunkMrUcap[kChunkMrGeoms] = {384, 640};
 constexpr int kChunkMrThreads[kChunkMrGeoms] = {256, 512};
 struct ChunkMrBlocks {
   int geom = 0, nrb = 0;

@@ -88,17 +88,6 @@ struct LocalBlocks {  // local-column row blocks of a CSR pattern (device form: 
   std::vector<uint8_t> lidx;  // 1 or 2 bytes per nonzero, plus kFinePad padding entries
 };
 
-struct ChunkBlocks {  // row blocks of the chunk kernel (device form: FineBlocks)
-  std::vector<int32_t> rb, ubp, ucol;
-  std::vector<uint32_t> lo;  // per chunk: low bytes of its four column positions
-  std::vector<uint8_t> hi;   // per chunk: the bits above them, 2 per position
-};
-
-struct ChunkMrHost {  // blocks of one geometry of the multi-right-hand-side chunk kernel (device form: ChunkMrBlocks)
-  ChunkBlocks cb;
-  std::vector<uint8_t> ord;  // per block, its rows in order of decreasing row length
-};
-
 struct MrHost {  // blocks of one staging class of the multi-right-hand-side kernel (device form: MrBlocks)
   LocalBlocks lb;
   std::vector<int32_t> ord;  // per block, its rows in order of decreasing row length
@@ -135,8 +124,6 @@ struct Analysis {
   // geometries (block offsets, distinct-column offsets and lists, local column index bytes per nonzero)
   std::vector<int32_t> rb[3];
   LocalBlocks loc[4];
-  std::vector<int32_t> cptr;             // chunk offsets of the rows: every row padded to whole chunks of four
-  ChunkBlocks chunk;
   std::vector<uint8_t> constrained;      // internal order
   std::vector<uint8_t> constrained_user; // caller's order
   std::vector<int32_t> owner;            // internal point -> level-1 box, -1 if constrained
@@ -166,8 +153,6 @@ std::unique_ptr<Analysis> analyze(const double* coords, int64_t n, const int64_t
 void encode_fine(Analysis& an);
 // blocks of staging class cls (kMrCap / kMrRows / kMrUcap) of the multi-right-hand-side kernel over the fine level
 void encode_mr_blocks(const Analysis& an, int cls, MrHost& out);
-// blocks of geometry g of the multi-right-hand-side chunk kernel over the fine level (fills an.cptr if it is empty)
-void encode_chunk_mr(Analysis& an, int g, ChunkMrHost& out);
 
 // bisection R-tree (Section 3, Section 4 point-based agglomeration); offsets[k] per depth k
 void bisection_rtree(const double* coords, int64_t n, int d, int leaf, int& depth, std::vector<int32_t>& order,
@@ -232,11 +217,12 @@ struct DevLevel {
   DBuf<uint8_t> lidx[kLocalGeomsAll];
   DBuf<int32_t> lmeta[kLocalGeomsAll];  // per-block records of the local-column blocks (FineBlocks::meta)
   FineBlocks fb[kStreamShapes];  // l = 0: row blocks of every kernel shape
-  // l = 0: the chunk kernel's blocks, and the chunked values in the precisions whose chosen shape reads them
+  // l = 0: chunk offsets of the rows (every row padded to whole chunks of four), the blocks over them per geometry, each
+  // built where a kernel first needs it, and the chunked values in the precisions whose chosen kernels read them
   int64_t nchunk = 0;
-  DBuf<int32_t> cptr, cucol, cmeta;
-  DBuf<uint32_t> clo;
-  DBuf<uint8_t> chi;
+  DBuf<int32_t> cptr, cucol[kChunkGeoms], cmeta[kChunkGeoms];
+  DBuf<uint32_t> clo[kChunkGeoms];
+  DBuf<uint8_t> chi[kChunkGeoms], cord[kChunkMrGeoms];
   DBuf<float> cval32;
   DBuf<double> cval64;
   // l = 0: blocks of the LDS-staged multi-right-hand-side kernel per staging class, built at the first
@@ -244,11 +230,7 @@ struct DevLevel {
   DBuf<int32_t> mrb[kMrClasses], mubp[kMrClasses], mucol[kMrClasses], mord[kMrClasses], mmeta[kMrClasses];
   DBuf<uint16_t> mlidx[kMrClasses];
   MrBlocks mr[kMrClasses];
-  // l = 0: blocks of the multi-right-hand-side chunk kernel per geometry, built likewise; chunk_mr32 / chunk_mr64: a
-  // timed choice reads the chunked values in that precision
-  DBuf<int32_t> cmrmeta[kChunkMrGeoms], cmrucol[kChunkMrGeoms];
-  DBuf<uint32_t> cmrlo[kChunkMrGeoms];
-  DBuf<uint8_t> cmrhi[kChunkMrGeoms], cmrord[kChunkMrGeoms];
+  // l = 0: chunk_mr32 / chunk_mr64: a timed choice for several columns reads the chunked values in that precision
   ChunkMrBlocks cmr[kChunkMrGeoms];
   bool chunk_mr32 = false, chunk_mr64 = false;
   double shape_bytes[kStreamShapes] = {};  // algorithmic bytes of one application with each shape

@@ -196,8 +196,10 @@ constexpr int kCodeSplit = 100;
 constexpr int kCodeSplit2 = 200;
 constexpr int kCodeBox = 300;    // agglomerated levels: the box kernel on the matrix cores
 constexpr int kCodeChunk = 400;  // fine level: kCodeChunk + g = the chunk kernel over blocks of geometry g
-// The chunk kernel's blocks are encoded on the host at a handle's first block solve (about 10 ms for 1.4 M nonzeros), so
-// it has to be 5% faster than a kernel over the CSR arrays.
+// The chunk kernel's blocks are encoded at a handle's first block solve, which a kernel over the CSR arrays does not need:
+// first V-cycle of four columns on 3D Q2 24^3 1.6 against 1.2 ms (on the host it was 26).  So it has to be 5% faster: a
+// solve of 1.1 ms (3D Q2 16^3, four columns) then repays its 0.3 ms of encoding within six solves; the usual gain is 10 to
+// 25%.
 constexpr float kChunkMrMargin = 1.05f;
 
 // Block geometry of the chunk kernel for several right-hand sides, -1 = not a candidate.  Long rows need the larger
@@ -415,40 +417,76 @@ static void keep_chunks(DevLevel& D, bool fp32, hipStream_t s) {
   }
 }
 
+// blocks of geometry g over the chunked rows of the fine level, on the device once; the number of them
+static int build_chunks(const Analysis& an, DevLevel& D, int g, hipStream_t s) {
+  if (!D.cptr.p) {
+    std::vector<int32_t> cptr((size_t)an.n + 1, 0);
+    for (int64_t r = 0; r < an.n; ++r) cptr[r + 1] = cptr[r] + (an.rowptr[r + 1] - an.rowptr[r] + 3) / 4;
+    D.nchunk = cptr[an.n];
+    D.cptr.upload(cptr, s);
+    R3MG_HIP_CHECK(hipStreamSynchronize(s));  // the host list is released
+  }
+  if (D.cmeta[g].p) return (int)(D.cmeta[g].n / 4) - 1;
+  ChunkLists c;
+  c.geom = g;
+  c.n = (int)an.n;
+  c.nseg = (int)std::max<int64_t>(1, an.n / kChunkSegRows);
+  c.rowptr = D.rowptr.p;
+  c.cptr = D.cptr.p;
+  c.col = D.col.p;
+  DBuf<int2> cut;  // step 1: the blocks, then the segments' totals
+  cut.alloc((size_t)an.n + c.nseg);
+  c.blk = cut.p;
+  c.segn = cut.p + an.n;
+  launch_chunk_cut(c, s);
+  std::vector<int2> segn(c.nseg);
+  R3MG_HIP_CHECK(hipMemcpyAsync(segn.data(), c.segn, segn.size() * sizeof(int2), hipMemcpyDeviceToHost, s));
+  R3MG_HIP_CHECK(hipStreamSynchronize(s));
+  int64_t ucols = 0;
+  for (const int2& t : segn) {
+    c.nrb += t.x;
+    ucols += t.y;
+  }
+  DBuf<int32_t> meta;
+  meta.alloc(4 * ((size_t)c.nrb + 1));
+  D.cucol[g].alloc((size_t)ucols);
+  D.clo[g].alloc((size_t)D.nchunk);
+  D.chi[g].alloc((size_t)D.nchunk);
+  if (g < kChunkMrGeoms) D.cord[g].alloc((size_t)an.n);
+  c.meta = meta.p;
+  c.ucol = D.cucol[g].p;
+  c.clo = D.clo[g].p;
+  c.chi = D.chi[g].p;
+  c.ord = g < kChunkMrGeoms ? D.cord[g].p : nullptr;
+  launch_chunk_lists(c, s);
+  R3MG_HIP_CHECK(hipStreamSynchronize(s));  // `cut` is released
+  D.cmeta[g] = std::move(meta);
+  return c.nrb;
+}
+
+// bytes of one application over the blocks of geometry g: values and positions of the chunks, distinct columns, block
+// records, chunk offsets, 7 vector streams of nr columns
+static double chunk_bytes(const DevLevel& D, int g, double esz, int nr) {
+  return (double)D.nchunk * (4 * esz + 5) + 4.0 * (double)D.cucol[g].n + 4.0 * (double)D.cmeta[g].n + 4.0 * (D.n + 1) +
+         7.0 * D.n * esz * nr;
+}
+
 // Blocks of geometry g of the multi-right-hand-side chunk kernel and the chunked values in element size esz, built the
 // first time a tuning needs them (false: the fine level is matrix-free)
 static bool ensure_chunk_mr(Ctx& c, int g, int esz, hipStream_t s) {
   DevLevel& D = c.dv.lv[0];
   if (g < 0 || g >= kChunkMrGeoms || D.mf) return false;
-  if (D.cmr[g].nrb == 0) {
-    ChunkMrHost h;
-    encode_chunk_mr(c.an, g, h);
-    const size_t nb = h.cb.rb.size();
-    std::vector<int32_t> meta(nb * 4, 0);
-    for (size_t k = 0; k < nb; ++k) {
-      meta[4 * k] = h.cb.rb[k];
-      meta[4 * k + 1] = c.an.cptr[h.cb.rb[k]];
-      meta[4 * k + 2] = h.cb.ubp[k];
-    }
-    if (!D.cptr.p) {
-      D.cptr.upload(c.an.cptr, s);
-      D.nchunk = c.an.cptr[c.an.n];
-    }
-    D.cmrmeta[g].upload(meta, s);
-    D.cmrucol[g].upload(h.cb.ucol, s);
-    D.cmrlo[g].upload(h.cb.lo, s);
-    D.cmrhi[g].upload(h.cb.hi, s);
-    D.cmrord[g].upload(h.ord, s);
-    R3MG_HIP_CHECK(hipStreamSynchronize(s));  // the host vectors are released on return
-    ChunkMrBlocks& m = D.cmr[g];
+  ChunkMrBlocks& m = D.cmr[g];
+  if (m.nrb == 0) {
+    const int nrb = build_chunks(c.an, D, g, s);
     m.geom = g;
-    m.meta = D.cmrmeta[g].p;
-    m.ucol = D.cmrucol[g].p;
+    m.meta = D.cmeta[g].p;
+    m.ucol = D.cucol[g].p;
     m.cptr = D.cptr.p;
-    m.clo = D.cmrlo[g].p;
-    m.chi = D.cmrhi[g].p;
-    m.ord = D.cmrord[g].p;
-    m.nrb = (int)nb - 1;
+    m.clo = D.clo[g].p;
+    m.chi = D.chi[g].p;
+    m.ord = D.cord[g].p;
+    m.nrb = nrb;
   }
   if (esz == 4 && !D.cval32.p) {
     D.cval32.alloc(4 * (size_t)D.nchunk);
@@ -1331,32 +1369,15 @@ void device_setup(HandleImpl& h, hipStream_t s) {
     };
     same_blocks(kLocalFirst + kLocalGeoms, kLocalFirst);
     for (int sh : {kVecTwoFirst, kVecTwoFirst + 1}) same_blocks(sh, sh - 2);
-    if (!an.cptr.empty()) {  // chunk shape
-      D.nchunk = an.cptr[an.n];
-      D.cptr.upload(an.cptr, s);
-      const ChunkBlocks& cb = an.chunk;
-      const size_t nb = cb.rb.size();
-      std::vector<int32_t> meta(nb * 4, 0);
-      for (size_t k = 0; k < nb; ++k) {
-        meta[4 * k] = cb.rb[k];
-        meta[4 * k + 1] = an.cptr[cb.rb[k]];
-        meta[4 * k + 2] = cb.ubp[k];
-      }
-      D.cmeta.upload(meta, s);
-      D.cucol.upload(cb.ucol, s);
-      D.clo.upload(cb.lo, s);
-      D.chi.upload(cb.hi, s);
-      R3MG_HIP_CHECK(hipStreamSynchronize(s));  // the records are released on return
+    if (an.opt.fine_kernel < 0) {  // chunk shape
       FineBlocks& f = D.fb[kChunkShape];
-      f.nrb = (int)nb - 1;
-      f.ucol = D.cucol.p;
-      f.meta = D.cmeta.p;
+      f.nrb = build_chunks(an, D, kChunkOneGeom, s);
+      f.ucol = D.cucol[kChunkOneGeom].p;
+      f.meta = D.cmeta[kChunkOneGeom].p;
       f.cptr = D.cptr.p;
-      f.clo = D.clo.p;
-      f.chi = D.chi.p;
-      // values and positions of the chunks, distinct columns, block records, chunk offsets, 7 vector streams
-      D.shape_bytes[kChunkShape] = (double)D.nchunk * (4 * sv0 + 5) + 4.0 * cb.ucol.size() + 16.0 * nb +
-                                   4.0 * (an.n + 1) + 7.0 * an.n * sv0;
+      f.clo = D.clo[kChunkOneGeom].p;
+      f.chi = D.chi[kChunkOneGeom].p;
+      D.shape_bytes[kChunkShape] = chunk_bytes(D, kChunkOneGeom, sv0, 1);
     }
     D.dinv64.alloc(D.n);
     if (fp32) {
@@ -2225,10 +2246,7 @@ static double level_bytes(Ctx& c, int l, int nr, int esz) {
       return nnz * (esz + 2) + 4.0 * nuc + 16.0 * (nrb + 1) + 4.0 * n + 4.0 * (n + 1) + vec * nr;
     }
     if (it != c.dv.tuned.end() && it->second >= kCodeChunk) {
-      // values and positions of the chunks, distinct columns, block records, row order, chunk offsets
-      const int g = it->second - kCodeChunk;
-      return (double)D.nchunk * (4.0 * esz + 5) + 4.0 * (double)D.cmrucol[g].n + 16.0 * (D.cmr[g].nrb + 1.0) + n +
-             4.0 * (n + 1) + vec * nr;
+      return chunk_bytes(D, it->second - kCodeChunk, esz, nr) + n;  // and the row order
     }
     return nnz * (esz + 4) + 4.0 * (n + 1) + vec * nr;  // CSR kernels
   }

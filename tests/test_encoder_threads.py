@@ -1,6 +1,6 @@
-"""The row-block encoders share their segments (4,096 rows or more) among threads from two segments on.  A preloaded
-pthread_create counts the threads that one r3mg_analyze starts: with the chunk blocks encoded it starts more of them
-than without, on a matrix of three segments."""
+"""The host encoder of the local-column row blocks shares its segments (4,096 rows or more) among threads from two
+segments on.  A preloaded pthread_create counts the threads that one r3mg_analyze starts: with the blocks of a
+local-column shape encoded it starts more of them than without, on a matrix of three segments."""
 import os
 import subprocess
 import sys
@@ -31,7 +31,7 @@ made = ctypes.CDLL(sys.argv[2]).threads_made
 prob = F.structured_qp(3, 12, 2)
 assert prob.n == 15625
 out = []
-for fine in (0, -1):
+for fine in (0, 6):
     o = P.Options(dim=3, coarse_degree=1, leaf_size=256, skip_leaf_level=1, fine_kernel=fine, multi_rhs_kernel=0)
     before = made()
     P.Hierarchy(prob.coords, prob.row_ptr, prob.col, prob.val, o, factor=False).close()
@@ -40,7 +40,7 @@ print("threads", *out)
 """
 
 
-def test_chunk_blocks_are_encoded_by_several_threads(tmp_path):
+def test_local_blocks_are_encoded_by_several_threads(tmp_path):
     if (os.cpu_count() or 1) < 2 or len(os.sched_getaffinity(0)) < 2:
         pytest.skip("one processor")
     src, lib = tmp_path / "counter.c", tmp_path / "counter.so"

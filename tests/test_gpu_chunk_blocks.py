@@ -1,0 +1,180 @@
+"""The chunk kernels' blocks are encoded on the device, in independent segments of at least 4,096 rows: matrices of
+several segments with uneven ends (and rows beyond the limits inside them) for the one-column kernel and both
+geometries of the several-column kernel, and the time that the encoding adds to a handle's first block call.
+
+Tolerances: the one-column kernel adds a row's products in CSR shape 0's order (bitwise; a row beyond the limits is
+added in another order, 1e-14 for the operator); several columns are held to the bars of the V-cycle against another
+kernel, 1e-11 in float64 and 1e-5 in float32.
+"""
+import dataclasses
+import time
+
+import numpy as np
+import pytest
+
+import fixtures as F
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+SHAPE, LANES, BLOCKS = 14, 8, 400
+
+
+def _need_gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+def _t(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to("cuda")
+
+
+def _wide(counts):
+    """2D Q1 110^2 (12,321 rows: three segments) with one interior DoF per entry of counts, spread over the square,
+    coupled to others so that its row holds that many entries (symmetric positive semi-definite couplings)."""
+    import scipy.sparse as sp
+    prob = F.structured_qp(2, 110, 1)
+    A = prob.scipy().tocsr()
+    free = np.flatnonzero(~prob.boundary)
+    hubs = free[np.linspace(0, len(free) - 1, len(counts) + 2).astype(int)[1:-1]]
+    rest = np.setdiff1d(free, hubs)
+    for k, count in zip(hubs, counts):
+        js = np.setdiff1d(rest, A.indices[A.indptr[k]:A.indptr[k + 1]])
+        js = js[::len(js) // count][:count - (A.indptr[k + 1] - A.indptr[k])]
+        v = np.full(len(js), 1e-2)
+        C = sp.csr_matrix((np.concatenate([v, v, v, [v.sum()]]),
+                           (np.concatenate([np.full(len(js), k), js, js, [k]]),
+                            np.concatenate([js, np.full(len(js), k), js, [k]]))), shape=A.shape)
+        A = (A + C).tocsr()
+    A.sort_indices()
+    assert sorted(np.diff(A.indptr))[-len(counts):] == sorted(counts)
+    return prob.coords, A, 2
+
+
+def _plain(d, N, p):
+    prob = F.structured_qp(d, N, p, jitter=0.2 if d == 2 else 0.0, cfg=2)
+    return prob.coords, prob.scipy().tocsr(), d
+
+
+def _headline():
+    prob = F.workload(2).problem
+    return prob.coords, prob.scipy().tocsr(), 2
+
+
+CASES = {
+    "2d_q3": lambda: _plain(2, 60, 3),               # 32,761 rows, the chunk limit
+    "3d_q2": lambda: _plain(3, 14, 2),               # 24,389 rows, the column limit
+    "wide511": lambda: _wide([383, 384, 511]),       # rows at the column limits of geometry 0 and of one column
+    "wide": lambda: _wide([383, 384, 511, 639]),     # and of geometry 1
+    "wider": lambda: _wide([512, 640, 3000, 4500]),  # and beyond them, the last one beyond the chunk limits as well
+}
+
+
+def _handle(case, fp32, **kw):
+    import paper_2607_28235_amd as P
+    coords, A, d = case
+    o = P.Options(dim=d, coarse_degree=1, leaf_size=64 if d == 2 else 150, max_coarse_dofs=600,
+                  skip_leaf_level=int(d == 3), vcycle_fp32=fp32)
+    return P.Hierarchy(coords, A.indptr.astype(np.int64), A.indices.astype(np.int32), A.data,
+                       dataclasses.replace(o, **kw))
+
+
+def _force(path, pick, code):
+    """Append `code` for the keys of the tuning cache that pick selects."""
+    keys = {ln.rsplit(" ", 1)[0] for ln in open(path) if pick(ln)}
+    assert keys
+    with open(path, "a") as f:
+        f.writelines(f"{k} {code}\n" for k in sorted(keys))
+
+
+@pytest.mark.parametrize("name", [*CASES, "2d_q3_591k"])
+def test_one_column(name, tmp_path, monkeypatch):
+    _need_gpu()
+    case = _headline() if name == "2d_q3_591k" else CASES[name]()
+    A = case[1]
+    n = A.shape[0]
+    path = tmp_path / "tune"
+    monkeypatch.setenv("R3MG_TUNE_CACHE", str(path))
+    r = np.random.default_rng(2).standard_normal(n)
+    for fp32 in (0, 1):
+        print(f"[gpu-case] chunk blocks {name} fp32={fp32}", flush=True)
+        _handle(case, fp32).close()
+        _force(path, lambda ln: f"/fine1/f{32 if fp32 else 64}" in ln, SHAPE + 100 * SHAPE)
+        h, ref = _handle(case, fp32), _handle(case, fp32, fine_kernel=0)
+        assert h.info()[0]["kernel"].startswith("k_level_chunk<")
+        for scale in (1.0, 1.75):
+            if scale != 1.0:
+                for q in (h, ref):
+                    q.update_values(_t(A.data * scale))
+            out = []
+            for q in (h, ref):
+                y, z = (torch.zeros(n, dtype=torch.float64, device="cuda") for _ in range(2))
+                q.level_apply(0, _t(r), y)
+                q.vcycle(_t(r), z)
+                out.append((y.cpu().numpy(), z.cpu().numpy()))
+            want = scale * (A @ r)
+            assert np.linalg.norm(out[0][0] - want) <= 1e-14 * np.linalg.norm(want)
+            if np.diff(A.indptr).max() > 511:  # beyond the one-column kernel's limit
+                assert np.linalg.norm(out[0][1] - out[1][1]) <= (1e-5 if fp32 else 1e-11) * np.linalg.norm(out[1][1])
+            else:
+                assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
+        h.close()
+        ref.close()
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_several_columns(name, tmp_path, monkeypatch):
+    _need_gpu()
+    case = CASES[name]()
+    n = case[1].shape[0]
+    R = _t(np.random.default_rng(3).standard_normal((4, n)))
+    for fp32 in (0, 1):
+        print(f"[gpu-case] chunk blocks of four columns {name} fp32={fp32}", flush=True)
+        path = tmp_path / f"tune{fp32}"
+        monkeypatch.setenv("R3MG_TUNE_CACHE", str(path))
+        h = _handle(case, fp32)
+        h.vcycle(R, torch.empty_like(R))
+        h.close()
+        out = []
+        for code in (LANES, BLOCKS, BLOCKS + 1):
+            _force(path, lambda ln: "/mr/0/" in ln or "/mr/-1/" in ln, code)
+            before = open(path).read()
+            h = _handle(case, fp32)
+            Z = torch.empty_like(R)
+            h.vcycle(R, Z)
+            out.append(Z.cpu().numpy())
+            assert open(path).read() == before
+            h.close()
+        for z in out[1:]:
+            for j in range(4):
+                assert np.linalg.norm(z[j] - out[0][j]) <= (1e-5 if fp32 else 1e-11) * np.linalg.norm(out[0][j])
+
+
+def test_first_block_call_takes_no_host_encoding(tmp_path, monkeypatch):
+    """The first V-cycle of four columns on a new handle whose kernel choice is known (117,649 rows, 6.5 M nonzeros).
+    With the chunk kernel it also encodes the blocks: about a millisecond on the device, where the host took 25 ms and
+    more.  Bar: 6 ms above the column-split kernel, which reads the CSR arrays; the best of four handles each."""
+    _need_gpu()
+    print("[gpu-case] first block call", flush=True)
+    case = _plain(3, 24, 2)
+    n = case[1].shape[0]
+    R = _t(np.random.default_rng(4).standard_normal((4, n)))
+    path = tmp_path / "tune"
+    monkeypatch.setenv("R3MG_TUNE_CACHE", str(path))
+    h = _handle(case, 1)
+    h.vcycle(R, torch.empty_like(R))
+    h.close()
+    best = {}
+    for code in (216, BLOCKS + 1):
+        _force(path, lambda ln: "/mr/0/" in ln or "/mr/-1/" in ln, code)
+        for _ in range(4):
+            h = _handle(case, 1)
+            Z = torch.empty_like(R)
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            h.vcycle(R, Z)
+            torch.cuda.synchronize()
+            best[code] = min(best.get(code, 1e9), time.perf_counter() - t)
+            h.close()
+    print("first call ms", {k: 1e3 * v for k, v in best.items()}, flush=True)
+    assert best[BLOCKS + 1] <= best[216] + 6e-3
