@@ -230,9 +230,11 @@ struct DevLevel {
   DBuf<int32_t> mrb[kMrClasses], mubp[kMrClasses], mucol[kMrClasses], mord[kMrClasses], mmeta[kMrClasses];
   DBuf<uint16_t> mlidx[kMrClasses];
   MrBlocks mr[kMrClasses];
-  // l = 0: chunk_mr32 / chunk_mr64: a timed choice for several columns reads the chunked values in that precision
+  // l = 0, several columns: chunk_mr32 / chunk_mr64: a choice reads the chunked values in that precision; bit g of
+  // chunk_mr_geoms: a choice reads the blocks of geometry g
   ChunkMrBlocks cmr[kChunkMrGeoms];
   bool chunk_mr32 = false, chunk_mr64 = false;
+  int chunk_mr_geoms = 0;
   double shape_bytes[kStreamShapes] = {};  // algorithmic bytes of one application with each shape
   int shape = 0;        // l = 0: kernel shape chosen by timing at set-up
   int shape64 = 0;      // l = 0: shape of the float64 operator PCG applies (with a float64 V-cycle: shape)

@@ -399,26 +399,51 @@ static void fill_chunks(DevLevel& D, int esz, hipStream_t s) {
   if (esz == 4 && D.cval32.p) launch_chunk_values<float>((int)D.n, D.rowptr.p, D.cptr.p, D.val32.p, D.cval32.p, s);
 }
 
-// keeps a chunked copy of the fine values for exactly the precisions in which the chosen kernels read one
-static void keep_chunks(DevLevel& D, bool fp32, hipStream_t s) {
-  const size_t count = 4 * (size_t)D.nchunk;
-  const bool want32 = fp32 && (D.shape == kChunkShape || D.chunk_mr32);
-  const bool want64 = D.shape64 == kChunkShape || D.chunk_mr64;
-  R3MG_HIP_CHECK(hipStreamSynchronize(s));  // the copies may still be read by the timing
-  if (!want32) D.cval32.release();
-  if (!want64) D.cval64.release();
-  if (want32 && !D.cval32.p) {
-    D.cval32.alloc(count);
-    fill_chunks(D, 4, s);
+// the chunked fine values in element size esz; false: no device memory for them
+static bool hold_chunks(DevLevel& D, int esz, hipStream_t s) {
+  if (esz == 4 ? D.cval32.p != nullptr : D.cval64.p != nullptr) return true;
+  try {
+    if (esz == 4)
+      D.cval32.alloc(4 * (size_t)D.nchunk);
+    else
+      D.cval64.alloc(4 * (size_t)D.nchunk);
+  } catch (const Error& e) {
+    if (e.code != R3MG_ERR_OOM) throw;
+    return false;
   }
-  if (want64 && !D.cval64.p) {
-    D.cval64.alloc(count);
-    fill_chunks(D, 8, s);
+  fill_chunks(D, esz, s);
+  return true;
+}
+
+static void release_chunk_lists(DevLevel& D, int g) {
+  D.cmeta[g].release();
+  D.cucol[g].release();
+  D.clo[g].release();
+  D.chi[g].release();
+  if (g < kChunkMrGeoms) {
+    D.cord[g].release();
+    D.cmr[g] = ChunkMrBlocks{};
+  } else {
+    D.fb[kChunkShape] = FineBlocks{};
   }
 }
 
-// blocks of geometry g over the chunked rows of the fine level, on the device once; the number of them
-static int build_chunks(const Analysis& an, DevLevel& D, int g, hipStream_t s) {
+// gives back the chunked values in the precisions, and the block lists of the geometries, that no chosen kernel reads
+static void drop_unread_chunks(DevLevel& D, bool fp32, hipStream_t s) {
+  R3MG_HIP_CHECK(hipStreamSynchronize(s));  // the timing may still read them
+  if (!(fp32 && (D.shape == kChunkShape || D.chunk_mr32))) D.cval32.release();
+  if (!(D.shape64 == kChunkShape || D.chunk_mr64)) D.cval64.release();
+  if (D.shape != kChunkShape && D.shape64 != kChunkShape) release_chunk_lists(D, kChunkOneGeom);
+  for (int g = 0; g < kChunkMrGeoms; ++g)
+    if (!(D.chunk_mr_geoms >> g & 1)) release_chunk_lists(D, g);
+  bool any = false;
+  for (const auto& m : D.cmeta) any = any || m.p;
+  if (!any) D.cptr.release();
+}
+
+// blocks of geometry g over the chunked rows of the fine level, on the device once: the number of them, 0 where there is
+// no device memory for them
+static int build_chunks(const Analysis& an, DevLevel& D, int g, hipStream_t s) try {
   if (!D.cptr.p) {
     std::vector<int32_t> cptr((size_t)an.n + 1, 0);
     for (int64_t r = 0; r < an.n; ++r) cptr[r + 1] = cptr[r] + (an.rowptr[r + 1] - an.rowptr[r] + 3) / 4;
@@ -462,6 +487,11 @@ static int build_chunks(const Analysis& an, DevLevel& D, int g, hipStream_t s) {
   R3MG_HIP_CHECK(hipStreamSynchronize(s));  // `cut` is released
   D.cmeta[g] = std::move(meta);
   return c.nrb;
+} catch (const Error& e) {
+  if (e.code != R3MG_ERR_OOM) throw;
+  R3MG_HIP_CHECK(hipStreamSynchronize(s));
+  release_chunk_lists(D, g);
+  return 0;
 }
 
 // bytes of one application over the blocks of geometry g: values and positions of the chunks, distinct columns, block
@@ -471,14 +501,31 @@ static double chunk_bytes(const DevLevel& D, int g, double esz, int nr) {
          7.0 * D.n * esz * nr;
 }
 
+// the one-column chunk shape with its values in element size esz (false: no device memory)
+static bool ensure_chunk_one(const Analysis& an, DevLevel& D, int esz, hipStream_t s) {
+  FineBlocks& f = D.fb[kChunkShape];
+  if (f.nrb == 0) {
+    f.nrb = build_chunks(an, D, kChunkOneGeom, s);
+    if (f.nrb == 0) return false;
+    f.ucol = D.cucol[kChunkOneGeom].p;
+    f.meta = D.cmeta[kChunkOneGeom].p;
+    f.cptr = D.cptr.p;
+    f.clo = D.clo[kChunkOneGeom].p;
+    f.chi = D.chi[kChunkOneGeom].p;
+    D.shape_bytes[kChunkShape] = chunk_bytes(D, kChunkOneGeom, an.opt.vcycle_fp32 ? 4 : 8, 1);
+  }
+  return hold_chunks(D, esz, s);
+}
+
 // Blocks of geometry g of the multi-right-hand-side chunk kernel and the chunked values in element size esz, built the
-// first time a tuning needs them (false: the fine level is matrix-free)
+// first time a tuning needs them (false: the fine level is matrix-free, or there is no device memory for them)
 static bool ensure_chunk_mr(Ctx& c, int g, int esz, hipStream_t s) {
   DevLevel& D = c.dv.lv[0];
   if (g < 0 || g >= kChunkMrGeoms || D.mf) return false;
   ChunkMrBlocks& m = D.cmr[g];
   if (m.nrb == 0) {
     const int nrb = build_chunks(c.an, D, g, s);
+    if (nrb == 0) return false;
     m.geom = g;
     m.meta = D.cmeta[g].p;
     m.ucol = D.cucol[g].p;
@@ -488,15 +535,7 @@ static bool ensure_chunk_mr(Ctx& c, int g, int esz, hipStream_t s) {
     m.ord = D.cord[g].p;
     m.nrb = nrb;
   }
-  if (esz == 4 && !D.cval32.p) {
-    D.cval32.alloc(4 * (size_t)D.nchunk);
-    fill_chunks(D, 4, s);
-  }
-  if (esz == 8 && !D.cval64.p) {
-    D.cval64.alloc(4 * (size_t)D.nchunk);
-    fill_chunks(D, 8, s);
-  }
-  return true;
+  return hold_chunks(D, esz, s);
 }
 
 static void ensure_level_vectors(Ctx& c, int nr) {
@@ -616,6 +655,7 @@ static void autotune_spmm(Ctx& c, int nr, hipStream_t s) {
   }
   const int forced = c.an.opt.multi_rhs_kernel;  // -1 timed, 0 lanes, 1 / 2 LDS-staged, 3 / 4 column-split
   const bool cache = forced == -1 && c.an.opt.tune_cache != 0 && !dv.tune_sig.empty();
+  bool room = true;  // false: a chunk kernel was left out for want of device memory (such a choice is not cached)
   const int fl = F_RHO_STORE | F_X_ADD | F_D_OUT;
   // column-split kernels: the lanes per row that have won somewhere (4 for 2D Q2, 16 for Q1, 32 for 3D Q3)
   const int splitFirst = forced == -1 ? 4 : 1, splitLast = forced == -1 ? 32 : 64;
@@ -658,8 +698,10 @@ static void autotune_spmm(Ctx& c, int nr, hipStream_t s) {
       LevelOp<T> opc = op;
       opc.ptr = D.rowptr.p;
       opc.idx = D.col.p;
-      if (forced == -1 && ensure_chunk_mr(c, chunk_mr_geom(D, c.fp32), (int)sizeof(T), s)) {
-        const int g = chunk_mr_geom(D, c.fp32);
+      const int g = forced == -1 ? chunk_mr_geom(D, c.fp32) : -1;
+      if (g >= 0 && !ensure_chunk_mr(c, g, (int)sizeof(T), s)) {
+        room = false;
+      } else if (g >= 0) {
         opc.cval = level_op<T>(c, 0).cval;
         consider(kCodeChunk + g, kChunkMrMargin, [&] {
           launch_level_chunk_mr<T>(D.cmr[g], opc, nr, vbuf<T>(D.dA), vbuf<T>(D.b), vbuf<T>(D.rho), vbuf<T>(D.x),
@@ -687,8 +729,10 @@ static void autotune_spmm(Ctx& c, int nr, hipStream_t s) {
           });
       }
     }
+    // the next precision is timed without a copy that this one does not take
+    if (fine && sizeof(T) == 4 && bestCode < kCodeChunk && D.shape != kChunkShape && !D.chunk_mr32) D.cval32.release();
     dv.tuned[{l, tag}] = bestCode;
-    if (cache) tune_cache_put(mr_tune_key(dv, l, nr, (int)sizeof(T)), bestCode);
+    if (cache && room) tune_cache_put(mr_tune_key(dv, l, nr, (int)sizeof(T)), bestCode);
     R3MG_HIP_CHECK(hipMemsetAsync(D.x.p, 0, D.x.n, s));
   }
   // PCG's float64 q = A p and <p, q>: lanes kernel with fused partial dots (at most 8 lanes: bounded number of
@@ -730,8 +774,10 @@ static void autotune_spmm(Ctx& c, int nr, hipStream_t s) {
     op.ptr = D0.rowptr.p;
     op.idx = D0.col.p;
     need_partials(dv, (int64_t)kPcgBlocks * 2 * nr);
-    if (forced == -1 && ensure_chunk_mr(c, chunk_mr_geom(D0, c.fp32), 8, s)) {
-      const int g = chunk_mr_geom(D0, c.fp32);
+    const int g = forced == -1 && !D0.mf ? chunk_mr_geom(D0, c.fp32) : -1;
+    if (g >= 0 && !ensure_chunk_mr(c, g, 8, s)) {
+      room = false;
+    } else if (g >= 0) {
       op.cval = level_op<double>(c, 0).cval;
       consider(kCodeChunk + g, kChunkMrMargin, [&] {
         launch_level_chunk_mr<double>(D0.cmr[g], op, nr, dv.pp.p, nullptr, dv.pq.p, nullptr, nullptr, 0.0, 0.0,
@@ -771,17 +817,19 @@ static void autotune_spmm(Ctx& c, int nr, hipStream_t s) {
     if (bestCode <= 8 && bestCode > 0)
       need_partials(dv, (int64_t)((c.an.n + 256 / bestCode - 1) / (256 / bestCode)) * nr);
     dv.tuned[{-1, nr * 2}] = bestCode;
-    if (cache) tune_cache_put(mr_tune_key(dv, -1, nr, 8), bestCode);
+    if (cache && room) tune_cache_put(mr_tune_key(dv, -1, nr, 8), bestCode);
   }
-  // chunked values stay in the precisions that some choice reads (levels 0 and -1, any column count)
+  // chunked values and block lists stay where some choice reads them (levels 0 and -1, any column count)
   DevLevel& Df = dv.lv[0];
   Df.chunk_mr32 = Df.chunk_mr64 = false;
+  Df.chunk_mr_geoms = 0;
   for (const auto& t : dv.tuned)
     if (t.first.first <= 0 && t.second >= kCodeChunk) {
       const bool f32 = t.first.first == 0 && (t.first.second & 1);
       (f32 ? Df.chunk_mr32 : Df.chunk_mr64) = true;
+      Df.chunk_mr_geoms |= 1 << (t.second - kCodeChunk);
     }
-  keep_chunks(Df, c.fp32, s);
+  drop_unread_chunks(Df, c.fp32, s);
 }
 
 // Chebyshev coefficients of a level: first direction scale 1/theta, then (c1, c2) of steps k = 1..K-1
@@ -1155,87 +1203,70 @@ static void tune_stream_shape(HandleImpl& h, hipStream_t s) {
     D.bytes_apply = D.shape_bytes[D.shape];
     return;
   }
-  // the tuning cache holds shape + 100 shape64
+  auto choose = [&](int sh, int sh64) {
+    D.shape = sh;
+    D.shape64 = sh64;
+    D.bytes_apply = D.shape_bytes[sh];
+    drop_unread_chunks(D, c.fp32, s);
+  };
+  // the tuning cache holds shape + 100 shape64.  Where the chunk shape's copy finds no device memory, shape 0 serves (and
+  // is not entered in the cache).
   const bool cache = an.opt.tune_cache != 0 && !dv.tune_sig.empty();
   const std::string key = dv.tune_sig + "/fine1/" + (c.fp32 ? "f32" : "f64");
   int cached = 0;
   if (cache && tune_cache_get(key, &cached) && cached >= 0 && timed_shape(cached % 100) && timed_shape(cached / 100) &&
       (c.fp32 || cached / 100 == cached % 100)) {
-    D.shape = cached % 100;
-    D.shape64 = cached / 100;
-    D.bytes_apply = D.shape_bytes[D.shape];
-    keep_chunks(D, c.fp32, s);
+    auto usable = [&](int sh, int esz) { return sh != kChunkShape || ensure_chunk_one(an, D, esz, s) ? sh : 0; };
+    const int sh = usable(cached % 100, c.fp32 ? 4 : 8);
+    choose(sh, c.fp32 ? usable(cached / 100, 8) : sh);
     return;
   }
-  if (c.fp32) {
-    D.cval32.alloc(4 * (size_t)D.nchunk);
-    fill_chunks(D, 4, s);
-  }
-  D.cval64.alloc(4 * (size_t)D.nchunk);
-  fill_chunks(D, 8, s);
-  const int fl = F_RHO_STORE | F_X_ADD | F_D_OUT;
-  // two interleaved rounds, best of each shape
-  float best[kStreamShapes];
-  for (int sh = 0; sh < kStreamShapes; ++sh) best[sh] = 1e30f;
-  for (int round = 0; round < 2; ++round) {
-    for (int sh = 0; sh < kStreamShapes; ++sh) {
-      if (!timed_shape(sh)) continue;
-      float ms;
-      if (c.fp32) {
-        LevelOp<float> op = level_op<float>(c, 0);
-        ms = time_launches(s, 10, best[sh], [&] {
-          launch_level_stream<float>(sh, D.fb[sh], op, vbuf<float>(D.dA), vbuf<float>(D.b),
-                                     vbuf<float>(D.rho), vbuf<float>(D.x), vbuf<float>(D.dB), 0.0, 0.0,
-                                     fl | D.keep32, nullptr, nullptr, s);
-        });
-      } else {
-        LevelOp<double> op = level_op<double>(c, 0);
-        ms = time_launches(s, 10, best[sh], [&] {
-          launch_level_stream<double>(sh, D.fb[sh], op, vbuf<double>(D.dA), vbuf<double>(D.b),
-                                      vbuf<double>(D.rho), vbuf<double>(D.x), vbuf<double>(D.dB), 0.0, 0.0,
-                                      fl | D.keep64, nullptr, nullptr, s);
-        });
-      }
-      best[sh] = std::min(best[sh], ms);
+  // two interleaved rounds, best of each shape; a precision's copy is given back before the next one is timed
+  bool room = true;
+  auto pick = [&](int esz, auto&& launch) {
+    if (!ensure_chunk_one(an, D, esz, s)) {
+      room = false;
+      return 0;
     }
-  }
-  auto pick = [&]() {
-    const float chunk = best[kChunkShape];
-    const bool csr = std::min(best[0], chunk) < 0.03f ? 4 * D.nchunk > 2 * D.nnz : best[0] < 0.97f * chunk;
+    float t0 = 1e30f, chunk = 1e30f;
+    for (int round = 0; round < 2; ++round) {
+      t0 = std::min(t0, time_launches(s, 10, t0, [&] { launch(0); }));
+      chunk = std::min(chunk, time_launches(s, 10, chunk, [&] { launch(kChunkShape); }));
+    }
+    const bool csr = std::min(t0, chunk) < 0.03f ? 4 * D.nchunk > 2 * D.nnz : t0 < 0.97f * chunk;
+    if (csr) (esz == 4 ? D.cval32.release() : D.cval64.release());
     return csr ? 0 : kChunkShape;
   };
-  int bestS = pick();
-  D.shape = D.shape64 = bestS;
-  D.bytes_apply = D.shape_bytes[D.shape];
+  const int fl = F_RHO_STORE | F_X_ADD | F_D_OUT;
+  int sh, sh64;
+  if (c.fp32) {
+    sh = pick(4, [&](int k) {
+      launch_level_stream<float>(k, D.fb[k], level_op<float>(c, 0), vbuf<float>(D.dA), vbuf<float>(D.b),
+                                 vbuf<float>(D.rho), vbuf<float>(D.x), vbuf<float>(D.dB), 0.0, 0.0, fl | D.keep32, nullptr,
+                                 nullptr, s);
+    });
+    // float32 V-cycle: PCG's float64 operator y = A p is timed on its own (the float64 values double the LDS
+    // staging, so the other shape can win)
+    DBuf<double> u64, y64;
+    u64.alloc((size_t)an.n);
+    y64.alloc((size_t)an.n);
+    R3MG_HIP_CHECK(hipMemsetAsync(u64.p, 0, u64.n * sizeof(double), s));
+    sh64 = pick(8, [&](int k) {
+      launch_level_stream<double>(k, D.fb[k], level_op<double>(c, 0), u64.p, nullptr, y64.p, nullptr, nullptr, 0.0, 0.0,
+                                  F_PLAIN | D.keep64, nullptr, nullptr, s);
+    });
+    R3MG_HIP_CHECK(hipStreamSynchronize(s));  // u64 and y64 are released
+  } else {
+    sh = sh64 = pick(8, [&](int k) {
+      launch_level_stream<double>(k, D.fb[k], level_op<double>(c, 0), vbuf<double>(D.dA), vbuf<double>(D.b),
+                                  vbuf<double>(D.rho), vbuf<double>(D.x), vbuf<double>(D.dB), 0.0, 0.0, fl | D.keep64,
+                                  nullptr, nullptr, s);
+    });
+  }
   R3MG_HIP_CHECK(hipMemsetAsync(D.x.p, 0, D.x.n, s));
   R3MG_HIP_CHECK(hipMemsetAsync(D.rho.p, 0, D.rho.n, s));
-  if (!c.fp32) {
-    if (cache) tune_cache_put(key, D.shape + 100 * D.shape64);
-    keep_chunks(D, false, s);
-    return;
-  }
-  // float32 V-cycle: PCG's float64 operator y = A p is timed on its own (the float64 values double the LDS
-  // staging, so another shape can win); the same two rounds and 3% rule
-  DBuf<double> u64, y64;
-  u64.alloc((size_t)an.n);
-  y64.alloc((size_t)an.n);
-  R3MG_HIP_CHECK(hipMemsetAsync(u64.p, 0, u64.n * sizeof(double), s));
-  LevelOp<double> op = level_op<double>(c, 0);
-  for (int sh = 0; sh < kStreamShapes; ++sh) best[sh] = 1e30f;
-  for (int round = 0; round < 2; ++round)
-    for (int sh = 0; sh < kStreamShapes; ++sh) {
-      if (!timed_shape(sh)) continue;
-      const float ms = time_launches(s, 10, best[sh], [&] {
-        launch_level_stream<double>(sh, D.fb[sh], op, u64.p, nullptr, y64.p, nullptr, nullptr, 0.0, 0.0,
-                                    F_PLAIN | D.keep64, nullptr, nullptr, s);
-      });
-      best[sh] = std::min(best[sh], ms);
-    }
-  bestS = pick();
-  D.shape64 = bestS;
-  keep_chunks(D, true, s);
-  if (cache) tune_cache_put(key, D.shape + 100 * D.shape64);
-  R3MG_HIP_CHECK(hipStreamSynchronize(s));
+  choose(sh, sh64);
+  if (cache && room) tune_cache_put(key, D.shape + 100 * D.shape64);
 }
 
 // uploads local-column row blocks into slot g of a level and points the kernel shape kLocalFirst + g at them
@@ -1369,16 +1400,6 @@ void device_setup(HandleImpl& h, hipStream_t s) {
     };
     same_blocks(kLocalFirst + kLocalGeoms, kLocalFirst);
     for (int sh : {kVecTwoFirst, kVecTwoFirst + 1}) same_blocks(sh, sh - 2);
-    if (an.opt.fine_kernel < 0) {  // chunk shape
-      FineBlocks& f = D.fb[kChunkShape];
-      f.nrb = build_chunks(an, D, kChunkOneGeom, s);
-      f.ucol = D.cucol[kChunkOneGeom].p;
-      f.meta = D.cmeta[kChunkOneGeom].p;
-      f.cptr = D.cptr.p;
-      f.clo = D.clo[kChunkOneGeom].p;
-      f.chi = D.chi[kChunkOneGeom].p;
-      D.shape_bytes[kChunkShape] = chunk_bytes(D, kChunkOneGeom, sv0, 1);
-    }
     D.dinv64.alloc(D.n);
     if (fp32) {
       D.xi32.alloc(D.xi64.n);
