@@ -283,6 +283,7 @@ void launch_diag_inv(int n, int blk, const int* ptr, const int* idx, const doubl
 // (block index, first partial slot, partials) of the blocks split into several items, part = the partial blocks.
 struct GalerkinWork {
   int64_t nitem = 0, nmulti = 0;
+  size_t nslot = 0;  // partial blocks
   const int *item = nullptr, *multi = nullptr;  // 16-byte records
   double* part = nullptr;
 };

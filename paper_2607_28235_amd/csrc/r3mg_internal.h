@@ -290,9 +290,9 @@ struct Device {
   DBuf<char> state;       // PcgState
   DBuf<double> hist;      // CG coefficients and squared residual norms per iteration (PcgState::hist, rhist)
   int hist_rows = 0;
-  // numeric set-up, kept for the next one: Lanczos vectors (diag, v, vprev, w, A v of the largest level), its alpha
-  // and beta per level and step followed by one error flag per level, and the dense factorisation's scratch (kept up
-  // to kKeepDenseBytes)
+  // numeric set-up, kept from the first re-set-up on (r3mg_update_values; r3mg_factor gives it back, as most handles are
+  // set up once): Lanczos vectors (diag, v, vprev, w, A v of the largest level), its alpha and beta per level and step
+  // followed by one error flag per level, and the dense factorisation's scratch (kept up to kKeepDenseBytes)
   DBuf<double> lzv, lzs;
   DBuf<double> dense, tiles, ybuf;
   DenseLookAhead look;

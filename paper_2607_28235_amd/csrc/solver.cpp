@@ -1065,7 +1065,8 @@ static void cheb_level(const Analysis& an, DevLevel& D, const double* sc) {
   D.cheb_c2 = ch.c2;
 }
 
-void numeric_setup(HandleImpl& h, hipStream_t s) {
+// keep: the scratch stays with the handle for the next one
+void numeric_setup(HandleImpl& h, hipStream_t s, bool keep) {
   Analysis& an = *h.an;
   Device& dv = *h.dev;
   Ctx c{an, dv, an.opt.vcycle_fp32 != 0};
@@ -1079,6 +1080,8 @@ void numeric_setup(HandleImpl& h, hipStream_t s) {
     const int64_t nblk = H.bptr[H.nbox];
     if (l == 1) {
       DevLevel& F0 = dv.lv[0];
+      D.gal_part.alloc(D.gal.nslot * B * B);
+      D.gal.part = D.gal_part.p;
       launch_galerkin0(D.gal, an.d, an.pc, D.gal_up.p, D.gal_mir.p, D.brow.p, D.bptr.p, D.gal_ent.p, F0.owner.p,
                        F0.xi64.p, F0.col.p, F0.val64.p, D.val64.p, s);
     } else {
@@ -1152,10 +1155,15 @@ void numeric_setup(HandleImpl& h, hipStream_t s) {
   std::vector<double> back(nscal + nflag);
   R3MG_HIP_CHECK(hipMemcpyAsync(back.data(), dv.lzs.p, back.size() * sizeof(double), hipMemcpyDeviceToHost, s));
   R3MG_HIP_CHECK(hipStreamSynchronize(s));
-  if (2 * dv.dense.n * sizeof(double) > kKeepDenseBytes) {
+  if (!keep || 2 * dv.dense.n * sizeof(double) > kKeepDenseBytes) {
     dv.dense.release();
     dv.ybuf.release();
     dv.tiles.release();
+  }
+  if (!keep) {
+    dv.lzv.release();
+    dv.lzs.release();
+    if (L > 0) dv.lv[1].gal_part.release();
   }
   const int* flags = reinterpret_cast<const int*>(back.data() + nscal);
   for (int l = 0; l < L; ++l)
@@ -1330,13 +1338,12 @@ static void upload_galerkin_items(const Analysis& an, DevLevel& D, hipStream_t s
   }
   D.gal_item.upload(item, s);
   D.gal_multi.upload(multi, s);
-  D.gal_part.alloc((size_t)slots * an.B * an.B);
   R3MG_HIP_CHECK(hipStreamSynchronize(s));  // the host lists are released on return
   D.gal.nitem = (int64_t)item.size() / 4;
   D.gal.nmulti = (int64_t)multi.size() / 4;
   D.gal.item = D.gal_item.p;
   D.gal.multi = D.gal_multi.p;
-  D.gal.part = D.gal_part.p;
+  D.gal.nslot = (size_t)slots;
 }
 
 void device_setup(HandleImpl& h, hipStream_t s) {
@@ -1458,7 +1465,7 @@ void device_setup(HandleImpl& h, hipStream_t s) {
       D.bytes_apply = D.shape_bytes[D.shape];
     }
   }
-  numeric_setup(h, s);
+  numeric_setup(h, s, false);  // most handles are set up once
   dv.tune_sig = tune_signature(an, dv);
   tune_stream_shape(h, s);
   R3MG_HIP_CHECK(hipStreamSynchronize(s));
@@ -1470,7 +1477,7 @@ void update_values(HandleImpl& h, const double* vals_dev, hipStream_t s) {
   detach_matrix_free(h);  // the cell description no longer matches the new values
   Device& dv = *h.dev;
   launch_gather_vals(h.an->nnz, dv.src.p, vals_dev, dv.lv[0].val64.p, s);
-  numeric_setup(h, s);
+  numeric_setup(h, s, true);
   R3MG_HIP_CHECK(hipStreamSynchronize(s));
 }
 

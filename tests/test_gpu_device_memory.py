@@ -239,3 +239,26 @@ if not any(int(v) >= 400 for k, v in lines if "/mr/0/" in k or "/mr/-1/" in k):
     assert held() == 0
 h.close()
 """, tmp_path / "tune")
+
+
+@pytest.mark.parametrize("fp32", [0, 1])
+def test_setup_scratch_stays_only_with_handles_that_are_set_up_again(recorder, fp32, tmp_path):
+    """r3mg_factor gives back the dense factorisation's two n x n arrays, the Lanczos vectors and the partial Galerkin
+    blocks; they come with the first r3mg_update_values and stay for the next one."""
+    print(f"[gpu-case] set-up scratch, fp32={fp32}", flush=True)
+    _child(recorder, rf"""
+prob = problem(2, 40, 3)
+h = handle(prob, vcycle_fp32={fp32}, max_coarse_dofs=1200)
+nc = h.info()[-1]["n"]
+dense, lanczos = 8 * nc * nc, 5 * 8 * prob.n
+def counts():
+    return rec.rec_live(dense), rec.rec_live(lanczos)
+assert nc > 300 and counts() == (1, 0), counts()     # the inverse alone
+want = solve(h, prob)
+for rep in range(3):
+    h.update_values(torch.from_numpy(prob.val).cuda())
+    assert counts() == (3, 1), counts()
+assert np.array_equal(solve(h, prob), want)
+h.close()
+assert counts() == (0, 0)
+""", tmp_path / "tune")
