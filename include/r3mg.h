@@ -40,7 +40,7 @@ typedef struct r3mg_handle_* r3mg_handle;
    2 x 34 GB at this size.  The paper's coarsest solve is a sparse direct one (Section 6); this library inverts
    the coarsest operator densely on the device, which fits HBM up to this size.  Up to 10,240 DoFs the inverse's
    upper-triangular 64 x 64 tiles are kept as well (about half its size), and V-cycles over up to 4 right-hand
-   sides read those instead of the whole inverse. */
+   sides read those instead of the whole inverse (two-level hierarchies with a float64 V-cycle: above 1,024 DoFs). */
 #define R3MG_MAX_COARSEST_DOFS 65536
 
 typedef enum {

@@ -832,6 +832,18 @@ static void autotune_spmm(Ctx& c, int nr, hipStream_t s) {
   drop_unread_chunks(Df, c.fp32, s);
 }
 
+// Float64 coarsest systems of up to this many unknowns are multiplied row by row from the full inverse, in one launch
+// instead of two, where no prolongation is fused into the second; larger ones read the packed half.  Two-level solves,
+// packed -> rows, one column / four: 32 unknowns 525 -> 492 us / 609 -> 576, 512 628 -> 593 / 738 -> 725, 1,024 628 -> 610 /
+// 788 -> 780; 1,152 562 -> 550 / 657 -> 664, 2,048 646 -> 700 / 938 -> 949.
+constexpr int64_t kDenseRowsMax = 1024;
+
+// whether a handle's coarsest products read the packed inverse (a prolongation is fused wherever levels lie between the
+// coarsest and the fine one); where they do not, it is not formed
+static bool packed_coarsest(bool fp32, int L, int64_t nc) {
+  return (nc + kDenseTile - 1) / kDenseTile <= kDenseSymMaxTiles && (fp32 || L > 1 || nc > kDenseRowsMax);
+}
+
 // Chebyshev coefficients of a level: first direction scale 1/theta, then (c1, c2) of steps k = 1..K-1
 struct Cheb {
   double inv_theta;
@@ -852,12 +864,6 @@ static Cheb cheb_coeffs(double lo, double hi, int K) {
   return ch;
 }
 
-// Float64 coarsest systems of up to this many unknowns are multiplied row by row from the full inverse, in one launch
-// instead of two, where no prolongation is fused into the second; larger ones read the packed half.  Two-level solves,
-// packed -> rows, one column / four: 32 unknowns 525 -> 492 us / 609 -> 576, 512 628 -> 593 / 738 -> 725, 1,024 628 -> 610 /
-// 788 -> 780; 1,152 562 -> 550 / 657 -> 664, 2,048 646 -> 700 / 938 -> 949.
-constexpr int64_t kDenseRowsMax = 1024;
-
 // Coarsest solve x = A_L^{-1} b: the symmetric inverse's packed tiles (float32 tiles for the float32 V-cycle) for
 // up to kDenseSymMaxNR columns, else the full float64 inverse.  With pr, the prolongation to the level above
 // follows (fused into the tiled product's last pass, else k_prolong_c).
@@ -865,8 +871,7 @@ template <typename T>
 static void coarsest_apply(Ctx& c, int nr, const T* b, T* x, const DenseProlong<T>* pr, const int* skip,
                            hipStream_t s) {
   Device& dv = c.dv;
-  const bool rows = sizeof(T) == 8 && !pr && dv.nc <= kDenseRowsMax;
-  if (dv.ct > 0 && nr <= kDenseSymMaxNR && !rows) {
+  if (dv.ct > 0 && nr <= kDenseSymMaxNR) {
     if constexpr (sizeof(T) == 4) {
       if (dv.csym32.p) {
         launch_dense_apply_sym<T, float>((int)dv.nc, dv.ct, nr, dv.csym32.p, dv.ctile.p, dv.cpart.p, b, x, pr, skip,
@@ -1127,7 +1132,7 @@ void numeric_setup(HandleImpl& h, hipStream_t s, bool keep) {
     // the symmetric inverse's upper tiles, read once per product by up to kDenseSymMaxNR columns (the pass-1
     // slots cost nr/16 of the bytes saved, so wider blocks keep the full inverse)
     const int nt = (int)((D.n + kDenseTile - 1) / kDenseTile);
-    if (nt <= kDenseSymMaxTiles) {
+    if (packed_coarsest(c.fp32, L, D.n)) {
       const int ntiles = nt * (nt + 1) / 2;
       if (dv.ct != nt) {  // once per handle: the level sizes do not change
         std::vector<int32_t> tl;

@@ -262,3 +262,21 @@ assert np.array_equal(solve(h, prob), want)
 h.close()
 assert counts() == (0, 0)
 """, tmp_path / "tune")
+
+
+# (cells, p', levels, fp32, whether the packed inverse is read): two-level float64 up to 1,024 unknowns reads the rows of the
+# full inverse, and forms no packed one
+@pytest.mark.parametrize("N,pc,levels,fp32,packed", [(48, 1, 2, 0, 0), (48, 1, 2, 1, 1), (32, 2, 2, 0, 1), (48, 1, 3, 0, 1)])
+def test_packed_coarsest_inverse_only_where_it_is_read(recorder, N, pc, levels, fp32, packed, tmp_path):
+    print(f"[gpu-case] packed inverse N={N} p'={pc} levels={levels} fp32={fp32}", flush=True)
+    _child(recorder, rf"""
+prob = problem(2, {N}, 2)
+h = handle(prob, coarse_degree={pc}, leaf_size={40 if N == 48 else 64}, max_coarse_dofs=3000 if {levels} == 2 else 300,
+           max_levels={levels}, vcycle_fp32={fp32})
+assert h.nlevels == {levels}
+nt = -(-h.info()[-1]["n"] // 64)
+size = nt * (nt + 1) // 2 * 64 * 64 * (4 if {fp32} else 8)
+assert rec.rec_live(size) == {packed}
+solve(h, prob)
+solve(h, prob, 4)
+""", tmp_path / "tune")
