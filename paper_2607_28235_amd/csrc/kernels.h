@@ -170,10 +170,10 @@ template <typename T>
 void launch_level_boxrow(const LevelOp<T>& op, int maxnb, const T* u, const T* b, T* rho, T* x, T* dout, double c1,
                          double c2, int flags, const int* skip, hipStream_t s, const BoxRestrict<T>* rs = nullptr);
 
-// Wide block rows (maxnb * blk large): one workgroup per (box, 8-row chunk).
+// Wide block rows, boxes of 8, 9, 16, 27 or 64 rows: one workgroup per (box, 8 or 9 of its rows).
 template <typename T>
-void launch_level_blockrow_wg(const LevelOp<T>& op, int maxnb, const T* u, const T* b, T* rho, T* x, T* dout,
-                              double c1, double c2, int flags, const int* skip, hipStream_t s);
+void launch_level_blockrow_wg(const LevelOp<T>& op, const T* u, const T* b, T* rho, T* x, T* dout, double c1, double c2,
+                              int flags, const int* skip, hipStream_t s);
 
 // Blocks of one geometry over the chunked rows, encoded on the device from the CSR arrays in two steps.  Step 1 cuts the
 // rows into blocks, greedily within nseg independent row segments: blk[first row of the segment + k] = (first row,

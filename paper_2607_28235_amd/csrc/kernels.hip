@@ -2323,10 +2323,9 @@ static void launch_blockrow_wg_b(const LevelOp<T>& op, const T* u, const T* b, T
 }
 
 template <typename T>
-void launch_level_blockrow_wg(const LevelOp<T>& op, int maxnb, const T* u, const T* b, T* rho, T* x, T* dout,
+void launch_level_blockrow_wg(const LevelOp<T>& op, const T* u, const T* b, T* rho, T* x, T* dout,
                               double c1, double c2, int flags, const int* skip, hipStream_t s) {
   if (op.n == 0) return;
-  (void)maxnb;
   // rows of a workgroup: enough workgroups for the smaller levels, and R x NP values of a thread in registers
   switch (op.blk) {
     case 8: launch_blockrow_wg_b<T, 8, 8, 2>(op, u, b, rho, x, dout, c1, c2, flags, skip, s); break;
@@ -2338,9 +2337,9 @@ void launch_level_blockrow_wg(const LevelOp<T>& op, int maxnb, const T* u, const
   }
   check_launch("k_level_blockrow_wg");
 }
-template void launch_level_blockrow_wg<float>(const LevelOp<float>&, int, const float*, const float*, float*, float*,
+template void launch_level_blockrow_wg<float>(const LevelOp<float>&, const float*, const float*, float*, float*,
                                               float*, double, double, int, const int*, hipStream_t);
-template void launch_level_blockrow_wg<double>(const LevelOp<double>&, int, const double*, const double*, double*,
+template void launch_level_blockrow_wg<double>(const LevelOp<double>&, const double*, const double*, double*,
                                                double*, double*, double, double, int, const int*, hipStream_t);
 
 // Fine level for several right-hand sides over chunked rows (see k_level_chunk; n x NR interleaved vectors).  A workgroup

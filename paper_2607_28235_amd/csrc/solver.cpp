@@ -236,16 +236,15 @@ static bool launch_fine_code(int code, const DevLevel& D, const LevelOp<T>& op, 
   return launch_level_split<T>(op, nr, code - kCodeSplit, u, b, rho, x, dout, c1, c2, flags, skip, s);
 }
 
-// Kernel that applies level l for nr right-hand sides in element size esz: the row-block kernel on the fine
-// level for one right-hand side, a block-row kernel on coarse levels whose block rows fit LDS, the
-// lanes-per-row kernel otherwise.
+// Kernel that applies level l for nr right-hand sides in element size esz: the row-block kernel on the fine level for one
+// right-hand side; on coarse levels the box-row kernel, the block-row workgroup kernel for wide rows of boxes of 8 rows or
+// more (any width, as it holds u in registers: 512 boxes of 27 rows, one coupled to all others, float64, 84 us with lanes
+// per row, 33 with this), the block-row kernel where a row of u fits LDS; else lanes per row.
 LevelKernel level_kernel(const Analysis& an, const DevLevel& D, int l, int nr, int esz) {
   if (l == 0 && D.mf) return LevelKernel::MatFree;
   if (l > 0 && nr == 1 && D.boxrow) return LevelKernel::BoxRow;
   if (nr == 1 && D.fb[D.shape].nrb > 0 && (l == 0 || D.shape >= kLocalFirst + kLocalGeoms)) return LevelKernel::Stream;
-  if (l > 0 && nr == 1 && D.maxnb > 0 && an.B >= 8 && (int64_t)D.maxnb * an.B >= 256 &&
-      (int64_t)D.maxnb * an.B * esz <= 65536)
-    return LevelKernel::BlockRowWG;
+  if (l > 0 && nr == 1 && an.B >= 8 && (int64_t)D.maxnb * an.B >= 256) return LevelKernel::BlockRowWG;
   if (l > 0 && nr == 1 && D.maxnb > 0 && an.B <= 64 && blockrow_lds_bytes(an.B, D.maxnb * an.B, esz) <= 65536)
     return LevelKernel::BlockRow;
   return LevelKernel::Lanes;
@@ -356,7 +355,7 @@ void apply_level(Ctx& c, int l, int nr, const T* u, const T* b, T* rho, T* x, T*
       launch_level_boxrow<T>(op, D.maxnb, u, b, rho, x, dout, c1, c2, flags | keep_flag<T>(D), skip, s, rs);
       break;
     case LevelKernel::BlockRowWG:
-      launch_level_blockrow_wg<T>(op, D.maxnb, u, b, rho, x, dout, c1, c2, flags | keep_flag<T>(D), skip, s);
+      launch_level_blockrow_wg<T>(op, u, b, rho, x, dout, c1, c2, flags | keep_flag<T>(D), skip, s);
       break;
     case LevelKernel::BlockRow:
       launch_level_blockrow<T>(op, D.maxnb, u, b, rho, x, dout, c1, c2, flags | keep_flag<T>(D), skip, s);
