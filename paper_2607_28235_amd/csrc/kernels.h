@@ -26,8 +26,9 @@ constexpr double kKeepCachedBytes = 128.0 * 1024 * 1024;
 
 constexpr int kMaxNR = 16;
 
-// Device-side PCG state of one block of up to kMaxNR columns.  all_done must stay the first word: every kernel
-// of an iteration reads it through the `skip` pointer and returns at once when it is set.
+// Device-side PCG state of one block of up to kMaxNR columns.  all_done must stay the first word: the vector kernels of
+// an iteration and its product A p read it (the fine-level kernels through their `skip` pointer) and return at once when
+// it is set.  The V-cycle between them runs on.
 struct PcgState {
   int all_done, nr, flexible, restart;  // restart: set by the true-residual check when a converged column's true
                                         // residual fails the stop rule (float32 V-cycle: residual replacement)
@@ -148,7 +149,7 @@ void launch_chunk_values(int n, const int* ptr, const int* cptr, const T* val, T
 size_t blockrow_lds_bytes(int blk, int maxw, size_t esz);
 template <typename T>
 void launch_level_blockrow(const LevelOp<T>& op, int maxnb, const T* u, const T* b, T* rho, T* x, T* dout, double c1,
-                           double c2, int flags, const int* skip, hipStream_t s);
+                           double c2, int flags, hipStream_t s);
 
 // Boxes of 4, 9 or 16 rows (2D agglomerated levels, p' = 1, 2, 3) with block rows of at most 64 * kBoxRowMaxNP
 // entries: one wave per box, each lane owning positions of the block row in all the box's rows.
@@ -168,12 +169,12 @@ struct BoxRestrict {
 };
 template <typename T>
 void launch_level_boxrow(const LevelOp<T>& op, int maxnb, const T* u, const T* b, T* rho, T* x, T* dout, double c1,
-                         double c2, int flags, const int* skip, hipStream_t s, const BoxRestrict<T>* rs = nullptr);
+                         double c2, int flags, hipStream_t s, const BoxRestrict<T>* rs = nullptr);
 
 // Wide block rows, boxes of 8, 9, 16, 27 or 64 rows: one workgroup per (box, 8 or 9 of its rows).
 template <typename T>
 void launch_level_blockrow_wg(const LevelOp<T>& op, const T* u, const T* b, T* rho, T* x, T* dout, double c1, double c2,
-                              int flags, const int* skip, hipStream_t s);
+                              int flags, hipStream_t s);
 
 // Blocks of one geometry over the chunked rows, encoded on the device from the CSR arrays in two steps.  Step 1 cuts the
 // rows into blocks, greedily within nseg independent row segments: blk[first row of the segment + k] = (first row,
@@ -211,7 +212,7 @@ void launch_level_chunk_mr(const ChunkMrBlocks& cb, const LevelOp<T>& op, int nr
 bool box_mr_supported(int blk, int maxnb);
 template <typename T>
 void launch_level_box_mr(const LevelOp<T>& op, int nr, const T* u, const T* b, T* rho, T* x, T* dout, double c1,
-                         double c2, int flags, const int* skip, hipStream_t s);
+                         double c2, int flags, hipStream_t s);
 
 // q = A p (float64, CSR), per-block partial <p, q> -> partials[blk * nr + k]; returns number of blocks
 int launch_spmv_dot(const LevelOp<double>& op, int nr, const double* p, double* q, double* partials,
@@ -221,22 +222,21 @@ int launch_spmv_dot(const LevelOp<double>& op, int nr, const double* p, double* 
 template <typename T>
 void launch_restrict0(int nbox, int64_t n_points, int d, int pc, int nr, const int* leaf_off, const int* owner,
                       const T* xi, const T* src, T* bnext, const T* dinv_next, T* dnext, double inv_theta_next,
-                      const int* skip, hipStream_t s);
+                      hipStream_t s);
 // (several columns: one workgroup per level-1 box, nbox boxes with points leaf_off[K] .. leaf_off[K+1] - 1)
 template <typename T>
 void launch_prolong0(int n, int nbox, int d, int pc, int nr, const int* leaf_off, const int* owner, const T* xi,
-                     const T* e, const T* epend, T* v, const int* skip, hipStream_t s);
+                     const T* e, const T* epend, T* v, hipStream_t s);
 template <typename T>
 void launch_restrict_c(int nbox_next, int nbox, int shift, int d, int pc, int nr, const T* pt, const T* src,
-                       T* bnext, const T* dinv_next, T* dnext, double inv_theta_next, const int* skip,
-                       hipStream_t s);
+                       T* bnext, const T* dinv_next, T* dnext, double inv_theta_next, hipStream_t s);
 template <typename T>
 void launch_prolong_c(int nbox, int shift, int d, int pc, int nr, const T* pt, const T* e, const T* epend, T* v,
-                      const int* skip, hipStream_t s);
+                      hipStream_t s);
 
 // elementwise helpers
 template <typename T>
-void launch_xupdate(int64_t count, T* x, const T* v, int assign, const int* skip, hipStream_t s);
+void launch_xupdate(int64_t count, T* x, const T* v, int assign, hipStream_t s);
 template <typename T>
 void launch_vc_entry(int n, int nr, const int* perm, const double* r_user, int64_t ld_user, T* b0,
                      const T* dinv, T* d0, double inv_theta, hipStream_t s);
@@ -244,7 +244,7 @@ template <typename T>
 void launch_vc_exit(int n, int nr, const int* perm, const T* x0, const T* dpend, double* z_user, int64_t ld_user,
                     hipStream_t s);
 template <typename T>
-void launch_dense_apply(int nc, int nr, const double* cinv, const T* b, T* x, const int* skip, hipStream_t s);
+void launch_dense_apply(int nc, int nr, const double* cinv, const T* b, T* x, hipStream_t s);
 // The same product with the symmetric inverse read once: its upper-triangular 64 x 64 tiles (I <= J), listed in
 // `tiles` as (I, J) pairs and packed in that order, each row-major and zero beyond nc.  Pass 1 forms every
 // tile's row products and, off the diagonal, its transposed products, into part (nt x nt x 64 x nr float64,
@@ -267,7 +267,7 @@ struct DenseProlong {
 };
 template <typename T, typename M>
 void launch_dense_apply_sym(int nc, int nt, int nr, const M* packed, const int* tiles, double* part, const T* b,
-                            T* x, const DenseProlong<T>* pr, const int* skip, hipStream_t s);
+                            T* x, const DenseProlong<T>* pr, hipStream_t s);
 void launch_gather_cols(int n, int nr, int nuser, const int* perm, const double* user, int64_t ld_user,
                         double* out, hipStream_t s);
 void launch_scatter_cols(int n, int nr, int nuser, const int* perm, const double* in, double* user,

@@ -63,22 +63,7 @@ Basis1D<T> make_basis(int pc) {
   return b;
 }
 
-// l_j(s) = w_j prod_{m != j} (s - t_m)
-template <typename T>
-__device__ inline void lag1d(const Basis1D<T>& bs, T s, T* l) {
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    if (j < bs.k) {
-      T v = bs.w[j];
-#pragma unroll
-      for (int m = 0; m < 4; ++m)
-        if (m < bs.k && m != j) v *= (s - bs.t[m]);
-      l[j] = v;
-    }
-  }
-}
-
-// compile-time forms of lag1d / phi_q (same operations in the same order)
+// l_j(s) = w_j prod_{m != j} (s - t_m) for KB nodes
 template <typename T, int KB>
 __device__ inline void lag1d_k(const Basis1D<T>& bs, T s, T* l) {
 #pragma unroll
@@ -1964,8 +1949,7 @@ __global__ __launch_bounds__(256) void k_level_blockrow(int nbox, int blk, int m
                                                         const int* __restrict__ bcol, const T* __restrict__ val,
                                                         const T* __restrict__ u, const T* __restrict__ b, T* rho, T* x,
                                                         const T* __restrict__ dinv, T* dout, T c1, T c2, int flags,
-                                                        const int* __restrict__ skip, int nlog) {
-  if (skip && *skip) return;
+                                                        int nlog) {
   extern __shared__ unsigned char smem_raw[];
   const int lb = xcd_block(nlog);
   if (lb < 0) return;
@@ -2039,7 +2023,7 @@ size_t blockrow_lds_bytes(int blk, int maxw, size_t esz) {
 
 template <typename T>
 void launch_level_blockrow(const LevelOp<T>& op, int maxnb, const T* u, const T* b, T* rho, T* x, T* dout, double c1,
-                           double c2, int flags, const int* skip, hipStream_t s) {
+                           double c2, int flags, hipStream_t s) {
   const int nbox = op.n / op.blk;
   const int nlog = (nbox + 3) / 4;
   if (nlog == 0) return;
@@ -2049,16 +2033,16 @@ void launch_level_blockrow(const LevelOp<T>& op, int maxnb, const T* u, const T*
   if (op.blk > 64) throw std::runtime_error("block-row kernel: more than 64 rows per box");
   if (flags & F_KEEP)
     hipLaunchKernelGGL((k_level_blockrow<T, 16, true>), dim3(xcd_grid(nlog)), dim3(256), shm, s, nbox, op.blk, maxw,
-                       op.ptr, op.idx, op.val, u, b, rho, x, op.dinv, dout, (T)c1, (T)c2, flags, skip, nlog);
+                       op.ptr, op.idx, op.val, u, b, rho, x, op.dinv, dout, (T)c1, (T)c2, flags, nlog);
   else
     hipLaunchKernelGGL((k_level_blockrow<T, 16, false>), dim3(xcd_grid(nlog)), dim3(256), shm, s, nbox, op.blk, maxw,
-                       op.ptr, op.idx, op.val, u, b, rho, x, op.dinv, dout, (T)c1, (T)c2, flags, skip, nlog);
+                       op.ptr, op.idx, op.val, u, b, rho, x, op.dinv, dout, (T)c1, (T)c2, flags, nlog);
   check_launch("k_level_blockrow");
 }
 template void launch_level_blockrow<float>(const LevelOp<float>&, int, const float*, const float*, float*, float*,
-                                           float*, double, double, int, const int*, hipStream_t);
+                                           float*, double, double, int, hipStream_t);
 template void launch_level_blockrow<double>(const LevelOp<double>&, int, const double*, const double*, double*,
-                                            double*, double*, double, double, int, const int*, hipStream_t);
+                                            double*, double*, double, double, int, hipStream_t);
 
 // Residual staging of the fused restriction: wave w's rows at [w BLK, (w + 1) BLK) of one LDS array.
 template <typename T, int BLK>
@@ -2085,9 +2069,8 @@ __global__ __launch_bounds__(256) void k_level_boxrow(int nbox, const int* __res
                                                       const int* __restrict__ bcol, const T* __restrict__ val,
                                                       const T* __restrict__ u, const T* __restrict__ b, T* rho, T* x,
                                                       const T* __restrict__ dinv, T* dout, T c1, T c2, int flags,
-                                                      const int* __restrict__ skip, int nlog, BoxRestrict<T> rs) {
+                                                      int nlog, BoxRestrict<T> rs) {
   static_assert(BLK <= 16, "rows per box");
-  if (skip && *skip) return;
   const int lb = xcd_block(nlog);
   if (lb < 0) return;
   // the wave index is uniform: the box's block-row record then comes through scalar loads
@@ -2185,7 +2168,7 @@ bool boxrow_supported(int blk, int maxnb) {
 
 template <typename T>
 void launch_level_boxrow(const LevelOp<T>& op, int maxnb, const T* u, const T* b, T* rho, T* x, T* dout, double c1,
-                         double c2, int flags, const int* skip, hipStream_t s, const BoxRestrict<T>* rs) {
+                         double c2, int flags, hipStream_t s, const BoxRestrict<T>* rs) {
   if (!boxrow_supported(op.blk, maxnb)) throw std::runtime_error("box-row kernel: unsupported box shape");
   const int nbox = op.n / op.blk;
   const int nlog = (nbox + 3) / 4;
@@ -2199,18 +2182,18 @@ void launch_level_boxrow(const LevelOp<T>& op, int maxnb, const T* u, const T* b
     if (rs) {                                                                                                     \
       if (flags & F_KEEP)                                                                                         \
         hipLaunchKernelGGL((k_level_boxrow<T, B, N, true, true>), dim3(xcd_grid(nlog)), dim3(256), 0, s, nbox,   \
-                           op.ptr, op.idx, op.val, u, b, rho, x, op.dinv, dout, (T)c1, (T)c2, flags, skip, nlog,  \
+                           op.ptr, op.idx, op.val, u, b, rho, x, op.dinv, dout, (T)c1, (T)c2, flags, nlog,  \
                            ra);                                                                                   \
       else                                                                                                        \
         hipLaunchKernelGGL((k_level_boxrow<T, B, N, false, true>), dim3(xcd_grid(nlog)), dim3(256), 0, s, nbox,  \
-                           op.ptr, op.idx, op.val, u, b, rho, x, op.dinv, dout, (T)c1, (T)c2, flags, skip, nlog,  \
+                           op.ptr, op.idx, op.val, u, b, rho, x, op.dinv, dout, (T)c1, (T)c2, flags, nlog,  \
                            ra);                                                                                   \
     } else if (flags & F_KEEP) {                                                                                  \
       hipLaunchKernelGGL((k_level_boxrow<T, B, N, true, false>), dim3(xcd_grid(nlog)), dim3(256), 0, s, nbox,    \
-                         op.ptr, op.idx, op.val, u, b, rho, x, op.dinv, dout, (T)c1, (T)c2, flags, skip, nlog, ra); \
+                         op.ptr, op.idx, op.val, u, b, rho, x, op.dinv, dout, (T)c1, (T)c2, flags, nlog, ra); \
     } else {                                                                                                      \
       hipLaunchKernelGGL((k_level_boxrow<T, B, N, false, false>), dim3(xcd_grid(nlog)), dim3(256), 0, s, nbox,   \
-                         op.ptr, op.idx, op.val, u, b, rho, x, op.dinv, dout, (T)c1, (T)c2, flags, skip, nlog, ra); \
+                         op.ptr, op.idx, op.val, u, b, rho, x, op.dinv, dout, (T)c1, (T)c2, flags, nlog, ra); \
     }                                                                                                             \
   } while (0)
   if (op.blk == 4) {
@@ -2224,10 +2207,10 @@ void launch_level_boxrow(const LevelOp<T>& op, int maxnb, const T* u, const T* b
   check_launch("k_level_boxrow");
 }
 template void launch_level_boxrow<float>(const LevelOp<float>&, int, const float*, const float*, float*, float*,
-                                         float*, double, double, int, const int*, hipStream_t,
+                                         float*, double, double, int, hipStream_t,
                                          const BoxRestrict<float>*);
 template void launch_level_boxrow<double>(const LevelOp<double>&, int, const double*, const double*, double*,
-                                          double*, double*, double, double, int, const int*, hipStream_t,
+                                          double*, double*, double, double, int, hipStream_t,
                                           const BoxRestrict<double>*);
 
 // Block-row kernel for wide block rows (3D), one right-hand side: a workgroup takes R rows of a box.  A thread owns
@@ -2242,9 +2225,8 @@ __global__ __launch_bounds__(256) void k_level_blockrow_wg(int nbox, const int* 
                                                            const int* __restrict__ bcol, const T* __restrict__ val,
                                                            const T* __restrict__ u, const T* __restrict__ b, T* rho,
                                                            T* x, const T* __restrict__ dinv, T* dout, T c1, T c2,
-                                                           int flags, const int* __restrict__ skip, int nlog) {
+                                                           int flags, int nlog) {
   constexpr int CH = (B + R - 1) / R, S = pow2_at_least(R);
-  if (skip && *skip) return;
   const int lb = xcd_block(nlog);
   if (lb < 0) return;
   __shared__ T rs[4][S];
@@ -2309,12 +2291,12 @@ __global__ __launch_bounds__(256) void k_level_blockrow_wg(int nbox, const int* 
 
 template <typename T, int B, int R, int NP>
 static void launch_blockrow_wg_b(const LevelOp<T>& op, const T* u, const T* b, T* rho, T* x, T* dout, double c1,
-                                 double c2, int flags, const int* skip, hipStream_t s) {
+                                 double c2, int flags, hipStream_t s) {
   const int nbox = op.n / B;
   const int nlog = nbox * ((B + R - 1) / R);
   auto go = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, dim3(xcd_grid(nlog)), dim3(256), 0, s, nbox, op.ptr, op.idx, op.val, u, b, rho, x, op.dinv,
-                       dout, (T)c1, (T)c2, flags, skip, nlog);
+                       dout, (T)c1, (T)c2, flags, nlog);
   };
   if (flags & F_KEEP)
     go(k_level_blockrow_wg<T, B, R, NP, true>);
@@ -2324,23 +2306,23 @@ static void launch_blockrow_wg_b(const LevelOp<T>& op, const T* u, const T* b, T
 
 template <typename T>
 void launch_level_blockrow_wg(const LevelOp<T>& op, const T* u, const T* b, T* rho, T* x, T* dout,
-                              double c1, double c2, int flags, const int* skip, hipStream_t s) {
+                              double c1, double c2, int flags, hipStream_t s) {
   if (op.n == 0) return;
   // rows of a workgroup: enough workgroups for the smaller levels, and R x NP values of a thread in registers
   switch (op.blk) {
-    case 8: launch_blockrow_wg_b<T, 8, 8, 2>(op, u, b, rho, x, dout, c1, c2, flags, skip, s); break;
-    case 9: launch_blockrow_wg_b<T, 9, 9, 2>(op, u, b, rho, x, dout, c1, c2, flags, skip, s); break;
-    case 16: launch_blockrow_wg_b<T, 16, 8, 2>(op, u, b, rho, x, dout, c1, c2, flags, skip, s); break;
-    case 27: launch_blockrow_wg_b<T, 27, 9, 3>(op, u, b, rho, x, dout, c1, c2, flags, skip, s); break;
-    case 64: launch_blockrow_wg_b<T, 64, 8, 4>(op, u, b, rho, x, dout, c1, c2, flags, skip, s); break;
+    case 8: launch_blockrow_wg_b<T, 8, 8, 2>(op, u, b, rho, x, dout, c1, c2, flags, s); break;
+    case 9: launch_blockrow_wg_b<T, 9, 9, 2>(op, u, b, rho, x, dout, c1, c2, flags, s); break;
+    case 16: launch_blockrow_wg_b<T, 16, 8, 2>(op, u, b, rho, x, dout, c1, c2, flags, s); break;
+    case 27: launch_blockrow_wg_b<T, 27, 9, 3>(op, u, b, rho, x, dout, c1, c2, flags, s); break;
+    case 64: launch_blockrow_wg_b<T, 64, 8, 4>(op, u, b, rho, x, dout, c1, c2, flags, s); break;
     default: throw std::runtime_error("block-row kernel: unsupported box size");
   }
   check_launch("k_level_blockrow_wg");
 }
 template void launch_level_blockrow_wg<float>(const LevelOp<float>&, const float*, const float*, float*, float*,
-                                              float*, double, double, int, const int*, hipStream_t);
+                                              float*, double, double, int, hipStream_t);
 template void launch_level_blockrow_wg<double>(const LevelOp<double>&, const double*, const double*, double*,
-                                               double*, double*, double, double, int, const int*, hipStream_t);
+                                               double*, double*, double, double, int, hipStream_t);
 
 // Fine level for several right-hand sides over chunked rows (see k_level_chunk; n x NR interleaved vectors).  A workgroup
 // takes a block of at most CAPC chunks, RPB rows and UCAP - 1 distinct columns and stages its values, positions,
@@ -2842,12 +2824,10 @@ template <typename T, int B, int NR>
 __global__ __launch_bounds__(256) void k_level_box_mr(int nbox, const int* __restrict__ bptr,
                                                       const int* __restrict__ bcol, const T* __restrict__ val,
                                                       const T* __restrict__ u, const T* __restrict__ b, T* rho, T* x,
-                                                      const T* __restrict__ dinv, T* dout, T c1, T c2, int flags,
-                                                      const int* __restrict__ skip) {
+                                                      const T* __restrict__ dinv, T* dout, T c1, T c2, int flags) {
   using M = Mfma16<T>;
   constexpr int MT = (B + 15) / 16, KV = M::KV, KS = 4 * KV, UN = 2;
   constexpr int EP = (B * NR + 255) / 256;
-  if (skip && *skip) return;
   const int K = xcd_block(nbox);
   if (K < 0) return;
   __shared__ T red[4][MT * 16][NR];
@@ -2937,11 +2917,11 @@ bool box_mr_supported(int blk, int maxnb) {
 
 template <typename T, int B>
 static void launch_box_mr_b(const LevelOp<T>& op, int nr, const T* u, const T* b, T* rho, T* x, T* dout, double c1,
-                            double c2, int flags, const int* skip, hipStream_t s) {
+                            double c2, int flags, hipStream_t s) {
   const int nbox = op.n / B;
   auto go = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, dim3(xcd_grid(nbox)), dim3(256), 0, s, nbox, op.ptr, op.idx, op.val, u, b, rho, x, op.dinv,
-                       dout, (T)c1, (T)c2, flags, skip);
+                       dout, (T)c1, (T)c2, flags);
   };
   switch (nr) {
     case 2: go(k_level_box_mr<T, B, 2>); break;
@@ -2954,23 +2934,23 @@ static void launch_box_mr_b(const LevelOp<T>& op, int nr, const T* u, const T* b
 
 template <typename T>
 void launch_level_box_mr(const LevelOp<T>& op, int nr, const T* u, const T* b, T* rho, T* x, T* dout, double c1,
-                         double c2, int flags, const int* skip, hipStream_t s) {
+                         double c2, int flags, hipStream_t s) {
   if (op.n == 0) return;
   switch (op.blk) {
-    case 4: launch_box_mr_b<T, 4>(op, nr, u, b, rho, x, dout, c1, c2, flags, skip, s); break;
-    case 8: launch_box_mr_b<T, 8>(op, nr, u, b, rho, x, dout, c1, c2, flags, skip, s); break;
-    case 9: launch_box_mr_b<T, 9>(op, nr, u, b, rho, x, dout, c1, c2, flags, skip, s); break;
-    case 16: launch_box_mr_b<T, 16>(op, nr, u, b, rho, x, dout, c1, c2, flags, skip, s); break;
-    case 27: launch_box_mr_b<T, 27>(op, nr, u, b, rho, x, dout, c1, c2, flags, skip, s); break;
-    case 64: launch_box_mr_b<T, 64>(op, nr, u, b, rho, x, dout, c1, c2, flags, skip, s); break;
+    case 4: launch_box_mr_b<T, 4>(op, nr, u, b, rho, x, dout, c1, c2, flags, s); break;
+    case 8: launch_box_mr_b<T, 8>(op, nr, u, b, rho, x, dout, c1, c2, flags, s); break;
+    case 9: launch_box_mr_b<T, 9>(op, nr, u, b, rho, x, dout, c1, c2, flags, s); break;
+    case 16: launch_box_mr_b<T, 16>(op, nr, u, b, rho, x, dout, c1, c2, flags, s); break;
+    case 27: launch_box_mr_b<T, 27>(op, nr, u, b, rho, x, dout, c1, c2, flags, s); break;
+    case 64: launch_box_mr_b<T, 64>(op, nr, u, b, rho, x, dout, c1, c2, flags, s); break;
     default: throw std::runtime_error("multi-RHS box kernel: unsupported box size");
   }
   check_launch("k_level_box_mr");
 }
 template void launch_level_box_mr<float>(const LevelOp<float>&, int, const float*, const float*, float*, float*, float*,
-                                         double, double, int, const int*, hipStream_t);
+                                         double, double, int, hipStream_t);
 template void launch_level_box_mr<double>(const LevelOp<double>&, int, const double*, const double*, double*, double*,
-                                          double*, double, double, int, const int*, hipStream_t);
+                                          double*, double, double, int, hipStream_t);
 
 // q = A p with per-block partial sums of p.q (float64 CSR)
 template <int NR>
@@ -3085,10 +3065,9 @@ template <typename T, int D, int KB>
 __global__ __launch_bounds__(512) void k_restrict0(Basis1D<T> bs, int nr, const int* __restrict__ leaf_off,
                                                    const int* __restrict__ owner, const T* __restrict__ xi,
                                                    const T* __restrict__ src, T* bnext, const T* __restrict__ dinv_next,
-                                                   T* dnext, T inv_theta_next, const int* __restrict__ skip) {
+                                                   T* dnext, T inv_theta_next) {
   constexpr int B = D == 3 ? KB * KB * KB : KB * KB;
   constexpr int S = pow2_at_least(B);
-  if (skip && *skip) return;
   __shared__ T wt[8][S];
   const int NT = blockDim.x, W = NT >> 6;
   const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -3146,12 +3125,10 @@ template <typename T, int D, int KB, int NR>
 __global__ __launch_bounds__(512) void k_restrict0_mr(Basis1D<T> bs, const int* __restrict__ leaf_off,
                                                       const int* __restrict__ owner, const T* __restrict__ xi,
                                                       const T* __restrict__ src, T* bnext,
-                                                      const T* __restrict__ dinv_next, T* dnext, T inv_theta_next,
-                                                      const int* __restrict__ skip) {
+                                                      const T* __restrict__ dinv_next, T* dnext, T inv_theta_next) {
   using M = Mfma16<T>;
   constexpr int B = D == 3 ? KB * KB * KB : KB * KB;
   constexpr int MT = (B + 15) / 16, UN = 2;
-  if (skip && *skip) return;
   __shared__ T red[8][MT * 16][NR];
   const int W = blockDim.x >> 6, wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int i = lane & 15, kk = lane >> 4, n = i % NR;
@@ -3226,9 +3203,8 @@ __global__ __launch_bounds__(512) void k_restrict0_mr(Basis1D<T> bs, const int* 
 template <typename T>
 void launch_restrict0(int nbox, int64_t n_points, int d, int pc, int nr, const int* leaf_off, const int* owner,
                       const T* xi, const T* src, T* bnext, const T* dinv_next, T* dnext, double inv_theta_next,
-                      const int* skip, hipStream_t s) {
+                      hipStream_t s) {
   const int k = pc + 1;
-  const int B = (d == 3) ? k * k * k : k * k;
   if (nbox == 0) return;
   // waves per box: two points a thread in an average box, at most eight waves
   int W = 1;
@@ -3241,7 +3217,7 @@ void launch_restrict0(int nbox, int64_t n_points, int d, int pc, int nr, const i
     box_dispatch(d, k, [&](auto dk) {
       auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3(nbox), dim3(64 * Wm), 0, s, bs, leaf_off, owner, xi, src, bnext, dinv_next, dnext,
-                           (T)inv_theta_next, skip);
+                           (T)inv_theta_next);
       };
       switch (nr) {
         case 2: go(k_restrict0_mr<T, dk.D, dk.K, 2>); break;
@@ -3255,7 +3231,7 @@ void launch_restrict0(int nbox, int64_t n_points, int d, int pc, int nr, const i
   }
 #define R3MG_R0(DD, KK)                                                                                           \
   hipLaunchKernelGGL((k_restrict0<T, DD, KK>), dim3(nbox), dim3(64 * W), 0, s, bs, nr, leaf_off, owner, xi, src, \
-                     bnext, dinv_next, dnext, (T)inv_theta_next, skip)
+                     bnext, dinv_next, dnext, (T)inv_theta_next)
   switch (d * 8 + k) {
     case 17: R3MG_R0(2, 1); break;
     case 18: R3MG_R0(2, 2); break;
@@ -3271,9 +3247,9 @@ void launch_restrict0(int nbox, int64_t n_points, int d, int pc, int nr, const i
   check_launch("k_restrict0");
 }
 template void launch_restrict0<float>(int, int64_t, int, int, int, const int*, const int*, const float*,
-                                      const float*, float*, const float*, float*, double, const int*, hipStream_t);
+                                      const float*, float*, const float*, float*, double, hipStream_t);
 template void launch_restrict0<double>(int, int64_t, int, int, int, const int*, const int*, const double*,
-                                       const double*, double*, const double*, double*, double, const int*,
+                                       const double*, double*, const double*, double*, double,
                                        hipStream_t);
 
 // Prolongation from the first agglomerated level: v_i = sum_q phi^K_q(xi_i) (e + epend)[K*B+q] (0 if i is
@@ -3281,10 +3257,9 @@ template void launch_restrict0<double>(int, int64_t, int, int, int, const int*, 
 template <typename T, int D, int KB>
 __global__ __launch_bounds__(256) void k_prolong0(int n, Basis1D<T> bs, int nr, const int* __restrict__ owner,
                                                   const T* __restrict__ xi, const T* __restrict__ e,
-                                                  const T* __restrict__ epend, T* v, const int* __restrict__ skip,
+                                                  const T* __restrict__ epend, T* v,
                                                   int nlog) {
   constexpr int B = D == 3 ? KB * KB * KB : KB * KB;
-  if (skip && *skip) return;
   const int lb = xcd_block(nlog);
   if (lb < 0) return;
   const int i = lb * 256 + threadIdx.x;
@@ -3316,9 +3291,8 @@ template <typename T, int D, int KB>
 __global__ __launch_bounds__(256) void k_prolong0_box(Basis1D<T> bs, int nr, int per, const int* __restrict__ leaf_off,
                                                       const int* __restrict__ owner, const T* __restrict__ xi,
                                                       const T* __restrict__ e, const T* __restrict__ epend, T* v,
-                                                      const int* __restrict__ skip, int nlog) {
+                                                      int nlog) {
   constexpr int B = D == 3 ? KB * KB * KB : KB * KB;
-  if (skip && *skip) return;
   const int lb = xcd_block(nlog);
   if (lb < 0) return;
   __shared__ T es[B];
@@ -3364,11 +3338,9 @@ __global__ __launch_bounds__(256) void k_prolong0_box(Basis1D<T> bs, int nr, int
 template <typename T, int D, int KB, int VW>
 __global__ __launch_bounds__(256) void k_prolong0_mr(Basis1D<T> bs, int nr, int per, const int* __restrict__ leaf_off,
                                                      const int* __restrict__ owner, const T* __restrict__ xi,
-                                                     const T* __restrict__ e, const T* __restrict__ epend, T* v,
-                                                     const int* __restrict__ skip) {
+                                                     const T* __restrict__ e, const T* __restrict__ epend, T* v) {
   using VT = typename ColVec<T, VW>::type;
   constexpr int B = D == 3 ? KB * KB * KB : KB * KB;
-  if (skip && *skip) return;
   extern __shared__ __align__(16) unsigned char smem_raw[];
   VT* es = reinterpret_cast<VT*>(smem_raw);  // [B][nch]
   const int nch = nr / VW;
@@ -3396,7 +3368,7 @@ __global__ __launch_bounds__(256) void k_prolong0_mr(Basis1D<T> bs, int nr, int 
 
 template <typename T>
 void launch_prolong0(int n, int nbox, int d, int pc, int nr, const int* leaf_off, const int* owner, const T* xi,
-                     const T* e, const T* epend, T* v, const int* skip, hipStream_t s) {
+                     const T* e, const T* epend, T* v, hipStream_t s) {
   const Basis1D<T> bs = make_basis<T>(pc);
   constexpr int VW = col_vw<T>();
   if (nr > 1 && nr % std::min(nr, VW) == 0 && aligned16(e) && (!epend || aligned16(epend)) && aligned16(v)) {
@@ -3411,10 +3383,10 @@ void launch_prolong0(int n, int nbox, int d, int pc, int nr, const int* leaf_off
   do {                                                                                                             \
     if (vw == 2)                                                                                                   \
       hipLaunchKernelGGL((k_prolong0_mr<T, DD, KK, 2>), dim3(nbox * per), dim3(256), shm, s, bs, nr, per, leaf_off, owner, xi, \
-                         e, epend, v, skip);                                                                         \
+                         e, epend, v);                                                                         \
     else                                                                                                           \
       hipLaunchKernelGGL((k_prolong0_mr<T, DD, KK, VW>), dim3(nbox * per), dim3(256), shm, s, bs, nr, per, leaf_off, owner, \
-                         xi, e, epend, v, skip);                                                                     \
+                         xi, e, epend, v);                                                                     \
   } while (0)
     switch (d * 8 + pc + 1) {
       case 17: R3MG_P0M(2, 1); break;
@@ -3440,10 +3412,10 @@ void launch_prolong0(int n, int nbox, int d, int pc, int nr, const int* leaf_off
   do {                                                                                                               \
     if (boxed)                                                                                                       \
       hipLaunchKernelGGL((k_prolong0_box<T, DD, KK>), dim3(xcd_grid(nlog)), dim3(256), 0, s, bs, nr, per, leaf_off,  \
-                         owner, xi, e, epend, v, skip, nlog);                                                        \
+                         owner, xi, e, epend, v, nlog);                                                        \
     else                                                                                                             \
       hipLaunchKernelGGL((k_prolong0<T, DD, KK>), dim3(xcd_grid(nlog)), dim3(256), 0, s, n, bs, nr, owner, xi, e,    \
-                         epend, v, skip, nlog);                                                                      \
+                         epend, v, nlog);                                                                      \
   } while (0)
   switch (d * 8 + pc + 1) {
     case 17: R3MG_P0(2, 1); break;
@@ -3460,9 +3432,9 @@ void launch_prolong0(int n, int nbox, int d, int pc, int nr, const int* leaf_off
   check_launch("k_prolong0");
 }
 template void launch_prolong0<float>(int, int, int, int, int, const int*, const int*, const float*, const float*,
-                                     const float*, float*, const int*, hipStream_t);
+                                     const float*, float*, hipStream_t);
 template void launch_prolong0<double>(int, int, int, int, int, const int*, const int*, const double*,
-                                      const double*, const double*, double*, const int*, hipStream_t);
+                                      const double*, const double*, double*, hipStream_t);
 
 // P~ entry [q'][q] of child box c: prod_a M_c[a][q'_a][q_a]
 template <typename T>
@@ -3527,11 +3499,9 @@ struct BoxLanes {
 template <typename T, int D, int KB>
 __global__ __launch_bounds__(256) void k_restrict_c(int nbox_next, int nbox, int shift, int nr,
                                                     const T* __restrict__ pt, const T* __restrict__ src, T* bnext,
-                                                    const T* __restrict__ dinv_next, T* dnext, T inv_theta_next,
-                                                    const int* __restrict__ skip) {
+                                                    const T* __restrict__ dinv_next, T* dnext, T inv_theta_next) {
   using BL = BoxLanes<D, KB>;
   constexpr int B = BL::B, GL = BL::GL, NG = BL::NG, M = BL::M;
-  if (skip && *skip) return;
   extern __shared__ unsigned char smem_raw[];
   __shared__ T sa[NG][B], sb[NG][B], sm[NG][M];
   T* part = reinterpret_cast<T*>(smem_raw);  // [children][B]
@@ -3567,10 +3537,8 @@ __global__ __launch_bounds__(256) void k_restrict_c(int nbox_next, int nbox, int
 template <typename T, int VW>
 __global__ __launch_bounds__(512) void k_restrict_c_mr(int nbox_next, int nbox, int shift, int d, int k, int nr,
                                                        const T* __restrict__ pt, const T* __restrict__ src, T* bnext,
-                                                       const T* __restrict__ dinv_next, T* dnext, T inv_theta_next,
-                                                       const int* __restrict__ skip) {
+                                                       const T* __restrict__ dinv_next, T* dnext, T inv_theta_next) {
   using VT = typename ColVec<T, VW>::type;
-  if (skip && *skip) return;
   extern __shared__ __align__(16) unsigned char smem_raw[];
   const int B = (d == 3) ? k * k * k : k * k;
   const int kk = k * k;
@@ -3611,7 +3579,7 @@ __global__ __launch_bounds__(512) void k_restrict_c_mr(int nbox_next, int nbox, 
 
 template <typename T>
 void launch_restrict_c(int nbox_next, int nbox, int shift, int d, int pc, int nr, const T* pt, const T* src,
-                       T* bnext, const T* dinv_next, T* dnext, double inv_theta_next, const int* skip,
+                       T* bnext, const T* dinv_next, T* dnext, double inv_theta_next,
                        hipStream_t s) {
   const int k = pc + 1;
   const int B = (d == 3) ? k * k * k : k * k;
@@ -3625,34 +3593,32 @@ void launch_restrict_c(int nbox_next, int nbox, int shift, int d, int pc, int nr
     const size_t shmm = sizeof(T) * ((size_t)B * nr + (size_t)(1 << shift) * d * k * k);
     if (vw == 2)
       hipLaunchKernelGGL((k_restrict_c_mr<T, 2>), dim3(nbox_next), dim3(thr), shmm, s, nbox_next, nbox, shift, d, k, nr,
-                         pt, src, bnext, dinv_next, dnext, (T)inv_theta_next, skip);
+                         pt, src, bnext, dinv_next, dnext, (T)inv_theta_next);
     else
       hipLaunchKernelGGL((k_restrict_c_mr<T, VW>), dim3(nbox_next), dim3(thr), shmm, s, nbox_next, nbox, shift, d, k,
-                         nr, pt, src, bnext, dinv_next, dnext, (T)inv_theta_next, skip);
+                         nr, pt, src, bnext, dinv_next, dnext, (T)inv_theta_next);
     check_launch("k_restrict_c_mr");
     return;
   }
   const size_t shm = sizeof(T) * ((size_t)B << shift);
   box_dispatch(d, k, [&](auto dk) {
     hipLaunchKernelGGL((k_restrict_c<T, dk.D, dk.K>), dim3((unsigned)nbox_next), dim3(256), shm, s, nbox_next, nbox, shift,
-                       nr, pt, src, bnext, dinv_next, dnext, (T)inv_theta_next, skip);
+                       nr, pt, src, bnext, dinv_next, dnext, (T)inv_theta_next);
   });
   check_launch("k_restrict_c");
 }
 template void launch_restrict_c<float>(int, int, int, int, int, int, const float*, const float*, float*,
-                                       const float*, float*, double, const int*, hipStream_t);
+                                       const float*, float*, double, hipStream_t);
 template void launch_restrict_c<double>(int, int, int, int, int, int, const double*, const double*, double*,
-                                        const double*, double*, double, const int*, hipStream_t);
+                                        const double*, double*, double, hipStream_t);
 
 // Prolongation between agglomerated levels: v[C B + a] = sum_q P~_C[a][q] (e + epend)[G B + q], G = C >> shift the
 // parent of child box C; a group of lanes per child box, axis by axis.
 template <typename T, int D, int KB>
 __global__ __launch_bounds__(256) void k_prolong_c(int nbox, int shift, int nr, const T* __restrict__ pt,
-                                                   const T* __restrict__ e, const T* __restrict__ epend, T* v,
-                                                   const int* __restrict__ skip) {
+                                                   const T* __restrict__ e, const T* __restrict__ epend, T* v) {
   using BL = BoxLanes<D, KB>;
   constexpr int B = BL::B, GL = BL::GL, NG = BL::NG, M = BL::M;
-  if (skip && *skip) return;
   __shared__ T sa[NG][B], sb[NG][B], sm[NG][M];
   const int g = threadIdx.x / GL, q = threadIdx.x % GL;
   const int C = blockIdx.x * NG + g;
@@ -3677,9 +3643,8 @@ __global__ __launch_bounds__(256) void k_prolong_c(int nbox, int shift, int nr, 
 template <typename T, int VW>
 __global__ __launch_bounds__(256) void k_prolong_c_mr(int nbox, int shift, int d, int k, int nr,
                                                       const T* __restrict__ pt, const T* __restrict__ e,
-                                                      const T* __restrict__ epend, T* v, const int* __restrict__ skip) {
+                                                      const T* __restrict__ epend, T* v) {
   using VT = typename ColVec<T, VW>::type;
-  if (skip && *skip) return;
   const int B = (d == 3) ? k * k * k : k * k;
   const int nch = nr / VW;
   const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -3700,7 +3665,7 @@ __global__ __launch_bounds__(256) void k_prolong_c_mr(int nbox, int shift, int d
 
 template <typename T>
 void launch_prolong_c(int nbox, int shift, int d, int pc, int nr, const T* pt, const T* e, const T* epend, T* v,
-                      const int* skip, hipStream_t s) {
+                      hipStream_t s) {
   const int k = pc + 1;
   const int B = (d == 3) ? k * k * k : k * k;
   constexpr int VW = col_vw<T>();
@@ -3710,10 +3675,10 @@ void launch_prolong_c(int nbox, int shift, int d, int pc, int nr, const T* pt, c
     if (totm == 0) return;
     if (vw == 2)
       hipLaunchKernelGGL((k_prolong_c_mr<T, 2>), dim3((unsigned)((totm + 255) / 256)), dim3(256), 0, s, nbox, shift, d,
-                         k, nr, pt, e, epend, v, skip);
+                         k, nr, pt, e, epend, v);
     else
       hipLaunchKernelGGL((k_prolong_c_mr<T, VW>), dim3((unsigned)((totm + 255) / 256)), dim3(256), 0, s, nbox, shift,
-                         d, k, nr, pt, e, epend, v, skip);
+                         d, k, nr, pt, e, epend, v);
     check_launch("k_prolong_c_mr");
     return;
   }
@@ -3721,33 +3686,32 @@ void launch_prolong_c(int nbox, int shift, int d, int pc, int nr, const T* pt, c
   box_dispatch(d, k, [&](auto dk) {
     constexpr int NG = BoxLanes<dk.D, dk.K>::NG;
     hipLaunchKernelGGL((k_prolong_c<T, dk.D, dk.K>), dim3((unsigned)((nbox + NG - 1) / NG)), dim3(256), 0, s, nbox, shift,
-                       nr, pt, e, epend, v, skip);
+                       nr, pt, e, epend, v);
   });
   check_launch("k_prolong_c");
 }
 template void launch_prolong_c<float>(int, int, int, int, int, const float*, const float*, const float*, float*,
-                                      const int*, hipStream_t);
+                                      hipStream_t);
 template void launch_prolong_c<double>(int, int, int, int, int, const double*, const double*, const double*,
-                                       double*, const int*, hipStream_t);
+                                       double*, hipStream_t);
 
 // =============================================================================================
 // Elementwise helpers
 // =============================================================================================
 template <typename T>
-__global__ void k_xupdate(int64_t count, T* x, const T* __restrict__ v, int assign, const int* __restrict__ skip) {
-  if (skip && *skip) return;
+__global__ void k_xupdate(int64_t count, T* x, const T* __restrict__ v, int assign) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i >= count) return;
   x[i] = assign ? v[i] : x[i] + v[i];
 }
 template <typename T>
-void launch_xupdate(int64_t count, T* x, const T* v, int assign, const int* skip, hipStream_t s) {
+void launch_xupdate(int64_t count, T* x, const T* v, int assign, hipStream_t s) {
   if (count == 0) return;
-  hipLaunchKernelGGL((k_xupdate<T>), dim3((unsigned)((count + 255) / 256)), dim3(256), 0, s, count, x, v, assign, skip);
+  hipLaunchKernelGGL((k_xupdate<T>), dim3((unsigned)((count + 255) / 256)), dim3(256), 0, s, count, x, v, assign);
   check_launch("k_xupdate");
 }
-template void launch_xupdate<float>(int64_t, float*, const float*, int, const int*, hipStream_t);
-template void launch_xupdate<double>(int64_t, double*, const double*, int, const int*, hipStream_t);
+template void launch_xupdate<float>(int64_t, float*, const float*, int, hipStream_t);
+template void launch_xupdate<double>(int64_t, double*, const double*, int, hipStream_t);
 
 // V-cycle entry: b0[i] = r_user[perm[i]] (column c at r_user + c*ld), d0 = dinv * b0 * inv_theta
 template <typename T>
@@ -3798,8 +3762,7 @@ template void launch_vc_exit<double>(int, int, const int*, const double*, const 
 // Dense coarsest solve x = A_L^{-1} b with the float64 explicit inverse (one wave per row).
 template <typename T, int NR>
 __global__ __launch_bounds__(256) void k_dense_apply(int nc, const double* __restrict__ cinv, const T* __restrict__ b,
-                                                     T* x, const int* __restrict__ skip) {
-  if (skip && *skip) return;
+                                                     T* x) {
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   if (row >= nc) return;
@@ -3834,11 +3797,10 @@ __global__ __launch_bounds__(256) void k_dense_apply(int nc, const double* __res
 // steps at once).  Fewer than four unknowns (the last four of a row are read as one vector) keep the kernel above.
 template <typename T, int NR>
 __global__ __launch_bounds__(1024) void k_dense_apply_mr(int nc, const double* __restrict__ cinv,
-                                                         const T* __restrict__ b, T* x, const int* __restrict__ skip) {
+                                                         const T* __restrict__ b, T* x) {
   using M = Mfma16<double>;
   constexpr int NW = 16, UN = 4;
   typedef double V4 __attribute__((ext_vector_type(4), aligned(8)));
-  if (skip && *skip) return;
   __shared__ double red[NW][256];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int i = lane & 15, kk = lane >> 4;
@@ -3877,13 +3839,13 @@ __global__ __launch_bounds__(1024) void k_dense_apply_mr(int nc, const double* _
   }
 }
 template <typename T>
-void launch_dense_apply(int nc, int nr, const double* cinv, const T* b, T* x, const int* skip, hipStream_t s) {
+void launch_dense_apply(int nc, int nr, const double* cinv, const T* b, T* x, hipStream_t s) {
 #define R3_DAP(NRV)                                                                                              \
   case NRV:                                                                                                      \
     if (NRV == 1 || nc < 4)                                                                                      \
-      hipLaunchKernelGGL((k_dense_apply<T, NRV>), dim3((nc + 3) / 4), dim3(256), 0, s, nc, cinv, b, x, skip);    \
+      hipLaunchKernelGGL((k_dense_apply<T, NRV>), dim3((nc + 3) / 4), dim3(256), 0, s, nc, cinv, b, x);    \
     else                                                                                                         \
-      hipLaunchKernelGGL((k_dense_apply_mr<T, NRV>), dim3((nc + 15) / 16), dim3(1024), 0, s, nc, cinv, b, x, skip); \
+      hipLaunchKernelGGL((k_dense_apply_mr<T, NRV>), dim3((nc + 15) / 16), dim3(1024), 0, s, nc, cinv, b, x); \
     break;
   switch (nr) {
     R3_DAP(1)
@@ -3896,8 +3858,8 @@ void launch_dense_apply(int nc, int nr, const double* cinv, const T* b, T* x, co
 #undef R3_DAP
   check_launch("k_dense_apply");
 }
-template void launch_dense_apply<float>(int, int, const double*, const float*, float*, const int*, hipStream_t);
-template void launch_dense_apply<double>(int, int, const double*, const double*, double*, const int*, hipStream_t);
+template void launch_dense_apply<float>(int, int, const double*, const float*, float*, hipStream_t);
+template void launch_dense_apply<double>(int, int, const double*, const double*, double*, hipStream_t);
 
 // Symmetric dense coarsest product.  Pass 1: one workgroup per upper tile (I, J); wave w holds the tile's rows
 // 16 w .. 16 w + 15 in registers (stored as M = float64, or float32 for the float32 V-cycle, and widened to
@@ -3909,8 +3871,7 @@ template void launch_dense_apply<double>(int, int, const double*, const double*,
 template <typename T, typename M, int NR>
 __global__ __launch_bounds__(256) void k_dense_sym_tiles(int nc, int nt, const M* __restrict__ packed,
                                                          const int2* __restrict__ tiles, const T* __restrict__ b,
-                                                         double* part, const int* __restrict__ skip) {
-  if (skip && *skip) return;
+                                                         double* part) {
   __shared__ double sh[4][64];
   __shared__ T sbr[4][16 * NR];  // wave w's 16 rows of b (0 past the last row), read at use (fewer registers)
   const int t = blockIdx.x;
@@ -3990,9 +3951,7 @@ __device__ inline double dense_sum16(const double (*sh)[17], int i) {
 
 // Pass 2 alone: rows 16 Q .. 16 Q + 15 of row block R = blockIdx.x / 4 (Q = blockIdx.x % 4).
 template <typename T, int NR>
-__global__ __launch_bounds__(256) void k_dense_sym_reduce(int nc, int nt, const double* __restrict__ part, T* x,
-                                                          const int* __restrict__ skip) {
-  if (skip && *skip) return;
+__global__ __launch_bounds__(256) void k_dense_sym_reduce(int nc, int nt, const double* __restrict__ part, T* x) {
   __shared__ double sh[16][17];
   const int R = blockIdx.x >> 2, i = 16 * (blockIdx.x & 3) + (threadIdx.x & 15), g = threadIdx.x >> 4;
   const int row = R * kDenseTile + i;
@@ -4012,11 +3971,9 @@ __global__ __launch_bounds__(256) void k_dense_sym_reduce(int nc, int nt, const 
 template <typename T, int D, int KB, int NR>
 __global__ __launch_bounds__(256) void k_dense_sym_reduce_prolong(int nbox, int shift, int nt,
                                                                   const double* __restrict__ part, T* x,
-                                                                  const T* __restrict__ pt, T* v,
-                                                                  const int* __restrict__ skip) {
+                                                                  const T* __restrict__ pt, T* v) {
   using BL = BoxLanes<D, KB>;
   constexpr int B = BL::B, GL = BL::GL, NG = BL::NG, M = BL::M;
-  if (skip && *skip) return;
   __shared__ double sh[16][17];
   __shared__ T xs[B * NR];
   __shared__ T sa[NG][B], sb[NG][B], sm[NG][M];
@@ -4074,7 +4031,7 @@ template void launch_dense_pack_sym<float>(int, int, const double*, const int*, 
 
 template <typename T, typename M>
 void launch_dense_apply_sym(int nc, int nt, int nr, const M* packed, const int* tiles, double* part, const T* b,
-                            T* x, const DenseProlong<T>* pr, const int* skip, hipStream_t s) {
+                            T* x, const DenseProlong<T>* pr, hipStream_t s) {
   const int ntiles = nt * (nt + 1) / 2;
   const int2* tl = reinterpret_cast<const int2*>(tiles);
   int B = 0;
@@ -4085,15 +4042,14 @@ void launch_dense_apply_sym(int nc, int nt, int nr, const M* packed, const int* 
   }
   switch (nr) {
 #define R3_DS(NRV)                                                                                                  \
-  hipLaunchKernelGGL((k_dense_sym_tiles<T, M, NRV>), dim3(ntiles), dim3(256), 0, s, nc, nt, packed, tl, b, part,   \
-                     skip);                                                                                         \
+  hipLaunchKernelGGL((k_dense_sym_tiles<T, M, NRV>), dim3(ntiles), dim3(256), 0, s, nc, nt, packed, tl, b, part);  \
   if (pr)                                                                                                           \
     box_dispatch(pr->d, pr->pc + 1, [&](auto dk) {                                                                   \
       hipLaunchKernelGGL((k_dense_sym_reduce_prolong<T, dk.D, dk.K, NRV>), dim3(pr->nbox_coarse), dim3(256), 0, s,   \
-                         pr->nbox, pr->shift, nt, part, x, pr->pt, pr->v, skip);                                     \
+                         pr->nbox, pr->shift, nt, part, x, pr->pt, pr->v);                                     \
     });                                                                                                              \
   else                                                                                                              \
-    hipLaunchKernelGGL((k_dense_sym_reduce<T, NRV>), dim3(4 * nt), dim3(256), 0, s, nc, nt, part, x, skip);        \
+    hipLaunchKernelGGL((k_dense_sym_reduce<T, NRV>), dim3(4 * nt), dim3(256), 0, s, nc, nt, part, x);        \
   break;
     case 1: R3_DS(1)
     case 2: R3_DS(2)
@@ -4104,13 +4060,12 @@ void launch_dense_apply_sym(int nc, int nt, int nr, const M* packed, const int* 
   check_launch("k_dense_sym");
 }
 template void launch_dense_apply_sym<float, float>(int, int, int, const float*, const int*, double*, const float*,
-                                                   float*, const DenseProlong<float>*, const int*, hipStream_t);
+                                                   float*, const DenseProlong<float>*, hipStream_t);
 template void launch_dense_apply_sym<float, double>(int, int, int, const double*, const int*, double*,
-                                                    const float*, float*, const DenseProlong<float>*, const int*,
+                                                    const float*, float*, const DenseProlong<float>*,
                                                     hipStream_t);
 template void launch_dense_apply_sym<double, double>(int, int, int, const double*, const int*, double*,
-                                                     const double*, double*, const DenseProlong<double>*,
-                                                     const int*, hipStream_t);
+                                                     const double*, double*, const DenseProlong<double>*, hipStream_t);
 
 __global__ void k_gather_cols(int n, int nr, int nuser, const int* __restrict__ perm,
                               const double* __restrict__ user, int64_t ld, double* out) {

@@ -352,13 +352,13 @@ void apply_level(Ctx& c, int l, int nr, const T* u, const T* b, T* rho, T* x, T*
       break;
     }
     case LevelKernel::BoxRow:
-      launch_level_boxrow<T>(op, D.maxnb, u, b, rho, x, dout, c1, c2, flags | keep_flag<T>(D), skip, s, rs);
+      launch_level_boxrow<T>(op, D.maxnb, u, b, rho, x, dout, c1, c2, flags | keep_flag<T>(D), s, rs);
       break;
     case LevelKernel::BlockRowWG:
-      launch_level_blockrow_wg<T>(op, u, b, rho, x, dout, c1, c2, flags | keep_flag<T>(D), skip, s);
+      launch_level_blockrow_wg<T>(op, u, b, rho, x, dout, c1, c2, flags | keep_flag<T>(D), s);
       break;
     case LevelKernel::BlockRow:
-      launch_level_blockrow<T>(op, D.maxnb, u, b, rho, x, dout, c1, c2, flags | keep_flag<T>(D), skip, s);
+      launch_level_blockrow<T>(op, D.maxnb, u, b, rho, x, dout, c1, c2, flags | keep_flag<T>(D), s);
       break;
     default: {
       if (nr > 1) {
@@ -374,7 +374,7 @@ void apply_level(Ctx& c, int l, int nr, const T* u, const T* b, T* rho, T* x, T*
             break;
           }
           if (it->second == kCodeBox) {
-            launch_level_box_mr<T>(op, nr, u, b, rho, x, dout, c1, c2, flags, skip, s);
+            launch_level_box_mr<T>(op, nr, u, b, rho, x, dout, c1, c2, flags, s);
             break;
           }
           if (it->second >= kCodeSplit) {  // fine level: column-split or chunk kernel
@@ -867,25 +867,24 @@ static Cheb cheb_coeffs(double lo, double hi, int K) {
 // up to kDenseSymMaxNR columns, else the full float64 inverse.  With pr, the prolongation to the level above
 // follows (fused into the tiled product's last pass, else k_prolong_c).
 template <typename T>
-static void coarsest_apply(Ctx& c, int nr, const T* b, T* x, const DenseProlong<T>* pr, const int* skip,
-                           hipStream_t s) {
+static void coarsest_apply(Ctx& c, int nr, const T* b, T* x, const DenseProlong<T>* pr, hipStream_t s) {
   Device& dv = c.dv;
   if (dv.ct > 0 && nr <= kDenseSymMaxNR) {
     if constexpr (sizeof(T) == 4) {
       if (dv.csym32.p) {
-        launch_dense_apply_sym<T, float>((int)dv.nc, dv.ct, nr, dv.csym32.p, dv.ctile.p, dv.cpart.p, b, x, pr, skip,
+        launch_dense_apply_sym<T, float>((int)dv.nc, dv.ct, nr, dv.csym32.p, dv.ctile.p, dv.cpart.p, b, x, pr,
                                          s);
         return;
       }
     }
     if (dv.csym.p) {
-      launch_dense_apply_sym<T, double>((int)dv.nc, dv.ct, nr, dv.csym.p, dv.ctile.p, dv.cpart.p, b, x, pr, skip,
+      launch_dense_apply_sym<T, double>((int)dv.nc, dv.ct, nr, dv.csym.p, dv.ctile.p, dv.cpart.p, b, x, pr,
                                         s);
       return;
     }
   }
-  launch_dense_apply<T>((int)dv.nc, nr, dv.cinv.p, b, x, skip, s);
-  if (pr) launch_prolong_c<T>(pr->nbox, pr->shift, c.an.d, c.an.pc, nr, pr->pt, x, nullptr, pr->v, skip, s);
+  launch_dense_apply<T>((int)dv.nc, nr, dv.cinv.p, b, x, s);
+  if (pr) launch_prolong_c<T>(pr->nbox, pr->shift, c.an.d, c.an.pc, nr, pr->pt, x, nullptr, pr->v, s);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -895,7 +894,7 @@ static void coarsest_apply(Ctx& c, int nr, const T* b, T* x, const DenseProlong<
 // added to x_l by the consumer.
 // ---------------------------------------------------------------------------------------------
 template <typename T>
-T* vcycle_rec(Ctx& c, int l, int nr, const T* b_override, const int* skip, hipStream_t s) {
+T* vcycle_rec(Ctx& c, int l, int nr, const T* b_override, hipStream_t s) {
   Analysis& an = c.an;
   Device& dv = c.dv;
   const int L = an.nlevels() - 1;
@@ -903,12 +902,11 @@ T* vcycle_rec(Ctx& c, int l, int nr, const T* b_override, const int* skip, hipSt
   T* b = b_override ? const_cast<T*>(b_override) : wv<T>(c, l, W_B);
   T* x = wv<T>(c, l, W_X);
   if (l == L) {
-    coarsest_apply<T>(c, nr, b, x, nullptr, skip, s);
+    coarsest_apply<T>(c, nr, b, x, nullptr, s);
     return nullptr;
   }
   const r3mg_options& o = an.opt;
   const int K = o.cheb_degree;
-  LevelOp<T> op = level_op<T>(c, l);
   T* rho = wv<T>(c, l, W_RHO);
   T* buf[2] = {wv<T>(c, l, W_DA), wv<T>(c, l, W_DB)};
   bool x_zero = true, rho_is_b = true;
@@ -919,7 +917,7 @@ T* vcycle_rec(Ctx& c, int l, int nr, const T* b_override, const int* skip, hipSt
     ++done_spmv;
     if (done_spmv < total_spmv) fl |= F_RHO_STORE;  // the level's last residual is never read
     if (dout_on) fl |= F_D_OUT;
-    apply_level<T>(c, l, nr, u, b, rho, x, dout, c1, c2, fl, skip, s, rs);
+    apply_level<T>(c, l, nr, u, b, rho, x, dout, c1, c2, fl, nullptr, s, rs);
     x_zero = false;
     rho_is_b = false;
   };
@@ -971,10 +969,10 @@ T* vcycle_rec(Ctx& c, int l, int nr, const T* b_override, const int* skip, hipSt
     const T* xi;
     if constexpr (sizeof(T) == 4) xi = D.xi32.p; else xi = D.xi64.p;
     launch_restrict0<T>((int)N.nbox, an.n, an.d, an.pc, nr, D.leaf_off.p, D.owner.p, xi, src, wv<T>(c, l + 1, W_B), dinv_next,
-                        dnext, next_inv_theta, skip, s);
+                        dnext, next_inv_theta, s);
   } else {
     launch_restrict_c<T>((int)N.nbox, (int)D.nbox, N.child_shift, an.d, an.pc, nr, pt, src, wv<T>(c, l + 1, W_B),
-                         dinv_next, dnext, next_inv_theta, skip, s);
+                         dinv_next, dnext, next_inv_theta, s);
   }
 
   // coarse correction
@@ -989,21 +987,21 @@ T* vcycle_rec(Ctx& c, int l, int nr, const T* b_override, const int* skip, hipSt
     pr.pc = an.pc;
     pr.pt = pt;
     pr.v = v;
-    coarsest_apply<T>(c, nr, wv<T>(c, l + 1, W_B), wv<T>(c, l + 1, W_X), &pr, skip, s);
+    coarsest_apply<T>(c, nr, wv<T>(c, l + 1, W_B), wv<T>(c, l + 1, W_X), &pr, s);
   } else if (l == 0) {
-    T* pend_c = vcycle_rec<T>(c, l + 1, nr, nullptr, skip, s);
+    T* pend_c = vcycle_rec<T>(c, l + 1, nr, nullptr, s);
     const T* xi;
     if constexpr (sizeof(T) == 4) xi = D.xi32.p; else xi = D.xi64.p;
     launch_prolong0<T>((int)D.n, (int)N.nbox, an.d, an.pc, nr, D.leaf_off.p, D.owner.p, xi, wv<T>(c, l + 1, W_X),
-                       pend_c, v, skip, s);
+                       pend_c, v, s);
   } else {
-    T* pend_c = vcycle_rec<T>(c, l + 1, nr, nullptr, skip, s);
-    launch_prolong_c<T>((int)D.nbox, N.child_shift, an.d, an.pc, nr, pt, wv<T>(c, l + 1, W_X), pend_c, v, skip, s);
+    T* pend_c = vcycle_rec<T>(c, l + 1, nr, nullptr, s);
+    launch_prolong_c<T>((int)D.nbox, N.child_shift, an.d, an.pc, nr, pt, wv<T>(c, l + 1, W_X), pend_c, v, s);
   }
 
   // post-smoothing from the corrected iterate
   if (o.post_steps == 0) {
-    launch_xupdate<T>(D.n * nr, x, v, x_zero ? 1 : 0, skip, s);
+    launch_xupdate<T>(D.n * nr, x, v, x_zero ? 1 : 0, s);
     return nullptr;
   }
   T* u = v;
@@ -1518,7 +1516,7 @@ static void vcycle_api_t(HandleImpl& h, const double* r, double* z, int nrhs, hi
       launch_vc_prep<T>((int)an.n, NR, dv.pb.p, b0, dinv0, smooth0 ? vbuf<T>(D0.dA) : nullptr,
                         2.0 / (D0.lam_hi + D0.lam_lo), nullptr, s);
     }
-    T* pend = (L == 0) ? nullptr : vcycle_rec<T>(c, 0, NR, nullptr, nullptr, s);
+    T* pend = (L == 0) ? nullptr : vcycle_rec<T>(c, 0, NR, nullptr, s);
     if (NR == nb) {
       launch_vc_exit<T>((int)an.n, NR, dv.perm.p, vbuf<T>(D0.x), pend, z + (int64_t)c0 * an.n, an.n, s);
     } else {
@@ -1580,7 +1578,7 @@ static void vcycle_noalloc_t(HandleImpl& h, const double* r, double* z, int nrhs
   if constexpr (sizeof(T) == 4) dinv0 = D0.dinv32.p; else dinv0 = D0.dinv64.p;
   launch_vc_entry<T>((int)an.n, NR, dv.perm.p, r, an.n, b0, dinv0, smooth0 ? wv<T>(c, 0, W_DA) : nullptr,
                      2.0 / (D0.lam_hi + D0.lam_lo), s);
-  T* pend = (L == 0) ? nullptr : vcycle_rec<T>(c, 0, NR, nullptr, nullptr, s);
+  T* pend = (L == 0) ? nullptr : vcycle_rec<T>(c, 0, NR, nullptr, s);
   launch_vc_exit<T>((int)an.n, NR, dv.perm.p, wv<T>(c, 0, W_X), pend, z, an.n, s);
 }
 
@@ -1639,7 +1637,7 @@ static void pcg_operator(Ctx& c, int NR, const double* p, double* q, const int* 
   launch_level<double>(op64, NR, p, nullptr, q, nullptr, nullptr, 0.0, 0.0, F_PLAIN, skip, s);
 }
 
-// One PCG iteration (all launches skip once every column has converged).  part 0: the whole iteration; part 1:
+// One PCG iteration (its launches, those of the V-cycle apart, skip once every column has converged).  part 0: all; part 1:
 // q = A p, alpha, the x and r updates and the stop test; part 2: the V-cycle, z, beta and the new p.
 template <typename T>
 static void pcg_iteration(Ctx& c, int NR, bool flexible, hipStream_t s, int part = 0) {
@@ -1673,7 +1671,7 @@ static void pcg_iteration(Ctx& c, int NR, bool flexible, hipStream_t s, int part
     const T* bl0 = (sizeof(T) == 4) ? vbuf<T>(D0.b) : reinterpret_cast<const T*>(dv.pr.p);
     T* pend = nullptr;
     // the V-cycle's kernels do not read the skip flag (one memory latency less each)
-    if (L > 0) pend = vcycle_rec<T>(c, 0, 1, bl0, nullptr, s);
+    if (L > 0) pend = vcycle_rec<T>(c, 0, 1, bl0, s);
     const T* x0 = (L > 0) ? vbuf<T>(D0.x) : bl0;
     launch_pcg_z1<T>(n, st, part == 0, x0, pend, dv.pz.p, dv.pr.p, flexible ? dv.pq.p : nullptr, P, s);
     launch_pcg_p1(n, st, dv.pz.p, dv.pp.p, P, s);
@@ -1685,10 +1683,6 @@ static void pcg_iteration(Ctx& c, int NR, bool flexible, hipStream_t s, int part
     if (D0.mf) {
       apply_level<double>(c, 0, NR, dv.pp.p, nullptr, dv.pq.p, nullptr, nullptr, 0.0, 0.0, F_PLAIN, skip, s);
       launch_pcg_dot_alpha(n, NR, dv.pp.p, dv.pq.p, dv.partials.p, st, s);
-    } else if (NR == 1 && D0.fb[D0.shape].nrb > 0) {
-      launch_level_stream<double>(D0.shape64, D0.fb[D0.shape64], op64, dv.pp.p, nullptr, dv.pq.p, nullptr, nullptr, 0, 0,
-                                  F_PLAIN | D0.keep64, skip, nullptr, s);
-      launch_pcg_dot_alpha(n, 1, dv.pp.p, dv.pq.p, dv.partials.p, st, s);
     } else {
       auto it = dv.tuned.find({-1, NR * 2});
       if (it != dv.tuned.end() && (it->second < 0 || it->second >= kCodeSplit)) {
@@ -1725,7 +1719,7 @@ static void pcg_iteration(Ctx& c, int NR, bool flexible, hipStream_t s, int part
   // start of each of its ~45 kernels would put one more memory latency on each of them.
   const T* bl0 = (sizeof(T) == 4) ? vbuf<T>(D0.b) : reinterpret_cast<const T*>(dv.pr.p);
   T* pend = nullptr;
-  if (L > 0) pend = vcycle_rec<T>(c, 0, NR, bl0, nullptr, s);
+  if (L > 0) pend = vcycle_rec<T>(c, 0, NR, bl0, s);
   const T* x0 = (L > 0) ? vbuf<T>(D0.x) : bl0;
   launch_pcg_z<T>(n, NR, st, 2, x0, pend, dv.pz.p, dv.pr.p, flexible ? dv.pq.p : nullptr, nullptr, dv.partials.p, s);
   launch_pcg_p(n, NR, st, dv.pz.p, dv.pp.p, s);
@@ -1764,7 +1758,7 @@ static void pcg_start(Ctx& c, int NR, int nb, double rtol, double atol, bool fle
                     skip, s);
   const T* bl0 = (sizeof(T) == 4) ? vbuf<T>(D0.b) : reinterpret_cast<const T*>(dv.pr.p);
   T* pend = nullptr;
-  if (L > 0) pend = vcycle_rec<T>(c, 0, NR, bl0, nullptr, s);
+  if (L > 0) pend = vcycle_rec<T>(c, 0, NR, bl0, s);
   const T* x0 = (L > 0) ? vbuf<T>(D0.x) : bl0;
   // one column: <r, z> partials in area 2, where the first iteration's alpha kernel forms gamma from them
   double* zpart = NR == 1 ? dv.partials.p + 2 * pcg_blocks(n) : dv.partials.p;
