@@ -47,6 +47,18 @@ def recorded_traffic(kernel: str):
     return float(rec[key])
 
 
+def roofline_entry(kernel, stored, csr, ms, ms_cold, traffic):
+    """The roofline record of a fine-level kernel: rates and their fractions of the HBM peak by the bytes that its
+    storage format moves (`stored`).  csr_bytes_per_launch is what a CSR form with a 4-byte index per nonzero would
+    move, for comparison with other storage formats; no rate or fraction is formed from it."""
+    rate, cold = stored / (ms * 1e-3) / 1e9, stored / (ms_cold * 1e-3) / 1e9
+    return {"bound": "hbm", "achieved": rate, "peak": PEAK_HBM_GBS, "unit": "GB/s", "frac": rate / PEAK_HBM_GBS,
+            "traffic": traffic, "kernel": kernel, "bytes_per_launch": stored, "us_per_launch": ms * 1e3,
+            "csr_bytes_per_launch": csr,
+            "hbm_only": {"us_per_launch": ms_cold * 1e3, "achieved": cold, "frac": cold / PEAK_HBM_GBS,
+                         "method": "each launch timed alone after a 1 GiB read+write pass"}}
+
+
 def log(*a):
     print("[bench]", *a, file=sys.stderr, flush=True)
 
@@ -158,43 +170,34 @@ def main():
         vc[name] = e0.elapsed_time(e1) / reps
     lv_info = {"fp32": h32.info(), "fp64": h64.info()}
 
-    def apply_bytes(lv, l, s):
-        """Algorithmic bytes of one operator application with the fused Chebyshev update: the matrix with a
-        4-byte index per nonzero (CSR, fine level) or per stored B x B block (coarse levels), 4-byte row or
-        block-row pointers, and 7 vector streams (u read, x read and written, rho read and written, D^-1, d)."""
-        if l == 0:
-            return lv["nnz"] * (s + 4) + 4 * (lv["n"] + 1) + 7 * lv["n"] * s
-        B = (w.coarse_degree + 1) ** prob.d
-        return lv["nnz"] * s + 4 * lv["nnz"] / (B * B) + 4 * (lv["nboxes"] + 1) + 7 * lv["n"] * s
-
-    def vcycle_bytes(inf, fp32, stored):
-        """Algorithmic bytes of one V-cycle: K(pre+post) operator applications per smoothed level (apply_bytes,
-        or with stored=True the bytes of the storage format the library reports), 4 transfer vector passes per
-        level, the dense coarsest inverse (float64) and the entry/exit passes of the fine level."""
+    def vcycle_bytes(inf, fp32):
+        """Bytes of one V-cycle: K(pre+post) operator applications per smoothed level in the storage format the library
+        reports (matrix as stored and 7 vector streams), 4 transfer vector passes per level, the coarsest inverse
+        (its upper tiles in the V-cycle precision) and the entry/exit passes of the fine level."""
         K, nu = 3, w.pre_steps + w.post_steps
         s = 4 if fp32 else 8
         tot = 0.0
         for l, lv in enumerate(inf):
             if l < len(inf) - 1:
-                tot += K * nu * (lv["bytes_per_apply"] if stored else apply_bytes(lv, l, s))
-                tot += 4 * lv["n"] * s
+                tot += K * nu * lv["bytes_per_apply"] + 4 * lv["n"] * s
             else:
-                tot += lv["n"] * lv["n"] * 8.0
-        tot += 2 * prob.n * 8 + 3 * prob.n * s
-        return tot
+                tiles = -(-lv["n"] // 64)
+                tot += tiles * (tiles + 1) / 2 * 64 * 64 * s
+        return tot + 2 * prob.n * 8 + 3 * prob.n * s
 
-    vb = {k: vcycle_bytes(lv_info[k], k == "fp32", False) for k in vc}
+    vb = {k: vcycle_bytes(lv_info[k], k == "fp32") for k in vc}
     vgbs = {k: vb[k] / (vc[k] * 1e-3) / 1e9 for k in vc}
-    vb_stored = {k: vcycle_bytes(lv_info[k], k == "fp32", True) for k in vc}
     log(f"V-cycle: fp32 {vc['fp32']:.3f} ms ({vgbs['fp32']:.0f} GB/s), fp64 {vc['fp64']:.3f} ms ({vgbs['fp64']:.0f} GB/s)")
 
     # dominant kernel: fused level-0 smoother step, timed live with hipEvents on the launch stream, back to back
     # as a smoothing sweep runs it, and alone after a 1 GiB pass that evicts the caches (HBM only)
     kms, kbytes = h32.time_smoother_kernel(0, 200)
     kms_cold, _ = h32.time_smoother_kernel(0, 40, flush_bytes=1 << 30)
-    abytes = apply_bytes(info[0], 0, 4)
-    kgbs = abytes / (kms * 1e-3) / 1e9
-    kgbs_cold = abytes / (kms_cold * 1e-3) / 1e9
+    # a CSR form: a 4-byte index per nonzero, row pointers, 7 vector streams (u, x and rho read, x, rho and d written, D^-1)
+    csr = info[0]["nnz"] * (4 + 4) + 4 * (prob.n + 1) + 7 * prob.n * 4
+    traffic = recorded_traffic(info[0]["kernel"]) if args.workload == "solve2d" and args.scale is None else None
+    roofline = roofline_entry(info[0]["kernel"] + " (fine-level fused SpMV + Chebyshev step)", kbytes, csr, kms, kms_cold,
+                              traffic)
     per_level = []
     for l in range(len(info) - 1):
         ms_l, by_l = h32.time_smoother_kernel(l, 100)
@@ -202,7 +205,8 @@ def main():
                           "us_per_launch": ms_l * 1e3,
                           "bytes_per_launch": by_l, "GBps": by_l / (ms_l * 1e-3) / 1e9})
     log(f"level-0 fp32 smoother kernel: {kms * 1e3:.1f} us back to back, {kms_cold * 1e3:.1f} us from HBM; "
-        f"{abytes / 1e6:.1f} MB algorithmic ({kbytes / 1e6:.1f} MB as stored): {kgbs:.0f} / {kgbs_cold:.0f} GB/s")
+        f"{kbytes / 1e6:.1f} MB as stored ({csr / 1e6:.1f} MB as CSR): {roofline['achieved']:.0f} / "
+        f"{roofline['hbm_only']['achieved']:.0f} GB/s")
 
     # CPU baseline: the FP64 oracle, same inputs, timed on the host cores
     cpu = None
@@ -265,20 +269,9 @@ def main():
         "vcycle_ms": vc,
         "vcycle_GBps": vgbs,
         "vcycle_frac_of_peak": {k: v / PEAK_HBM_GBS for k, v in vgbs.items()},
-        "vcycle_GBps_as_stored": {k: vb_stored[k] / (vc[k] * 1e-3) / 1e9 for k in vc},
         "smoother_kernel_per_level_fp32": per_level,
         "solution_rel_diff": err,
-        "roofline": {"bound": "hbm", "achieved": kgbs, "peak": PEAK_HBM_GBS, "unit": "GB/s",
-                     "frac": kgbs / PEAK_HBM_GBS,
-                     "traffic": (recorded_traffic(info[0]["kernel"])
-                                 if (args.workload == "solve2d" and args.scale is None) else None),
-                     "kernel": info[0]["kernel"] + " (fine-level fused SpMV + Chebyshev step)",
-                     "bytes_per_launch": abytes, "us_per_launch": kms * 1e3,
-                     "bytes_per_launch_as_stored": kbytes,
-                     "frac_as_stored": kbytes / (kms * 1e-3) / 1e9 / PEAK_HBM_GBS,
-                     "hbm_only": {"us_per_launch": kms_cold * 1e3, "achieved": kgbs_cold,
-                                  "frac": kgbs_cold / PEAK_HBM_GBS,
-                                  "method": "each launch timed alone after a 1 GiB read+write pass"}},
+        "roofline": roofline,
         "cpu_baseline": cpu,
     }
     print(json.dumps(out), flush=True)
@@ -338,20 +331,13 @@ def bench_batch16(args):
     log(f"16 rhs: {t16 * 1e3:.1f} ms ({16 * prob.n / t16:.3e} DoF/s), 1 rhs: {t1 * 1e3:.1f} ms")
     # dominant kernel: the fine-level fused smoother step for 16 columns (the tuned multi-RHS kernel), timed live
     # with hipEvents on the launch stream, back to back and alone after a 1 GiB pass that evicts the caches.
-    # Algorithmic bytes: the matrix once with a 4-byte index per nonzero, row pointers, 7 vector streams of 16
-    # float32 columns.
     kms, kbytes = h.time_smoother_kernel(0, 40, nrhs=16)
     kms_cold, _ = h.time_smoother_kernel(0, 10, flush_bytes=1 << 30, nrhs=16)
-    abytes = info[0]["nnz"] * (4 + 4) + 4 * (prob.n + 1) + 7 * prob.n * 4 * 16
-    kgbs, kgbs_cold = abytes / (kms * 1e-3) / 1e9, abytes / (kms_cold * 1e-3) / 1e9
+    csr = info[0]["nnz"] * (4 + 4) + 4 * (prob.n + 1) + 7 * prob.n * 4 * 16
+    roofline = roofline_entry("fine-level fused SpMV + Chebyshev step, 16 float32 columns", kbytes, csr, kms, kms_cold, None)
     log(f"level-0 16-rhs fp32 smoother kernel: {kms * 1e3:.1f} us back to back, {kms_cold * 1e3:.1f} us from HBM; "
-        f"{abytes / 1e6:.1f} MB algorithmic ({kbytes / 1e6:.1f} MB as stored): {kgbs:.0f} / {kgbs_cold:.0f} GB/s")
-    roofline = {"bound": "hbm", "achieved": kgbs, "peak": PEAK_HBM_GBS, "unit": "GB/s", "frac": kgbs / PEAK_HBM_GBS,
-                "traffic": None, "kernel": "fine-level fused SpMV + Chebyshev step, 16 float32 columns",
-                "bytes_per_launch": abytes, "us_per_launch": kms * 1e3, "bytes_per_launch_as_stored": kbytes,
-                "frac_as_stored": kbytes / (kms * 1e-3) / 1e9 / PEAK_HBM_GBS,
-                "hbm_only": {"us_per_launch": kms_cold * 1e3, "achieved": kgbs_cold, "frac": kgbs_cold / PEAK_HBM_GBS,
-                             "method": "each launch timed alone after a 1 GiB read+write pass"}}
+        f"{kbytes / 1e6:.1f} MB as stored ({csr / 1e6:.1f} MB as CSR): {roofline['achieved']:.0f} / "
+        f"{roofline['hbm_only']['achieved']:.0f} GB/s")
     mf = None
     if args.matfree:
         # the same solves with the matrix-free fine operator (cell kernel looping over the 16 columns)
