@@ -344,7 +344,9 @@ class Assembler:
 
 
 def solve_group(hs: Sequence[Hierarchy], bs, xs, rtol=1e-10, maxit=500, stream=None):
-    """Several independent problems solved by PCG in one hipGraph launch sequence."""
+    """Several independent problems solved by PCG side by side: each problem's launches run on a stream of the library's
+    own, after the work that `stream` (the current one) holds at the call.  Returns (iters, relres, all converged) with
+    every solution written."""
     k = len(hs)
     H = (C.c_void_p * k)(*[h._h for h in hs])
     Bp = (C.c_void_p * k)(*[b.data_ptr() for b in bs])
