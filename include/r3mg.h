@@ -221,7 +221,8 @@ r3mg_status r3mg_pcg_solve_ex(r3mg_handle h, const double* b_dev, double* x_dev,
 
 /* Several independent problems (each with its own handle, one right-hand side each) solved by PCG at once: the
  * iterations of each problem run on a stream of the library's own, beside those of the others.
- * b[k], x[k] are device vectors of handle k.  iters/relres: host arrays of `count` (may be NULL).  Synchronises. */
+ * b[k], x[k] are device vectors of handle k; every problem starts from them as they are at the call, also where b[k]
+ * is another problem's x[j].  iters/relres: host arrays of `count` (may be NULL).  Synchronises. */
 r3mg_status r3mg_pcg_solve_group(int count, r3mg_handle* hs, const double* const* b, double* const* x,
                                  double rtol, int maxit, void* stream, int* iters, double* relres);
 

@@ -2007,6 +2007,18 @@ Branches& branches(int dev, int count) {
   return b;
 }
 
+// whether a problem's right-hand side or initial guess overlaps another problem's solution
+bool shares_vectors(int count, HandleImpl** hs, const double* const* b, double* const* x) {
+  auto overlap = [&](const double* v, int i, int j) {
+    const uintptr_t a = reinterpret_cast<uintptr_t>(v), c = reinterpret_cast<uintptr_t>(x[j]);
+    return a < c + sizeof(double) * hs[j]->an->n && c < a + sizeof(double) * hs[i]->an->n;
+  };
+  for (int i = 0; i < count; ++i)
+    for (int j = 0; j < count; ++j)
+      if (i != j && (overlap(b[i], i, j) || overlap(x[i], i, j))) return true;
+  return false;
+}
+
 struct GroupTask {
   HandleImpl* h = nullptr;
   hipStream_t s = nullptr;
@@ -2089,14 +2101,21 @@ r3mg_status pcg_group(int count, HandleImpl** hs, const double* const* b, double
         for (int part = 0; part < 3; ++part)
           t.ex[part] = t.f32 ? iteration_graph<float>(c, 1, true, part) : iteration_graph<double>(c, 1, false, part);
     }
+    auto gather = [&](int q, hipStream_t on) {
+      Device& dv = *hs[q]->dev;
+      const int n = (int)hs[q]->an->n;
+      launch_gather_cols(n, 1, 1, dv.perm.p, b[q], n, dv.pb.p, on);
+      launch_gather_cols(n, 1, 1, dv.perm.p, x[q], n, dv.px.p, on);
+    };
+    // where a problem reads what another one writes, all of them read before any starts
+    const bool first = shares_vectors(count, hs, b, x);
+    for (int q = 0; first && q < count; ++q) gather(q, s);
     R3MG_HIP_CHECK(hipEventRecord(br.fork, s));
     for (int q : order) {
       GroupTask& t = tasks[q];
       Device& dv = *t.h->dev;
-      const int n = (int)t.h->an->n;
       R3MG_HIP_CHECK(hipStreamWaitEvent(t.s, br.fork, 0));
-      launch_gather_cols(n, 1, 1, dv.perm.p, b[q], n, dv.pb.p, t.s);
-      launch_gather_cols(n, 1, 1, dv.perm.p, x[q], n, dv.px.p, t.s);
+      if (!first) gather(q, t.s);
       start(t, false);
       enqueue_to(t, predict_first(dv, record_key(1, t.f32), rtol, 0.0, maxit));
       finish_chunk(t, x[q]);

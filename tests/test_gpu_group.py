@@ -143,3 +143,20 @@ def test_inputs_still_being_written_on_the_callers_stream():
         side.synchronize()
         _same((xs, it, rr, ok), want, gs)
         assert all(torch.equal(t, 2.0 * w[0]) for t, w in zip(twice, want))
+
+
+def test_right_hand_side_that_is_another_problems_unknown():
+    """b of one problem is x of another: every problem starts from the vectors as they were at the call."""
+    _need_gpu()
+    print("[gpu-case] group: shared vectors", flush=True)
+    import paper_2607_28235_amd as P
+    gs, hs, bs = _pairs([(9, 1), (9, 0), (9, 1)])
+    first = [bs[1].clone(), bs[2].clone(), bs[0].clone()]    # the initial guesses
+    want = []
+    for h, b, s in zip(hs, (first[1], first[2], bs[2]), first):
+        x = s.clone()
+        it, rr, ok = h.pcg(b.clone(), x, rtol=1e-10, maxit=100)
+        want.append((x, int(it[0]), float(rr[0]), ok, h.history()))
+    xs = [s.clone() for s in first]
+    it, rr, ok = P.solve_group(gs, [xs[1], xs[2], bs[2]], xs, rtol=1e-10, maxit=100)
+    _same((xs, it, rr, ok), want, gs)
