@@ -303,7 +303,7 @@ struct Device {
   hipStream_t cap_stream = nullptr;
   void* pinned = nullptr;      // host pinned buffer: the PcgState read back at the end of a chunk of iterations
   void* pinned_dev = nullptr;  // its device address (written by a kernel, no copy engine involved)
-  hipEvent_t ev[2] = {nullptr, nullptr};
+  hipEvent_t chunk_done = nullptr;
   // iterations of the last converged solve per (nr, precision) key: the rtol and atol it ran to, the iterations
   // of its slowest column and their mean squared residual reduction per iteration (the first chunk of the next
   // solve is enqueued from it)

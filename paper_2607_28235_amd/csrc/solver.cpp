@@ -137,8 +137,7 @@ void drop_graphs(Device& dv) {
 
 Device::~Device() {
   drop_graphs(*this);
-  for (auto e : ev)
-    if (e) (void)hipEventDestroy(e);
+  if (chunk_done) (void)hipEventDestroy(chunk_done);
   if (cap_stream) (void)hipStreamDestroy(cap_stream);
   if (pinned) (void)hipHostFree(pinned);
 }
@@ -1725,6 +1724,11 @@ static void pcg_iteration(Ctx& c, int NR, bool flexible, hipStream_t s, int part
   launch_pcg_p(n, NR, st, dv.pz.p, dv.pp.p, s);
 }
 
+// the event that the host waits for at the end of a chunk of iterations
+static void ensure_event(Device& dv) {
+  if (!dv.chunk_done) R3MG_HIP_CHECK(hipEventCreateWithFlags(&dv.chunk_done, hipEventDisableTiming));
+}
+
 // room for the CG coefficients and residual norms of maxit iterations (a reallocation invalidates the captured
 // graphs)
 static void ensure_hist(Device& dv, int maxit) {
@@ -1858,10 +1862,7 @@ static r3mg_status pcg_block(HandleImpl& h, const double* b, double* x, int c0, 
   const int n = (int)an.n;
   const bool flexible = sizeof(T) == 4;
   PcgState* dst = reinterpret_cast<PcgState*>(dv.state.p);
-  if (!dv.ev[0]) {
-    R3MG_HIP_CHECK(hipEventCreateWithFlags(&dv.ev[0], hipEventDisableTiming));
-    R3MG_HIP_CHECK(hipEventCreateWithFlags(&dv.ev[1], hipEventDisableTiming));
-  }
+  ensure_event(dv);
   launch_gather_cols(n, NR, nb, dv.perm.p, b + (int64_t)c0 * n, n, dv.pb.p, s);
   launch_gather_cols(n, NR, nb, dv.perm.p, x + (int64_t)c0 * n, n, dv.px.p, s);
   pcg_start<T>(c, NR, nb, rtol, atol, flexible, false, s);
@@ -1897,8 +1898,8 @@ static r3mg_status pcg_block(HandleImpl& h, const double* b, double* x, int c0, 
     }
     launch_scatter_cols(n, NR, nb, dv.perm.p, dv.px.p, x + (int64_t)c0 * n, n, s);
     launch_pcg_state_out(dst, static_cast<PcgState*>(dv.pinned_dev), s);
-    R3MG_HIP_CHECK(hipEventRecord(dv.ev[0], s));
-    R3MG_HIP_CHECK(hipEventSynchronize(dv.ev[0]));
+    R3MG_HIP_CHECK(hipEventRecord(dv.chunk_done, s));
+    R3MG_HIP_CHECK(hipEventSynchronize(dv.chunk_done));
     std::memcpy(&st, dv.pinned, sizeof(PcgState));
   };
   const int key = record_key(NR, flexible);
@@ -1979,14 +1980,14 @@ int residual_history(HandleImpl& h, int col, double* rr, int cap) {
 // prediction fell short.  (One graph with a branch per problem ran the branches nearly one after another: four 3D Q2
 // cubes of 13 to 25 cells an axis took 4.28 ms that way, 2.14 ms on their own streams.)
 namespace {
-// streams and events of the branches, created once per thread and device and reused by every group solve
+// Streams of the group solves, created once per thread and device and reused by every one: one per problem up to
+// kGroupStreams, which more problems share in turn (the card runs a process's streams on four hardware queues).
+constexpr int kGroupStreams = 8;
 struct Branches {
   std::vector<hipStream_t> s;
-  std::vector<hipEvent_t> ev;
   hipEvent_t fork = nullptr;
   ~Branches() {
     for (auto q : s) (void)hipStreamDestroy(q);
-    for (auto e : ev) (void)hipEventDestroy(e);
     if (fork) (void)hipEventDestroy(fork);
   }
 };
@@ -1994,15 +1995,10 @@ Branches& branches(int dev, int count) {
   static thread_local std::map<int, Branches> pool;
   Branches& b = pool[dev];
   if (!b.fork) R3MG_HIP_CHECK(hipEventCreateWithFlags(&b.fork, hipEventDisableTiming));
-  while ((int)b.s.size() < count) {
+  while ((int)b.s.size() < std::min(count, kGroupStreams)) {
     hipStream_t q;
     R3MG_HIP_CHECK(hipStreamCreateWithFlags(&q, hipStreamNonBlocking));
     b.s.push_back(q);
-  }
-  while ((int)b.ev.size() < count) {
-    hipEvent_t e;
-    R3MG_HIP_CHECK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
-    b.ev.push_back(e);
   }
   return b;
 }
@@ -2087,13 +2083,15 @@ r3mg_status pcg_group(int count, HandleImpl** hs, const double* const* b, double
   };
   try {
     // buffers and iteration graphs of every problem first: these may allocate
-    for (int q = 0; q < count; ++q) {
+    for (int r = 0; r < count; ++r) {
+      const int q = order[r];
       GroupTask& t = tasks[q];
       t.h = hs[q];
-      t.s = br.s[q];
-      t.ev = br.ev[q];
+      t.s = br.s[r % br.s.size()];
       t.f32 = hs[q]->an->opt.vcycle_fp32 != 0;
       Ctx c = ctx(t);
+      ensure_event(c.dv);
+      t.ev = c.dv.chunk_done;
       ensure_level_vectors(c, 1);
       ensure_pcg_vectors(c, 1);
       ensure_hist(c.dv, std::max(maxit, 1));

@@ -1,8 +1,9 @@
-"""Device memory: what a handle holds, and what it does where the memory for an optional copy is not to be had.
+"""Device memory and streams: what a handle or a group solve holds, and what a handle does where the memory for an
+optional copy is not to be had.
 
-Each check runs in a child process whose hipMalloc and hipFree pass through a preloaded recorder: it counts the live
-allocations of a given size and refuses chosen sizes (hipErrorOutOfMemory, as the runtime answers), so that nothing
-depends on how much memory the card has left.
+Each check runs in a child process whose hipMalloc, hipFree and hipStreamCreateWithFlags pass through a preloaded
+recorder: it counts the live allocations of a given size and the streams made, and refuses chosen sizes
+(hipErrorOutOfMemory, as the runtime answers), so that nothing depends on how much memory the card has left.
 """
 import os
 import subprocess
@@ -68,6 +69,13 @@ int hipMalloc(void** p, size_t n) {
   }
   pthread_mutex_unlock(&mu);
   return rc;
+}
+static int streams;
+int rec_streams(void) { return streams; }
+int hipStreamCreateWithFlags(void** s, unsigned flags) {
+  int (*real)(void**, unsigned) = (int (*)(void**, unsigned))real_of("hipStreamCreateWithFlags");
+  ++streams;
+  return real(s, flags);
 }
 int hipFree(void* p) {
   int (*real)(void*) = (int (*)(void*))real_of("hipFree");
@@ -279,4 +287,22 @@ size = nt * (nt + 1) // 2 * 64 * 64 * (4 if {fp32} else 8)
 assert rec.rec_live(size) == {packed}
 solve(h, prob)
 solve(h, prob, 4)
+""", tmp_path / "tune")
+
+
+def test_group_solves_keep_a_bounded_number_of_streams(recorder, tmp_path):
+    """Twelve problems share eight streams, which every later group solve reuses, with the solutions of single solves."""
+    print("[gpu-case] streams of a group solve", flush=True)
+    _child(recorder, r"""
+probs = [problem(3, n, 2) for n in (5, 6, 7, 8, 5, 6, 7, 8, 5, 6, 7, 8)]
+hs = [handle(p, use_graph=0, tune_cache=0, vcycle_fp32=k % 2) for k, p in enumerate(probs)]
+bs = [torch.from_numpy(np.where(p.boundary, 0.0, np.random.default_rng(1).standard_normal((1, p.n))[0])).cuda()
+      for p in probs]
+before = rec.rec_streams()
+for rtol in (1e-6, 1e-10, 1e-10):
+    xs = [torch.zeros_like(b) for b in bs]
+    it, rr, ok = P.solve_group(hs, bs, xs, rtol=rtol, maxit=100)
+    assert ok and rec.rec_streams() - before == 8, rec.rec_streams() - before
+for p, h, x in zip(probs, hs, xs):
+    assert np.array_equal(solve(h, p), x.cpu().numpy())
 """, tmp_path / "tune")
