@@ -278,9 +278,9 @@ void launch_gather_vals(int64_t nnz, const int64_t* src, const double* user_vals
 // set-up kernels
 void launch_diag_inv(int n, int blk, const int* ptr, const int* idx, const double* val, double* dinv, double* diag,
                      int* bad, hipStream_t s);
-// nup blocks formed: up[t] (K <= K'), whose transpose also fills block mir[t] (-1 on the diagonal)
-// Work items of the fine-level Galerkin product: item = (block index, first entry, end, partial slot or -1), multi =
-// (block index, first partial slot, partials) of the blocks split into several items, part = the partial blocks.
+// Fine-level Galerkin product.  The blocks formed are up[t] (K <= K'), whose transpose also fills block mir[t] (-1 on the
+// diagonal).  Work items: item = (t, first entry, end, partial slot or -1), multi = (t, first partial slot, partials) of
+// the blocks split into several items, part = the partial blocks.
 struct GalerkinWork {
   int64_t nitem = 0, nmulti = 0;
   size_t nslot = 0;  // partial blocks
@@ -345,7 +345,6 @@ inline int mr_class(int nr, int esz) {
 template <typename T>
 bool launch_level_lmr(const MrBlocks& mb, const LevelOp<T>& op, int nr, bool pipelined, const T* u, const T* b,
                       T* rho, T* x, T* dout, double c1, double c2, int flags, const int* skip, hipStream_t s);
-// partial sums of w_i x_i y_i (w may be null) -> partials (returns count)
 void launch_axpby(int64_t n, double a, const double* x, double b, double* y, hipStream_t s);   // y = a x + b y
 // Lanczos steps in the D inner product (diag = D), at most kLanczosBlocks blocks and twice as many partials.
 // normalise: v /= ||v||_D.  step: w = D^{-1} Av - beta_prev vprev, alpha = <w, v>_D, w -= alpha v, beta = ||w||_D and
@@ -355,7 +354,6 @@ void launch_lanczos_normalise(int64_t n, const double* diag, double* v, double* 
 void launch_lanczos_step(int64_t n, const double* dinv, const double* diag, const double* Av, const double* v,
                          double* vprev, bool first, bool last, double* w, const double* beta_prev, double* alpha,
                          double* beta, double* partials, hipStream_t s);
- // u = dinv*Av - beta_prev*vprev
 
 // ---- matrix-free fine operator: the Q_p Laplace stiffness action on multilinear cells ----
 // 1D tables of the cell kernel: B[q][i] = l_i(g_q) and G[q][i] = l_i'(g_q) for the Lagrange basis l_i on the

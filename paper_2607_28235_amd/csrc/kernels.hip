@@ -3330,11 +3330,9 @@ __global__ __launch_bounds__(256) void k_prolong0_box(Basis1D<T> bs, int nr, int
   }
 }
 
-
-// The same for nr > 1 columns: one workgroup per level-1 box K (its points are leaf_off[K] .. leaf_off[K+1] - 1,
-// owned by K or constrained).  The box's B coarse entries of e + epend (all columns) are formed once in LDS; thread
-// (i, j) of the box then takes fine point i and column chunk j (chunks of one point adjacent), in k_prolong0's
-// order.  Reading the entries from LDS instead of L2 for every point and chunk was what bounded the kernel.
+// The same for nr > 1 columns: `per` workgroups per level-1 box K (its points are leaf_off[K] .. leaf_off[K+1] - 1,
+// owned by K or constrained).  Each forms the box's B coarse entries of e + epend (all columns) in LDS; thread (i, j) of
+// the box then takes fine point i and column chunk j (chunks of one point adjacent), in k_prolong0's order.  Reading the entries from LDS instead of L2 for every point and chunk was what bounded the kernel.
 template <typename T, int D, int KB, int VW>
 __global__ __launch_bounds__(256) void k_prolong0_mr(Basis1D<T> bs, int nr, int per, const int* __restrict__ leaf_off,
                                                      const int* __restrict__ owner, const T* __restrict__ xi,

@@ -425,7 +425,8 @@ __global__ __launch_bounds__(64 * K) void k_mf_cell3(int ncells, const int* __re
 
 // Sum of a DoF's cell outputs Y[inc[s0 .. s1)] in ascending order, NB at a time: their list entries and outputs are
 // loaded from clamped positions and masked afterwards, so that each batch is two round trips for the whole wave (a loop
-// over a lane's own count is two round trips per output).  NB = 2^d, the most cells an interior vertex belongs to.
+// over a lane's own count is two round trips per output).  NB = 2^d, the cells around an interior vertex of a structured
+// mesh; a DoF of more cells takes more batches.
 template <typename T, int NB>
 __device__ __forceinline__ T incidence_sum(const int* __restrict__ inc, const T* __restrict__ Y, int s0, int s1) {
   T t = 0;

@@ -1356,7 +1356,7 @@ void device_setup(HandleImpl& h, hipStream_t s) {
   const int B = an.B;
   const bool fp32 = an.opt.vcycle_fp32 != 0;
   dv.lv.resize(L + 1);
-  dv.partials.alloc(4096);  // set-up reductions (at most 1024 partials); grown by the solvers
+  dv.partials.alloc(4096);  // set-up reductions (2 kLanczosBlocks partials); grown by the solvers
   dv.perm.upload(an.order, s);
   dv.src.upload(an.src, s);
   // fine level
