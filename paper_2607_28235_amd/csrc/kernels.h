@@ -181,7 +181,8 @@ void launch_level_blockrow_wg(const LevelOp<T>& op, const T* u, const T* b, T* r
 // distinct columns) of its k-th block, segn[segment] = (blocks, their distinct columns in all).  Step 2, once the arrays
 // are sized by the sums of segn, fills the block records, the column lists, the positions and, where ord is set, the rows
 // of every block by decreasing number of chunks.
-constexpr int kChunkSegRows = 4096;  // rows of a segment, at least (a matrix of fewer is one segment)
+constexpr int kChunkSegRows = 4096;  // rows of a segment, at least (a matrix of fewer is one segment) ...
+constexpr int kChunkSegs = 256;      // ... and segments, at most: one on each compute unit
 struct ChunkLists {
   int geom = 0, n = 0, nseg = 0, nrb = 0;
   const int *rowptr = nullptr, *cptr = nullptr, *col = nullptr;

@@ -2333,8 +2333,8 @@ template void launch_level_blockrow_wg<double>(const LevelOp<double>&, const dou
 // LDS to the epilogue, whose operands were fetched first and whose accesses are consecutive.
 // One application, best of the other kernels -> this one: float32, 16 columns, 3D Q3 16^3 53.8 -> 41.8 us and 28^3
 // 243 -> 213; 8 columns, 2D Q3 200^2 44.3 -> 24.4; float64, 4 columns, 3D Q2 20^3 21.3 -> 14.1.  With 16 float64
-// columns the column-split kernel stays ahead (62 against 66 us).  At 16 float32 columns LDS is busy 46% of the time
-// (a quarter of that bank conflicts), the vector units 50%, and 16 waves per compute unit wait half of theirs: no one
+// columns the column-split kernel stays ahead (62 against 66 us).  At 16 float32 columns LDS is busy 52% of the time
+// (a quarter of that bank conflicts), the vector units 59%, and 16 waves per compute unit wait 55% of theirs: no one
 // unit bounds it, and reading two chunks a step ahead changed nothing.
 template <typename T, int NR>
 struct MrShape {

@@ -453,7 +453,7 @@ static int build_chunks(const Analysis& an, DevLevel& D, int g, hipStream_t s) t
   ChunkLists c;
   c.geom = g;
   c.n = (int)an.n;
-  c.nseg = (int)std::max<int64_t>(1, an.n / kChunkSegRows);
+  c.nseg = (int)std::max<int64_t>(1, std::min<int64_t>(kChunkSegs, an.n / kChunkSegRows));
   c.rowptr = D.rowptr.p;
   c.cptr = D.cptr.p;
   c.col = D.col.p;
@@ -1066,8 +1066,19 @@ static void cheb_level(const Analysis& an, DevLevel& D, const double* sc) {
   D.cheb_c2 = ch.c2;
 }
 
-// keep: the scratch stays with the handle for the next one
-void numeric_setup(HandleImpl& h, hipStream_t s, bool keep) {
+static void release_dense_scratch(Device& dv) {
+  dv.dense.release();
+  dv.ybuf.release();
+  dv.tiles.release();
+}
+static void release_setup_scratch(Device& dv) {
+  release_dense_scratch(dv);
+  dv.lzv.release();
+  dv.lzs.release();
+  if (dv.lv.size() > 1) dv.lv[1].gal_part.release();
+}
+
+void numeric_setup(HandleImpl& h, hipStream_t s) {
   Analysis& an = *h.an;
   Device& dv = *h.dev;
   Ctx c{an, dv, an.opt.vcycle_fp32 != 0};
@@ -1156,16 +1167,7 @@ void numeric_setup(HandleImpl& h, hipStream_t s, bool keep) {
   std::vector<double> back(nscal + nflag);
   R3MG_HIP_CHECK(hipMemcpyAsync(back.data(), dv.lzs.p, back.size() * sizeof(double), hipMemcpyDeviceToHost, s));
   R3MG_HIP_CHECK(hipStreamSynchronize(s));
-  if (!keep || 2 * dv.dense.n * sizeof(double) > kKeepDenseBytes) {
-    dv.dense.release();
-    dv.ybuf.release();
-    dv.tiles.release();
-  }
-  if (!keep) {
-    dv.lzv.release();
-    dv.lzs.release();
-    if (L > 0) dv.lv[1].gal_part.release();
-  }
+  if (2 * dv.dense.n * sizeof(double) > kKeepDenseBytes) release_dense_scratch(dv);
   const int* flags = reinterpret_cast<const int*>(back.data() + nscal);
   for (int l = 0; l < L; ++l)
     if (flags[l]) throw Error{R3MG_ERR_NOT_SPD, "non-positive diagonal on level " + std::to_string(l)};
@@ -1466,10 +1468,11 @@ void device_setup(HandleImpl& h, hipStream_t s) {
       D.bytes_apply = D.shape_bytes[D.shape];
     }
   }
-  numeric_setup(h, s, false);  // most handles are set up once
+  numeric_setup(h, s);
   dv.tune_sig = tune_signature(an, dv);
   tune_stream_shape(h, s);
   R3MG_HIP_CHECK(hipStreamSynchronize(s));
+  release_setup_scratch(dv);  // most handles are set up once
   // the allocation-free V-cycle's scratch address on this device, looked up once at set-up
   (void)scratch_device_ptr(dv.dev);
 }
@@ -1478,7 +1481,7 @@ void update_values(HandleImpl& h, const double* vals_dev, hipStream_t s) {
   detach_matrix_free(h);  // the cell description no longer matches the new values
   Device& dv = *h.dev;
   launch_gather_vals(h.an->nnz, dv.src.p, vals_dev, dv.lv[0].val64.p, s);
-  numeric_setup(h, s, true);
+  numeric_setup(h, s);
   R3MG_HIP_CHECK(hipStreamSynchronize(s));
 }
 
