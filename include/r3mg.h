@@ -74,7 +74,8 @@ typedef struct {
   int fine_kernel;      /* row-block kernel of the fine level for one right-hand side: -1 = the chunk kernel (rows
                            in chunks of four entries, blocks of 3072 entries, 128 rows and 512 columns) or shape 0,
                            timed at r3mg_factor; below 30 us the chunk kernel unless padding to whole chunks doubles
-                           the matrix [-1]; 0..12 = that shape.  0..2: CSR row blocks of
+                           the matrix; shape 0 where the chunk kernel's copy finds no device memory [-1]; 0..12 = that
+                           shape.  0..2: CSR row blocks of
                            (2048 nonzeros, 64 rows), (4096, 128), (4096, 64); 3..5: the same blocks in a
                            persistent pipelined kernel; 6..8: local-column blocks (each block's distinct columns
                            staged once; 1-byte positions with 2048 nonzeros, 64 rows, 256 columns; 2-byte with
@@ -85,9 +86,10 @@ typedef struct {
                            separately.  Every shape sums a row in the same order, so results do not depend on this
                            choice when no row has more than 256 nonzeros. */
   int multi_rhs_kernel; /* fine-level kernel for several right-hand sides: -1 = the fastest of the chunk kernel and
-                           kernels 3 and 4, timed at the first multi-RHS solve [-1]; 0 = lanes-per-row CSR kernel
-                           (each lane all columns of its nonzeros); 1 / 2 = row blocks staged in LDS (values, 2-byte column positions and
-                           u at the block's distinct columns; each thread sums one row's 16-byte column chunk):
+                           kernels 3 and 4, timed at the first multi-RHS solve (3 and 4 alone where the chunk
+                           kernel's copy finds no device memory) [-1]; 0 = lanes-per-row CSR kernel (each lane all
+                           columns of its nonzeros); 1 / 2 = row blocks staged in LDS (values, 2-byte column positions
+                           and u at the block's distinct columns; each thread sums one row's 16-byte column chunk):
                            one persistent workgroup per compute unit that loads the next block while summing
                            one (1), or one workgroup per block (2), for 16 float or 8 / 16 double right-hand
                            sides (other counts: the lanes kernel); 3 = CSR with the
