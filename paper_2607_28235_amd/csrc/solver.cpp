@@ -397,7 +397,8 @@ static void fill_chunks(DevLevel& D, int esz, hipStream_t s) {
   if (esz == 4 && D.cval32.p) launch_chunk_values<float>((int)D.n, D.rowptr.p, D.cptr.p, D.val32.p, D.cval32.p, s);
 }
 
-// the chunked fine values in element size esz; false: no device memory for them
+// the chunked fine values in element size esz; false: no device memory for them, or too little left for the vectors of a
+// one-column solve beside them (six of PCG, allocated at the first solve, and two of the set-up timing)
 static bool hold_chunks(DevLevel& D, int esz, hipStream_t s) {
   if (esz == 4 ? D.cval32.p != nullptr : D.cval64.p != nullptr) return true;
   try {
@@ -407,6 +408,12 @@ static bool hold_chunks(DevLevel& D, int esz, hipStream_t s) {
       D.cval64.alloc(4 * (size_t)D.nchunk);
   } catch (const Error& e) {
     if (e.code != R3MG_ERR_OOM) throw;
+    return false;
+  }
+  size_t left = 0, total = 0;
+  R3MG_HIP_CHECK(hipMemGetInfo(&left, &total));
+  if (left < 8 * sizeof(double) * (size_t)D.n) {
+    (esz == 4 ? D.cval32.release() : D.cval64.release());
     return false;
   }
   fill_chunks(D, esz, s);

@@ -70,6 +70,14 @@ int hipMalloc(void** p, size_t n) {
   pthread_mutex_unlock(&mu);
   return rc;
 }
+static size_t left;
+void rec_left(size_t n) { left = n; }  /* what hipMemGetInfo says is left; 0: the truth */
+int hipMemGetInfo(size_t* f, size_t* t) {
+  int (*real)(size_t*, size_t*) = (int (*)(size_t*, size_t*))real_of("hipMemGetInfo");
+  int rc = real(f, t);
+  if (left) *f = left;
+  return rc;
+}
 static int streams;
 int rec_streams(void) { return streams; }
 int hipStreamCreateWithFlags(void** s, unsigned flags) {
@@ -94,7 +102,7 @@ import numpy as np, torch
 import fixtures as F
 import paper_2607_28235_amd as P
 rec = ctypes.CDLL(sys.argv[2])
-rec.rec_refuse.argtypes = rec.rec_live.argtypes = [ctypes.c_size_t]
+rec.rec_refuse.argtypes = rec.rec_live.argtypes = rec.rec_left.argtypes = [ctypes.c_size_t]
 torch.zeros(1, device="cuda")
 
 def problem(d, N, p):
@@ -305,4 +313,28 @@ for rtol in (1e-6, 1e-10, 1e-10):
     assert ok and rec.rec_streams() - before == 8, rec.rec_streams() - before
 for p, h, x in zip(probs, hs, xs):
     assert np.array_equal(solve(h, p), x.cpu().numpy())
+""", tmp_path / "tune")
+
+
+@pytest.mark.parametrize("fp32", [0, 1])
+def test_chunked_values_leave_room_for_a_solve(recorder, fp32, tmp_path):
+    """A chunked copy that leaves less than a one-column solve's vectors is not taken, from the tuning cache or not."""
+    print(f"[gpu-case] room for a solve, fp32={fp32}", flush=True)
+    _child(recorder, rf"""
+prob = problem(3, 10, 2)
+want = solve(handle(prob, fine_kernel=0, vcycle_fp32={fp32}, tune_cache=0), prob)
+held = lambda: sum(rec.rec_live(w * prob.chunks) for w in (4, 16, 32))
+assert held() == 0
+for known in (0, 1):
+    for left, kept in ((64 * prob.n - 1, False), (64 * prob.n, True)):
+        rec.rec_left(left)
+        h = handle(prob, vcycle_fp32={fp32}, tune_cache=known)
+        rec.rec_left(0)
+        chunk = h.info()[0]["kernel"].startswith("k_level_chunk<")
+        assert chunk == (held() > 0) and (kept or not chunk)
+        assert np.array_equal(solve(h, prob), want)
+        h.close()
+    h = handle(prob, vcycle_fp32={fp32})                 # fills the cache
+    assert h.info()[0]["kernel"].startswith("k_level_chunk<")
+    h.close()
 """, tmp_path / "tune")
