@@ -178,3 +178,47 @@ def test_first_block_call_takes_no_host_encoding(tmp_path, monkeypatch):
             h.close()
     print("first call ms", {k: 1e3 * v for k, v in best.items()}, flush=True)
     assert best[BLOCKS + 1] <= best[216] + 6e-3
+
+
+@pytest.mark.slow
+@pytest.mark.parametrize("fp32", [1, 0])
+def test_solves_with_the_chunk_kernels_against_the_oracle(fp32, tmp_path, monkeypatch):
+    """3D Q3 16^3 (117,649 rows, 28 segments), 16 columns, with the kernels that the timing picks at 48^3: the chunk shape
+    for one column, the chunk kernel over its larger blocks for 16 (the V-cycle and PCG's operator).  Columns 0 and 15
+    against the oracle (iterations within one, 1e-9 of its rtol-1e-13 solution), alone and in the block, and every
+    column's true residual at the stop rule."""
+    _need_gpu()
+    import oracle as O
+    import paper_2607_28235_amd as P
+    w = F.workload(4, scale=16)
+    prob = w.problem
+    print(f"[gpu-case] chunk kernels against the oracle n={prob.n} fp32={fp32}", flush=True)
+    kw = dict(coarse_degree=2, leaf_size=256, max_coarse_dofs=500)
+    ho = O.build_hierarchy(prob.coords, prob.scipy(), skip_leaf_level=True, **kw)
+    ref = {j: (O.pcg(ho, w.rhs[j], rtol=1e-10)[1], O.pcg(ho, w.rhs[j], rtol=1e-13)[0]) for j in (0, 15)}
+    path = tmp_path / "tune"
+    monkeypatch.setenv("R3MG_TUNE_CACHE", str(path))
+    make = lambda: P.Hierarchy(prob.coords, prob.row_ptr, prob.col, prob.val,  # noqa: E731
+                               P.Options(dim=3, skip_leaf_level=1, vcycle_fp32=fp32, **kw))
+    B = _t(w.rhs)
+    h = make()
+    h.pcg(B, torch.zeros_like(B), rtol=1e-2, maxit=5)
+    h.close()
+    _force(path, lambda ln: "/fine1/" in ln, SHAPE + 100 * SHAPE)
+    _force(path, lambda ln: "/mr/0/" in ln or "/mr/-1/" in ln, BLOCKS + 1)
+    before = open(path).read()
+    h = make()
+    assert h.info()[0]["kernel"].startswith("k_level_chunk<" + ("float" if fp32 else "double"))
+    X = torch.zeros_like(B)
+    iters, _, ok = h.pcg(B, X, rtol=1e-10, maxit=200)
+    assert ok and open(path).read() == before
+    for j, (ko, xt) in ref.items():
+        x = torch.zeros_like(B[j])
+        it, _, ok = h.pcg(B[j].contiguous(), x, rtol=1e-10, maxit=200)
+        assert ok
+        for k, got in ((int(iters[j]), X[j]), (int(it[0]), x)):
+            assert abs(k - ko) <= 1, (j, k, ko)
+            assert np.linalg.norm(got.cpu().numpy() - xt) <= 1e-9 * np.linalg.norm(xt), j
+    R = w.rhs - (prob.scipy() @ X.cpu().numpy().T).T
+    assert np.all(np.linalg.norm(R, axis=1) <= 1.01e-10 * np.linalg.norm(w.rhs, axis=1))
+    h.close()
