@@ -209,10 +209,13 @@ constexpr float kChunkMrMargin = 1.05f;
 //   float64: 3D Q3 14^3 x 16 9.05 / 8.11, 12^3 x 4 3.99 / 3.70; 3D Q2 20^3 x 16 3.94 / 4.15, x 4 1.79 / 1.85;
 //            2D Q2 150^2 x 5 3.14 / 3.47
 // Rows of nine entries (2D Q1) leave a quarter of their chunks empty: 40^2 x 16 0.88 / 0.92 against 0.76 for the
-// column-split kernel.  PCG's operator takes the V-cycle's geometry (within 2% either way), so that one set of blocks
+// column-split kernel.  Two float32 columns have no column-split kernel (8 bytes an entry): there the chunk kernel is a
+// candidate whatever the rows, 2D Q1 480^2 3.29 / 3.35 against 3.75 with two lanes per row, 300^2 1.15 / 1.13 against 1.24.
+// PCG's operator takes the V-cycle's geometry (within 2% either way), so that one set of blocks
 // is encoded.
-static int chunk_mr_geom(const DevLevel& D, bool fp32) {
-  return D.nnz < 12 * D.n ? -1 : D.nnz > (fp32 ? 40 : 80) * D.n ? 1 : 0;
+static bool has_split(int nr, int esz) { return nr * esz % 16 == 0; }
+static int chunk_mr_geom(const DevLevel& D, bool fp32, int nr, int esz) {
+  return D.nnz < 12 * D.n && has_split(nr, esz) ? -1 : D.nnz > (fp32 ? 40 : 80) * D.n ? 1 : 0;
 }
 
 // F_KEEP when the level's matrix stream in precision T is small enough to stay in the caches
@@ -685,13 +688,7 @@ static void autotune_spmm(Ctx& c, int nr, hipStream_t s) {
         bestCode = code;
       }
     };
-    const bool fine = l == 0;
-    if (!fine && box_mr_supported(c.an.B, D.maxnb)) {
-      // the box kernel wherever its tiles fit, untimed: 12.1 / 5.7 / 3.9 / 4.5 / 3.5 us against 50 / 14.1 / 10.5 / 5.6 /
-      // 4.9 for the best lane count (16 columns of 3D Q3 16^3, 8 of 2D Q2 150^2, level by level in the iteration graph),
-      // and below about 8 us launches timed one by one rank the host's launch gaps
-      bestCode = kCodeBox;
-    } else if (!fine || forced == 0) {
+    auto lanes = [&] {
       for (int G = 1; G <= 64; G <<= 1)
         consider(G, 1.0f, [&] {
           op.lanes = G;
@@ -699,11 +696,20 @@ static void autotune_spmm(Ctx& c, int nr, hipStream_t s) {
                           nullptr, s);
           return true;
         });
+    };
+    const bool fine = l == 0;
+    if (!fine && box_mr_supported(c.an.B, D.maxnb)) {
+      // the box kernel wherever its tiles fit, untimed: 12.1 / 5.7 / 3.9 / 4.5 / 3.5 us against 50 / 14.1 / 10.5 / 5.6 /
+      // 4.9 for the best lane count (16 columns of 3D Q3 16^3, 8 of 2D Q2 150^2, level by level in the iteration graph),
+      // and below about 8 us launches timed one by one rank the host's launch gaps
+      bestCode = kCodeBox;
+    } else if (!fine || forced == 0) {
+      lanes();
     } else {
       LevelOp<T> opc = op;
       opc.ptr = D.rowptr.p;
       opc.idx = D.col.p;
-      const int g = forced == -1 ? chunk_mr_geom(D, c.fp32) : -1;
+      const int g = forced == -1 ? chunk_mr_geom(D, c.fp32, nr, (int)sizeof(T)) : -1;
       if (g >= 0 && !ensure_chunk_mr(c, g, (int)sizeof(T), s)) {
         room = false;
       } else if (g >= 0) {
@@ -721,6 +727,7 @@ static void autotune_spmm(Ctx& c, int nr, hipStream_t s) {
             return launch_level_lmr<T>(D.mr[cls], opc, nr, g == 0, vbuf<T>(D.dA), vbuf<T>(D.b), vbuf<T>(D.rho),
                                        vbuf<T>(D.x), vbuf<T>(D.dB), 0.0, 0.0, fl | keep_flag<T>(D), nullptr, s);
           });
+      if (forced == -1 && !has_split(nr, (int)sizeof(T))) lanes();
       for (int G = splitLast; G >= splitFirst; G >>= 1) {
         if (forced == -1 || forced == 4)
           consider(kCodeSplit2 + G, 1.0f, [&] {
@@ -779,7 +786,7 @@ static void autotune_spmm(Ctx& c, int nr, hipStream_t s) {
     op.ptr = D0.rowptr.p;
     op.idx = D0.col.p;
     need_partials(dv, (int64_t)kPcgBlocks * 2 * nr);
-    const int g = forced == -1 && !D0.mf ? chunk_mr_geom(D0, c.fp32) : -1;
+    const int g = forced == -1 && !D0.mf ? chunk_mr_geom(D0, c.fp32, nr, 8) : -1;
     if (g >= 0 && !ensure_chunk_mr(c, g, 8, s)) {
       room = false;
     } else if (g >= 0) {

@@ -17,7 +17,7 @@
 namespace r3mg {
 
 // version of the kernel set the cached codes refer to (bump when shapes or codes change meaning)
-constexpr int kTuneCacheVersion = 7;
+constexpr int kTuneCacheVersion = 8;
 
 // key prefix naming the device (architecture, compute units) and the tuning version
 std::string tune_device_key(int dev);

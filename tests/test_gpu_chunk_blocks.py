@@ -222,3 +222,26 @@ def test_solves_with_the_chunk_kernels_against_the_oracle(fp32, tmp_path, monkey
     R = w.rhs - (prob.scipy() @ X.cpu().numpy().T).T
     assert np.all(np.linalg.norm(R, axis=1) <= 1.01e-10 * np.linalg.norm(w.rhs, axis=1))
     h.close()
+
+
+def test_two_float32_columns_on_short_rows_are_timed(tmp_path, monkeypatch):
+    """Two float32 columns have no column-split kernel.  On rows of nine entries (2D Q1 480^2) the chunk and lanes kernels
+    are timed for them: the chunk kernel takes 3.3 ms for a solve, the lanes kernels 3.7 (two lanes a row) and more."""
+    _need_gpu()
+    print("[gpu-case] two float32 columns, 2D Q1", flush=True)
+    path = tmp_path / "tune"
+    monkeypatch.setenv("R3MG_TUNE_CACHE", str(path))
+    case = _plain(2, 480, 1)
+    R = _t(np.random.default_rng(5).standard_normal((2, case[1].shape[0])))
+    h = _handle(case, 1)
+    Z = torch.empty_like(R)
+    h.vcycle(R, Z)
+    h.close()
+    code = [int(ln.split()[1]) for ln in open(path) if "/mr/0/2/4 " in ln]
+    assert code == [BLOCKS]
+    ref = _handle(case, 1, multi_rhs_kernel=0, tune_cache=0)
+    want = torch.empty_like(R)
+    ref.vcycle(R, want)
+    ref.close()
+    for j in range(2):
+        assert torch.linalg.norm(Z[j] - want[j]) <= 1e-5 * torch.linalg.norm(want[j])
