@@ -546,6 +546,8 @@ static bool ensure_chunk_mr(Ctx& c, int g, int esz, hipStream_t s) {
   return hold_chunks(D, esz, s);
 }
 
+// The capacities below count only complete sets of vectors: an allocation that fails half way leaves 0, so that a later,
+// smaller solve allocates again (and drops the graphs that read the old ones).
 static void ensure_level_vectors(Ctx& c, int nr) {
   const size_t s = c.fp32 ? sizeof(float) : sizeof(double);
   const int L = c.an.nlevels() - 1;
@@ -555,6 +557,7 @@ static void ensure_level_vectors(Ctx& c, int nr) {
     const int64_t entries = (int64_t)F.op.ncells * F.op.nlocp * nr;
     if (entries >= (int64_t(1) << 31) || (int64_t)F.op.n * nr >= (int64_t(1) << 31))
       throw Error{R3MG_ERR_INVALID, "matrix-free operator: too many cell-local entries for this many right-hand sides"};
+    F.mr_cap = 0;
     F.y64mr.alloc((size_t)entries);
     if (c.fp32) F.y32mr.alloc((size_t)entries);
     F.mr_cap = nr;
@@ -564,6 +567,7 @@ static void ensure_level_vectors(Ctx& c, int nr) {
     DevLevel& D = c.dv.lv[l];
     if (D.vec_cap >= D.n * nr) continue;
     const size_t bytes = (size_t)D.n * nr * s;
+    D.vec_cap = 0;
     DBuf<char>* bufs[5] = {&D.b, &D.x, &D.rho, &D.dA, &D.dB};
     for (DBuf<char>* bp : bufs) {
       bp->alloc(bytes);
@@ -578,12 +582,12 @@ static void ensure_pcg_vectors(Ctx& c, int nr) {
   Device& dv = c.dv;
   const int64_t n = c.an.n;
   if (dv.pcg_cap < n * nr) {
+    dv.pcg_cap = 0;
     DBuf<double>* bufs[6] = {&dv.px, &dv.pr, &dv.pp, &dv.pq, &dv.pz, &dv.pb};
     for (DBuf<double>* bp : bufs) {
       bp->alloc((size_t)n * nr);
       R3MG_HIP_CHECK(hipMemset(bp->p, 0, (size_t)n * nr * sizeof(double)));
     }
-    dv.pcg_cap = n * nr;
     // the fine-level SpMV uses 256 / lanes rows per block; vector kernels 256 rows per block
     const int64_t rpb = 256 / std::max(nr > 1 ? 8 : 1, dv.lv[0].lanes);
     const int64_t nlog_spmv = (n + rpb - 1) / rpb;
@@ -594,6 +598,7 @@ static void ensure_pcg_vectors(Ctx& c, int nr) {
     dv.partials.alloc(std::max<size_t>({(size_t)4096, (size_t)(nlog_spmv * nr), (size_t)(nlog_vec * 2 * nr), nrb_max,
                                         (size_t)kPcgBlocks * 2 * nr}));
     drop_graphs(dv);
+    dv.pcg_cap = n * nr;
   }
   if (!dv.state.p) {
     dv.state.alloc(sizeof(PcgState));

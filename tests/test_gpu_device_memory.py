@@ -338,3 +338,36 @@ for known in (0, 1):
     assert h.info()[0]["kernel"].startswith("k_level_chunk<")
     h.close()
 """, tmp_path / "tune")
+
+
+# what is refused at 16 columns: PCG's vectors, the V-cycle's of the fine level, PCG's partial sums
+@pytest.mark.parametrize("what", ["pcg", "level", "partials"])
+@pytest.mark.parametrize("fp32", [0, 1])
+def test_smaller_solve_after_a_block_solve_without_memory(recorder, what, fp32, tmp_path):
+    """A block solve whose vectors find no device memory says so; afterwards solves that fit give bitwise what they gave
+    before it, and the block solve works once there is room."""
+    print(f"[gpu-case] block solve without memory: {what}, fp32={fp32}", flush=True)
+    _child(recorder, rf"""
+prob = problem(2, 24, 3)
+opt = dict(fine_kernel=0, vcycle_fp32={fp32})     # the first handle's timed choices, by way of the tuning cache
+ref = handle(prob, **opt)
+want = {{nr: solve(ref, prob, nr) for nr in (1, 4, 16)}}
+h = handle(prob, **opt)
+for nr in (1, 4):
+    assert np.array_equal(solve(h, prob, nr), want[nr])
+refuse(dict(pcg=8 * 16 * prob.n, level={4 if fp32 else 8} * 16 * prob.n, partials=8 * 1024 * 2 * 16)["{what}"])
+for rep in range(2):
+    before = rec.rec_refused()
+    try:
+        solve(h, prob, 16)
+        assert False, "solved without memory"
+    except P.R3mgError as e:
+        assert "hipMalloc" in str(e), e
+    assert rec.rec_refused() > before
+    for nr in (1, 4, 1):
+        assert np.array_equal(solve(h, prob, nr), want[nr]), nr
+rec.rec_allow()
+for nr in (16, 4, 1):
+    assert np.array_equal(solve(h, prob, nr), want[nr]), nr
+h.close()
+""", tmp_path / "tune")
